@@ -159,7 +159,8 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * V=<columns per lane: 1, 2, 4, 8>, P=<lanes of a workgroup sharing a column group: a power of two up to 64>,
  * PK=0 (bf16: no packed queue words), XS=0 / XS=1 (exact_topk with k <= 512: never / also on small
  * inputs guess the threshold from a sample of the row first), XC=<elements of a row per workgroup of
- * exact_topk's sweeps: a power of two from 1024 to 16384>, LN=0 (k_b = 1: the general kernel instead of the
+ * exact_topk's sweeps: a power of two from 1024 to 16384>, XR=0 (exact_topk: no row is held in one workgroup's
+ * registers; XS and XC, which concern the paths of longer rows, imply it), LN=0 (k_b = 1: the general kernel instead of the
  * one specialised for running maxima), LM=0 (k_b = 1: the lanes of a column merge through per-part lists and
  * a pass over them instead of atomic maxima in LDS), HF=0 / HF=1 (never / whenever the shape allows, two
  * workgroups - a helper and a finisher - share a row of a Stage-2 plan), HQ=<sixty-fourths of the matrix rows

@@ -8,6 +8,7 @@
 #include <mutex>
 
 #include "atk_common.h"
+#include "atk_exact.h"
 #include "atk_select.h"
 
 namespace atk {
@@ -79,6 +80,7 @@ static PlanOverride parse_plan_override(const char *e) {
     if (const char *q = field("LM")) o.lm_off = atoi(q) == 0;
     if (const char *q = field("LN")) o.ln_off = atoi(q) == 0;
     if (const char *q = field("XS")) o.xs = atoi(q) == 0 ? -1 : 1;
+    if (const char *q = field("XR")) o.xr_off = atoi(q) == 0;
     if (const char *q = field("XC")) {
         const int v = atoi(q);
         if (v >= 1024 && v <= 16384 && (v & (v - 1)) == 0) o.xc = v;
@@ -901,16 +903,16 @@ static int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
 // rows go one per workgroup), and the pool sizes cover every block.  The last block has fewer rows and
 // is planned on its own by run_exact(): with fewer rows it may take paths the full blocks do not (the
 // copy-out buffer, a finer sweep), so its needs are not bounded by the first block's.
-static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, ExactPlan *first, int64_t *state_bytes,
+static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *first, int64_t *state_bytes,
                             int64_t *data_bytes) {
-    int rc = make_exact_plan(m > kExactRowsPerPass ? kExactRowsPerPass : m, n, k, dtype, first);
-    if (rc == ATK_OK && first->single_wg) rc = make_exact_plan(m, n, k, dtype, first);
+    int rc = make_exact_plan(m > kExactRowsPerPass ? kExactRowsPerPass : m, n, k, dtype, pairs, ptr16, first);
+    if (rc == ATK_OK && first->single_wg) rc = make_exact_plan(m, n, k, dtype, pairs, ptr16, first);
     if (rc != ATK_OK) return rc;
     *state_bytes = first->state_bytes;
     *data_bytes = first->scratch_bytes;
     if (!first->single_wg && m > kExactRowsPerPass && m % kExactRowsPerPass) {
         ExactPlan last;
-        rc = make_exact_plan(m % kExactRowsPerPass, n, k, dtype, &last);
+        rc = make_exact_plan(m % kExactRowsPerPass, n, k, dtype, pairs, ptr16, &last);
         if (rc != ATK_OK) return rc;
         *state_bytes = std::max(*state_bytes, last.state_bytes);
         *data_bytes = std::max(*data_bytes, last.scratch_bytes);
@@ -932,7 +934,7 @@ static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
     fp->data_bytes = fp->s1.scratch_lists_bytes;
     if (!fp->two_step) return ATK_OK;
     int64_t ex_state = 0, ex_data = 0;
-    rc = make_exact_plans(m, nc, k, dtype, &fp->ex, &ex_state, &ex_data);
+    rc = make_exact_plans(m, nc, k, dtype, true, true, &fp->ex, &ex_state, &ex_data);
     if (rc != ATK_OK) return rc;
     fp->ex.idx_n = n;
     fp->cand_vals_off = align256(fp->s1.scratch_lists_bytes);
@@ -957,7 +959,7 @@ static int run_exact(const ExactPlan &first, const void *x, const int32_t *xi, i
     for (int64_t r0 = 0; r0 < m; r0 += kExactRowsPerPass) {
         ExactPlan pl = first;
         if (m - r0 < pl.m) {
-            int rc = make_exact_plan(m - r0, n, k, dtype, &pl);
+            int rc = make_exact_plan(m - r0, n, k, dtype, xi != nullptr, ((uintptr_t)x & 15u) == 0, &pl);
             if (rc != ATK_OK) return rc;
             pl.idx_n = first.idx_n;
         }
@@ -1021,7 +1023,7 @@ int atk_check_exact(int64_t m, int64_t n, int64_t k, int dtype) {
     if (rc != ATK_OK) return rc;
     ExactPlan pl;
     int64_t state_bytes = 0, data_bytes = 0;
-    return make_exact_plans(m, n, k, dtype, &pl, &state_bytes, &data_bytes);
+    return make_exact_plans(m, n, k, dtype, false, true, &pl, &state_bytes, &data_bytes);
 }
 
 int atk_set_plan_override(const char *spec) {
@@ -1049,7 +1051,7 @@ int64_t atk_exact_workspace_bytes(int64_t m, int64_t n, int64_t k, int dtype) {
     if (rc != ATK_OK) return rc;
     ExactPlan pl;
     int64_t state_bytes = 0, data_bytes = 0;
-    rc = make_exact_plans(m, n, k, dtype, &pl, &state_bytes, &data_bytes);
+    rc = make_exact_plans(m, n, k, dtype, false, true, &pl, &state_bytes, &data_bytes);
     if (rc != ATK_OK) return rc;
     return state_bytes + data_bytes;
 }
@@ -1059,7 +1061,7 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
     int rc = check_common(m, n, k, dtype);
     if (rc != ATK_OK) return rc;
     ExactPlan pl;
-    return make_exact_plans(m, n, k, dtype, &pl, state_bytes, data_bytes);
+    return make_exact_plans(m, n, k, dtype, false, true, &pl, state_bytes, data_bytes);
 }
 
 int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment,
@@ -1149,7 +1151,7 @@ int exact_topk(const void *x, int64_t m, int64_t n, int64_t k, int dtype, void *
     if ((uintptr_t)out_idx & 3u) return ATK_ERR_ALIGN;
     ExactPlan pl;
     int64_t state_bytes = 0, data_bytes = 0;
-    rc = make_exact_plans(m, n, k, dtype, &pl, &state_bytes, &data_bytes);
+    rc = make_exact_plans(m, n, k, dtype, false, ((uintptr_t)x & 15u) == 0, &pl, &state_bytes, &data_bytes);
     if (rc != ATK_OK) return rc;
     void *state = nullptr, *data = nullptr;
     hipError_t e = get_pool(kPoolState, (size_t)state_bytes, &state, (hipStream_t)stream);

@@ -79,6 +79,7 @@ struct PlanOverride {
     bool lm_off;      // LM=0: lanes that share a column merge through the LDS exchange, not by LDS atomic maximum
     int xs;           // exact_topk sampled threshold: 0 not set, 1 forced on (XS=1), -1 off (XS=0)
     int xc;           // exact_topk sweep chunk in elements
+    bool xr_off;      // XR=0: exact_topk never holds a row in one workgroup's registers (nor with XS or XC, which are about longer rows)
     int hf;           // two workgroups per row (helper + finisher): 0 not set, 1 forced on where legal (HF=1), -1 off (HF=0)
     int hq;           // the helper's share of the matrix rows in 64ths (HQ=..), 0 not set
     int ht;           // HT=<lanes>: workgroup size of the two-workgroups-per-row plans, 0 not set
@@ -153,30 +154,6 @@ hipError_t launch_approx_contig(const Plan &plan, const void *x, void *out_vals,
 // (plan.scratch_ticket_bytes, zero between calls), else unused.  trace: as for launch_approx.
 hipError_t launch_approx_lean(const Plan &plan, const void *x, void *out_vals, int32_t *out_idx, void *state,
                               hipStream_t stream, void *trace = nullptr);
-
-// ------------------------------------------------------------------------------------
-// exact_topk plan
-struct ExactPlan {
-    int dtype;
-    int64_t m, n, k;
-    int64_t idx_n;          // column indices are below this (n, unless the rows are lists of (value, index) pairs)
-    bool single_wg;         // whole row fits one workgroup's LDS
-    int T;
-    int lds_bytes;
-    int chunks;             // workgroups per row of the global path
-    int chunk_elems;        // elements of a row that one of them sweeps
-    bool filter;            // small k: rows may finish through the copy-out buffer
-    int filter_cap;         // ... of this many elements per row
-    bool sample;            // very small k on big inputs: the copy-out threshold is first guessed from a sample of the row
-    int64_t scratch_bytes;  // data pool
-    int64_t state_bytes;    // zeroed-state pool
-};
-int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, ExactPlan *plan);
-// xi: NULL, or (device, m x n int32) the column index each element of x stands for: the rows are then
-// lists of (value, index) pairs with distinct indices below plan.idx_n, and the order among equal
-// values and out_idx follow those indices (Stage 2 over more candidates than fit one workgroup).
-hipError_t launch_exact(const ExactPlan &plan, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
-                        void *state, void *data, hipStream_t stream);
 
 // ------------------------------------------------------------------------------------
 // Device helpers.

@@ -1,0 +1,49 @@
+// exact_topk: plans and launch entry points.
+#pragma once
+
+#include "atk_common.h"
+
+namespace atk {
+
+// exact_topk plan: rows that one workgroup holds in registers (atk_exact_row.hip) ...
+constexpr int kRowMaxK = 16384;   // survivors that its selection orders in LDS
+constexpr int kRowBinMax = 64;    // fullest bin whose elements it ranks by comparing them with one another
+struct RowPlan {
+    int T, nv;          // threads per workgroup, 16-byte vectors of the row per lane
+    int lg_bins;        // log2 of the histogram's bins
+    int filed_words;    // composites that the LDS holds
+    int cap;            // elements at or above the first guess that pass through LDS (0: none do)
+    int lds_bytes;
+    int sub, gl;        // groups of the first guess: parts of a lane's elements, or lanes side by side
+};
+// false: the row does not fit.  pairs: the rows are lists of (value, index) pairs.  ptr16: x lies on a 16-byte boundary.
+bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, RowPlan *out);
+hipError_t launch_exact_row(const RowPlan &pl, int64_t m, int64_t n, int64_t k, int64_t idx_n, int dtype, const void *x,
+                            const int32_t *xi, void *out_vals, int32_t *out_idx, hipStream_t stream);
+// A kernel that is about to be launched with more dynamic LDS than a launch may ask for by default is told so, once per
+// device (told: that kernel's own flags).
+hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]);
+
+// ... and longer ones
+struct ExactPlan {
+    int dtype;
+    int64_t m, n, k;
+    int64_t idx_n;          // column indices are below this (n, unless the rows are lists of (value, index) pairs)
+    bool single_wg;         // one workgroup per row, the row in its registers (`row`)
+    RowPlan row;
+    int chunks;             // workgroups per row of the global path
+    int chunk_elems;        // elements of a row that one of them sweeps
+    bool filter;            // small k: rows may finish through the copy-out buffer
+    int filter_cap;         // ... of this many elements per row
+    bool sample;            // very small k on big inputs: the copy-out threshold is first guessed from a sample of the row
+    int64_t scratch_bytes;  // data pool
+    int64_t state_bytes;    // zeroed-state pool
+};
+int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *plan);
+// xi: NULL, or (device, m x n int32) the column index each element of x stands for: the rows are then
+// lists of (value, index) pairs with distinct indices below plan.idx_n, and the order among equal
+// values and out_idx follow those indices (Stage 2 over more candidates than fit one workgroup).
+hipError_t launch_exact(const ExactPlan &plan, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
+                        void *state, void *data, hipStream_t stream);
+
+}  // namespace atk

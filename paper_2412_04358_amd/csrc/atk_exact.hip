@@ -1,9 +1,8 @@
 // exact_topk: the exact comparison point (Section 1; RadixSelect of Appendix D.2).
 //
-// Small rows: one workgroup per row; the row's composites live in LDS and go through the
-// same radix select + ordering as Stage 2.
+// Rows that one workgroup holds in registers: atk_exact_row.hip.
 //
-// Long rows: the RadixSelect scheme on the 64-bit composite (value key, then index, so that
+// Longer rows: the RadixSelect scheme on the 64-bit composite (value key, then index, so that
 // ties at the k-th value resolve to the lowest indices - the "second collect step" the
 // listing's caption mentions), most significant digit first, 11-bit digits over the bits of the
 // composite that can differ between elements (see Squeeze).  One pass = a histogram kernel over
@@ -21,6 +20,7 @@
 #include <cstring>
 
 #include "atk_common.h"
+#include "atk_exact.h"
 #include "atk_select.h"
 
 namespace atk {
@@ -69,30 +69,24 @@ int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, ExactPlan *pl) {
+int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *pl) {
     ExactPlan p;
     p.dtype = dtype;
     p.m = m;
     p.n = n;
     p.k = k;
-    p.T = kMaxThreads;
     p.chunks = 1;
     p.chunk_elems = kExChunk;
     p.scratch_bytes = 0;
     p.state_bytes = 0;
-    p.lds_bytes = 0;
     p.filter = false;
     p.filter_cap = kFilterCap;
     p.sample = false;
     p.idx_n = n;
     if (m >= (1ll << 31)) return ATK_ERR_UNSUPPORTED;
-    const int64_t lds = select_lds_bytes(n, (int)pow2_ceil64(k < (1 << 20) ? k : (1 << 20)));
-    // One workgroup per row while the row fits 64 KB of LDS; up to all 160 KB of a CU (about 18000
-    // elements) when there is at most one row per CU: one launch instead of ten (128 x 8192: 41 -> 24 us).
-    // With more rows the sweeps of the long-row path use the chip better (2048 x 8192: 110 against 270 us).
-    p.single_wg = lds <= kLdsBudget || (lds <= kLdsBudgetWholeRow && m <= kNumCU);
+    const PlanOverride &ov = plan_override();
+    p.single_wg = !ov.xr_off && !ov.xs && !ov.xc && plan_exact_row(m, n, k, dtype, pairs, ptr16, &p.row);
     if (p.single_wg) {
-        p.lds_bytes = (int)lds;
         *pl = p;
         return ATK_OK;
     }
@@ -138,33 +132,6 @@ int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, ExactPlan *pl) {
     p.scratch_bytes = bytes;
     *pl = p;
     return ATK_OK;
-}
-
-// ------------------------------------------------------------------------------------ small rows
-template <int ELT>
-__global__ void __launch_bounds__(kMaxThreads) exact_small_kernel(const void *x, const int32_t *xi, int n, int k, int idx_bits,
-                                                                  void *out_vals, int32_t *out_idx) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    u64 *cand = (u64 *)smem;
-    const int r = blockIdx.x;
-    const int T = blockDim.x;
-    auto load_bits = [&](int i) -> uint32_t {
-        if (ELT == ATK_F32) return ((const uint32_t *)x)[(int64_t)r * n + i];
-        return ((uint32_t)((const uint16_t *)x)[(int64_t)r * n + i]) << 16;
-    };
-    auto index_of = [&](int i) -> int32_t { return xi ? xi[(int64_t)r * n + i] : i; };
-    int i = threadIdx.x;
-    for (; i + 3 * T < n; i += 4 * T) {  // four loads in flight
-        uint32_t b0 = load_bits(i), b1 = load_bits(i + T), b2 = load_bits(i + 2 * T), b3 = load_bits(i + 3 * T);
-        const int32_t i0 = index_of(i), i1 = index_of(i + T), i2 = index_of(i + 2 * T), i3 = index_of(i + 3 * T);
-        cand[i] = make_composite(b0, i0);
-        cand[i + T] = make_composite(b1, i1);
-        cand[i + 2 * T] = make_composite(b2, i2);
-        cand[i + 3 * T] = make_composite(b3, i3);
-    }
-    for (; i < n; i += T) cand[i] = make_composite(load_bits(i), index_of(i));
-    __syncthreads();
-    select_write<ELT>(cand, n, k, idx_bits, out_vals, out_idx, (int64_t)r);
 }
 
 // ------------------------------------------------------------------------------------ long rows
@@ -960,9 +927,7 @@ __global__ void __launch_bounds__(256) sort_rows_kernel(u64 *buf0, u64 *buf1, co
     for (int64_t i = tid; i < k; i += 256) write_composite<ELT>(src[i], out_vals, out_idx, (int64_t)r * k + i);
 }
 
-// A kernel that is about to be launched with more dynamic LDS than a launch may ask for by default is
-// told so, once per device (told: that kernel's own flags).
-static hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]) {
+hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -977,18 +942,6 @@ template <int ELT>
 static hipError_t launch_exact_t(const ExactPlan &pl, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
                                  void *state, void *data, hipStream_t stream) {
     const int64_t m = pl.m, n = pl.n, k = pl.k;
-    if (pl.single_wg) {
-        int small_bits = 1;
-        while (((int64_t)1 << small_bits) < pl.idx_n) ++small_bits;
-        if (pl.lds_bytes > 64 * 1024) {
-            static bool told[64] = {};
-            const hipError_t ea = allow_whole_cu_lds((const void *)exact_small_kernel<ELT>, told);
-            if (ea != hipSuccess) return ea;
-        }
-        hipLaunchKernelGGL(exact_small_kernel<ELT>, dim3((unsigned)m), dim3(pl.T), (size_t)pl.lds_bytes, stream, x, xi, (int)n,
-                           (int)k, small_bits, out_vals, out_idx);
-        return hipGetLastError();
-    }
     uint32_t *ghist = (uint32_t *)state;
     ExRowState *st = (ExRowState *)data;
     const int64_t st_bytes = ceil_div64(m * (int64_t)sizeof(ExRowState), 256) * 256;
@@ -1130,6 +1083,7 @@ static hipError_t launch_exact_t(const ExactPlan &pl, const void *x, const int32
 
 hipError_t launch_exact(const ExactPlan &pl, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
                         void *state, void *data, hipStream_t stream) {
+    if (pl.single_wg) return launch_exact_row(pl.row, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, stream);
     if (pl.dtype == ATK_F32) return launch_exact_t<ATK_F32>(pl, x, xi, out_vals, out_idx, state, data, stream);
     return launch_exact_t<ATK_BF16>(pl, x, xi, out_vals, out_idx, state, data, stream);
 }
