@@ -12,14 +12,20 @@ struct RowPlan {
     int T, nv;          // threads per workgroup, 16-byte vectors of the row per lane
     int lg_bins;        // log2 of the histogram's bins
     int filed_words;    // composites that the LDS holds
-    int cap;            // elements at or above the first guess that pass through LDS (0: none do)
+    int cap;            // elements at or above the first bound that pass through LDS (0: none do)
     int lds_bytes;
-    int sub, gl;        // groups of the first guess: parts of a lane's elements, or lanes side by side
+    int sub, rank;      // the first lower bound: the rank-th largest of the maxima of 64 * sub groups in every wavefront
+    int ve;             // elements per vector
+    int parts;          // > 0: workgroups to a row, each with part_vecs vectors of it, which pass on up to part_cap elements
+    int part_vecs, part_cap;
 };
 // false: the row does not fit.  pairs: the rows are lists of (value, index) pairs.  ptr16: x lies on a 16-byte boundary.
 bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, RowPlan *out);
 hipError_t launch_exact_row(const RowPlan &pl, int64_t m, int64_t n, int64_t k, int64_t idx_n, int dtype, const void *x,
-                            const int32_t *xi, void *out_vals, int32_t *out_idx, hipStream_t stream);
+                            const int32_t *xi, void *out_vals, int32_t *out_idx, void *state, void *data, hipStream_t stream);
+bool plan_exact_parts(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, RowPlan *out);
+int64_t exact_parts_state_bytes(int64_t m);
+int64_t exact_parts_data_bytes(const RowPlan &pl, int64_t m);
 // A kernel that is about to be launched with more dynamic LDS than a launch may ask for by default is told so, once per
 // device (told: that kernel's own flags).
 hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]);
@@ -30,6 +36,7 @@ struct ExactPlan {
     int64_t m, n, k;
     int64_t idx_n;          // column indices are below this (n, unless the rows are lists of (value, index) pairs)
     bool single_wg;         // one workgroup per row, the row in its registers (`row`)
+    bool parts;             // several, each with a part of it (`row`)
     RowPlan row;
     int chunks;             // workgroups per row of the global path
     int chunk_elems;        // elements of a row that one of them sweeps

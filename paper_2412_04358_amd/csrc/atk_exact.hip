@@ -83,12 +83,22 @@ int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
     p.filter_cap = kFilterCap;
     p.sample = false;
     p.idx_n = n;
+    p.single_wg = p.parts = false;
     if (m >= (1ll << 31)) return ATK_ERR_UNSUPPORTED;
     const PlanOverride &ov = plan_override();
-    p.single_wg = !ov.xr_off && !ov.xs && !ov.xc && plan_exact_row(m, n, k, dtype, pairs, ptr16, &p.row);
-    if (p.single_wg) {
-        *pl = p;
-        return ATK_OK;
+    if (!ov.xr_off && !ov.xs && !ov.xc) {
+        p.parts = !pairs && m <= 65535 && plan_exact_parts(m, n, k, dtype, ptr16, &p.row);
+        if (p.parts) {
+            p.state_bytes = exact_parts_state_bytes(m);
+            p.scratch_bytes = exact_parts_data_bytes(p.row, m);
+            *pl = p;
+            return ATK_OK;
+        }
+        p.single_wg = plan_exact_row(m, n, k, dtype, pairs, ptr16, &p.row);
+        if (p.single_wg) {
+            *pl = p;
+            return ATK_OK;
+        }
     }
     // inputs that do not fill the chip with 16384-element chunks: smaller ones, as long as the sweep stays a launch
     // whose last workgroup per row decides the digit (128 x 65536, k = 64: 55 -> 44 us; 1 x 2^20: 47 -> 34 us)
@@ -1083,7 +1093,8 @@ static hipError_t launch_exact_t(const ExactPlan &pl, const void *x, const int32
 
 hipError_t launch_exact(const ExactPlan &pl, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
                         void *state, void *data, hipStream_t stream) {
-    if (pl.single_wg) return launch_exact_row(pl.row, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, stream);
+    if (pl.single_wg || pl.parts)
+        return launch_exact_row(pl.row, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, state, data, stream);
     if (pl.dtype == ATK_F32) return launch_exact_t<ATK_F32>(pl, x, xi, out_vals, out_idx, state, data, stream);
     return launch_exact_t<ATK_BF16>(pl, x, xi, out_vals, out_idx, state, data, stream);
 }

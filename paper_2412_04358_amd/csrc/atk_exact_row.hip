@@ -2,26 +2,30 @@
 // select from): one launch, one workgroup per row, the row read once.
 //
 //   1. Every lane loads its share of the row, 16 bytes per load, all loads in flight together.
-//   2. A guess of a value that at least k elements reach: the smallest of the maxima of G groups of lanes (or of parts of a
-//      lane's elements).  With the elements spread over the groups at random, about G ln G of them lie at or above it
-//      (the coupon collector's count), so G is the smallest with half of that at k or more.  It is checked, not trusted.
-//   3. A histogram of the elements from there on, over bins linear in (value key, index) between the guess and the row's
-//      maximum; a descending prefix sum turns counts into places.  Fewer than k counted: again from -inf.  A bin too full
-//      to be ranked by comparing its elements with one another: again from the lower edge of the bin that holds the
-//      k-th, which is a range without what lies below (values around zero stretch a range of keys over every exponent).
+//   2. A lower bound on the k-th largest: every wavefront finds the rank-th largest of the maxima of its groups of elements (of
+//      a lane's elements, or of parts of them), with wavefronts times rank just over k, and the smallest of these is
+//      reached by at least k elements; among elements in no particular order, by not many more (k = 256 of 128256: 370; the
+//      minimum over as many groups' maxima, which needs no selection in the wavefront, lets 1400 through and now and then 3000).
+//   3. A histogram of the elements from there on, over bins linear in (value key, index) between the bound and the row's
+//      maximum; a descending prefix sum turns counts into places.  A bin too full to be ranked by comparing its elements
+//      with one another: again from the lower edge of the bin that holds the k-th, which is a range without what lies
+//      below (values around zero stretch a range of keys over every exponent).
 //   4. The elements of the bins down to the k-th's go to LDS, bin by bin; each finds its rank as its bin's start plus
 //      the larger elements of its bin.  Lanes side by side take places side by side, so the row is written nearly in order.
 // Rows whose bins stay crowded (long runs of one value) are selected digit by digit (RadixSelect, Appendix D.2) and ordered
 // by order_write(); they re-read the row, which is in the caches by then.
+// Longer rows, and long rows of small batches, are shared out between workgroups (ex_parts_kernel).
 //
 // What bounds it: with at most one row per CU, the rate at which one CU takes in a row (about 45 GB/s, measured: 256 KB in
 // 5.8 us) and then the operations on every element; with many rows the latter, shared out over the workgroups of a CU.
 // Measured against the launches this replaced (a histogram, a decision, a copy-out and a selection; one workgroup
-// with the row in LDS for short rows): 2048 x 8192 bf16, k = 512: 79.7 -> 22.5 us; 64 x 128256 bf16, k = 256: 28.7 -> 19.1;
-// 1024 x 65536 f32, k = 64: 106 -> 72; 128 x 65536 f32, k = 16384: 148 -> 57; one row of 65536 f32, k = 4096: 120 -> 31;
-// 2048 x 2048 f32, k = 64: 43 -> 10.4; 128 lists of 8192 pairs, k = 4096 (Stage 2): 118 -> 12.4.
+// with the row in LDS for short rows): 2048 x 8192 bf16, k = 512: 79.9 -> 19.5 us; 64 x 128256 bf16, k = 256: 28.9 -> 12.0;
+// 1024 x 65536 f32, k = 64: 106 -> 62; 128 x 65536 f32, k = 16384: 148 -> 57; one row of 65536 f32, k = 4096: 120 -> 32;
+// 2048 x 2048 f32, k = 64: 43 -> 8.2; 128 lists of 8192 pairs, k = 4096 (Stage 2): 118 -> 12.4.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "atk_common.h"
 #include "atk_exact.h"
@@ -36,8 +40,14 @@ struct RowParams {
     int32_t *out_idx;
     int n, k, idx_bits;
     int lg_bins, filed_words;
-    int cap;              // elements at or above the guess that LDS holds in passing (0: they stay in the registers)
-    int sub, gl;          // groups of the guess: sub > 1 parts of a lane's elements each, else gl lanes side by side
+    int cap;              // elements at or above the bound that LDS holds in passing (0: they stay in the registers)
+    int sub, rank;        // the bound: the rank-th largest of 64 * sub maxima in every wavefront
+    // several workgroups to a row
+    int parts, part_vecs;   // workgroups per row, 16-byte vectors of the row that each reads
+    int part_cap;           // elements that each passes on
+    u64 *lists;             // [row][part][part_cap] composites
+    u64 *heads;             // [row][part][2]: (bound << 32 | elements passed on), the part's largest key
+    uint32_t *tickets;      // one per row, kTicketStride apart, zero between calls
 };
 
 typedef uint32_t row_v4u __attribute__((ext_vector_type(4)));
@@ -133,11 +143,26 @@ __device__ __forceinline__ u64 row_composite(const RowParams &p, int64_t r, int 
     return make_composite(bits, p.xi ? p.xi[r * p.n + i] : i);
 }
 
+// f(composite) for every element of row r that this lane takes, eight loads in flight
+template <int ELT, typename F>
+__device__ __forceinline__ void row_sweep(const RowParams &p, int64_t r, F f) {
+    const int T = blockDim.x;
+    int i = threadIdx.x;
+    for (; i + 7 * T < p.n; i += 8 * T) {
+        u64 c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = row_composite<ELT>(p, r, i + u * T);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f(c[u]);
+    }
+    for (; i < p.n; i += T) f(row_composite<ELT>(p, r, i));
+}
+
 // Digit by digit over the row, most significant first, on the composite without the bits that carry nothing (the low 16
 // of a bf16 key, the index bits above idx_bits); the k survivors are then put in order.
 template <int ELT>
 __device__ __forceinline__ void row_by_digits(const RowParams &p, int64_t r, u64 *filed, uint32_t *cur, uint32_t *misc) {
-    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1);
+    const int tid = threadIdx.x, T = blockDim.x;
     const int drop = ELT == ATK_BF16 ? 16 : 0, keep = p.idx_bits + 1;
     auto squeeze = [&](u64 c) { return ((c >> (32 + drop)) << keep) | (c & ((1ull << keep) - 1ull)); };
     const int n_bins = 1 << p.lg_bins;
@@ -150,10 +175,10 @@ __device__ __forceinline__ void row_by_digits(const RowParams &p, int64_t r, u64
         const u64 hi_mask = top >= 64 ? 0ull : (~0ull << top);
         for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
         __syncthreads();
-        for (int i = tid; i < p.n; i += T) {
-            const u64 q = squeeze(row_composite<ELT>(p, r, i));
+        row_sweep<ELT>(p, r, [&](u64 c) {
+            const u64 q = squeeze(c);
             if ((q & hi_mask) == prefix) atomicAdd(&cur[(uint32_t)(q >> shift) & ((1u << w) - 1u)], 1u);
-        }
+        });
         __syncthreads();
         row_scan(cur, misc, n_bins, need);
         prefix |= (u64)misc[0] << shift;
@@ -166,47 +191,257 @@ __device__ __forceinline__ void row_by_digits(const RowParams &p, int64_t r, u64
     if (tid == 0) misc[5] = 0u;
     for (int i = tid; i < kRankMax; i += T) cur[i] = 0u;
     __syncthreads();
-    for (int i0 = 0; i0 < p.n; i0 += T) {
-        const int i = i0 + tid;
-        const u64 c = i < p.n ? row_composite<ELT>(p, r, i) : 0ull;
-        const bool take = i < p.n && squeeze(c) >= prefix;
-        const u64 mask = __ballot(take);
-        if (mask) {  // uniform over the wavefront
-            uint32_t at = 0;
-            if (lane == 0) at = atomicAdd(&misc[5], (uint32_t)__popcll(mask));
-            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
-                 __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-            if (take && at < (uint32_t)p.k) filed[at] = c;
+    row_sweep<ELT>(p, r, [&](u64 c) {
+        if (squeeze(c) >= prefix) {  // k of them
+            const uint32_t at = atomicAdd(&misc[5], 1u);
+            if (at < (uint32_t)p.k) filed[at] = c;
         }
-    }
+    });
     __syncthreads();
     order_write<ELT>(filed, p.k, cur, p.out_vals, p.out_idx, r);
+}
+
+// ---- a row, or a part of one, in the registers of a workgroup: lane t holds the vectors v0 + t, v0 + t + T, ... below v1
+template <int ELT, int NV>
+struct RowRegs {
+    static constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES, E = NV * VE;
+    row_v4u q[NV];
+    int i0;  // row position of the lane's first element
+
+    // The row from the 16-byte boundary at or before its first element to the one at or after its last (no vector without an
+    // element of the row is read); elements of the neighbours become NaN, which no comparison below lets through.
+    __device__ __forceinline__ void load(const RowParams &p, int64_t r, int v0, int v1, int rot) {
+        const int tid = threadIdx.x, T = blockDim.x;
+        const uintptr_t addr = (uintptr_t)p.x + (uintptr_t)(r * p.n) * ES;
+        const row_v4u *row = (const row_v4u *)(addr & ~(uintptr_t)15);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const int v = v0 + tid + j * T;
+            q[j] = row[v < v1 ? v : v0];
+        }
+        i0 = (v0 + tid) * VE - rot;
+    }
+    __device__ __forceinline__ void mask_ends(const RowParams &p, int v0, int v1, int rot) {
+        const int tid = threadIdx.x, T = blockDim.x;
+        const int end = rot + p.n, last = (end - 1) / VE;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const int v = v0 + tid + j * T;
+            if (v >= v1) {
+                const row_v4u none = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+                q[j] = none;
+            } else if (v == 0 || v == last) {
+#pragma unroll
+                for (int e = 0; e < VE; ++e) {
+                    const int at = v * VE + e;
+                    if (at < rot || at >= end) {
+                        if (ELT == ATK_F32)
+                            q[j][e] = 0xffffffffu;
+                        else
+                            q[j][e >> 1] |= (e & 1) ? 0xffff0000u : 0x0000ffffu;
+                    }
+                }
+            }
+        }
+    }
+
+    // f(value bits, position in the row, element number) for every element of this lane.  The words pass through an empty
+    // asm statement: else what is worked out from them (order keys, positions, comparisons) is kept in registers from one
+    // pass over the elements to the next, and spills.
+    template <typename F>
+    __device__ __forceinline__ void each(F f) {
+        const int T = blockDim.x;
+        int at = i0;
+        asm volatile("" : "+v"(at));
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int e = 0; e < VE; ++e) {
+                if (ELT == ATK_F32 || (e & 1) == 0) asm volatile("" : "+v"(q[j][ELT == ATK_F32 ? e : (e >> 1)]));
+                const uint32_t a = q[j][ELT == ATK_F32 ? e : (e >> 1)];
+                f(ELT == ATK_F32 ? a : ((e & 1) ? (a & 0xffff0000u) : (a << 16)), at + j * T * VE + e, j * VE + e);
+            }
+    }
+
+    // A lower bound: every wavefront's `rank`-th largest of the maxima of its groups - the smallest of these over the wavefronts is
+    // reached by rank elements in each of them (and the largest element).  sub (1, 2, 4 or 8) groups per lane.  Where a wavefront has
+    // fewer elements than that the bound is the lowest key there is.  rank 0: the smallest of the maxima.  Called by the whole workgroup; two barriers.
+    __device__ __forceinline__ void bound(int sub, int rank, uint32_t *misc, uint32_t &k_min, uint32_t &k_max) {
+        const int tid = threadIdx.x, lane = tid & (kWave - 1), n_waves = blockDim.x >> 6;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        constexpr int SM = NV * 4 < 8 ? 4 : 8;
+        float mx[SM];
+#pragma unroll
+        for (int i = 0; i < SM; ++i) mx[i] = __uint_as_float(0x7fc00000u);
+#pragma unroll
+        for (int w = 0; w < NV * 4; ++w) {
+            const uint32_t a = q[w >> 2][w & 3];
+            const float f = ELT == ATK_F32 ? __uint_as_float(a) : fmaxf(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u));
+            mx[w % SM] = fmaxf(mx[w % SM], f);  // (the number where one of the two is NaN)
+        }
+        auto key_of = [](float f) { return f == f ? ukey_of_bits(__float_as_uint(f)) : 0u; };
+        // The rank-th largest of the S * 64 keys of a wavefront, to its highest 16 bits (the bits below stay zero, which
+        // can only lower the bound, by under one part in 128): bit by bit from the top, counting the keys that agree so far.
+        auto nth = [&](auto s_tag) {
+            constexpr int S = decltype(s_tag)::value;
+            uint32_t key[S];
+            uint32_t top = 0u;
+#pragma unroll
+            for (int i = 0; i < S; ++i) {
+                float m = mx[i];
+#pragma unroll
+                for (int j = i + S; j < SM; j += S) m = fmaxf(m, mx[j]);
+                key[i] = key_of(m);
+                top = max(top, key[i]);
+            }
+            k_max = top;
+            if (rank == 0) {
+                k_min = 0xffffffffu;
+#pragma unroll
+                for (int i = 0; i < S; ++i) k_min = key[i] && key[i] < k_min ? key[i] : k_min;
+                k_min = wave_min_u32(k_min);
+                return;
+            }
+            uint32_t have = 0u;
+#pragma unroll
+            for (int bit = 31; bit >= 16; --bit) {
+                const uint32_t want = have | (1u << bit);
+                int cnt = 0;
+#pragma unroll
+                for (int i = 0; i < S; ++i) cnt += __popcll(__ballot(key[i] >= want));
+                if (cnt >= rank) have = want;
+            }
+            k_min = have;
+        };
+        if (sub == 1)
+            nth(std::integral_constant<int, 1>());
+        else if (sub == 2)
+            nth(std::integral_constant<int, 2>());
+        else if (sub == 4 || SM == 4)
+            nth(std::integral_constant<int, 4>());
+        else
+            nth(std::integral_constant<int, SM>());
+        k_max = wave_max_u32(k_max);
+        if (lane == 0) {
+            misc[8 + wave] = k_min;
+            misc[24 + wave] = k_max;
+        }
+        __syncthreads();
+        k_min = wave_min_u32(lane < n_waves ? misc[8 + lane] : 0xffffffffu);
+        k_max = wave_max_u32(lane < n_waves ? misc[24 + lane] : 0u);
+        if (k_min < 0x007fffffu) k_min = 0x007fffffu;  // (-inf's)
+        if (k_min > k_max) k_min = k_max;
+        __syncthreads();  // (the words are used again)
+    }
+
+    // Positions of the elements at or above v_lo to list[0 .. ] (at most cap of them); the cursor *count starts from zero and
+    // ends as their number.  Two operations per element set a bit each - a comparison and an addition of the mask
+    // to itself with the comparison as carry -, the few that are set are then taken one by one: storing an element under
+    // its own condition costs every element the six or so operations of a branch that few of the lanes take
+    // (64 x 128256 bf16, k = 256: 8.2 us of the kernel's 18).  Called by the whole workgroup; ends in a barrier.
+    __device__ __forceinline__ void list_from(float v_lo, int2 *list, uint32_t cap, uint32_t *count) {
+        const int lane = threadIdx.x & (kWave - 1), T = blockDim.x;
+        constexpr int M = (E + 31) / 32;  // masks of 32 elements, the last perhaps of fewer
+        uint32_t mk[M];
+#pragma unroll
+        for (int w = 0; w < M; ++w) mk[w] = 0u;
+        each([&](uint32_t bits, int, int en) {
+            asm volatile("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mk[en / 32]) : "v"(v_lo), "v"(bits) : "vcc");
+        });
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int w = 0; w < M; ++w) cnt += (uint32_t)__popc(mk[w]);
+        const uint32_t incl = wave_incl_scan_u32(cnt);
+        uint32_t at = 0;
+        if (lane == kWave - 1) at = atomicAdd(count, incl);
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + incl - cnt;
+#pragma unroll
+        for (int w = 0; w < M; ++w) {
+            uint32_t b = mk[w] << (32 - (E - 32 * w < 32 ? E - 32 * w : 32));  // the first element's bit is bit 31
+            while (b) {
+                const int t = __clz((int)b), en = w * 32 + t;
+                b &= ~(0x80000000u >> t);
+                if (at < cap) list[at].y = i0 + (en / VE) * T * VE + en % VE;
+                ++at;
+            }
+        }
+        __syncthreads();
+    }
+};
+
+// value bits of element `at` of row r
+template <int ELT>
+__device__ __forceinline__ uint32_t row_bits(const RowParams &p, int64_t r, int at) {
+    return (ELT == ATK_F32) ? ((const uint32_t *)p.x)[r * p.n + at] : ((uint32_t)((const uint16_t *)p.x)[r * p.n + at]) << 16;
+}
+
+// The filed elements (bin by bin, cur[b] the place behind bin b) find their ranks and are written.
+template <int ELT>
+__device__ __forceinline__ void row_rank_write(const RowParams &p, int64_t r, const RowBins &bins, const u64 *filed, int filed_n,
+                                               const uint32_t *cur, int n_bins) {
+    for (int i = threadIdx.x; i < filed_n; i += blockDim.x) {
+        const u64 c = filed[i];
+        const uint32_t b = bins.template bin<ELT>((uint32_t)(c >> 32), (uint32_t)c >> 1);
+        const int s = b + 1u < (uint32_t)n_bins ? (int)cur[b + 1] : 0, e = (int)cur[b];
+        u64 peer[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) peer[u] = filed[s + u < e ? s + u : i];  // (itself: not larger)
+        int rank = s;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rank += peer[u] > c ? 1 : 0;
+        for (int j = s + 4; j < e; ++j) rank += filed[j] > c ? 1 : 0;
+        if (rank < p.k) write_composite<ELT>(c, p.out_vals, p.out_idx, r * p.k + rank);
+    }
+}
+
+// Selects and writes the row's k largest from passed[0 .. n_passed) (value bits, column index), all at or above k_min, k or
+// more of them.  cur: zeroed bins.  False where a bin is too full to be ranked: nothing is written then, and k_min is raised to
+// the lower edge of the k-th largest's bin.  Called by the whole workgroup after a barrier.
+template <int ELT>
+__device__ __forceinline__ bool row_select_passed(const RowParams &p, int64_t r, const int2 *passed, uint32_t n_passed, uint32_t &k_min,
+                                                  uint32_t k_max, u64 *filed, uint32_t *cur, uint32_t *misc) {
+    const int tid = threadIdx.x, T = blockDim.x, n_bins = 1 << p.lg_bins;
+    RowBins bins;
+    bins.template set<ELT>(k_min, k_max, p.idx_bits, n_bins);
+    for (uint32_t i = tid; i < n_passed; i += T) {
+        const int2 w = passed[i];
+        atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits((uint32_t)w.x), 0x7fffffffu - (uint32_t)w.y)], 1u);
+    }
+    __syncthreads();
+    row_scan(cur, misc, n_bins, (uint32_t)p.k);
+    const uint32_t tb = misc[0];
+    if (misc[4] != 0u) {
+        const uint32_t lo = bins.template edge<ELT>(tb);
+        if (lo > k_min) k_min = lo;
+        __syncthreads();
+        return false;
+    }
+    for (uint32_t i = tid; i < n_passed; i += T) {
+        const int2 w = passed[i];
+        const uint32_t b = bins.template bin<ELT>(ukey_of_bits((uint32_t)w.x), 0x7fffffffu - (uint32_t)w.y);
+        if (b >= tb) filed[atomicAdd(&cur[b], 1u)] = make_composite((uint32_t)w.x, w.y);
+    }
+    __syncthreads();
+    row_rank_write<ELT>(p, r, bins, filed, (int)cur[tb], cur, n_bins);
+    return true;
 }
 
 template <int ELT, int NV, bool XI>
 __global__ void __launch_bounds__(1024) ex_row_kernel(RowParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES;
-    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1), n_waves = T >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, T = blockDim.x;
     const int64_t r = blockIdx.x;
     const int n_bins = 1 << p.lg_bins;
     u64 *filed = (u64 *)smem;
     uint32_t *cur = (uint32_t *)(filed + p.filed_words);  // [n_bins], then a zero: nothing lies above the last bin
     uint32_t *misc = cur + n_bins + 4;
+    int2 *passed = (int2 *)(misc + kRowMisc);
 
-    // ---- the row, from the 16-byte boundary at or before its first element to the one at or after its last (no vector
-    // without an element of the row is read); elements of the neighbours become NaN, which no comparison below lets through
-    const uintptr_t addr = (uintptr_t)p.x + (uintptr_t)(r * p.n) * ES;
-    const int rot = (int)(addr & 15) / ES, end = rot + p.n;
+    const int rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & 15) / ES, end = rot + p.n;
     const int n_vec = (end + VE - 1) / VE;
-    const row_v4u *row = (const row_v4u *)(addr & ~(uintptr_t)15);
-    row_v4u q[NV];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int v = tid + j * T;
-        q[j] = __builtin_nontemporal_load(row + (v < n_vec ? v : 0));
-    }
+    RowRegs<ELT, NV> regs;
+    regs.load(p, r, 0, n_vec, rot);
     int32_t xi[XI ? NV * VE : 1];
     if constexpr (XI) {
         // (the pairs' two arrays start on 16-byte boundaries, so a vector of values and its indices do together)
@@ -228,147 +463,35 @@ __global__ void __launch_bounds__(1024) ex_row_kernel(RowParams p) {
     }
     for (int i = tid; i < n_bins + 4; i += T) cur[i] = 0u;
     if (tid == 0) misc[5] = 0u;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int v = tid + j * T;
-        if (v >= n_vec) {
-            const row_v4u none = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-            q[j] = none;
-        } else if (v == 0 || v == n_vec - 1) {
-#pragma unroll
-            for (int e = 0; e < VE; ++e) {
-                const int at = v * VE + e;
-                if (at < rot || at >= end) {
-                    if (ELT == ATK_F32)
-                        q[j][e] = 0xffffffffu;
-                    else
-                        q[j][e >> 1] |= (e & 1) ? 0xffff0000u : 0x0000ffffu;
-                }
-            }
-        }
-    }
+    regs.mask_ends(p, 0, n_vec, rot);
+    uint32_t k_min, k_max;
+    regs.bound(p.sub, p.rank, misc, k_min, k_max);
 
-    // ---- the guess: maxima of groups
-    constexpr int SM = NV * 4 < 8 ? 4 : 8;
-    float mx[SM];
-#pragma unroll
-    for (int i = 0; i < SM; ++i) mx[i] = __uint_as_float(0x7fc00000u);
-#pragma unroll
-    for (int w = 0; w < NV * 4; ++w) {
-        const uint32_t a = q[w >> 2][w & 3];
-        const float f = ELT == ATK_F32 ? __uint_as_float(a) : fmaxf(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u));
-        mx[w % SM] = fmaxf(mx[w % SM], f);  // (the number where one of the two is NaN)
-    }
-    auto key_of = [](float f) { return f == f ? ukey_of_bits(__float_as_uint(f)) : 0u; };
-    uint32_t k_min = 0xffffffffu, k_max;
-    {
-        if (SM > 4 && p.sub <= 4) {
-#pragma unroll
-            for (int i = 0; i < SM / 2; ++i) mx[i] = fmaxf(mx[i], mx[i + SM / 2]);
-        }
-        if (p.sub <= 2) {
-            mx[0] = fmaxf(mx[0], mx[2]);
-            mx[1] = fmaxf(mx[1], mx[3]);
-        }
-        if (p.sub <= 1) mx[0] = fmaxf(mx[0], mx[1]);
-        float m = mx[0];
-        if (p.sub > 1) {
-#pragma unroll
-            for (int i = 0; i < SM; ++i)
-                if (i < p.sub) {
-                    const uint32_t key = key_of(mx[i]);
-                    k_min = key && key < k_min ? key : k_min;
-                    m = fmaxf(m, mx[i]);
-                }
-            k_max = key_of(m);
-        } else {
-            k_max = key_of(m);
-            uint32_t g = k_max;
-            if (p.gl >= 2) g = max(g, dpp_u32<0xB1>(g));
-            if (p.gl >= 4) g = max(g, dpp_u32<0x4E>(g));
-            if (p.gl >= 8) g = max(g, dpp_u32<0x141>(g));
-            if (p.gl >= 16) g = max(g, dpp_u32<0x140>(g));
-            if (p.gl >= 64) g = wave_max_u32(g);
-            k_min = g ? g : 0xffffffffu;
-        }
-    }
-    k_min = wave_min_u32(k_min);
-    k_max = wave_max_u32(k_max);
-    if (lane == 0) {
-        misc[8 + wave] = k_min;
-        misc[24 + wave] = k_max;
-    }
-    __syncthreads();
-    k_min = wave_min_u32(lane < n_waves ? misc[8 + lane] : 0xffffffffu);
-    k_max = wave_max_u32(lane < n_waves ? misc[24 + lane] : 0u);
-    if (k_min > k_max) k_min = k_max;
-    __syncthreads();  // (the words are used again by the scan)
-
-    // f(value, column index) for every element of this lane.  The words pass through an empty asm statement: else what is
-    // worked out from them (order keys, indices, comparisons) is kept in registers from one pass to the next, and spills.
-    auto each = [&](auto f) {
-        int i0 = tid * VE - rot;
-        asm volatile("" : "+v"(i0));
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-#pragma unroll
-            for (int e = 0; e < VE; ++e) {
-                if ((ELT == ATK_F32 || (e & 1) == 0)) asm volatile("" : "+v"(q[j][ELT == ATK_F32 ? e : (e >> 1)]));
-                const uint32_t a = q[j][ELT == ATK_F32 ? e : (e >> 1)];
-                const uint32_t bits = ELT == ATK_F32 ? a : ((e & 1) ? (a & 0xffff0000u) : (a << 16));
-                f(bits, XI ? xi[j * VE + e] : i0 + j * T * VE + e);
-            }
-    };
-    RowBins bins;
-    float v_lo;
-    uint32_t tb;  // bin of the k-th largest
-    bool in_lds = false;
-    int2 *passed = (int2 *)(misc + kRowMisc);
-    uint32_t n_passed = 0;
     int attempt = 0;
     if (p.cap) {
-        // few of the elements reach the guess: they go to LDS (value bits, index) side by side, and the histogram and the
+        // few of the elements reach the bound: they go to LDS (value bits, index) side by side, and the histogram and the
         // filing, a dozen operations and an LDS atomic per element each, run over them instead of over all registers with
-        // most lanes idle (2048 x 8192 bf16, k = 512: 29.7 -> 23.9 us; 2048 x 32768 bf16, k = 256: 68.9 -> 56.5)
-        v_lo = __uint_as_float(bits_of_ukey(k_min));
-        uint32_t cnt = 0;
-        each([&](uint32_t bits, int) { cnt += __uint_as_float(bits) >= v_lo ? 1u : 0u; });
-        const uint32_t incl = wave_incl_scan_u32(cnt);
-        uint32_t at = 0;
-        if (lane == kWave - 1) at = atomicAdd(&misc[5], incl);
-        at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + incl - cnt;
-        each([&](uint32_t bits, int idx) {
-            if (__uint_as_float(bits) >= v_lo) {
-                if (at < (uint32_t)p.cap) passed[at] = make_int2((int)bits, idx);
-                ++at;
-            }
-        });
-        __syncthreads();
-        n_passed = misc[5];
+        // most lanes idle (2048 x 8192 bf16, k = 512: 29.7 -> 20.3 us; 2048 x 32768 bf16, k = 256: 68.9 -> 37.7)
+        regs.list_from(__uint_as_float(bits_of_ukey(k_min)), passed, (uint32_t)p.cap, &misc[5]);
+        const uint32_t n_passed = misc[5];
         if (n_passed >= (uint32_t)p.k && n_passed <= (uint32_t)p.cap) {
-            bins.template set<ELT>(k_min, k_max, p.idx_bits, n_bins);
-            for (uint32_t i = tid; i < n_passed; i += T) {
-                const int2 w = passed[i];
-                atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits((uint32_t)w.x), 0x7fffffffu - (uint32_t)w.y)], 1u);
+            for (uint32_t i = tid; i < n_passed; i += T) {  // (each lane's own entries: no barrier before the histogram reads them)
+                const int at = passed[i].y;
+                passed[i] = make_int2((int)row_bits<ELT>(p, r, at), XI ? p.xi[r * p.n + at] : at);
             }
+            if (row_select_passed<ELT>(p, r, passed, n_passed, k_min, k_max, filed, cur, misc)) return;
+            attempt = 1;
+            for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
             __syncthreads();
-            row_scan(cur, misc, n_bins, (uint32_t)p.k);
-            in_lds = misc[4] == 0u;
-            if (!in_lds) {
-                const uint32_t lo = bins.template edge<ELT>(misc[0]);
-                if (lo > k_min) k_min = lo;
-                attempt = 1;
-                __syncthreads();
-                for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
-                __syncthreads();
-            }
         }
     }
-    for (; !in_lds; ++attempt) {
+    RowBins bins;
+    for (;; ++attempt) {
         bins.template set<ELT>(k_min, k_max, p.idx_bits, n_bins);
-        v_lo = __uint_as_float(bits_of_ukey(k_min));
-        each([&](uint32_t bits, int idx) {
-            if (__uint_as_float(bits) >= v_lo) atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)], 1u);
+        const float v_lo = __uint_as_float(bits_of_ukey(k_min));
+        regs.each([&](uint32_t bits, int at, int en) {
+            if (__uint_as_float(bits) >= v_lo)
+                atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)(XI ? xi[en] : at))], 1u);
         });
         __syncthreads();
         row_scan(cur, misc, n_bins, (uint32_t)p.k);
@@ -386,38 +509,164 @@ __global__ void __launch_bounds__(1024) ex_row_kernel(RowParams p) {
         for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
         __syncthreads();
     }
-
     // ---- the winners' bins, brought together; cur[b] ends as the place behind bin b, which is where bin b - 1 starts
-    tb = misc[0];
-    if (in_lds) {
-        for (uint32_t i = tid; i < n_passed; i += T) {
-            const int2 w = passed[i];
-            const uint32_t b = bins.template bin<ELT>(ukey_of_bits((uint32_t)w.x), 0x7fffffffu - (uint32_t)w.y);
-            if (b >= tb) filed[atomicAdd(&cur[b], 1u)] = make_composite((uint32_t)w.x, w.y);
-        }
-    } else {
-        v_lo = __uint_as_float(bits_of_ukey(bins.template edge<ELT>(tb)));
-        each([&](uint32_t bits, int idx) {
+    const uint32_t tb = misc[0];
+    {
+        const float v_lo = __uint_as_float(bits_of_ukey(bins.template edge<ELT>(tb)));
+        regs.each([&](uint32_t bits, int at, int en) {
             if (__uint_as_float(bits) >= v_lo) {
+                const int idx = XI ? xi[en] : at;
                 const uint32_t b = bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx);
                 if (b >= tb) filed[atomicAdd(&cur[b], 1u)] = make_composite(bits, idx);
             }
         });
     }
     __syncthreads();
-    const int filed_n = (int)cur[tb];
-    for (int i = tid; i < filed_n; i += T) {
-        const u64 c = filed[i];
-        const uint32_t b = bins.template bin<ELT>((uint32_t)(c >> 32), (uint32_t)c >> 1);
-        const int s = b + 1u < (uint32_t)n_bins ? (int)cur[b + 1] : 0, e = (int)cur[b];
-        u64 peer[4];
+    row_rank_write<ELT>(p, r, bins, filed, (int)cur[tb], cur, n_bins);
+}
+
+// Several workgroups to a row: each holds a part of it in registers, finds a lower bound of its own (fewer of its elements
+// have to reach it: k shared out over the parts, and a margin), and passes on what lies at or above it.  The workgroup
+// that draws the row's last ticket takes the largest of the bounds: every element of the row at or above that was passed on,
+// so if there are k of them they hold the k largest.  Else - parts unlike each other, long runs of ties - it goes through the
+// row digit by digit, alone.  One sweep over memory, one launch: 128 x 2^20 f32, k = 64: 135 us by sampling, copying out and
+// selecting, 103 here; k = 1024: 225 -> 127; one row of 2^20, k = 1000: 52 -> 13.4; 64 x 128256 bf16, k = 256: 13.8 us with a
+// workgroup per row, 11.6 with four (3.7 us to read and bound a part, 1.3 to list, 1.1 to hand over, 4 to select).  The lists go through memory as in the fused kernels' hand-over: agent-scope stores, a wait for
+// their acknowledgement, a ticket.
+template <int ELT, int NV>
+__global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES;
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1);
+    const int64_t r = blockIdx.x / (unsigned)p.parts;
+    const int part = (int)(blockIdx.x - (unsigned)r * (unsigned)p.parts);
+    const int n_bins = 1 << p.lg_bins;
+    u64 *filed = (u64 *)smem;
+    uint32_t *cur = (uint32_t *)(filed + p.filed_words);
+    uint32_t *misc = cur + n_bins + 4;
+    int2 *passed = (int2 *)(misc + kRowMisc);
+
+    const int rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & 15) / ES;
+    const int n_vec = (rot + p.n + VE - 1) / VE;
+    // (a part may be empty: the plan counts a vector more for rows off the 16-byte boundaries)
+    const int v0 = min(part * p.part_vecs, n_vec - 1), v1 = part * p.part_vecs < n_vec ? min(v0 + p.part_vecs, n_vec) : v0;
+    {
+        RowRegs<ELT, NV> regs;
+        regs.load(p, r, v0, v1, rot);
+        if (tid == 0) misc[5] = 0u;
+        regs.mask_ends(p, v0, v1, rot);
+        uint32_t k_min, k_max;
+        regs.bound(p.sub, p.rank, misc, k_min, k_max);
+        regs.list_from(__uint_as_float(bits_of_ukey(k_min)), passed, (uint32_t)p.part_cap, &misc[5]);
+        const uint32_t n_passed = misc[5];
+        u64 *list = p.lists + (r * p.parts + part) * p.part_cap;
+        if (n_passed <= (uint32_t)p.part_cap)
+            for (uint32_t i = tid; i < n_passed; i += T) {
+                const int at = passed[i].y;
+                __hip_atomic_store(&list[i], make_composite(row_bits<ELT>(p, r, at), at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        if (tid == 0) {
+            u64 *head = p.heads + (r * p.parts + part) * 2;
+            __hip_atomic_store(&head[0], ((u64)k_min << 32) | n_passed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&head[1], (u64)k_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // (a barrier alone does not wait for stores; the memory clobber keeps the compiler from moving the ticket above this)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t *ticket = p.tickets + r * kTicketStride;
+        const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.parts - 1u;
+        misc[6] = last ? 1u : 0u;
+        misc[5] = 0u;
+        misc[7] = 0u;
+        if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next call
+    }
+    __syncthreads();
+    if (!misc[6]) return;
+
+    // ---- the row's last workgroup
+    for (int i = tid; i < n_bins + 4; i += T) cur[i] = 0u;
+    // every wavefront reads all the heads: the largest bound, the largest key, whether a part had more than it could pass on,
+    // and how many pieces of 64 elements the lists make (lane i has part i)
+    uint32_t k_min = 0u, k_max = 0u, len = 0u;
+    if (lane < p.parts) {
+        const u64 *head = p.heads + (r * p.parts + lane) * 2;
+        const u64 h0 = __hip_atomic_load(&head[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const u64 h1 = __hip_atomic_load(&head[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        k_min = (uint32_t)(h0 >> 32);
+        k_max = (uint32_t)h1;
+        len = (uint32_t)h0;
+    }
+    k_min = wave_max_u32(k_min);
+    k_max = wave_max_u32(k_max);
+    const bool over = __ballot(len > (uint32_t)p.part_cap) != 0ull;
+    const uint32_t pieces = (len + kWave - 1) / kWave, pieces_end = wave_incl_scan_u32(pieces);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)pieces_end, kWave - 1);
+    __syncthreads();
+    bool done = false;
+    if (!over) {
+        // the wavefronts take the pieces in turn, eight loads in flight
+        constexpr int U = 8;
+        const u64 *lists = p.lists + r * p.parts * p.part_cap;
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (uint32_t)T >> 6;
+        for (uint32_t c0 = wave; c0 < total; c0 += U * n_waves) {
+            u64 c[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) peer[u] = filed[s + u < e ? s + u : i];  // (itself: not larger)
-        int rank = s;
+            for (int u = 0; u < U; ++u) {
+                const uint32_t id = c0 + u * n_waves;
+                c[u] = 0ull;
+                if (id < total) {  // uniform over the wavefront
+                    const int of = __popcll(__ballot(pieces_end <= id));  // the part whose piece it is
+                    const uint32_t n_of = (uint32_t)__builtin_amdgcn_readlane((int)len, of);
+                    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)(pieces_end - pieces), of);
+                    const uint32_t i = (id - first) * kWave + (uint32_t)lane;
+                    c[u] = __hip_atomic_load(&lists[(uint32_t)of * (uint32_t)p.part_cap + min(i, n_of - 1u)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (i >= n_of) c[u] = 0ull;
+                }
+            }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) rank += peer[u] > c ? 1 : 0;
-        for (int j = s + 4; j < e; ++j) rank += filed[j] > c ? 1 : 0;
-        if (rank < p.k) write_composite<ELT>(c, p.out_vals, p.out_idx, r * p.k + rank);
+            for (int u = 0; u < U; ++u) {
+                const bool take = (uint32_t)(c[u] >> 32) >= k_min && c[u] != 0ull;
+                const u64 mask = __ballot(take);
+                if (mask) {  // uniform over the wavefront
+                    uint32_t at = 0;
+                    if (lane == 0) at = atomicAdd(&misc[5], (uint32_t)__popcll(mask));
+                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+                         __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    if (take && at < (uint32_t)p.cap) passed[at] = make_int2((int)composite_bits(c[u]), composite_index(c[u]));
+                }
+            }
+        }
+        __syncthreads();
+        const uint32_t n_passed = misc[5];
+        if (n_passed >= (uint32_t)p.k && n_passed <= (uint32_t)p.cap) {
+            done = row_select_passed<ELT>(p, r, passed, n_passed, k_min, k_max, filed, cur, misc);
+            if (!done) {  // once more from the raised lower end
+                for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
+                if (tid == 0) misc[7] = 0u;
+                __syncthreads();
+                // (the elements below it drop out: in place, each lane looks at its own entries)
+                int2 own[8];
+                const int per = (int)((n_passed + T - 1) / T);
+                if (per <= 8) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) own[j] = passed[min((uint32_t)(tid + j * T), n_passed - 1u)];
+                    __syncthreads();
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const bool take = (uint32_t)(tid + j * T) < n_passed && ukey_of_bits((uint32_t)own[j].x) >= k_min;
+                        if (take) passed[atomicAdd(&misc[7], 1u)] = own[j];
+                    }
+                    __syncthreads();
+                    done = row_select_passed<ELT>(p, r, passed, misc[7], k_min, k_max, filed, cur, misc);
+                }
+            }
+        }
+    }
+    if (!done) {
+        __syncthreads();
+        row_by_digits<ELT>(p, r, filed, cur, misc);
     }
 }
 
@@ -429,26 +678,52 @@ static int row_nv(int64_t want, bool pairs) {  // vectors per lane of the smalle
     return 0;
 }
 
+// The bound that at least `want` elements reach: rank per wavefront, and the fewest groups per lane that keep the rank in
+// the upper half of a wavefront's maxima (close to all of them the bound falls off: the smallest of the maxima).  Returns how
+// many of the n_vec vectors' elements may be expected to reach it: among random elements the share above the
+// rank-th of the g maxima of groups of e is 1 - (1 - rank/g)^(1/e), and the smallest over the wavefronts lies
+// two or so deviations further down.
+static double row_bound_plan(RowPlan &p, int T, int64_t n_vec, double want) {
+    const int ve = p.ve, waves = T / kWave;
+    const int sm = p.nv * 4 < 8 ? 4 : 8;
+    p.rank = (int)std::ceil(want / waves);
+    p.sub = 1;
+    while (p.sub < sm && p.rank > 32 * p.sub) p.sub *= 2;
+    // Where much of the row is kept, finding the rank-th costs more than it drops: then the smallest of the maxima of G groups,
+    // which about G ln G elements reach where the groups are small parts of the row, with half of that at k or more (checked
+    // by the histogram; 128 lists of 8192 pairs, k = 4096: 26.6 us with the ranks, 23.2 so, 28.8 from the smallest element)
+    const bool most = want > 0.4 * (double)(n_vec * ve);
+    if (most) {
+        p.rank = 0;
+        for (p.sub = 1; p.sub < sm && 0.5 * T * p.sub * std::log((double)T * p.sub) < want;) p.sub *= 2;
+        return (double)(n_vec * ve);
+    }
+    const double g = 64.0 * p.sub, per_wave = (double)n_vec * ve / waves, e = per_wave / g > 1.0 ? per_wave / g : 1.0;
+    const double low = p.rank + 2.2 * std::sqrt((double)p.rank) + 1.0;
+    const double share = low < g * 0.98 ? 1.0 - std::pow(1.0 - low / g, 1.0 / e) : 1.0;
+    return share * per_wave * waves;
+}
+
 bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, RowPlan *out) {
     const int ve = dtype == ATK_F32 ? 4 : 8;
     RowPlan p;
     memset(&p, 0, sizeof p);
+    p.ve = ve;
     if (k > kRowMaxK || n > (int64_t)1024 * 16 * ve) return false;
     // vectors that hold an element of a row (rows off the 16-byte boundaries: with the worst alignment)
     const int64_t n_vec = ptr16 && n % ve == 0 ? n / ve : (n + 2 * ve - 2) / ve;
     // At most one row per CU: the biggest workgroup that still has a vector per lane.  More rows: several workgroups to a
-    // CU, so that one reads while others select, each with 4 to 8 vectors per lane (2048 rows: 8192 f32, k = 64: 21.1 us with
-    // 256 lanes, 40.3 with 1024; 2048 f32: 10.4 with 128, 14.4 with 512; 32768 bf16, k = 256: 53.9 with 512, 69.0 with 1024), and
-    // twice the lanes where a quarter of the row or more is kept, which the tables in LDS leave room for no more than a few
-    // of at a time (8192 f32, k = 2048: 78.5 with 256, 63.0 with 512), or where only some CUs get a second row
-    // (300 rows of 4096 f32: 7.4 with 256, 6.8 with 512).
+    // CU, so that one reads while others select, each with 4 to 16 vectors per lane (2048 rows: 8192 f32, k = 64: 16.9 us with
+    // 256 lanes, 39.3 with 1024; 2048 f32: 8.2 with 128, 14.6 with 512; 32768 bf16, k = 256: 37.7 with 256, 43.8 with 512), and
+    // twice the lanes where a quarter of the row or more is kept, of which the tables in LDS leave room for a few workgroups
+    // only (8192 f32, k = 2048: 82.3 with 256, 57.8 with 512).
     int T = kWave;
     if (m <= kNumCU) {
-        while (T < 1024 && T < n_vec) T <<= 1;
+        while (T < 1024 && 2 * T <= n_vec) T <<= 1;
     } else {
-        T = n_vec <= 512 ? 128 : (n_vec <= 2048 ? 256 : (n_vec <= 8192 ? 512 : 1024));
-        if ((4 * k >= n || m <= 2 * kNumCU) && T * 2 <= n_vec && T < 512) T *= 2;
-        while (T > kWave && T / 2 >= n_vec) T >>= 1;
+        T = n_vec <= 512 ? 128 : (n_vec <= 4096 ? 256 : (n_vec <= 8192 ? 512 : 1024));
+        if (4 * k >= n && T * 2 <= n_vec && T < 512) T *= 2;
+        while (T > kWave && T > n_vec) T >>= 1;
     }
     if (plan_override().T) T = plan_override().T;
     p.nv = row_nv((n_vec + T - 1) / T, pairs);
@@ -457,29 +732,10 @@ bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
         p.nv = row_nv((n_vec + T - 1) / T, pairs);
     }
     if (!p.nv) return false;
-    // groups of the guess: the fewest G with G ln G / 2 >= k
-    p.sub = 1;
-    p.gl = 1;
-    auto enough = [&](double g) { return g > 1.0 && 0.5 * g * std::log(g) >= (double)k; };
-    const int lanes = (int)(n_vec < T ? n_vec : T);
-    static const int gls[] = {64, 16, 8, 4, 2, 1};
-    double groups = 0.0;
-    for (int g : gls)
-        if (enough((double)(lanes / g))) {
-            p.gl = g;
-            groups = lanes / g;
-            break;
-        }
-    if (groups == 0.0) {
-        const int sm = p.nv * 4 < 8 ? 4 : 8;
-        for (p.sub = 2; p.sub < sm && !enough((double)lanes * p.sub);) p.sub *= 2;
-        groups = (double)lanes * p.sub;
-    }
-    // How many elements reach the guess: G (ln G + 0.58) on average, more than G (ln G + c) on one row in e^c (which then
-    // stays in the registers, at twice the time: rarer still where a launch is one round of rows and waits for its slowest).
-    // Where that is a small part of the row they pass through LDS.
-    const double expect = groups * (std::log(groups) + (m <= kNumCU ? 9.0 : 7.0));
-    p.cap = expect * 2.0 < (double)n && expect < 8192.0 ? ((int)expect + 1) & ~1 : 0;
+    const double expect = row_bound_plan(p, T, n_vec, (double)k);
+    // Where few of the elements reach the bound they pass through LDS (a row that has more stays in the registers).
+    const double cap = expect * 1.3 + 6.0 * std::sqrt(expect) + 128.0;
+    p.cap = cap * 1.6 < (double)n && cap < 8192.0 ? ((int)cap + 1) & ~1 : 0;
     int lg = 8;
     while (lg < 13 && ((1 << lg) < 2 * k || (1 << lg) < T)) ++lg;
     int64_t kp = 1;
@@ -496,43 +752,111 @@ bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
     return true;
 }
 
-template <int ELT, int NV, bool XI>
-static hipError_t launch_row(const RowPlan &pl, const RowParams &prm, int64_t m, hipStream_t stream) {
+// Several workgroups to a row.  false: the row is too long for that, or k too large.
+bool plan_exact_parts(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, RowPlan *out) {
+    const int ve = dtype == ATK_F32 ? 4 : 8;
+    RowPlan p;
+    memset(&p, 0, sizeof p);
+    p.ve = ve;
+    const int64_t n_vec = ptr16 && n % ve == 0 ? n / ve : (n + 2 * ve - 2) / ve;
+    const PlanOverride &ov = plan_override();
+    // Rows that one workgroup holds are shared out only where that gives CUs without a row something to do, down to 1024
+    // vectors a part, from 12288 vectors on (below, the hand-over costs what the second CU saves: 128 x 65536 f32, k = 1024:
+    // 18.7 us in one workgroup, 16.3 in two; 128 x 32768, k = 64: 8.4 against 10.5; one row of 65536 f32: 9.5, 7.9 in 16 parts).
+    // Longer rows take parts of up to 8192 vectors, two workgroups of 512 lanes to a CU.
+    int64_t parts = std::min<int64_t>(std::min<int64_t>(kNumCU / m, 32), n_vec / 1024);
+    if (parts < 1) parts = 1;
+    if (n_vec <= 16 * 1024 && (2 * m > kNumCU || n_vec < 12288) && !ov.S) return false;
+    if (ov.S) parts = ov.S;
+    int64_t pv = (n_vec + parts - 1) / parts;
+    int t_max = 1024;
+    if (pv > 8192) {
+        parts = (n_vec + 8191) / 8192;
+        t_max = 512;
+    }
+    pv = (n_vec + parts - 1) / parts;
+    parts = (n_vec + pv - 1) / pv;
+    if (parts < 2 || parts > kWave || m * parts >= (1ll << 31)) return false;
+    int T = kWave;  // (the last part may be some vectors shorter, and no wavefront should be without)
+    while (T < t_max && 2 * T + kWave <= pv) T <<= 1;
+    if (ov.T) T = ov.T;
+    p.nv = row_nv((pv + T - 1) / T, false);
+    if (!p.nv) return false;
+    p.parts = (int)parts;
+    p.part_vecs = (int)pv;
+    // The largest of the parts' bounds decides how many elements are left, so every part aims at k / parts and a margin
+    const double want = 1.2 * (double)k / (double)parts + 3.0 * std::sqrt((double)k / (double)parts) + 3.0;
+    if (want * 2.0 > (double)(pv * ve)) return false;
+    const double expect = row_bound_plan(p, T, std::min(pv, n_vec), want);
+    p.part_cap = (int)(expect * 1.5 + 8.0 * std::sqrt(expect) + 128.0);
+    const double total = (double)parts * expect;
+    p.cap = ((int)(1.3 * total + 512.0) + 1) & ~1;
+    if (p.cap > 16384) return false;
+    if (p.cap < p.part_cap) p.cap = (p.part_cap + 1) & ~1;
+    int lg = 8;
+    while (lg < 13 && ((1 << lg) < 2 * k || (1 << lg) < T)) ++lg;
+    int64_t kp = 1;
+    while (kp < k) kp <<= 1;
+    p.filed_words = (int)((kp > k + kRowBinMax ? kp : k + kRowBinMax) + 1) & ~1;
+    p.lg_bins = lg;
+    const int64_t lds = (int64_t)(p.filed_words + p.cap) * 8 + ((1 << lg) + 4 + kRowMisc) * 4;
+    if (lds > kLdsBudgetWholeRow) return false;
+    p.lds_bytes = (int)lds;
+    p.T = T;
+    *out = p;
+    return true;
+}
+int64_t exact_parts_data_bytes(const RowPlan &p, int64_t m) { return m * p.parts * (16 + (int64_t)p.part_cap * 8); }
+int64_t exact_parts_state_bytes(int64_t m) { return m * kTicketStride * 4; }
+
+template <typename K>
+static hipError_t launch_row(K kernel, const RowPlan &pl, const RowParams &prm, int64_t grid, bool (&told)[64], hipStream_t stream) {
     if (pl.lds_bytes > 64 * 1024) {
-        static bool told[64] = {};
-        const hipError_t e = allow_whole_cu_lds((const void *)ex_row_kernel<ELT, NV, XI>, told);
+        const hipError_t e = allow_whole_cu_lds((const void *)kernel, told);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((ex_row_kernel<ELT, NV, XI>), dim3((unsigned)m), dim3((unsigned)pl.T), (size_t)pl.lds_bytes, stream, prm);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)pl.T), (size_t)pl.lds_bytes, stream, prm);
     return hipGetLastError();
 }
 
 template <int ELT>
 static hipError_t launch_row_t(const RowPlan &pl, const RowParams &prm, int64_t m, hipStream_t stream) {
+#define ATK_ROW(KERNEL, GRID)                                        \
+    do {                                                             \
+        static bool told[64] = {};                                   \
+        return launch_row(KERNEL, pl, prm, GRID, told, stream);      \
+    } while (0)
     if (prm.xi) {
         switch (pl.nv) {
-            case 1: return launch_row<ELT, 1, true>(pl, prm, m, stream);
-            case 2: return launch_row<ELT, 2, true>(pl, prm, m, stream);
-            case 3: return launch_row<ELT, 3, true>(pl, prm, m, stream);
-            case 4: return launch_row<ELT, 4, true>(pl, prm, m, stream);
+            case 1: ATK_ROW((ex_row_kernel<ELT, 1, true>), m);
+            case 2: ATK_ROW((ex_row_kernel<ELT, 2, true>), m);
+            case 3: ATK_ROW((ex_row_kernel<ELT, 3, true>), m);
+            case 4: ATK_ROW((ex_row_kernel<ELT, 4, true>), m);
         }
         return hipErrorInvalidValue;
     }
+#define ATK_ROW_NV(NV)                                                       \
+    case NV:                                                                 \
+        if (pl.parts) ATK_ROW((ex_parts_kernel<ELT, NV>), m * pl.parts);     \
+        ATK_ROW((ex_row_kernel<ELT, NV, false>), m);
     switch (pl.nv) {
-        case 1: return launch_row<ELT, 1, false>(pl, prm, m, stream);
-        case 2: return launch_row<ELT, 2, false>(pl, prm, m, stream);
-        case 3: return launch_row<ELT, 3, false>(pl, prm, m, stream);
-        case 4: return launch_row<ELT, 4, false>(pl, prm, m, stream);
-        case 6: return launch_row<ELT, 6, false>(pl, prm, m, stream);
-        case 8: return launch_row<ELT, 8, false>(pl, prm, m, stream);
-        case 12: return launch_row<ELT, 12, false>(pl, prm, m, stream);
-        case 16: return launch_row<ELT, 16, false>(pl, prm, m, stream);
+        ATK_ROW_NV(1)
+        ATK_ROW_NV(2)
+        ATK_ROW_NV(3)
+        ATK_ROW_NV(4)
+        ATK_ROW_NV(6)
+        ATK_ROW_NV(8)
+        ATK_ROW_NV(12)
+        ATK_ROW_NV(16)
     }
+#undef ATK_ROW_NV
+#undef ATK_ROW
     return hipErrorInvalidValue;
 }
 
+// state, data: of plans with several workgroups to a row, exact_parts_state_bytes() zeroed and exact_parts_data_bytes()
 hipError_t launch_exact_row(const RowPlan &pl, int64_t m, int64_t n, int64_t k, int64_t idx_n, int dtype, const void *x,
-                            const int32_t *xi, void *out_vals, int32_t *out_idx, hipStream_t stream) {
+                            const int32_t *xi, void *out_vals, int32_t *out_idx, void *state, void *data, hipStream_t stream) {
     RowParams prm;
     memset(&prm, 0, sizeof prm);
     prm.x = x;
@@ -547,8 +871,15 @@ hipError_t launch_exact_row(const RowPlan &pl, int64_t m, int64_t n, int64_t k, 
     prm.filed_words = pl.filed_words;
     prm.cap = pl.cap;
     prm.sub = pl.sub;
-    prm.gl = pl.gl;
+    prm.rank = pl.rank;
+    prm.parts = pl.parts;
+    prm.part_vecs = pl.part_vecs;
+    prm.part_cap = pl.part_cap;
+    prm.heads = (u64 *)data;
+    prm.lists = prm.heads + m * pl.parts * 2;
+    prm.tickets = (uint32_t *)state;
     if (xi && (((uintptr_t)x | (uintptr_t)xi) & 15u)) return hipErrorInvalidValue;  // never: the pairs lie in the library's scratch
+    if (pl.parts && (xi || !state || !data)) return hipErrorInvalidValue;
     return dtype == ATK_F32 ? launch_row_t<ATK_F32>(pl, prm, m, stream) : launch_row_t<ATK_BF16>(pl, prm, m, stream);
 }
 

@@ -90,3 +90,23 @@ def test_pairs(dtype):
         ov, oi = oracle.approx_topk(workloads.as_numpy_bits(x), k, b, k_b, threads=8)
         assert np.array_equal(idx.cpu().numpy(), oi)
         assert np.array_equal(_bits(vals), ov.view(np.uint32) if ov.dtype == np.float32 else ov)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_in_parts(dtype):
+    """Rows shared out between workgroups: uneven parts, rows off the 16-byte boundaries, parts unlike each other, ties."""
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    ve = 4 if dtype == "f32" else 8
+    for (m, n, k) in [(1, 12288 * ve, 64), (2, 12289 * ve + 1, 1), (128, 16384 * ve, 100), (3, 16385 * ve, 1000), (2, 8192 * ve * 5 + 7, 300),
+                      (300, 16384 * ve + 3, 10), (1, 1 << 21, 1024), (2, 8192 * 8 * 64 + 1 if dtype == "bf16" else 8192 * 4 * 64 + 1, 33)]:
+        if m * n < 2.5e7:
+            _check(workloads.normal_rows(m, n, seed=n % 1000 + k, dtype=dtype), k, shift=1 if n % 2 else 0)
+    n = 20000 * ve
+    base = workloads.normal_rows(2, n, seed=3)
+    blocks = base.clone()
+    blocks[:, n // 3: n // 3 + 2000] += 50.0
+    for x in (base.sort(dim=1)[0], base.sort(dim=1, descending=True)[0], blocks, torch.zeros(2, n), torch.relu(base - 5.0)):
+        for k in (1, 90, 800):
+            _check(x.to(t), k)
+    _check(workloads.few_levels(2, n, levels=3, seed=9, dtype=dtype), 500)
+    _check(workloads.special_values(2, n, seed=9, dtype=dtype), 500)
