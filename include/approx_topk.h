@@ -139,8 +139,9 @@ int atk_check_exact(int64_t m, int64_t n, int64_t k, int dtype);
 /* Largest b*k_b for which Stage 2 runs on-chip in the same launch (more candidates take further launches). */
 int64_t atk_stage2_max_candidates(void);
 
-/* Bytes of library scratch an approx_topk / approx_topk_assign / exact_topk call with these arguments uses
- * (0 if none, <0 = error code). */
+/* Bytes of library scratch an approx_topk / approx_topk_assign / exact_topk call with these arguments uses at most
+ * (0 if none, <0 = error code): rows of more than 8192 elements (candidates, in the second step of approx_topk) count with what
+ * the digit-by-digit path would take, which plan overrides may choose. */
 int64_t atk_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype);
 int64_t atk_workspace_bytes_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment);
 int64_t atk_exact_workspace_bytes(int64_t m, int64_t n, int64_t k, int dtype);
@@ -160,7 +161,7 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * PK=0 (bf16: no packed queue words), XS=0 / XS=1 (exact_topk with k <= 512: never / also on small
  * inputs guess the threshold from a sample of the row first), XC=<elements of a row per workgroup of
  * exact_topk's sweeps: a power of two from 1024 to 16384>, XR=0 (exact_topk: no row is held in one workgroup's
- * registers; XS and XC, which concern the paths of longer rows, imply it), LN=0 (k_b = 1: the general kernel instead of the
+ * registers or dealt to bins; XS and XC, which concern the other paths, imply it), XD=0 (no dealing alone), LN=0 (k_b = 1: the general kernel instead of the
  * one specialised for running maxima), LM=0 (k_b = 1: the lanes of a column merge through per-part lists and
  * a pass over them instead of atomic maxima in LDS), HF=0 / HF=1 (never / whenever the shape allows, two
  * workgroups - a helper and a finisher - share a row of a Stage-2 plan), HQ=<sixty-fourths of the matrix rows

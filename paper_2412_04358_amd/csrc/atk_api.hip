@@ -80,6 +80,7 @@ static PlanOverride parse_plan_override(const char *e) {
     if (const char *q = field("LM")) o.lm_off = atoi(q) == 0;
     if (const char *q = field("LN")) o.ln_off = atoi(q) == 0;
     if (const char *q = field("XS")) o.xs = atoi(q) == 0 ? -1 : 1;
+    if (const char *q = field("XD")) o.xd_off = atoi(q) == 0;
     if (const char *q = field("XR")) o.xr_off = atoi(q) == 0;
     if (const char *q = field("XC")) {
         const int v = atoi(q);
@@ -903,8 +904,10 @@ static int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
 // rows go one per workgroup), and the pool sizes cover every block.  The last block has fewer rows and
 // is planned on its own by run_exact(): with fewer rows it may take paths the full blocks do not (the
 // copy-out buffer, a finer sweep), so its needs are not bounded by the first block's.
+// cover: sizes that hold for the digit-by-digit path of long rows as well, which a plan override may choose (what the
+// queries of the workspace report; a call reserves what its own plan takes).
 static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *first, int64_t *state_bytes,
-                            int64_t *data_bytes) {
+                            int64_t *data_bytes, bool cover = false) {
     int rc = make_exact_plan(m > kExactRowsPerPass ? kExactRowsPerPass : m, n, k, dtype, pairs, ptr16, first);
     if (rc == ATK_OK && first->single_wg) rc = make_exact_plan(m, n, k, dtype, pairs, ptr16, first);
     if (rc != ATK_OK) return rc;
@@ -917,11 +920,19 @@ static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pai
         *state_bytes = std::max(*state_bytes, last.state_bytes);
         *data_bytes = std::max(*data_bytes, last.scratch_bytes);
     }
+    if (cover && n > 8192) {
+        for (int64_t rows : {std::min(m, kExactRowsPerPass), m % kExactRowsPerPass}) {
+            ExactPlan digits;
+            if (rows < 1 || make_exact_plan(rows, n, k, dtype, pairs, ptr16, &digits, true) != ATK_OK) continue;
+            *state_bytes = std::max(*state_bytes, digits.state_bytes);
+            *data_bytes = std::max(*data_bytes, digits.scratch_bytes);
+        }
+    }
     return ATK_OK;
 }
 
 static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment,
-                          bool ptr16, FullPlan *fp, bool allow_pair = true) {
+                          bool ptr16, FullPlan *fp, bool allow_pair = true, bool cover = false) {
     if (assignment != ATK_INTERLEAVED && assignment != ATK_CONTIGUOUS) return ATK_ERR_BAD_PARAMS;
     const int es = (dtype == ATK_F32) ? 4 : 2;
     const int64_t nc = b * k_b;
@@ -934,7 +945,7 @@ static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
     fp->data_bytes = fp->s1.scratch_lists_bytes;
     if (!fp->two_step) return ATK_OK;
     int64_t ex_state = 0, ex_data = 0;
-    rc = make_exact_plans(m, nc, k, dtype, true, true, &fp->ex, &ex_state, &ex_data);
+    rc = make_exact_plans(m, nc, k, dtype, true, true, &fp->ex, &ex_state, &ex_data, cover);
     if (rc != ATK_OK) return rc;
     fp->ex.idx_n = n;
     fp->cand_vals_off = align256(fp->s1.scratch_lists_bytes);
@@ -1037,7 +1048,7 @@ int64_t atk_workspace_bytes_assign(int64_t m, int64_t n, int64_t k, int64_t b, i
     int rc = check_approx(m, n, k, b, k_b, dtype);
     if (rc != ATK_OK) return rc;
     FullPlan fp;
-    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, true, &fp);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, true, &fp, true, true);
     if (rc != ATK_OK) return rc;
     return fp.state_bytes + fp.data_bytes;
 }
@@ -1051,7 +1062,7 @@ int64_t atk_exact_workspace_bytes(int64_t m, int64_t n, int64_t k, int dtype) {
     if (rc != ATK_OK) return rc;
     ExactPlan pl;
     int64_t state_bytes = 0, data_bytes = 0;
-    rc = make_exact_plans(m, n, k, dtype, false, true, &pl, &state_bytes, &data_bytes);
+    rc = make_exact_plans(m, n, k, dtype, false, true, &pl, &state_bytes, &data_bytes, true);
     if (rc != ATK_OK) return rc;
     return state_bytes + data_bytes;
 }
@@ -1061,7 +1072,7 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
     int rc = check_common(m, n, k, dtype);
     if (rc != ATK_OK) return rc;
     ExactPlan pl;
-    return make_exact_plans(m, n, k, dtype, false, true, &pl, state_bytes, data_bytes);
+    return make_exact_plans(m, n, k, dtype, false, true, &pl, state_bytes, data_bytes, true);
 }
 
 int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment,
@@ -1070,7 +1081,7 @@ int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     int rc = check_approx(m, n, k, b, k_b, dtype);
     if (rc != ATK_OK) return rc;
     FullPlan fp;
-    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, true, &fp);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, true, &fp, true, true);
     if (rc != ATK_OK) return rc;
     const Plan &pl = fp.s1;
     // two steps: Stage 2 is the long-row exact selection over the candidates Stage 1 left in scratch

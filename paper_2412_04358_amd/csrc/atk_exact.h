@@ -30,7 +30,30 @@ int64_t exact_parts_data_bytes(const RowPlan &pl, int64_t m);
 // device (told: that kernel's own flags).
 hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]);
 
-// ... and longer ones
+// ... long rows with many winners (atk_exact_deal.hip) ...
+struct DealRow {          // per row, on the device
+    uint32_t k_min, k_max;   // range of the fine bins
+    uint32_t tb;             // the threshold: the lowest fine bin that counts
+    uint32_t cursor;         // candidates dealt
+    uint32_t failed;         // a bin holds more than a workgroup orders
+};
+struct DealPlan {
+    int chunks, bins;        // per row
+    int sample_rank;         // sampled elements above the threshold
+    int rank;                // of the sample's lower bound, as in RowPlan
+    int64_t pool_cap;        // candidates per row
+    int64_t rows_off, table_off, totals_off, segs_off, pool_off, rest_off, bytes;  // byte offsets into the data pool
+};
+bool plan_exact_deal(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, DealPlan *out);
+hipError_t launch_exact_deal(const DealPlan &pl, int64_t m, int64_t n, int64_t k, int64_t idx_n, int dtype, const void *x,
+                             const int32_t *xi, void *out_vals, int32_t *out_idx, void *data, hipStream_t stream);
+// The rows whose candidates number fewer than k or more than pool_cap, or that are marked failed: one workgroup per row.
+// buf0, buf1: m * k composites each.
+hipError_t launch_exact_rest_rows(int64_t m, int64_t n, int64_t k, int idx_bits, int dtype, const void *x, const int32_t *xi,
+                                  const DealRow *rows, int64_t pool_cap, u64 *buf0, u64 *buf1, void *out_vals, int32_t *out_idx,
+                                  hipStream_t stream);
+
+// ... and the rest
 struct ExactPlan {
     int dtype;
     int64_t m, n, k;
@@ -38,6 +61,8 @@ struct ExactPlan {
     bool single_wg;         // one workgroup per row, the row in its registers (`row`)
     bool parts;             // several, each with a part of it (`row`)
     RowPlan row;
+    bool dealt;             // dealt to bins (`deal`)
+    DealPlan deal;
     int chunks;             // workgroups per row of the global path
     int chunk_elems;        // elements of a row that one of them sweeps
     bool filter;            // small k: rows may finish through the copy-out buffer
@@ -46,7 +71,7 @@ struct ExactPlan {
     int64_t scratch_bytes;  // data pool
     int64_t state_bytes;    // zeroed-state pool
 };
-int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *plan);
+int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *plan, bool by_digits = false);
 // xi: NULL, or (device, m x n int32) the column index each element of x stands for: the rows are then
 // lists of (value, index) pairs with distinct indices below plan.idx_n, and the order among equal
 // values and out_idx follow those indices (Stage 2 over more candidates than fit one workgroup).

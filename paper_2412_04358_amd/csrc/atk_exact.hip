@@ -69,7 +69,7 @@ int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *pl) {
+int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *pl, bool by_digits) {
     ExactPlan p;
     p.dtype = dtype;
     p.m = m;
@@ -83,10 +83,10 @@ int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
     p.filter_cap = kFilterCap;
     p.sample = false;
     p.idx_n = n;
-    p.single_wg = p.parts = false;
+    p.single_wg = p.parts = p.dealt = false;
     if (m >= (1ll << 31)) return ATK_ERR_UNSUPPORTED;
     const PlanOverride &ov = plan_override();
-    if (!ov.xr_off && !ov.xs && !ov.xc) {
+    if (!ov.xr_off && !ov.xs && !ov.xc && !by_digits) {
         p.parts = !pairs && m <= 65535 && plan_exact_parts(m, n, k, dtype, ptr16, &p.row);
         if (p.parts) {
             p.state_bytes = exact_parts_state_bytes(m);
@@ -96,6 +96,12 @@ int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
         }
         p.single_wg = plan_exact_row(m, n, k, dtype, pairs, ptr16, &p.row);
         if (p.single_wg) {
+            *pl = p;
+            return ATK_OK;
+        }
+        p.dealt = !ov.xd_off && plan_exact_deal(m, n, k, dtype, ptr16, &p.deal);
+        if (p.dealt) {
+            p.scratch_bytes = p.deal.bytes;
             *pl = p;
             return ATK_OK;
         }
@@ -452,29 +458,15 @@ __global__ void __launch_bounds__(kMaxThreads) ex_collect_kernel(const void *x, 
     }, chunk_elems);
 }
 
-// Small k on rows of moderate length, after the first digit and the copy-out path: the rows that are still open
-// (more elements in play than the copy-out buffer holds: ties, values on few levels) are rare, and a launch cannot
-// be skipped without asking the device.  So instead of one launch per remaining digit plus two to collect and order,
-// all of which usually find nothing to do, this is one launch whose workgroups return at once unless their row is
-// open; a workgroup that stays takes its row through the remaining digits alone (LDS histogram over the whole row
-// per digit), collects the k survivors in LDS and writes them in order.
-constexpr int64_t kRestMaxRow = 1 << 18;  // longest row handled this way (one workgroup re-reads it once per digit)
+// The digit descent of row r by one workgroup of 256 lanes alone, from pass p on: the threshold (squeezed) that exactly k elements
+// reach.  prefix, need, done: as far as it is decided.
 template <int ELT>
-__global__ void __launch_bounds__(kMaxThreads) ex_rest_kernel(const void *x, const int32_t *xi, int64_t n, ExRowState *st, int k,
-                                                              int sq_bits, int n_passes, int chunk_elems, Squeeze sq,
-                                                              void *out_vals, int32_t *out_idx) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ uint32_t lh[kExBins];
-    __shared__ uint32_t wave_tot[4];
-    __shared__ u64 s_prefix;
-    __shared__ uint32_t s_need, s_done, s_cursor;
-    const int r = blockIdx.x, tid = threadIdx.x;
-    if (st[r].mode == 2u) return;  // finished by the copy-out path (uniform over the workgroup)
-    u64 prefix = st[r].prefix;
-    uint32_t need = st[r].need;
-    bool done = st[r].done != 0u;
+__device__ __forceinline__ u64 row_threshold(const void *x, const int32_t *xi, int64_t n, int r, int sq_bits, int p, int n_passes,
+                                             int chunk_elems, Squeeze sq, u64 prefix, uint32_t need, bool done, uint32_t *lh,
+                                             uint32_t *wave_tot, u64 &s_prefix, uint32_t &s_need, uint32_t &s_done) {
+    const int tid = threadIdx.x;
     const int chunks = (int)((n + chunk_elems - 1) / chunk_elems);
-    for (int p = 1; p < n_passes && !done; ++p) {
+    for (; p < n_passes && !done; ++p) {
         const int shift = p == n_passes - 1 ? 0 : sq_bits - kExDigit * (p + 1);
         const int width = p == n_passes - 1 ? sq_bits - kExDigit * (n_passes - 1) : kExDigit;
         const u64 hi_mask = (shift + width >= 64) ? 0ull : (~0ull << (shift + width));
@@ -519,6 +511,32 @@ __global__ void __launch_bounds__(kMaxThreads) ex_rest_kernel(const void *x, con
         done = s_done != 0u;
         __syncthreads();
     }
+    return prefix;
+}
+
+// Small k on rows of moderate length, after the first digit and the copy-out path: the rows that are still open
+// (more elements in play than the copy-out buffer holds: ties, values on few levels) are rare, and a launch cannot
+// be skipped without asking the device.  So instead of one launch per remaining digit plus two to collect and order,
+// all of which usually find nothing to do, this is one launch whose workgroups return at once unless their row is
+// open; a workgroup that stays takes its row through the remaining digits alone (LDS histogram over the whole row
+// per digit), collects the k survivors in LDS and writes them in order.
+constexpr int64_t kRestMaxRow = 1 << 18;  // longest row handled this way (one workgroup re-reads it once per digit)
+template <int ELT>
+__global__ void __launch_bounds__(kMaxThreads) ex_rest_kernel(const void *x, const int32_t *xi, int64_t n, ExRowState *st, int k,
+                                                              int sq_bits, int n_passes, int chunk_elems, Squeeze sq,
+                                                              void *out_vals, int32_t *out_idx) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t lh[kExBins];
+    __shared__ uint32_t wave_tot[4];
+    __shared__ u64 s_prefix;
+    __shared__ uint32_t s_need, s_done, s_cursor;
+    const int r = blockIdx.x, tid = threadIdx.x;
+    if (st[r].mode == 2u) return;  // finished by the copy-out path (uniform over the workgroup)
+    u64 prefix = st[r].prefix;
+    const uint32_t need = st[r].need;
+    const bool done = st[r].done != 0u;
+    const int chunks = (int)((n + chunk_elems - 1) / chunk_elems);
+    prefix = row_threshold<ELT>(x, xi, n, r, sq_bits, 1, n_passes, chunk_elems, sq, prefix, need, done, lh, wave_tot, s_prefix, s_need, s_done);
     // every element at or above the threshold: exactly k of them, into LDS
     u64 *sel = (u64 *)smem;
     uint32_t *rk = (uint32_t *)(sel + pow2_ceil_dev(k));
@@ -873,13 +891,11 @@ __global__ void __launch_bounds__(256) part_sort_big_kernel(const u64 *src, cons
 // bin = 255 - digit, so that ascending bins are descending digits.  shifts: bit s set = the digit at bit 8*s
 // differs between elements (the high bytes of the index field are the same in all of them).
 template <int ELT>
-__global__ void __launch_bounds__(256) sort_rows_kernel(u64 *buf0, u64 *buf1, const ExRowState *st, int64_t k, uint32_t shifts,
-                                                        void *out_vals, int32_t *out_idx) {
+__device__ __forceinline__ void sort_row(int r, u64 *buf0, u64 *buf1, int64_t k, uint32_t shifts, void *out_vals, int32_t *out_idx) {
     __shared__ uint32_t running[256];
     __shared__ uint32_t wcnt[4][256];
     __shared__ uint32_t wave_tot[4];
-    const int r = blockIdx.x, tid = threadIdx.x;
-    if (st[r].mode != 3u) return;  // uniform over the workgroup
+    const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     u64 *src = buf0 + (int64_t)r * k, *dst = buf1 + (int64_t)r * k;
     for (int d = 0; d < 8; ++d) {
@@ -935,6 +951,74 @@ __global__ void __launch_bounds__(256) sort_rows_kernel(u64 *buf0, u64 *buf1, co
         __syncthreads();  // this workgroup's writes to the new source are visible to its own reads (same CU)
     }
     for (int64_t i = tid; i < k; i += 256) write_composite<ELT>(src[i], out_vals, out_idx, (int64_t)r * k + i);
+}
+
+template <int ELT>
+__global__ void __launch_bounds__(256) sort_rows_kernel(u64 *buf0, u64 *buf1, const ExRowState *st, int64_t k, uint32_t shifts,
+                                                        void *out_vals, int32_t *out_idx) {
+    if (st[blockIdx.x].mode != 3u) return;  // uniform over the workgroup
+    sort_row<ELT>(blockIdx.x, buf0, buf1, k, shifts, out_vals, out_idx);
+}
+// Which of the 8-bit digits of the composites differ between elements: the index field holds 0x7fffffff - idx in bits
+// [31:1], idx below 2^idx_bits; bit 0 is the zero-sign flag.
+static uint32_t sort_shifts(int idx_bits) {
+    uint32_t shifts = 0;
+    for (int shift = 0; shift < 64; shift += 8)
+        if (!(shift < 32 && shift >= idx_bits + 1)) shifts |= 1u << (shift / 8);
+    return shifts;
+}
+
+// The rows that the dealing (atk_exact_deal.hip) could not finish: a sample that misjudged the row, a bin with more than one
+// workgroup orders.  Rare, and a launch cannot be skipped without asking the device, so this is one launch whose workgroups
+// return at once unless their row is such a one; a workgroup that stays takes its row through all digits alone, collects
+// the k survivors and sorts them.
+template <int ELT>
+__global__ void __launch_bounds__(kMaxThreads) ex_rest_rows_kernel(const void *x, const int32_t *xi, int64_t n, const DealRow *rows, int64_t k,
+                                                                   int64_t pool_cap, int sq_bits, int n_passes, Squeeze sq, u64 *buf0,
+                                                                   u64 *buf1, uint32_t shifts, void *out_vals, int32_t *out_idx) {
+    __shared__ uint32_t lh[kExBins];
+    __shared__ uint32_t wave_tot[4];
+    __shared__ u64 s_prefix;
+    __shared__ uint32_t s_need, s_done, s_cursor;
+    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
+    const DealRow row = rows[r];
+    if (!row.failed && (int64_t)row.cursor >= k && (int64_t)row.cursor <= pool_cap) return;  // uniform over the workgroup
+    if (tid == 0) s_cursor = 0u;
+    const u64 prefix = row_threshold<ELT>(x, xi, n, r, sq_bits, 0, n_passes, kExChunk, sq, 0ull, (uint32_t)k, false, lh, wave_tot, s_prefix,
+                                          s_need, s_done);
+    const u64 thr = sq.expand(prefix);
+    u64 *sel = buf0 + (int64_t)r * k;
+    const int chunks = (int)((n + kExChunk - 1) / kExChunk);
+    for (int c = 0; c < chunks; ++c)
+        for_chunk<ELT>(x, xi, n, r, c, [&](u64 cc, bool ok) {
+            const bool keep = ok && cc >= thr;
+            const u64 mask = __ballot(keep);
+            if (mask) {  // uniform over the wavefront
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&s_cursor, (uint32_t)__popcll(mask));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+                     __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (keep && (int64_t)at < k) sel[at] = cc;
+            }
+        });
+    __syncthreads();
+    sort_row<ELT>(r, buf0, buf1, k, shifts, out_vals, out_idx);
+}
+
+hipError_t launch_exact_rest_rows(int64_t m, int64_t n, int64_t k, int idx_bits, int dtype, const void *x, const int32_t *xi,
+                                  const DealRow *rows, int64_t pool_cap, u64 *buf0, u64 *buf1, void *out_vals, int32_t *out_idx,
+                                  hipStream_t stream) {
+    Squeeze sq;
+    sq.drop = dtype == ATK_BF16 ? 16 : 0;
+    sq.keep = idx_bits + 1;
+    const int sq_bits = 32 - sq.drop + sq.keep, n_passes = (sq_bits + kExDigit - 1) / kExDigit;
+    if (dtype == ATK_F32)
+        hipLaunchKernelGGL(ex_rest_rows_kernel<ATK_F32>, dim3((unsigned)m), dim3(kMaxThreads), 0, stream, x, xi, n, rows, k, pool_cap,
+                           sq_bits, n_passes, sq, buf0, buf1, sort_shifts(idx_bits), out_vals, out_idx);
+    else
+        hipLaunchKernelGGL(ex_rest_rows_kernel<ATK_BF16>, dim3((unsigned)m), dim3(kMaxThreads), 0, stream, x, xi, n, rows, k, pool_cap,
+                           sq_bits, n_passes, sq, buf0, buf1, sort_shifts(idx_bits), out_vals, out_idx);
+    return hipGetLastError();
 }
 
 hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]) {
@@ -1082,10 +1166,7 @@ static hipError_t launch_exact_t(const ExactPlan &pl, const void *x, const int32
     }
     // rows the partition sort could not take (mode 3): one launch, a workgroup per such row; digits that are the same
     // for every element (high bytes of the index field) are skipped
-    // (the index field holds 0x7fffffff - idx in bits [31:1]; bit 0 is the zero-sign flag)
-    uint32_t shifts = 0;
-    for (int shift = 0; shift < 64; shift += 8)
-        if (!(shift < 32 && shift >= idx_bits + 1)) shifts |= 1u << (shift / 8);
+    const uint32_t shifts = sort_shifts(idx_bits);
     hipLaunchKernelGGL(sort_rows_kernel<ELT>, dim3((unsigned)m), dim3(256), 0, stream, bufs[0], bufs[1], st, k, shifts, out_vals,
                        out_idx);
     return hipGetLastError();
@@ -1095,6 +1176,7 @@ hipError_t launch_exact(const ExactPlan &pl, const void *x, const int32_t *xi, v
                         void *state, void *data, hipStream_t stream) {
     if (pl.single_wg || pl.parts)
         return launch_exact_row(pl.row, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, state, data, stream);
+    if (pl.dealt) return launch_exact_deal(pl.deal, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, data, stream);
     if (pl.dtype == ATK_F32) return launch_exact_t<ATK_F32>(pl, x, xi, out_vals, out_idx, state, data, stream);
     return launch_exact_t<ATK_BF16>(pl, x, xi, out_vals, out_idx, state, data, stream);
 }

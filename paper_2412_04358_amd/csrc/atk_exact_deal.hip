@@ -1,0 +1,531 @@
+// exact_topk of long rows with many winners: the elements are dealt to value-ordered bins in one sweep over the row, and
+// every bin is ordered by a workgroup of its own.
+//
+//   ex_sample_kernel  one workgroup per row: a sample of 32768 elements (runs of 64 bytes, one at a random place in
+//                     every piece of the row) gives a threshold that a little more than k elements of the row reach, and cuts
+//                     what lies above it into bins of about 1000 elements: unions of fine bins that are linear in (value
+//                     key, index), so a bin's number is one multiplication and one look into a table.
+//   ex_deal_kernel    a workgroup per 16384 elements: what reaches the threshold is brought into the order of the
+//                     bins in LDS and written to the row's pool in one piece, with a table of where each bin starts.  (No bin has
+//                     space set aside for it: however unevenly the sample cut the row, the pool is as full as the threshold lets
+//                     through.)
+//   ex_bins_kernel    a workgroup per bin: its pieces from all the chunks, ordered in LDS by a second set of bins and exact
+//                     ranks, written to their places in the output.
+//   ex_rest_rows_kernel (atk_exact.hip): rows that did not come out - a sample that misjudged the row, a bin that
+//                     holds more than a workgroup orders (long runs of one value) - go digit by digit, one workgroup per row.
+//
+// Every element is read once and every candidate written and read once more; memory is what bounds it: 128 x 2^20 f32,
+// k = 2^18 reads 537 MB, writes and reads back 8 bytes for each of 1.05 k candidates and writes 268 MB of output.
+// Measured there: 22 us to sample, 156 to deal (5.2 TB/s), 187 to order (2.9 TB/s; a chain of short steps per bin that seven
+// workgroups of 256 lanes to a CU overlap - five with more tables in LDS took 262, two of 512 lanes 466), 4 for the last
+// launch that finds nothing to do: 374 us, against 1108 by digit passes, a collecting sweep and a partition sort in 18
+// launches.  k = 65536: 576 -> 193; 64 x 2^21 bf16, k = 2^19: 1690 -> 418; one row of 2^20, k = 2^18: 107 -> 33.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "atk_common.h"
+#include "atk_exact.h"
+#include "atk_exact_regs.h"
+#include "atk_select.h"
+
+namespace atk {
+
+constexpr int kDealT = 1024;            // threads of the sampling and dealing workgroups
+constexpr int kDealChunk = 16384;       // elements that a dealing workgroup takes
+constexpr int kDealSample = 32768;      // sampled elements of a row
+constexpr int kDealFine = 4096;         // fine bins
+constexpr int kDealStage = 6144;        // candidates of a chunk that LDS holds (more: written where they belong one by one)
+constexpr int kDealBinsMax = 1024;
+constexpr int kDealBinMean = 1024;      // candidates per bin aimed at
+constexpr int kBinT = 256;              // threads that order a bin
+constexpr int kBinCap = 2048;           // candidates of a bin that LDS holds
+constexpr int kBinSub = 1024;           // bins inside a bin
+constexpr int kDealChunksMax = 512;     // chunks of a row
+
+// What the rows of the sampling cost and save: the threshold lets through about 7 % more than k of a row's elements where k is a
+// quarter of it, twice k where 64 sampled elements lie among the k largest (the least that is taken; with fewer the copy-out path of
+// atk_exact.hip is there).
+struct DealParams : RowParams {
+    DealRow *rows;
+    uint16_t *table;      // [row][kDealFine]: bin of each fine bin (0: the largest values)
+    uint32_t *totals;     // [row][n_deal]: candidates per bin
+    uint32_t *segs;       // [row][chunk][n_deal + 1]: where the chunk's piece of each bin starts in the row's pool
+    u64 *pool;            // [row][pool_cap] candidates
+    int64_t pool_cap;
+    int n_deal, chunks;
+    int sample_rank;      // elements of the sample above the threshold
+};
+
+template <int ELT>
+__global__ void __launch_bounds__(kDealT) ex_sample_kernel(DealParams p) {
+    constexpr int VE = ELT == ATK_F32 ? 4 : 8, NV = kDealSample / kDealT / VE;
+    __shared__ __align__(16) uint32_t cur[kDealFine + 4];
+    __shared__ uint32_t misc[kRowMisc];
+    const int tid = threadIdx.x, T = kDealT;
+    const int64_t r = blockIdx.x;
+    const uintptr_t addr = (uintptr_t)p.x + (uintptr_t)(r * p.n) * (16 / VE);
+    const int rot = (int)(addr & 15) / (16 / VE);
+    const int n_vec = (rot + p.n + VE - 1) / VE - 2;  // whole vectors of the row: not the first and the last
+    const row_v4u *row = (const row_v4u *)(addr & ~(uintptr_t)15) + 1;
+    // runs of four vectors, each at a place of its own inside its piece of the row
+    constexpr int runs = NV * kDealT / 4;
+    const int len = n_vec / runs;  // vectors of a piece: at least 4
+    RowRegs<ELT, NV> regs;
+    int at[NV];  // row position of each vector's first element
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int u = tid + j * T, run = u >> 2;
+        const uint32_t hash = (((uint32_t)run * 2654435761u) ^ ((uint32_t)r * 2246822519u)) * 3266489917u;
+        const int v = (int)((int64_t)run * n_vec / runs) + (int)__umulhi(hash, (uint32_t)(len - 3)) + (u & 3);
+        at[j] = (v + 1) * VE - rot;
+        regs.q[j] = row[v];
+    }
+    regs.i0 = 0;
+    for (int i = tid; i < kDealFine + 4; i += T) cur[i] = 0u;
+    for (int i = tid; i < p.n_deal; i += T) p.totals[r * p.n_deal + i] = 0u;
+    // a lower bound from a part of the sample (eight elements per lane), with a margin: counted, not trusted
+    uint32_t k_min, k_max;
+    regs.template bound<true>(8, p.rank, misc, k_min, k_max);
+    RowBins bins;
+    for (int pass = 0;; ++pass) {
+        bins.template set<ELT>(k_min, k_max, p.idx_bits, kDealFine);
+        const float v_lo = __uint_as_float(bits_of_ukey(k_min));
+        regs.each([&](uint32_t bits, int, int en) {
+            if (__uint_as_float(bits) >= v_lo) {
+                int pos = at[en / VE];
+                asm volatile("" : "+v"(pos));  // (worked out again on each pass, not kept)
+                pos += en % VE;
+                const int idx = p.xi ? p.xi[r * p.n + pos] : pos;
+                atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)], 1u);
+            }
+        });
+        if (tid == 0) misc[0] = 0u;
+        __syncthreads();
+        row_scan(cur, misc, kDealFine, (uint32_t)p.sample_rank);
+        // too few: from -inf, and then from the lower edge of the threshold's bin (a range without what lies far below)
+        const bool few = misc[3] < (uint32_t)p.sample_rank;
+        if (pass == 2 || (pass == 0 ? !few : few)) break;
+        k_min = pass == 0 ? 0x007fffffu : bins.template edge<ELT>(misc[0]);
+        __syncthreads();
+        for (int i = tid; i < kDealFine; i += T) cur[i] = 0u;
+        __syncthreads();
+    }
+    // (a sample in which too few reach the bound - NaNs - leaves fewer than k candidates, or it does not: that is counted)
+    const uint32_t tb = misc[0];
+    uint16_t *table = p.table + r * kDealFine;
+    for (int f = tid; f < kDealFine; f += T) {
+        const uint32_t c = (uint32_t)((u64)cur[f] * (u64)p.n_deal / (u64)p.sample_rank);  // cur: sampled elements above
+        table[f] = (uint32_t)f < tb ? (uint16_t)0xffffu : (uint16_t)min(c, (uint32_t)p.n_deal - 1u);
+    }
+    if (tid == 0) {
+        DealRow d;
+        d.k_min = k_min;
+        d.k_max = k_max;
+        d.tb = tb;
+        d.cursor = 0u;
+        d.failed = 0u;
+        p.rows[r] = d;
+    }
+}
+
+template <int ELT>
+__global__ void __launch_bounds__(kDealT) ex_deal_kernel(DealParams p) {
+    constexpr int VE = ELT == ATK_F32 ? 4 : 8, NV = kDealChunk / kDealT / VE, T = kDealT;
+    constexpr int S = kDealStage / T;  // staged candidates per lane
+    extern __shared__ __align__(16) unsigned char smem[];
+    int2 *passed = (int2 *)smem;                       // (value bits, position), then the same bytes hold the ordered composites
+    u64 *staged = (u64 *)smem;
+    uint32_t *cnt = (uint32_t *)(staged + kDealStage);  // [n_deal + 1] (at most T + 4)
+    uint32_t *misc = cnt + kDealBinsMax + 4;
+    uint16_t *tab = (uint16_t *)(misc + kRowMisc);      // [kDealFine]
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), n_waves = T >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t r = blockIdx.y;
+    const int chunk = blockIdx.x;
+    const int rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * (16 / VE)) & 15) / (16 / VE);
+    const int n_vec = (rot + p.n + VE - 1) / VE;
+    const int v0 = min(chunk * (kDealChunk / VE), n_vec - 1);
+    const int v1 = chunk * (kDealChunk / VE) < n_vec ? min(v0 + kDealChunk / VE, n_vec) : v0;
+    RowRegs<ELT, NV> regs;
+    regs.load(p, r, v0, v1, rot);
+    const DealRow info = p.rows[r];
+    {
+        const uint4 *src = (const uint4 *)(p.table + r * kDealFine);
+        if (tid < kDealFine / 8) ((uint4 *)tab)[tid] = src[tid];
+    }
+    for (int i = tid; i <= p.n_deal; i += T) cnt[i] = 0u;
+    if (tid == 0) misc[5] = 0u;
+    RowBins bins;
+    bins.template set<ELT>(info.k_min, info.k_max, p.idx_bits, kDealFine);
+    const float v_lo = __uint_as_float(bits_of_ukey(bins.template edge<ELT>(info.tb)));
+    regs.mask_ends(p, v0, v1, rot);
+    __syncthreads();
+    // ---- what reaches the threshold, side by side in LDS
+    uint32_t mine = 0;
+    regs.each([&](uint32_t bits, int, int) { mine += __uint_as_float(bits) >= v_lo ? 1u : 0u; });
+    const uint32_t incl0 = wave_incl_scan_u32(mine);
+    uint32_t at = 0;
+    if (lane == kWave - 1) at = atomicAdd(&misc[5], incl0);
+    at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + incl0 - mine;
+    regs.each([&](uint32_t bits, int pos, int) {
+        if (__uint_as_float(bits) >= v_lo) {
+            if (at < (uint32_t)kDealStage) passed[at] = make_int2((int)bits, pos);
+            ++at;
+        }
+    });
+    __syncthreads();
+    const uint32_t n_passed = misc[5];
+    const bool fits = n_passed <= (uint32_t)kDealStage;
+    auto bin_of = [&](uint32_t bits, int idx) {
+        return (uint32_t)tab[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)];  // 0xffff: just below the threshold
+    };
+    auto index_of = [&](int pos) { return p.xi ? p.xi[r * p.n + pos] : pos; };
+    // ---- how many in each bin
+    u64 own[S];
+    uint32_t own_bin[S], own_pos[S];
+    if (fits) {
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            own_bin[i] = 0xffffu;
+            if (tid + i * T < (int)n_passed) {
+                const int2 w = passed[tid + i * T];
+                const int idx = index_of(w.y);
+                own[i] = make_composite((uint32_t)w.x, idx);
+                own_bin[i] = bin_of((uint32_t)w.x, idx);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+            if (own_bin[i] != 0xffffu) own_pos[i] = atomicAdd(&cnt[own_bin[i]], 1u);
+    } else {
+        regs.each([&](uint32_t bits, int pos, int) {
+            if (__uint_as_float(bits) >= v_lo) {
+                const uint32_t b = bin_of(bits, index_of(pos));
+                if (b != 0xffffu) atomicAdd(&cnt[b], 1u);
+            }
+        });
+    }
+    __syncthreads();
+    // ---- places: lane b has bin b
+    const uint32_t c = tid < p.n_deal ? cnt[tid] : 0u;
+    const uint32_t incl = wave_incl_scan_u32(c);
+    if (lane == kWave - 1) misc[8 + wave] = incl;
+    __syncthreads();
+    const uint32_t tot = lane < n_waves ? misc[8 + lane] : 0u;
+    const uint32_t tot_incl = wave_incl_scan_u32(tot);
+    uint32_t off = incl - c;
+    if (wave > 0) off += (uint32_t)__builtin_amdgcn_readlane((int)tot_incl, wave - 1);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)tot_incl, n_waves - 1);
+    if (tid < p.n_deal) {
+        cnt[tid] = off;
+        if (c) atomicAdd(&p.totals[r * p.n_deal + tid], c);
+    }
+    if (tid == 0) misc[6] = atomicAdd(&p.rows[r].cursor, total);
+    __syncthreads();
+    const int64_t base = misc[6];
+    uint32_t *segs = p.segs + (r * p.chunks + chunk) * (p.n_deal + 1);
+    if (tid < p.n_deal) segs[tid] = (uint32_t)base + off;
+    if (tid == 0) segs[p.n_deal] = (uint32_t)base + total;
+    u64 *pool = p.pool + r * p.pool_cap;
+    if (fits) {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+            if (own_bin[i] != 0xffffu) staged[cnt[own_bin[i]] + own_pos[i]] = own[i];
+        __syncthreads();
+        for (uint32_t i = tid; i < total; i += T)
+            if (base + i < p.pool_cap) pool[base + i] = staged[i];
+    } else {
+        // (every bin's place counts up from here on; the bins' starts have been written)
+        regs.each([&](uint32_t bits, int pos, int) {
+            if (__uint_as_float(bits) >= v_lo) {
+                const int idx = index_of(pos);
+                const uint32_t b = bin_of(bits, idx);
+                if (b != 0xffffu) {
+                    const int64_t to = base + atomicAdd(&cnt[b], 1u);
+                    if (to < p.pool_cap) pool[to] = make_composite(bits, idx);
+                }
+            }
+        });
+    }
+}
+
+// One bin of one row.
+template <int ELT>
+__global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
+    constexpr int T = kBinT, S = kBinCap / T, W = T >> 6;
+    __shared__ __align__(16) u64 buf[kBinCap];
+    __shared__ __align__(16) uint32_t cur[kBinSub + 4];
+    __shared__ uint32_t misc[kRowMisc];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t r = blockIdx.y;
+    // Workgroups go to the eight XCDs in turn; each XCD takes an eighth of the bins side by side (their number is a multiple of
+    // eight): the ends of the pieces and the table of their places share lines with the neighbouring bins'.
+    const int bin = (int)(blockIdx.x & 7u) * (p.n_deal >> 3) + (int)(blockIdx.x >> 3);
+    // (everything that the first steps want is asked for together)
+    const uint32_t cursor = p.rows[r].cursor;
+    const uint32_t *totals = p.totals + r * p.n_deal;
+    const uint32_t count = totals[bin];
+    uint32_t before = 0;  // candidates in the bins before this one: where its outputs start
+    for (int i = tid; i < bin; i += T) before += totals[i];
+    for (int i = tid; i < kBinSub; i += T) cur[i] = 0u;
+    if (cursor < (uint32_t)p.k || (int64_t)cursor > p.pool_cap || count == 0u) return;  // (uniform) no bin, or the row is left to the last launch
+    before = wave_incl_scan_u32(before);
+    if (lane == kWave - 1) misc[4 + wave] = before;
+    // f(candidate) for every candidate of the bin, and its place among them: the pieces of 64 chunks at a time (lane i of every
+    // wavefront looks up chunk i's), 16 lanes side by side on each, four pieces with two loads each in flight (a piece holds 16
+    // candidates on average where a quarter of the row is kept)
+    const u64 *pool = p.pool + r * p.pool_cap;
+    const uint32_t *segs = p.segs + r * p.chunks * (p.n_deal + 1) + bin;
+    auto gather = [&](auto f) {
+        constexpr int G = 16;
+        const int sl = lane & (G - 1);
+        uint32_t carry = 0;
+        for (int c0 = 0; c0 < p.chunks; c0 += kWave) {
+            uint32_t s0 = 0, len = 0;
+            if (c0 + lane < p.chunks) {
+                const uint32_t *sg = segs + (int64_t)(c0 + lane) * (p.n_deal + 1);
+                s0 = sg[0];
+                len = sg[1] - s0;
+            }
+            const uint32_t incl = wave_incl_scan_u32(len);
+            const uint32_t to = carry + incl - len;
+            carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+            uint32_t ps[4], pl[4], pt[4];
+            u64 v[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int src = u * (T / G) + wave * (kWave / G) + (lane / G);
+                ps[u] = (uint32_t)__shfl((int)s0, src);
+                pl[u] = (uint32_t)__shfl((int)len, src);
+                pt[u] = (uint32_t)__shfl((int)to, src);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) v[u][h] = pool[ps[u] + ((uint32_t)(sl + h * G) < pl[u] ? sl + h * G : 0)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if ((uint32_t)(sl + h * G) < pl[u]) f(v[u][h], pt[u] + sl + h * G);
+                for (uint32_t i = sl + 2 * G; i < pl[u]; i += G) f(pool[ps[u] + i], pt[u] + i);
+            }
+        }
+    };
+    static_assert(4 * (T / 16) == kWave, "64 chunks at a time");
+    const bool fits = count <= (uint32_t)kBinCap;  // uniform
+    uint32_t k_min = 0xffffffffu, k_max = 0u;
+    gather([&](u64 c, uint32_t place) {
+        const uint32_t key = (uint32_t)(c >> 32);
+        k_min = min(k_min, key);
+        k_max = max(k_max, key);
+        if (fits) buf[place] = c;
+    });
+    k_min = wave_min_u32(k_min);
+    k_max = wave_max_u32(k_max);
+    if (lane == 0) {
+        misc[8 + wave] = k_min;
+        misc[24 + wave] = k_max;
+    }
+    __syncthreads();
+    uint32_t start = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        start += misc[4 + w];
+        k_min = min(k_min, misc[8 + w]);
+        k_max = max(k_max, misc[24 + w]);
+    }
+    if (start >= (uint32_t)p.k) return;  // uniform
+    const int64_t out = r * p.k + start;
+    const uint32_t room = (uint32_t)p.k - start;  // outputs left from here on
+    int lg = 8;  // about a bin per candidate
+    while ((1 << lg) < kBinSub && (1 << lg) < (int)count) ++lg;
+    const int n_sub = 1 << lg;
+    RowBins bins;
+    bins.template set<ELT>(k_min, k_max, p.idx_bits, n_sub);
+    auto sub_of = [&](u64 c) { return bins.template bin<ELT>((uint32_t)(c >> 32), (uint32_t)c >> 1); };
+    // ranks of the ordered-by-sub-bin candidates buf[0 .. n), which are places [first, first + n) of the bin
+    auto rank_write = [&](uint32_t n, uint32_t first, auto start_of, auto end_of) {
+        for (uint32_t i = tid; i < n; i += T) {
+            const u64 c = buf[i];
+            const uint32_t b = sub_of(c);
+            const uint32_t s = start_of(b) - first, e = end_of(b) - first;
+            u64 peer[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) peer[u] = buf[s + u < e ? s + u : i];  // (itself: not larger)
+            uint32_t rank = first + s;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += peer[u] > c ? 1u : 0u;
+            for (uint32_t j = s + 4; j < e; ++j) rank += buf[j] > c ? 1u : 0u;
+            if (rank < room) write_composite<ELT>(c, p.out_vals, p.out_idx, out + rank);
+        }
+    };
+    if (!fits) {
+        // More than the LDS holds (a place of the row that the sample saw too little of): the pieces are read once to count and
+        // then once for every stretch of sub-bins that fits.
+        __syncthreads();  // (misc has been read)
+        gather([&](u64 c, uint32_t) { atomicAdd(&cur[sub_of(c)], 1u); });
+        __syncthreads();
+        row_scan(cur, misc, n_sub, count);
+        if (misc[4] != 0u) {  // ties by the dozen: left to the last launch
+            if (tid == 0) p.rows[r].failed = 1u;
+            return;
+        }
+        // (a sub-bin holds kRowBinMax at most, so those that start inside a window of kBinCap - kRowBinMax places fit)
+        constexpr uint32_t window = kBinCap - kRowBinMax;
+        uint32_t first = 0;  // the window's first place, and its highest sub-bin
+        for (int top = n_sub - 1; top >= 0 && first < room && first < count;) {
+            uint32_t low = (uint32_t)top;  // its lowest sub-bin
+            for (int b = tid; b <= top; b += T)
+                if (cur[b] < first + window) low = min(low, (uint32_t)b);
+            low = wave_min_u32(low);
+            if (lane == 0) misc[8 + wave] = low;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < W; ++w) low = min(low, misc[8 + w]);
+            const uint32_t end = low > 0u ? cur[low - 1u] : count;
+            // cur[b] moves from the place where sub-bin b starts to its end, which is where b - 1 starts
+            gather([&](u64 c, uint32_t) {
+                const uint32_t b = sub_of(c);
+                if (b >= low && b <= (uint32_t)top) buf[atomicAdd(&cur[b], 1u) - first] = c;
+            });
+            __syncthreads();
+            rank_write(end - first, first, [&](uint32_t b) { return b == (uint32_t)top ? first : cur[b + 1u]; }, [&](uint32_t b) { return cur[b]; });
+            __syncthreads();
+            first = end;
+            top = (int)low - 1;
+        }
+        return;
+    }
+    // ---- into registers and counted
+    u64 own[S];
+    uint32_t at[S];  // sub-bin, and place among its arrivals in the upper half
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        own[i] = 0ull;
+        if (i * T < (int)count && tid + i * T < (int)count) own[i] = buf[tid + i * T];
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+        if (i * T < (int)count && own[i]) {
+            const uint32_t b = sub_of(own[i]);
+            at[i] = b | (atomicAdd(&cur[b], 1u) << 16);
+        }
+    __syncthreads();
+    row_scan(cur, misc, n_sub, count);
+    if (misc[4] != 0u) {
+        // many candidates in one place of the bin's range (ties): a bitonic network over the bin, the places past its
+        // end up to a power of two counting as empty - every comparison puts the larger one first (the first step of a size
+        // pairs places mirrored in their block, the others places `stride` apart), so nothing is ever moved there
+        int kp = 1;
+        while (kp < (int)count) kp <<= 1;
+        for (int size = 2; size <= kp; size <<= 1)
+            for (int stride = size >> 1; stride >= 1; stride >>= 1) {
+                for (int i = tid; i < (kp >> 1); i += T) {
+                    const int lo = ((i & ~(stride - 1)) << 1) | (i & (stride - 1));
+                    const int hi = stride == (size >> 1) ? (lo | (size - 1)) - (lo & (size - 1)) : lo + stride;
+                    if (hi < (int)count) {
+                        const u64 x = buf[lo], y = buf[hi];
+                        if (y > x) {
+                            buf[lo] = y;
+                            buf[hi] = x;
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+        for (uint32_t i = tid; i < count && i < room; i += T) write_composite<ELT>(buf[i], p.out_vals, p.out_idx, out + i);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+        if (i * T < (int)count && own[i]) buf[cur[at[i] & 0xffffu] + (at[i] >> 16)] = own[i];
+    __syncthreads();
+    rank_write(count, 0u, [&](uint32_t b) { return cur[b]; }, [&](uint32_t b) { return b > 0u ? cur[b - 1u] : count; });
+}
+
+// ------------------------------------------------------------------------------------ host
+static int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
+
+// Rows of more than 2 * 32768 elements (shorter ones would be sampled nearly whole) with at most 512 chunks, and k for which
+// the sample says something: 64 of its elements or more among the k largest.
+bool plan_exact_deal(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, DealPlan *out) {
+    DealPlan p;
+    memset(&p, 0, sizeof p);
+    const int ve = dtype == ATK_F32 ? 4 : 8;
+    if (n < 2 * kDealSample || m > 65535) return false;
+    const double q = (double)k / (double)n, expect = q * kDealSample;
+    if (expect < 64.0 || q > 0.6) return false;
+    // (rows off the 16-byte boundaries: up to ve - 1 more elements)
+    p.chunks = (int)((n + (ptr16 && n % ve == 0 ? 0 : ve - 1) + kDealChunk - 1) / kDealChunk);
+    if (p.chunks > kDealChunksMax) return false;
+    int64_t bins = (k + kDealBinMean - 1) / kDealBinMean;
+    bins = (bins + 7) / 8 * 8;
+    if (bins > kDealBinsMax) return false;
+    p.bins = (int)bins;
+    // six standard deviations of the sample's count above what k of n elements make of it; the pool takes as many again
+    p.sample_rank = (int)std::ceil(expect + 6.0 * std::sqrt(expect * (1.0 - q)) + 6.0);
+    const double most = ((double)p.sample_rank + 6.0 * std::sqrt((double)p.sample_rank) + 32.0) * (double)n / kDealSample;
+    p.pool_cap = std::min<int64_t>(n, (int64_t)most);
+    // the sample's lower bound: 8192 of its 32768 elements, 512 in each wavefront, five deviations below the threshold
+    const double part = (double)p.sample_rank / 4.0 / (kDealT / kWave);
+    p.rank = std::min(512, (int)std::ceil(part + 5.0 * std::sqrt(part) + 2.0));
+    int64_t off = 0;
+    auto take = [&](int64_t bytes) {
+        const int64_t at = off;
+        off += align256(bytes);
+        return at;
+    };
+    p.rows_off = take(m * (int64_t)sizeof(DealRow));
+    p.table_off = take(m * kDealFine * 2);
+    p.totals_off = take(m * bins * 4);
+    p.segs_off = take(m * p.chunks * (bins + 1) * 4);
+    p.pool_off = take(m * p.pool_cap * 8);
+    p.rest_off = take(m * k * 16);  // two buffers of k per row for the rows that go digit by digit
+    p.bytes = off;
+    *out = p;
+    return true;
+}
+
+template <int ELT>
+static hipError_t launch_deal_t(const DealPlan &pl, const DealParams &prm, int64_t m, hipStream_t stream) {
+    const size_t lds = (size_t)kDealStage * 8 + (kDealBinsMax + 4 + kRowMisc) * 4 + kDealFine * 2;
+    static_assert(kDealStage * 8 + (kDealBinsMax + 4 + kRowMisc) * 4 + kDealFine * 2 <= 64 * 1024, "dynamic LDS without asking");
+    hipLaunchKernelGGL(ex_sample_kernel<ELT>, dim3((unsigned)m), dim3(kDealT), 0, stream, prm);
+    hipLaunchKernelGGL(ex_deal_kernel<ELT>, dim3((unsigned)pl.chunks, (unsigned)m), dim3(kDealT), lds, stream, prm);
+    hipLaunchKernelGGL(ex_bins_kernel<ELT>, dim3((unsigned)pl.bins, (unsigned)m), dim3(kBinT), 0, stream, prm);
+    return hipGetLastError();
+}
+
+hipError_t launch_exact_deal(const DealPlan &pl, int64_t m, int64_t n, int64_t k, int64_t idx_n, int dtype, const void *x,
+                             const int32_t *xi, void *out_vals, int32_t *out_idx, void *data, hipStream_t stream) {
+    DealParams prm;
+    memset(&prm, 0, sizeof prm);
+    unsigned char *base = (unsigned char *)data;
+    prm.x = x;
+    prm.xi = xi;
+    prm.out_vals = out_vals;
+    prm.out_idx = out_idx;
+    prm.n = (int)n;
+    prm.k = (int)k;
+    prm.idx_bits = 1;
+    while (((int64_t)1 << prm.idx_bits) < idx_n) ++prm.idx_bits;
+    prm.rank = pl.rank;
+    prm.rows = (DealRow *)(base + pl.rows_off);
+    prm.table = (uint16_t *)(base + pl.table_off);
+    prm.totals = (uint32_t *)(base + pl.totals_off);
+    prm.segs = (uint32_t *)(base + pl.segs_off);
+    prm.pool = (u64 *)(base + pl.pool_off);
+    prm.pool_cap = pl.pool_cap;
+    prm.n_deal = pl.bins;
+    prm.chunks = pl.chunks;
+    prm.sample_rank = pl.sample_rank;
+    const hipError_t e = dtype == ATK_F32 ? launch_deal_t<ATK_F32>(pl, prm, m, stream) : launch_deal_t<ATK_BF16>(pl, prm, m, stream);
+    if (e != hipSuccess) return e;
+    u64 *buf0 = (u64 *)(base + pl.rest_off);
+    return launch_exact_rest_rows(m, n, k, prm.idx_bits, dtype, x, xi, prm.rows, pl.pool_cap, buf0, buf0 + m * k, out_vals, out_idx, stream);
+}
+
+}  // namespace atk
