@@ -79,9 +79,9 @@ enum {
  * n need not be a multiple of b: bucket j holds the indices j, j+b, ... below n (the short
  * buckets of Figure 2); k_b <= floor(n/b) keeps every bucket long enough.
  *
- * Stage 2 runs inside the same kernel launch as long as its b*k_b candidates fit one workgroup
- * (atk_stage2_max_candidates()); with more, Stage 1 leaves the candidates in library scratch and
- * the long-row exact selection picks the k largest of them in further launches.
+ * Stage 2 runs inside the same kernel launch where its b*k_b candidates fit one workgroup (at most
+ * atk_stage2_max_candidates()) and that is the faster way; else Stage 1 leaves the candidates in library scratch and
+ * the exact selection picks the k largest of them in a further launch or several.
  *
  * ATK_ERR_UNSUPPORTED: k_b > ATK_MAX_KB.
  */
@@ -136,7 +136,7 @@ int atk_last_hip_error(void);
 int atk_check_approx(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype);
 int atk_check_exact(int64_t m, int64_t n, int64_t k, int dtype);
 
-/* Largest b*k_b for which Stage 2 runs on-chip in the same launch (more candidates take further launches). */
+/* Largest b*k_b for which Stage 2 can run on-chip in the same launch (more candidates take further launches). */
 int64_t atk_stage2_max_candidates(void);
 
 /* Bytes of library scratch an approx_topk / approx_topk_assign / exact_topk call with these arguments uses at most
@@ -161,7 +161,8 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * PK=0 (bf16: no packed queue words), XS=0 / XS=1 (exact_topk with k <= 512: never / also on small
  * inputs guess the threshold from a sample of the row first), XC=<elements of a row per workgroup of
  * exact_topk's sweeps: a power of two from 1024 to 16384>, XR=0 (exact_topk: no row is held in one workgroup's
- * registers or dealt to bins; XS and XC, which concern the other paths, imply it), XD=0 (no dealing alone), LN=0 (k_b = 1: the general kernel instead of the
+ * registers or dealt to bins; XS and XC, which concern the other paths, imply it), XD=0 (no dealing alone), TS=0 / TS=1 (Stage 2 in a
+ * launch of its own only where it has to be / wherever there is one), LN=0 (k_b = 1: the general kernel instead of the
  * one specialised for running maxima), LM=0 (k_b = 1: the lanes of a column merge through per-part lists and
  * a pass over them instead of atomic maxima in LDS), HF=0 / HF=1 (never / whenever the shape allows, two
  * workgroups - a helper and a finisher - share a row of a Stage-2 plan), HQ=<sixty-fourths of the matrix rows

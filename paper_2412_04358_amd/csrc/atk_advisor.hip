@@ -10,6 +10,7 @@
 #include <cstdint>
 
 #include "atk_common.h"
+#include "atk_exact.h"
 
 namespace atk {
 
@@ -34,6 +35,14 @@ static double eq1_recall(int64_t k, int64_t b, int64_t k_b) {
 // workgroups when rows are split, and Stage 2.  Small launches are bound by the chain of
 // hand-overs instead (workgroup merge, ticket, merge of the splits, Stage 2): a floor.
 static double estimate_us(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype) {
+    if (b * k_b > k && (b * k_b > atk_stage2_max_candidates() || stage2_apart(m, n, k, b, k_b, dtype))) {
+        // Stage 2 as a launch of its own over the (value, index) pairs that Stage 1 leaves in scratch: a launch, a chain of steps
+        // that grows a little with the candidates of a row, and the work on all of them (2048 lists of 1024, k = 512: 10 us;
+        // 128 lists of 8192, k = 4096: 12); lists that no workgroup holds take several launches
+        const double nc = (double)(b * k_b);
+        return estimate_us(m, n, b * k_b, b, k_b, dtype) + 5.0 + 0.0005 * std::min(nc, 16384.0) + (double)m * (nc + 2.0 * (double)k) * 1.6e-6 +
+               (nc > 16384.0 ? 15.0 : 0.0);
+    }
     const double es = (dtype == ATK_F32) ? 4.0 : 2.0;
     const double rd = (double)m * (double)n * es, wr = (double)m * (double)k * (es + 4.0), bytes = rd + wr;
     int KB = 1;
@@ -74,9 +83,6 @@ static double estimate_us(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
     if (stage2 && KB >= 2) us += 0.005 * cand;
     // more than four candidates per lane of the selecting workgroup: digit by digit (k = 512, b = 4096: 32 us)
     if (stage2 && cand > 2048.0) us += 0.004 * cand;
-    // more candidates than one workgroup holds: Stage 1 leaves them in scratch and exact_topk's kernels select from
-    // the pairs (further launches; one workgroup per row in LDS up to 160 KB, sweeps beyond)
-    if (stage2 && b * k_b > atk_stage2_max_candidates()) us += 35.0 + 0.02 * (double)k + (double)m * cand * 24.0 / 5.0e6;
     // more rows than CUs: the selections of the rows that share a CU queue up behind each other (measured 2 us
     // a row at 1024 candidates, k = 256; 3 us at k = 512)
     if (stage2 && m > 256) us += (double)m / 256.0 * (0.001 * cand + 0.004 * (double)k);

@@ -80,6 +80,7 @@ static PlanOverride parse_plan_override(const char *e) {
     if (const char *q = field("LM")) o.lm_off = atoi(q) == 0;
     if (const char *q = field("LN")) o.ln_off = atoi(q) == 0;
     if (const char *q = field("XS")) o.xs = atoi(q) == 0 ? -1 : 1;
+    if (const char *q = field("TS")) o.ts = atoi(q) == 0 ? -1 : 1;
     if (const char *q = field("XD")) o.xd_off = atoi(q) == 0;
     if (const char *q = field("XR")) o.xr_off = atoi(q) == 0;
     if (const char *q = field("XC")) {
@@ -733,6 +734,34 @@ int make_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype
     return make_plan_aligned(m, n, k, b, k_b, dtype, true, pl);
 }
 
+// Whether Stage 2 over candidates that the fused kernels could select from (at most kStage2MaxCand) is better off as a launch
+// of its own: Stage 1 writes its survivors to scratch as pairs, and the row kernel of exact_topk (atk_exact_row.hip) selects
+// from them.  The fused selection is quick where its bins serve: a lane for every four candidates or more, and values whose keys
+// do not spread over every exponent.  Measured fused -> apart (us):
+bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype) {
+    if (plan_override().ts) return plan_override().ts > 0;
+    const int64_t nc = b * k_b, len = n / b;
+    const int64_t es = (dtype == ATK_F32) ? 4 : 2;
+    // More candidates than 512 lanes hold in registers go digit by digit and through a bitonic sort: 128 x 65536 f32, k = 1024,
+    // b = 512, k_b = 8: 98 -> 28; k = 64, b = 4096: 23 -> 15; k = 2000, b = 4000: 47 -> 17; 2048 x 65536, b = 1024, k_b = 4, k = 2048: 244 -> 138; one row of
+    // 8192 bf16, k = 2000, b = 4000: 40 -> 17.
+    // (few winners among them on rows past 2^17 elements stay: there few rows run as column blocks that one launch brings together)
+    if (nc > 2048 && (16 * k >= nc || n <= (1 << 17))) return true;
+    // Short buckets, and a large share of the survivors kept: a bucket whose k_b-th survivor is not positive comes up now and then
+    // (one in 2^8 with eight elements), stretches the range of the keys, and its row goes the long way too.  4 x 8192 f32,
+    // k = 1024, b = 2048: 24 -> 8; 128 x 16384 bf16, k = 1024, b = 1024, k_b = 2: 30 -> 13; 128 x 8192, k = 512, b = 1024: 17 -> 11 (four
+    // rows: 6 -> 8); with twice the elements per bucket 128 x 16384 stays at 7 (10 apart).
+    const int64_t few_rows = m < 32 ? 4 : 8;
+    if (4 * k >= nc && len <= few_rows * k_b && nc >= (k_b == 1 ? (m >= 512 ? 512 : 1024) : 2048)) return true;
+    // Many short rows with queues: the lanes that select hold LDS and registers that the streaming of other rows wants (2048 x
+    // 8192 bf16, b = 512, k_b = 2: 10.8 without Stage 2, k = 512: 35.5 -> 21.3, k = 64: 32.5 -> 17.1; 1024 x 4096 f32, k = 512: 38 -> 15;
+    // 2048 x 8192 f32, k = 64, b = 128, k_b = 8: 54 -> 37).  Rows past 32 KB stream long enough to hide it (2048 x 32768 f32, b = 512,
+    // k_b = 2: 49 -> 57), and so do batches of 700 rows; in f32 few winners of 2048 are quick to find (1024 x 8192, k = 64,
+    // b = 1024, k_b = 2: 17 -> 21; bf16: 21 -> 13).
+    if (m >= 1024 && k_b >= 2 && nc >= 1024 && n * es <= (32 << 10) && (dtype == ATK_BF16 || nc <= 1024 || 4 * k >= nc)) return true;
+    return false;
+}
+
 // ------------------------------------------------------------------------------------ scratch pool
 // Two grow-only allocations per device: `state` (tickets and other words that every kernel
 // leaves zeroed, so that the next call can rely on zeros) and `data` (partial lists and
@@ -932,11 +961,11 @@ static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pai
 }
 
 static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment,
-                          bool ptr16, FullPlan *fp, bool allow_pair = true, bool cover = false) {
+                          bool ptr16, FullPlan *fp, bool allow_pair = true, bool cover = false, bool allow_two = true) {
     if (assignment != ATK_INTERLEAVED && assignment != ATK_CONTIGUOUS) return ATK_ERR_BAD_PARAMS;
     const int es = (dtype == ATK_F32) ? 4 : 2;
     const int64_t nc = b * k_b;
-    fp->two_step = nc > k && nc > kStage2MaxCand;
+    fp->two_step = nc > k && (nc > kStage2MaxCand || (allow_two && stage2_apart(m, n, k, b, k_b, dtype)));
     const int64_t k1 = fp->two_step ? nc : k;  // two steps: Stage 1 writes all its candidates, bucket by bucket
     int rc = (assignment == ATK_CONTIGUOUS) ? make_contig_plan(m, n, k1, b, k_b, dtype, ptr16, &fp->s1)
                                             : make_plan_aligned(m, n, k1, b, k_b, dtype, ptr16, &fp->s1, allow_pair);
@@ -992,7 +1021,7 @@ static int run_approx(const void *x, int64_t m, int64_t n, int64_t k, int64_t b,
     if (((uintptr_t)x | (uintptr_t)out_vals) & (uintptr_t)(es - 1)) return ATK_ERR_ALIGN;
     if ((uintptr_t)out_idx & 3u) return ATK_ERR_ALIGN;
     FullPlan fp;
-    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, ((uintptr_t)x & 15u) == 0, &fp);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, ((uintptr_t)x & 15u) == 0, &fp, true, false, trace == nullptr);
     if (rc != ATK_OK) return rc;
     if (trace) {  // measurement build: the lean kernels alone, and room for every wavefront's timestamps
         if (fp.two_step || assignment != ATK_INTERLEAVED || !fp.s1.lean) return ATK_ERR_UNSUPPORTED;
@@ -1127,7 +1156,7 @@ int approx_topk_noalloc(const void *x, int64_t m, int64_t n, int64_t k, int64_t 
     if ((uintptr_t)out_idx & 3u) return ATK_ERR_ALIGN;
     FullPlan fp;
     // (no pair plans here: their mailbox has to be zero between calls, and this entry point shares its array)
-    rc = make_full_plan(m, n, k, b, k_b, dtype, ATK_INTERLEAVED, ((uintptr_t)x & 15u) == 0, &fp, false);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, ATK_INTERLEAVED, ((uintptr_t)x & 15u) == 0, &fp, false, false, false);
     if (rc != ATK_OK) return rc;
     if (fp.two_step) return ATK_ERR_UNSUPPORTED;  // Stage 2 over more candidates than one workgroup holds: approx_topk only
     if (fp.state_bytes > ATK_NOALLOC_STATE_BYTES || fp.data_bytes > ATK_NOALLOC_SCRATCH_BYTES - ATK_NOALLOC_STATE_BYTES)
@@ -1177,7 +1206,7 @@ int64_t atk_trace_bytes(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b,
     int rc = check_approx(m, n, k, b, k_b, dtype);
     if (rc != ATK_OK) return rc;
     FullPlan fp;
-    rc = make_full_plan(m, n, k, b, k_b, dtype, ATK_INTERLEAVED, true, &fp);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, ATK_INTERLEAVED, true, &fp, true, false, false);
     if (rc != ATK_OK) return rc;
     return fp.s1.grid * kTraceWaves * kTracePhases * 8;
 }

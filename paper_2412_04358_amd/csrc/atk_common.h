@@ -79,6 +79,7 @@ struct PlanOverride {
     bool lm_off;      // LM=0: lanes that share a column merge through the LDS exchange, not by LDS atomic maximum
     int xs;           // exact_topk sampled threshold: 0 not set, 1 forced on (XS=1), -1 off (XS=0)
     int xc;           // exact_topk sweep chunk in elements
+    int ts;           // Stage 2 as a launch of its own: 0 not set, 1 wherever there is a Stage 2 (TS=1), -1 only where it has to be (TS=0)
     bool xd_off;      // XD=0: exact_topk never deals the elements of long rows to bins
     bool xr_off;      // XR=0: exact_topk never holds a row in one workgroup's registers (nor with XS or XC, which are about longer rows)
     int hf;           // two workgroups per row (helper + finisher): 0 not set, 1 forced on where legal (HF=1), -1 off (HF=0)

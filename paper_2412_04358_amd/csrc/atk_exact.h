@@ -78,4 +78,7 @@ int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
 hipError_t launch_exact(const ExactPlan &plan, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
                         void *state, void *data, hipStream_t stream);
 
+// approx_topk: Stage 2 over candidates that the fused kernels could select from as a launch of its own (planner, estimate).
+bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype);
+
 }  // namespace atk
