@@ -69,19 +69,36 @@ __device__ __forceinline__ void insert(float (&val)[KB], int (&tt)[KB], float v,
     tt[0] = c[0] ? t : tt[0];
 }
 
-// ---- batch scan for long queues (k_b > 8) -------------------------------------------------------------------------
+// ---- batch scan for long queues (k_b > 4) -------------------------------------------------------------------------
 // Inserting element by element costs about five lane operations per slot and element.  Where most elements enter
 // the queue (short buckets: the top quarter of every bucket is kept when b*k_b = k = n/4) it is cheaper to take
 // k_b matrix rows at a time, sort them with a network, and fold the sorted batch into the queue with the
-// bitonic merge that also joins the lanes' queues: about 3.3 lane operations per slot and element.  A network has no
-// notion of "earlier element wins ties", so the queues hold words that are distinct: [63:32] the value's order
-// key, [31:1] 0x7fffffff - matrix row, [0] "was -0" (the composite word with the row in place of the column index).
-__device__ __forceinline__ u64 row_word(uint32_t bits, int t) {
-    return ((u64)ukey_of_bits(bits) << 32) | ((0x7fffffffu - (uint32_t)t) << 1) | (bits == 0x80000000u ? 1u : 0u);
+// bitonic merge that also joins the lanes' queues.  A network has no notion of "earlier element wins ties", so the queues
+// hold words that are distinct: [62:31] the value's order key, [30:1] 0x3fffffff - the element's number among
+// the lane's rows, [0] "was -0"; 0 = empty.  Bit 63 is clear and, for every number, the exponent field neither
+// all ones nor zero (the key of +inf is 0xff800000, of -inf 0x007fffff), so a word is the bit pattern of a positive normal
+// double and the order of the words is the order of the doubles: a compare-exchange is v_max_f64 and v_min_f64, two
+// instructions at full rate, instead of a 64-bit compare and four selects (128 x 65536 f32, k = 16384: k_b = 16:
+// 27.5 -> 20.2 us; k_b = 8, element by element
+// before: 20.2 -> 18.5; one row of 2^20, b = 1024, k_b = 8: 132 -> 30; 64 x 2^20, k = 1024, b = 1024, k_b = 8: 140 -> 88).
+__device__ __forceinline__ double word_max(double a, double b) {
+    double d;
+    asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));  // (fmax() would quiet its operands first)
+    return d;
+}
+__device__ __forceinline__ double word_min(double a, double b) {
+    double d;
+    asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ double row_word(uint32_t bits, uint32_t s) {
+    const uint32_t key = ukey_of_bits(bits);
+    const uint32_t lo = (key << 31) | ((0x3fffffffu - s) << 1) | (bits == 0x80000000u ? 1u : 0u);
+    return __hiloint2double((int)(key >> 1), (int)lo);
 }
 // Batcher's odd-even merge sort of N words, largest first (N a power of two; 19 compare-exchanges for 8, 63 for 16).
 template <int N>
-__device__ __forceinline__ void sort_desc(u64 (&a)[N]) {
+__device__ __forceinline__ void sort_desc(double (&a)[N]) {
 #pragma unroll
     for (int p = 1; p < N; p *= 2)
 #pragma unroll
@@ -91,18 +108,32 @@ __device__ __forceinline__ void sort_desc(u64 (&a)[N]) {
 #pragma unroll
                 for (int i = 0; i < k; ++i)
                     if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
-                        const u64 x = a[i + j], y = a[i + j + k];
-                        const bool sw = y > x;
-                        a[i + j] = sw ? y : x;
-                        a[i + j + k] = sw ? x : y;
+                        const double x = a[i + j], y = a[i + j + k];
+                        a[i + j] = word_max(x, y);
+                        a[i + j + k] = word_min(x, y);
                     }
 }
-// one word into a queue sorted largest first
-template <int KB>
-__device__ __forceinline__ void insert_word(u64 (&q)[KB], u64 c) {
+// mine <- the N largest of (mine U theirs); both sorted descending, result sorted descending.
+template <int N>
+__device__ __forceinline__ void merge_words(double (&mine)[N], const double (&theirs)[N]) {
 #pragma unroll
-    for (int j = KB - 1; j >= 1; --j) q[j] = (c > q[j - 1]) ? q[j - 1] : (c > q[j] ? c : q[j]);
-    q[0] = c > q[0] ? c : q[0];
+    for (int j = 0; j < N; ++j) mine[j] = word_max(mine[j], theirs[N - 1 - j]);
+#pragma unroll
+    for (int stride = N / 2; stride >= 1; stride >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if ((i & stride) == 0) {
+                const double x = mine[i], y = mine[i + stride];
+                mine[i] = word_max(x, y);
+                mine[i + stride] = word_min(x, y);
+            }
+}
+// one word into a queue sorted largest first
+template <int N>
+__device__ __forceinline__ void insert_word(double (&q)[N], double c) {
+#pragma unroll
+    for (int j = N - 1; j >= 1; --j) q[j] = word_max(q[j], word_min(q[j - 1], c));  // (q[j-1] >= q[j]: c clamped between them)
+    q[0] = word_max(q[0], c);
 }
 
 // mine <- the N largest of (mine U theirs), as multisets; both sorted descending, result sorted descending.
@@ -359,10 +390,8 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     trace_mark<TR>(p.trace, 0);  // the wavefront has started
     constexpr int ES = (ELT == ATK_F32) ? 4 : 2;
     constexpr bool PK = PKF && ELT == ATK_BF16 && KB >= 4;  // packed 32-bit queues (host: rows per split < 32766)
-    // queues of distinct 64-bit words, fed k_b matrix rows at a time: pays from sixteen slots on (128 x 65536 f32,
-    // k = 16384, k_b = 16: 44.8 -> 36.0 us; with eight slots the 64-bit compares cost more than the shorter
-    // network saves: 19.2 -> 21.8 us, and 164 -> 185 us on 128 x 2^20, b = 8)
-    constexpr bool BATCH = KB >= 16 && !PK;
+    // queues of distinct 64-bit words, fed k_b matrix rows at a time (the pooled floors work on the other form)
+    constexpr bool BATCH = KB >= 8 && !PK && !RF;
     const int tid = threadIdx.x, T = blockDim.x;
     int wg = blockIdx.x, cb, sp, r, cgl, ph;
     divmod(wg, p.colblocks, p.cb_shift, wg, cb);
@@ -407,7 +436,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     float val[V][KB];
     int tt[V][KB];
     uint32_t pk[PK ? V : 1][PK ? KB : 1];
-    u64 qw[BATCH ? V : 1][BATCH ? KB : 1];  // BATCH: the queues, as row words
+    double qw[BATCH ? V : 1][BATCH ? KB : 1];  // BATCH: the queues, as row words
     float last_f[BATCH ? V : 1];            // ... and the value of each queue's last slot (NaN while it is empty)
 #pragma unroll
     for (int e = 0; e < V; ++e)
@@ -417,7 +446,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
             tt[e][j] = kEmptyT;
             if constexpr (PK) pk[e][j] = 0u;
             if constexpr (BATCH) {
-                qw[e][j] = 0ull;
+                qw[e][j] = 0.0;
                 last_f[e] = __uint_as_float(0x7fc00000u);
             }
         }
@@ -426,7 +455,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
         if constexpr (PK)                                                                            \
             insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0x7fff - ((row) - t0)) << 1));             \
         else if constexpr (BATCH)                                                                    \
-            insert_word<KB>(qw[e], row_word(xb, (row)));                                             \
+            insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - t0 - ph) / p.P)));                                             \
         else                                                                                         \
             insert<KB>(val[e], tt[e], __uint_as_float(xb), (row));                                   \
     } while (0)
@@ -562,6 +591,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
             // k_b matrix rows at a time; the next batch's loads are issued before this one is worked on.  Rows past
             // the end re-read row t and are dropped.
             RowVec<ELT, V> v[KB], w[KB];
+            uint32_t seq = (uint32_t)((t - t0 - ph) / step);  // number of the batch's first row among the lane's
             bool have = t < t1;
             if (have) {
 #pragma unroll
@@ -591,18 +621,19 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
                 if (__ballot(any) != 0ull) {
 #pragma unroll
                     for (int e = 0; e < V; ++e) {
-                        u64 bt[KB];
+                        double bt[KB];
 #pragma unroll
                         for (int u = 0; u < KB; ++u) {
-                            const int tu = t + u * step;
-                            bt[u] = tu < t1 ? row_word(elem_bits<ELT, V>(v[u], e), tu) : 0ull;
+                            const double c = row_word(elem_bits<ELT, V>(v[u], e), seq + (uint32_t)u);
+                            bt[u] = t + u * step < t1 ? c : 0.0;
                         }
                         sort_desc<KB>(bt);
-                        merge_topk<KB>(qw[e], bt);
-                        const uint32_t lk = (uint32_t)(qw[e][KB - 1] >> 32);
-                        last_f[e] = __uint_as_float(qw[e][KB - 1] ? bits_of_ukey(lk) : 0x7fc00000u);
+                        merge_words<KB>(qw[e], bt);
+                        const u64 lw = (u64)__double_as_longlong(qw[e][KB - 1]);
+                        last_f[e] = __uint_as_float(lw ? bits_of_ukey((uint32_t)(lw >> 31)) : 0x7fc00000u);
                     }
                 }
+                seq += KB;
 #pragma unroll
                 for (int u = 0; u < KB; ++u) v[u] = w[u];
                 t = tn;
@@ -719,10 +750,10 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
         for (int e = 0; e < V; ++e)
 #pragma unroll
             for (int j = 0; j < KB; ++j) {
-                const u64 c = qw[e][j];
+                const u64 c = (u64)__double_as_longlong(qw[e][j]);
                 if (c != 0ull) {
-                    val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 32)));
-                    tt[e][j] = (int)(0x7fffffffu - ((uint32_t)c >> 1));
+                    val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 31)));
+                    tt[e][j] = t0 + ph + (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu)) * p.P;
                 }
             }
     }
