@@ -751,7 +751,7 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
     // (one in 2^8 with eight elements), stretches the range of the keys, and its row goes the long way too.  4 x 8192 f32,
     // k = 1024, b = 2048: 24 -> 8; 128 x 16384 bf16, k = 1024, b = 1024, k_b = 2: 30 -> 13; 128 x 8192, k = 512, b = 1024: 17 -> 11 (four
     // rows: 6 -> 8); with twice the elements per bucket 128 x 16384 stays at 7 (10 apart).
-    const int64_t few_rows = m < 32 ? 4 : 8;
+    const int64_t few_rows = m < 32 && k_b == 1 ? 4 : 8;
     if (4 * k >= nc && len <= few_rows * k_b && nc >= (k_b == 1 ? (m >= 512 ? 512 : 1024) : 2048)) return true;
     // Many short rows with queues: the lanes that select hold LDS and registers that the streaming of other rows wants (2048 x
     // 8192 bf16, b = 512, k_b = 2: 10.8 without Stage 2, k = 512: 35.5 -> 21.3, k = 64: 32.5 -> 17.1; 1024 x 4096 f32, k = 512: 38 -> 15;
