@@ -130,16 +130,6 @@ def exact_topk_raw(x_ptr, m, n, k, dtype, out_vals_ptr, out_idx_ptr, stream_ptr=
     return load_library().exact_topk(x_ptr, m, n, k, dtype, out_vals_ptr, out_idx_ptr, stream_ptr)
 
 
-def _dtype_code(t):
-    import torch
-
-    if t.dtype == torch.float32:
-        return ATK_F32
-    if t.dtype == torch.bfloat16:
-        return ATK_BF16
-    raise TypeError("x must be float32 or bfloat16")
-
-
 def _tensor_args(x):
     import torch
 
@@ -147,7 +137,38 @@ def _tensor_args(x):
         raise ValueError("x must live on the GPU")
     if x.dim() != 2 or not x.is_contiguous():
         raise ValueError("x must be a contiguous (m, n) tensor")
-    return torch, x.shape[0], x.shape[1], _dtype_code(x)
+    dtype = x.dtype
+    if dtype is torch.float32:
+        code = ATK_F32
+    elif dtype is torch.bfloat16:
+        code = ATK_BF16
+    else:
+        raise TypeError("x must be float32 or bfloat16")
+    m, n = x.shape
+    return torch, m, n, code
+
+
+def _on_device(torch, x, k, out, call):
+    """call(out_vals address, out_idx address, stream) with x's device current, on torch's current stream of it.
+
+    A call of a few microseconds on the GPU waits for its host side, so that is kept short: the device is only made
+    current where it is not, and the stream is asked for as the raw handle (torch.cuda.device() and
+    torch.cuda.current_stream(), each with an object of its own, took 4 of the 12 us of a small call)."""
+    device = x.device
+    index = device.index
+    if torch._C._cuda_getDevice() != index:
+        with torch.cuda.device(device):
+            return _on_device(torch, x, k, out, call)
+    if out is None:
+        m = x.shape[0]
+        vals = x.new_empty((m, k))
+        idx = torch.empty((m, k), dtype=torch.int32, device=device)
+    else:
+        vals, idx = out
+    code = call(vals.data_ptr(), idx.data_ptr(), torch._C._cuda_getCurrentRawStream(index))
+    if code:
+        _check(code)
+    return vals, idx
 
 
 def approx_topk(x, k, b, k_b, out=None, assignment=None):
@@ -158,33 +179,18 @@ def approx_topk(x, k, b, k_b, out=None, assignment=None):
     ATK_INTERLEAVED / ATK_CONTIGUOUS call approx_topk_assign.
     """
     torch, m, n, dt = _tensor_args(x)
-    with torch.cuda.device(x.device):
-        if out is None:
-            vals = torch.empty((m, k), dtype=x.dtype, device=x.device)
-            idx = torch.empty((m, k), dtype=torch.int32, device=x.device)
-        else:
-            vals, idx = out
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-        if assignment is None:
-            _check(approx_topk_raw(x.data_ptr(), m, n, k, b, k_b, dt, vals.data_ptr(), idx.data_ptr(), stream))
-        else:
-            _check(approx_topk_assign_raw(x.data_ptr(), m, n, k, b, k_b, dt, int(assignment), vals.data_ptr(),
-                                          idx.data_ptr(), stream))
-    return vals, idx
+    lib = _lib or load_library()
+    if assignment is None:
+        return _on_device(torch, x, k, out, lambda v, i, s: lib.approx_topk(x.data_ptr(), m, n, k, b, k_b, dt, v, i, s))
+    return _on_device(torch, x, k, out,
+                      lambda v, i, s: lib.approx_topk_assign(x.data_ptr(), m, n, k, b, k_b, dt, int(assignment), v, i, s))
 
 
 def exact_topk(x, k, out=None):
     """Exact top-k (largest first) of every row of a GPU tensor x (m, n)."""
     torch, m, n, dt = _tensor_args(x)
-    with torch.cuda.device(x.device):
-        if out is None:
-            vals = torch.empty((m, k), dtype=x.dtype, device=x.device)
-            idx = torch.empty((m, k), dtype=torch.int32, device=x.device)
-        else:
-            vals, idx = out
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-        _check(exact_topk_raw(x.data_ptr(), m, n, k, dt, vals.data_ptr(), idx.data_ptr(), stream))
-    return vals, idx
+    lib = _lib or load_library()
+    return _on_device(torch, x, k, out, lambda v, i, s: lib.exact_topk(x.data_ptr(), m, n, k, dt, v, i, s))
 
 
 def plan_describe(m, n, k, b, k_b, dtype=ATK_F32, assignment=ATK_INTERLEAVED) -> str:
