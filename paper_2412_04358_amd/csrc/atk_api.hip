@@ -647,7 +647,11 @@ int make_contig_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, in
     const int t_max = max_threads_for_kb(p.KB);
     const int64_t chunks = ceil_div(n, b) / p.V;  // of the longest bucket (V > 1: of every bucket)
     const int64_t want_lanes = 512 * (int64_t)kNumCU;
-    if (chunks <= kWave) {
+    // A lane group reads whole 128-byte lines where the buckets allow vector loads, and no more lanes than that share a
+    // bucket of a few lines: every lane more is a merge by shuffles more (128 x 65536 f32, 512 buckets of 32 vectors, k_b = 2:
+    // 17.3 us with 32 lanes a bucket, 9.5 with 8; 2^20, b = 8192: 215 -> 91; b = 256, k_b = 4, k = 256: 34.6 -> 16.4)
+    const int64_t g_line = p.V > 1 ? 128 / (p.V * es) : 1;
+    if (chunks <= (p.V > 1 ? g_line : (int64_t)kWave)) {
         // Short buckets: as many lanes per bucket as it has loads (rounded up to a power of two),
         // so that a wavefront reads one contiguous stretch, and NB buckets per lane group in turn.
         int64_t Gs = pow2_ceil(chunks);
@@ -681,7 +685,7 @@ int make_contig_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, in
         *pl = p;
         return ATK_OK;
     }
-    int64_t Gs = 1;
+    int64_t Gs = g_line < t_max ? g_line : t_max;
     while (Gs * 2 <= t_max && Gs * 16 <= chunks) Gs <<= 1;                          // about 8..16 loads per lane
     while (Gs * 2 <= t_max && Gs * 2 <= chunks && m * b * Gs < want_lanes) Gs <<= 1;  // more lanes, down to one load each
     if (T_forced && Gs > T_forced) Gs = T_forced;
@@ -690,7 +694,7 @@ int make_contig_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, in
     if (Gs > kWave) {
         T = (int)Gs;  // a whole workgroup per bucket
     } else {
-        T = T_forced ? T_forced : 256;
+        T = T_forced ? T_forced : (p.stage2 && p.V > 1 ? 512 : 256);
         if (T > t_max) T = t_max;
         const int64_t need = ceil_div(b * Gs, kWave) * kWave;  // lanes that cover one row's buckets
         if (need < T) T = (int)need;
@@ -966,6 +970,14 @@ static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
     const int es = (dtype == ATK_F32) ? 4 : 2;
     const int64_t nc = b * k_b;
     fp->two_step = nc > k && (nc > kStage2MaxCand || (allow_two && stage2_apart(m, n, k, b, k_b, dtype)));
+    if (!fp->two_step && nc > k && allow_two && !plan_override().ts && assignment == ATK_CONTIGUOUS) {
+        // contiguous buckets: several workgroups per row that meet through a ticket, on launches past two workgroups per CU (128 x
+        // 65536 f32, k = 256, b = 512, k_b = 2: 20.7 -> 15.3 us; 512 rows, k = 64, k_b = 1: 48 -> 29; 32 rows: 9.7, 10.5 apart)
+        Plan c;
+        if (make_contig_plan(m, n, k, b, k_b, dtype, ptr16, &c) == ATK_OK && c.NB == 0 && c.V > 1 && c.S == 1 && c.use_scratch &&
+            m * c.bblocks >= 2 * kNumCU)
+            fp->two_step = true;
+    }
     const int64_t k1 = fp->two_step ? nc : k;  // two steps: Stage 1 writes all its candidates, bucket by bucket
     int rc = (assignment == ATK_CONTIGUOUS) ? make_contig_plan(m, n, k1, b, k_b, dtype, ptr16, &fp->s1)
                                             : make_plan_aligned(m, n, k1, b, k_b, dtype, ptr16, &fp->s1, allow_pair);
