@@ -746,6 +746,7 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
     if (plan_override().ts) return plan_override().ts > 0;
     const int64_t nc = b * k_b, len = n / b;
     const int64_t es = (dtype == ATK_F32) ? 4 : 2;
+    if (m * nc * (es + 4) > (1ll << 30)) return false;  // the pairs of a call take no more than 1 GB of scratch
     // More candidates than 512 lanes hold in registers go digit by digit and through a bitonic sort: 128 x 65536 f32, k = 1024,
     // b = 512, k_b = 8: 98 -> 28; k = 64, b = 4096: 23 -> 15; k = 2000, b = 4000: 47 -> 17; 2048 x 65536, b = 1024, k_b = 4, k = 2048: 244 -> 138; one row of
     // 8192 bf16, k = 2000, b = 4000: 40 -> 17.
@@ -975,7 +976,7 @@ static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
         // 65536 f32, k = 256, b = 512, k_b = 2: 20.7 -> 15.3 us; 512 rows, k = 64, k_b = 1: 48 -> 29; 32 rows: 9.7, 10.5 apart)
         Plan c;
         if (make_contig_plan(m, n, k, b, k_b, dtype, ptr16, &c) == ATK_OK && c.NB == 0 && c.V > 1 && c.S == 1 && c.use_scratch &&
-            m * c.bblocks >= 2 * kNumCU)
+            m * c.bblocks >= 2 * kNumCU && m * nc * (es + 4) <= (1ll << 30))
             fp->two_step = true;
     }
     const int64_t k1 = fp->two_step ? nc : k;  // two steps: Stage 1 writes all its candidates, bucket by bucket

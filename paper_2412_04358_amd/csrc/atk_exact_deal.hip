@@ -468,7 +468,7 @@ bool plan_exact_deal(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Dea
     // six standard deviations of the sample's count above what k of n elements make of it; the pool takes as many again
     p.sample_rank = (int)std::ceil(expect + 6.0 * std::sqrt(expect * (1.0 - q)) + 6.0);
     const double most = ((double)p.sample_rank + 6.0 * std::sqrt((double)p.sample_rank) + 32.0) * (double)n / kDealSample;
-    p.pool_cap = std::min<int64_t>(n, (int64_t)most);
+    p.pool_cap = std::max<int64_t>(k, std::min<int64_t>(n, (int64_t)most));
     // the sample's lower bound: 8192 of its 32768 elements, 512 in each wavefront, five deviations below the threshold
     const double part = (double)p.sample_rank / 4.0 / (kDealT / kWave);
     p.rank = std::min(512, (int)std::ceil(part + 5.0 * std::sqrt(part) + 2.0));
@@ -483,7 +483,7 @@ bool plan_exact_deal(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Dea
     p.totals_off = take(m * bins * 4);
     p.segs_off = take(m * p.chunks * (bins + 1) * 4);
     p.pool_off = take(m * p.pool_cap * 8);
-    p.rest_off = take(m * k * 16);  // two buffers of k per row for the rows that go digit by digit
+    p.rest_off = take(m * k * 8);  // for the rows that go digit by digit: one buffer of k, the other is the pool, done with by then
     p.bytes = off;
     *out = p;
     return true;
@@ -524,8 +524,8 @@ hipError_t launch_exact_deal(const DealPlan &pl, int64_t m, int64_t n, int64_t k
     prm.sample_rank = pl.sample_rank;
     const hipError_t e = dtype == ATK_F32 ? launch_deal_t<ATK_F32>(pl, prm, m, stream) : launch_deal_t<ATK_BF16>(pl, prm, m, stream);
     if (e != hipSuccess) return e;
-    u64 *buf0 = (u64 *)(base + pl.rest_off);
-    return launch_exact_rest_rows(m, n, k, prm.idx_bits, dtype, x, xi, prm.rows, pl.pool_cap, buf0, buf0 + m * k, out_vals, out_idx, stream);
+    return launch_exact_rest_rows(m, n, k, prm.idx_bits, dtype, x, xi, prm.rows, pl.pool_cap, (u64 *)(base + pl.rest_off), prm.pool, out_vals,
+                                  out_idx, stream);
 }
 
 }  // namespace atk

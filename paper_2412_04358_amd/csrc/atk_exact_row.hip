@@ -602,7 +602,18 @@ hipError_t launch_exact_row(const RowPlan &pl, int64_t m, int64_t n, int64_t k, 
     prm.tickets = (uint32_t *)state;
     if (xi && (((uintptr_t)x | (uintptr_t)xi) & 15u)) return hipErrorInvalidValue;  // never: the pairs lie in the library's scratch
     if (pl.parts && (xi || !state || !data)) return hipErrorInvalidValue;
-    return dtype == ATK_F32 ? launch_row_t<ATK_F32>(pl, prm, m, stream) : launch_row_t<ATK_BF16>(pl, prm, m, stream);
+    // (a launch holds fewer than 2^32 lanes)
+    const int64_t es = dtype == ATK_F32 ? 4 : 2, rows = pl.parts ? m : ((int64_t)1 << 31) / pl.T;
+    for (int64_t r0 = 0; r0 < m; r0 += rows) {
+        prm.x = (const unsigned char *)x + r0 * n * es;
+        prm.xi = xi ? xi + r0 * n : nullptr;
+        prm.out_vals = (unsigned char *)out_vals + r0 * k * es;
+        prm.out_idx = out_idx + r0 * k;
+        const int64_t now = std::min(rows, m - r0);
+        const hipError_t e = dtype == ATK_F32 ? launch_row_t<ATK_F32>(pl, prm, now, stream) : launch_row_t<ATK_BF16>(pl, prm, now, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace atk

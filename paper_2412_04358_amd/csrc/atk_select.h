@@ -1,6 +1,6 @@
 // Workgroup-level exact selection in LDS: radix select on composite words, then an
 // ordered write-out.  This is Stage 2 of the method (Section 2: "if b*k_b > k, use an
-// exact top-k to select the k largest values") and the body of the small-row exact_topk.
+// exact top-k to select the k largest values") where it runs in the launch of Stage 1, and of exact_topk's copy-out path.
 // The radix descent follows the RadixSelect scheme of Appendix D.2 (most significant
 // digit first, keep the digit bucket that contains the k-th element), with 8-bit digits
 // and an LDS histogram.  Two departures: the descent starts at the highest bit in which
