@@ -66,12 +66,47 @@ def test_rows_unlike_their_samples(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [200000, 1 << 18, 1 << 20])
+def test_elements_above_the_sampled_ones(n, dtype):
+    """Winners above every sampled element: masked and rising rows, a few spikes over a long run of one value."""
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    base = workloads.normal_rows(2, n, seed=n % 1001)
+    rows = [base.sort(dim=1)[0]]
+    for part in (4, 2):
+        for fill in (float("-inf"), 0.0):
+            masked = base.clone()
+            masked[:, : n // part] = fill
+            rows.append(masked)
+    for at in ([5], [n - 7], [3, n // 3, (n * 6) // 7]):
+        for fill in (torch.zeros(2, n), torch.full((2, n), float("-inf")), base.clamp(max=1.0)):
+            spikes = fill.clone()
+            spikes[:, at] = torch.arange(len(at), 0, -1).float() + 7.0
+            rows.append(spikes)
+    for x in rows:
+        for k in (n // 8, n // 4):
+            _check(x.to(t), k)
+
+
+def test_many_long_bf16_rows():
+    _check(workloads.normal_rows(64, 1 << 21, seed=11, dtype="bf16"), 1 << 19)
+
+
+def _check_pairs(x, k, b, k_b, assignment=None):
+    vals, idx = atk.approx_topk(x.cuda(), k, b, k_b, assignment=assignment)
+    torch.cuda.synchronize()
+    ov, oi = oracle.approx_topk(workloads.as_numpy_bits(x), k, b, k_b, threads=8,
+                                assignment=oracle.CONTIGUOUS if assignment == atk.ATK_CONTIGUOUS else oracle.INTERLEAVED)
+    assert np.array_equal(idx.cpu().numpy(), oi)
+    assert np.array_equal(_bits(vals), ov.view(np.uint32) if ov.dtype == np.float32 else ov)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_pairs(dtype):
     """Stage 2 over long lists of (value, index) pairs."""
     for (m, n, k, b, k_b) in [(2, 600000, 20000, 70001, 1), (1, 1 << 20, 40000, 1 << 16, 2)]:
+        _check_pairs(workloads.normal_rows(m, n, seed=b, dtype=dtype), k, b, k_b)
         x = workloads.normal_rows(m, n, seed=b, dtype=dtype)
-        vals, idx = atk.approx_topk(x.cuda(), k, b, k_b)
-        torch.cuda.synchronize()
-        ov, oi = oracle.approx_topk(workloads.as_numpy_bits(x), k, b, k_b, threads=8)
-        assert np.array_equal(idx.cpu().numpy(), oi)
-        assert np.array_equal(_bits(vals), ov.view(np.uint32) if ov.dtype == np.float32 else ov)
+        x[:, : n // 4] = float("-inf")
+        _check_pairs(x, k, b, k_b, assignment=atk.ATK_CONTIGUOUS)
+        x[:, : n // 4] = 0.0
+        _check_pairs(x, k, b, k_b, assignment=atk.ATK_CONTIGUOUS)
