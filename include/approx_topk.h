@@ -24,10 +24,11 @@
  * the library; it grows on demand (growing allocates, which may synchronise the device)
  * and is shared by all calls on a device.  A call that needs the pool on another stream than
  * the call before it first waits, on the host, for that earlier stream to drain (calls
- * that stay on one stream never wait); calls from different host threads are serialised by
- * a lock around the pool, not around the launches, so threads that share a device should
- * share a stream or order their calls themselves.  Because of the allocation and the wait,
- * approx_topk and exact_topk are not for streams under graph capture: approx_topk_noalloc is.
+ * that stay on one stream never wait); calls from different host threads enqueue their kernels
+ * one call after the other.  approx_topk calls that take the pool only because Stage 2 in a launch
+ * of its own is faster (see there) never wait for another stream: they run fused then, as they
+ * do under graph capture and where the pool cannot grow.  Because of the allocation and the wait,
+ * approx_topk and exact_topk are not for streams under graph capture in general: approx_topk_noalloc is.
  *
  * Every function returns ATK_OK (0) or a negative error code.  Arguments are checked on
  * the host before any HIP call is made; nothing is launched when a check fails.
@@ -105,8 +106,9 @@ int approx_topk_assign(const void *x, int64_t m, int64_t n, int64_t k, int64_t b
  * scratch of plans whose workgroups hand partial lists over (few rows of long rows; Stage 2 over rows split
  * between workgroups) is a fixed array of ATK_NOALLOC_SCRATCH_BYTES inside the library's code object, one
  * per device, held until the process ends: the call allocates and frees nothing, and never synchronises.
- *   - ATK_ERR_WORKSPACE when the plan needs more than the array holds (atk_workspace_bytes() tells:
- *     at most ATK_NOALLOC_STATE_BYTES of tickets and the rest of the array in lists), ATK_ERR_UNSUPPORTED
+ *   - ATK_ERR_WORKSPACE when the plan needs more than the array holds (at most ATK_NOALLOC_STATE_BYTES of
+ *     tickets and the rest of the array in lists; atk_workspace_bytes() is an upper bound: it counts
+ *     the survivors that approx_topk passes to a Stage 2 in a launch of its own, which here runs fused), ATK_ERR_UNSUPPORTED
  *     when Stage 2 would run over more than atk_stage2_max_candidates() candidates.  Nothing is launched then.
  *   - The array keeps the last call's contents; the call clears the tickets it uses with a small fill
  *     kernel before its own launch (one more launch when the plan uses scratch, none otherwise).

@@ -773,57 +773,79 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
 // other buffers that carry nothing from call to call).  Both are zero-filled when
 // (re)allocated.  They are kept apart so that one call's data can never alias what a later
 // call, with other sizes, takes for zeroed state.
-static std::mutex g_pool_mu;
 enum { kPoolState = 0, kPoolData = 1 };
+static std::mutex g_pool_mu[64];
 static void *g_pool_ptr[64][2];
 static size_t g_pool_bytes[64][2];
 static hipStream_t g_pool_stream[64];  // the stream of the last call that took a pool on the device
 static bool g_pool_stream_set[64];
 
-// The pools are per device, not per stream: work queued on one stream may still be using them when a call arrives
-// on another.  Such a call first waits, on the host, for the stream of the call before it (calls that stay on one
-// stream never wait: their kernels are ordered by the stream).
-static hipError_t get_pool(int which, size_t bytes, void **out, hipStream_t stream) {
-    *out = nullptr;
-    if (bytes == 0) return hipSuccess;
+// The pools are per device, neither per stream nor per thread.  A call that takes one holds the device's lock until its last
+// kernel is enqueued, so that what another thread enqueues comes after all of it; and work queued on one stream may still
+// be using the pools when a call arrives on another: such a call first waits, on the host, for the stream of the call before it
+// (calls that stay on one stream never wait: their kernels are ordered by the stream).
+struct PoolUse {
+    std::unique_lock<std::mutex> lock;
     int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(g_pool_mu);
-    if (g_pool_stream_set[dev] && g_pool_stream[dev] != stream) {
-        if (hipStreamSynchronize(g_pool_stream[dev]) != hipSuccess) {  // (the stream may be gone by now)
-            (void)hipGetLastError();
-            e = hipDeviceSynchronize();
-            if (e != hipSuccess) return e;
-        }
-    }
-    g_pool_stream[dev] = stream;
-    g_pool_stream_set[dev] = true;
-    if (g_pool_bytes[dev][which] < bytes) {
-        if (g_pool_ptr[dev][which]) {
-            e = hipFree(g_pool_ptr[dev][which]);  // waits for work that may still use it
-            g_pool_ptr[dev][which] = nullptr;
-            g_pool_bytes[dev][which] = 0;
-            if (e != hipSuccess) return e;
-        }
-        size_t want = bytes + bytes / 4;
-        if (which == kPoolState && want < 64 * 1024) want = 64 * 1024;
-        void *p = nullptr;
-        e = hipMalloc(&p, want);
+    hipError_t begin() {
+        const hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
-        e = hipMemset(p, 0, want);
-        if (e == hipSuccess) e = hipDeviceSynchronize();
-        if (e != hipSuccess) {
-            (void)hipFree(p);
-            return e;
-        }
-        g_pool_ptr[dev][which] = p;
-        g_pool_bytes[dev][which] = want;
+        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+        lock = std::unique_lock<std::mutex>(g_pool_mu[dev]);
+        return hipSuccess;
     }
-    *out = g_pool_ptr[dev][which];
-    return hipSuccess;
-}
+    // Whether a call that can do without the pools had better: the stream is being captured (a graph would keep the address
+    // of a pool that a later call replaces, and neither allocation nor wait can be captured), it is each thread's own
+    // (one handle for many streams), or another stream's work with the pools is not over.
+    bool awkward(hipStream_t stream) const {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (stream == hipStreamPerThread || hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return true;
+        }
+        if (!g_pool_stream_set[dev] || g_pool_stream[dev] == stream) return false;
+        const bool busy = hipStreamQuery(g_pool_stream[dev]) == hipErrorNotReady;
+        (void)hipGetLastError();
+        return busy;
+    }
+    hipError_t get(int which, size_t bytes, void **out, hipStream_t stream) {
+        *out = nullptr;
+        if (bytes == 0) return hipSuccess;
+        hipError_t e;
+        if (g_pool_stream_set[dev] && g_pool_stream[dev] != stream) {
+            if (hipStreamSynchronize(g_pool_stream[dev]) != hipSuccess) {  // (the stream may be gone by now)
+                (void)hipGetLastError();
+                e = hipDeviceSynchronize();
+                if (e != hipSuccess) return e;
+            }
+        }
+        g_pool_stream[dev] = stream;
+        g_pool_stream_set[dev] = true;
+        if (g_pool_bytes[dev][which] < bytes) {
+            if (g_pool_ptr[dev][which]) {
+                e = hipFree(g_pool_ptr[dev][which]);  // waits for work that may still use it
+                g_pool_ptr[dev][which] = nullptr;
+                g_pool_bytes[dev][which] = 0;
+                if (e != hipSuccess) return e;
+            }
+            size_t want = bytes + bytes / 4;
+            if (which == kPoolState && want < 64 * 1024) want = 64 * 1024;
+            void *p = nullptr;
+            e = hipMalloc(&p, want);
+            if (e != hipSuccess) return e;
+            e = hipMemset(p, 0, want);
+            if (e == hipSuccess) e = hipDeviceSynchronize();
+            if (e != hipSuccess) {
+                (void)hipFree(p);
+                return e;
+            }
+            g_pool_ptr[dev][which] = p;
+            g_pool_bytes[dev][which] = want;
+        }
+        *out = g_pool_ptr[dev][which];
+        return hipSuccess;
+    }
+};
 
 // ------------------------------------------------------------------------------------ fixed scratch
 // Scratch of the allocation-free entry point: one array per device that the library runs on, part of the
@@ -832,6 +854,7 @@ static hipError_t get_pool(int which, size_t bytes, void **out, hipStream_t stre
 static __device__ __align__(256) unsigned char scratch[ATK_NOALLOC_SCRATCH_BYTES];
 // The array's name is a host-side stand-in, not a device address: the address on each device comes from
 // hipGetSymbolAddress, once per device, with that device current, and only that pointer is used afterwards.
+static std::mutex g_fixed_mu;
 static void *g_fixed_scratch[64];
 static hipError_t fixed_scratch(void **out) {
     *out = nullptr;
@@ -839,7 +862,7 @@ static hipError_t fixed_scratch(void **out) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(g_pool_mu);
+    std::lock_guard<std::mutex> lock(g_fixed_mu);
     if (!g_fixed_scratch[dev]) {
         void *p = nullptr;
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
@@ -1041,10 +1064,33 @@ static int run_approx(const void *x, int64_t m, int64_t n, int64_t k, int64_t b,
         if (trace_bytes < fp.s1.grid * kTraceWaves * kTracePhases * 8 || fp.s1.T > kTraceWaves * kWave) return ATK_ERR_BAD_SHAPE;
     }
     void *state = nullptr, *data = nullptr;
-    hipError_t e = get_pool(kPoolState, (size_t)fp.state_bytes, &state, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e);
-    e = get_pool(kPoolData, (size_t)fp.data_bytes, &data, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e);
+    PoolUse pool;
+    hipError_t e = hipSuccess;
+    if (fp.state_bytes || fp.data_bytes) {
+        e = pool.begin();
+        if (e != hipSuccess) return hip_fail(e);
+        // Stage 2 in a launch of its own takes the pools where the fused form of most such calls takes nothing: those run
+        // fused where the pools are not to be had at once (another stream's or thread's work, a capture, no memory left).
+        FullPlan fused;
+        const bool can_fuse = fp.two_step && b * k_b <= kStage2MaxCand;
+        auto fuse = [&]() {
+            if (make_full_plan(m, n, k, b, k_b, dtype, assignment, ((uintptr_t)x & 15u) == 0, &fused, true, false, false) != ATK_OK ||
+                fused.two_step || fused.state_bytes || fused.data_bytes)
+                return false;
+            fp = fused;
+            pool.lock.unlock();
+            return true;
+        };
+        if (!(can_fuse && pool.awkward((hipStream_t)stream) && fuse())) {
+            e = pool.get(kPoolState, (size_t)fp.state_bytes, &state, (hipStream_t)stream);
+            if (e == hipSuccess) e = pool.get(kPoolData, (size_t)fp.data_bytes, &data, (hipStream_t)stream);
+            if (e != hipSuccess && can_fuse && fuse()) {
+                (void)hipGetLastError();
+                e = hipSuccess;
+            }
+            if (e != hipSuccess) return hip_fail(e);
+        }
+    }
     void *s1_vals = out_vals;
     int32_t *s1_idx = out_idx;
     if (fp.two_step) {
@@ -1207,10 +1253,13 @@ int exact_topk(const void *x, int64_t m, int64_t n, int64_t k, int dtype, void *
     rc = make_exact_plans(m, n, k, dtype, false, ((uintptr_t)x & 15u) == 0, &pl, &state_bytes, &data_bytes);
     if (rc != ATK_OK) return rc;
     void *state = nullptr, *data = nullptr;
-    hipError_t e = get_pool(kPoolState, (size_t)state_bytes, &state, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e);
-    e = get_pool(kPoolData, (size_t)data_bytes, &data, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e);
+    PoolUse pool;
+    if (state_bytes || data_bytes) {
+        hipError_t e = pool.begin();
+        if (e == hipSuccess) e = pool.get(kPoolState, (size_t)state_bytes, &state, (hipStream_t)stream);
+        if (e == hipSuccess) e = pool.get(kPoolData, (size_t)data_bytes, &data, (hipStream_t)stream);
+        if (e != hipSuccess) return hip_fail(e);
+    }
     return run_exact(pl, x, nullptr, m, n, k, dtype, out_vals, out_idx, state, state_bytes, data, data_bytes,
                      (hipStream_t)stream);
 }
