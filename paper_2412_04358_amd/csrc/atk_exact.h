@@ -18,6 +18,7 @@ struct RowPlan {
     int ve;             // elements per vector
     int parts;          // > 0: workgroups to a row, each with part_vecs vectors of it, which pass on up to part_cap elements
     int part_vecs, part_cap;
+    int rank_up;        // the rank of an upper bound, where LDS does not hold what a row's parts pass on
 };
 // false: the row does not fit.  pairs: the rows are lists of (value, index) pairs.  ptr16: x lies on a 16-byte boundary.
 bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, RowPlan *out);

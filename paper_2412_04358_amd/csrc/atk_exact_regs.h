@@ -23,16 +23,18 @@ struct RowParams {
     // several workgroups to a row
     int parts, part_vecs;   // workgroups per row, 16-byte vectors of the row that each reads
     int part_cap;           // elements that each passes on
-    u64 *lists;             // [row][part][part_cap] composites
-    u64 *heads;             // [row][part][2]: (bound << 32 | elements passed on), the part's largest key
+    int rank_up;            // the upper bound (0: there is none)
+    u64 *lists;             // [row][part][part_cap] composites: those at or above the upper bound from the front, the rest from the back
+    u64 *heads;             // [row][part][4]: (a key that none of the list lies below << 32 | elements in front), (the part's largest
+                            // key << 32 | elements at the back), the upper bound, unused
     uint32_t *tickets;      // one per row, kTicketStride apart, zero between calls
 };
 
 typedef uint32_t row_v4u __attribute__((ext_vector_type(4)));
 
 // LDS words behind the bins: [0] bin of the need-th largest, [1] elements in higher bins, [2] its elements, [3] all counted,
-// [4] crowded, [5] cursor, [8..24) and [24..40) per-wavefront words
-constexpr int kRowMisc = 40;
+// [4] crowded, [5] and [7] cursors, [8..24), [24..40) and [40..56) per-wavefront words
+constexpr int kRowMisc = 56;
 
 // Counts cur[0 .. n_bins) -> elements in higher bins, in place; finds the bin of the need-th largest.  n_bins is a power
 // of two and at least the workgroup's size, which is one too; cur lies on a 16-byte boundary.  Called by the whole workgroup after a barrier; ends in one.
@@ -154,8 +156,11 @@ struct RowRegs {
     // reached by rank elements in each of them (and the largest element).  sub (1, 2, 4 or 8) groups per lane.  Where a wavefront has
     // fewer elements than that the bound is the lowest key there is.  rank 0: the smallest of the maxima.  Called by the whole workgroup; two barriers.
     // FIRST: the groups are the lane's first eight elements, one each (the largest element then is theirs, too).
-    template <bool FIRST = false>
-    __device__ __forceinline__ void bound(int sub, int rank, uint32_t *misc, uint32_t &k_min, uint32_t &k_max) {
+    // SUM: not the smallest of the wavefronts' candidates but the largest that, all wavefronts together, rank maxima per wavefront reach:
+    // wavefronts may be unlike each other then (masked in part, sorted).  words: 32 words of LDS.  k_up: the same with rank_up (0: none).
+    template <bool FIRST = false, bool SUM = false>
+    __device__ __forceinline__ void bound(int sub, int rank, uint32_t *misc, uint32_t &k_min, uint32_t &k_max, uint32_t *words = nullptr,
+                                          int rank_up = 0, uint32_t *k_up = nullptr) {
         const int tid = threadIdx.x, lane = tid & (kWave - 1), n_waves = blockDim.x >> 6;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         constexpr int SM = NV * 4 < 8 ? 4 : 8;
@@ -178,6 +183,7 @@ struct RowRegs {
             }
         }
         auto key_of = [](float f) { return f == f ? ukey_of_bits(__float_as_uint(f)) : 0u; };
+        if (SUM && tid < 32) words[tid] = 0u;
         // The rank-th largest of the S * 64 keys of a wavefront, to its highest 16 bits (the bits below stay zero, which
         // can only lower the bound, by under one part in 128): bit by bit from the top, counting the keys that agree so far.
         auto nth = [&](auto s_tag) {
@@ -193,23 +199,53 @@ struct RowRegs {
                 top = max(top, key[i]);
             }
             k_max = top;
+            auto count = [&](uint32_t from) {
+                int cnt = 0;
+#pragma unroll
+                for (int i = 0; i < S; ++i) cnt += __popcll(__ballot(key[i] >= from));
+                return cnt;
+            };
+            auto nth_key = [&](int of) {
+                uint32_t have = 0u;
+#pragma unroll
+                for (int bit = 31; bit >= 16; --bit) {
+                    const uint32_t want = have | (1u << bit);
+                    if (count(want) >= of) have = want;
+                }
+                return have;
+            };
             if (rank == 0) {
                 k_min = 0xffffffffu;
 #pragma unroll
                 for (int i = 0; i < S; ++i) k_min = key[i] && key[i] < k_min ? key[i] : k_min;
                 k_min = wave_min_u32(k_min);
-                return;
+            } else {
+                k_min = nth_key(rank);
             }
-            uint32_t have = 0u;
-#pragma unroll
-            for (int bit = 31; bit >= 16; --bit) {
-                const uint32_t want = have | (1u << bit);
-                int cnt = 0;
-#pragma unroll
-                for (int i = 0; i < S; ++i) cnt += __popcll(__ballot(key[i] >= want));
-                if (cnt >= rank) have = want;
+            if constexpr (SUM) {
+                const uint32_t top_of_wave = wave_max_u32(k_max), up = rank_up ? nth_key(rank_up) : 0u;
+                if (lane == 0) {
+                    misc[8 + wave] = k_min;
+                    misc[24 + wave] = top_of_wave;
+                    misc[40 + wave] = up;
+                }
+                __syncthreads();
+                const bool is = lane < n_waves;
+                auto reached = [&](uint32_t theirs, uint32_t *sums) {  // lane j: the j-th wavefront's candidate
+                    int mine = 0;  // maxima of this wavefront that reach it
+                    for (int j = 0; j < n_waves; ++j) {
+                        const int cnt = count((uint32_t)__builtin_amdgcn_readlane((int)theirs, j));
+                        if (lane == j) mine = cnt;
+                    }
+                    if (is && mine) atomicAdd(&sums[lane], (uint32_t)mine);
+                };
+                const uint32_t theirs = is ? misc[8 + lane] : 0u, theirs_up = is ? misc[40 + lane] : 0u;
+                reached(theirs, words);
+                if (rank_up) reached(theirs_up, words + 16);
+                __syncthreads();
+                k_min = wave_max_u32(is && words[lane] >= (uint32_t)(rank * n_waves) ? theirs : 0u);
+                if (rank_up) *k_up = wave_max_u32(is && words[16 + lane] >= (uint32_t)(rank_up * n_waves) ? theirs_up : 0u);
             }
-            k_min = have;
         };
         if (sub == 1)
             nth(std::integral_constant<int, 1>());
@@ -219,33 +255,41 @@ struct RowRegs {
             nth(std::integral_constant<int, 4>());
         else
             nth(std::integral_constant<int, SM>());
-        k_max = wave_max_u32(k_max);
-        if (lane == 0) {
-            misc[8 + wave] = k_min;
-            misc[24 + wave] = k_max;
+        if constexpr (!SUM) {
+            k_max = wave_max_u32(k_max);
+            if (lane == 0) {
+                misc[8 + wave] = k_min;
+                misc[24 + wave] = k_max;
+            }
+            __syncthreads();
+            k_min = wave_min_u32(lane < n_waves ? misc[8 + lane] : 0xffffffffu);
         }
-        __syncthreads();
-        k_min = wave_min_u32(lane < n_waves ? misc[8 + lane] : 0xffffffffu);
         k_max = wave_max_u32(lane < n_waves ? misc[24 + lane] : 0u);
         if (k_min < 0x007fffffu) k_min = 0x007fffffu;  // (-inf's)
         if (k_min > k_max) k_min = k_max;
+        if constexpr (SUM) *k_up = rank_up ? min(*k_up, k_max) : 0u;
         __syncthreads();  // (the words are used again)
     }
 
-    // Positions of the elements at or above v_lo to list[0 .. ] (at most cap of them); the cursor *count starts from zero and
-    // ends as their number.  Two operations per element set a bit each - a comparison and an addition of the mask
-    // to itself with the comparison as carry -, the few that are set are then taken one by one: storing an element under
-    // its own condition costs every element the six or so operations of a branch that few of the lanes take
-    // (64 x 128256 bf16, k = 256: 8.2 us of the kernel's 18).  Called by the whole workgroup; ends in a barrier.
-    __device__ __forceinline__ void list_from(float v_lo, int2 *list, uint32_t cap, uint32_t *count) {
-        const int lane = threadIdx.x & (kWave - 1), T = blockDim.x;
-        constexpr int M = (E + 31) / 32;  // masks of 32 elements, the last perhaps of fewer
-        uint32_t mk[M];
+    static constexpr int M = (E + 31) / 32;  // masks of 32 elements, the last perhaps of fewer: element en has bit 31 - en % 32 of word en / 32
+
+    // Which elements reach v_lo.  Two operations per element: a comparison, and an addition of the mask to itself with the
+    // comparison as carry.
+    __device__ __forceinline__ void masks_from(float v_lo, uint32_t (&mk)[M]) {
 #pragma unroll
         for (int w = 0; w < M; ++w) mk[w] = 0u;
         each([&](uint32_t bits, int, int en) {
             asm volatile("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mk[en / 32]) : "v"(v_lo), "v"(bits) : "vcc");
         });
+#pragma unroll
+        for (int w = 0; w < M; ++w) mk[w] <<= 32 - (E - 32 * w < 32 ? E - 32 * w : 32);
+    }
+    // Positions of the elements whose bits are set to list[0 .. ] (at most cap of them); the cursor *count starts from zero and
+    // ends as their number.  The few that are set are taken one by one: storing an element under its own condition costs every
+    // element the six or so operations of a branch that few of the lanes take (64 x 128256 bf16, k = 256: 8.2 us of the
+    // kernel's 18).  Called by the whole workgroup; ends in a barrier.
+    __device__ __forceinline__ void list_masks(const uint32_t (&mk)[M], int2 *list, uint32_t cap, uint32_t *count) {
+        const int lane = threadIdx.x & (kWave - 1), T = blockDim.x;
         uint32_t cnt = 0;
 #pragma unroll
         for (int w = 0; w < M; ++w) cnt += (uint32_t)__popc(mk[w]);
@@ -255,17 +299,211 @@ struct RowRegs {
         at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + incl - cnt;
 #pragma unroll
         for (int w = 0; w < M; ++w) {
-            uint32_t b = mk[w] << (32 - (E - 32 * w < 32 ? E - 32 * w : 32));  // the first element's bit is bit 31
-            while (b) {
+            uint32_t b = mk[w];
+            while (b && at < cap) {  // (once the list is full, the number alone matters)
                 const int t = __clz((int)b), en = w * 32 + t;
                 b &= ~(0x80000000u >> t);
-                if (at < cap) list[at].y = i0 + (en / VE) * T * VE + en % VE;
-                ++at;
+                list[at++].y = i0 + (en / VE) * T * VE + en % VE;
             }
         }
         __syncthreads();
     }
+    __device__ __forceinline__ void list_from(float v_lo, int2 *list, uint32_t cap, uint32_t *count) {
+        uint32_t mk[M];
+        masks_from(v_lo, mk);
+        list_masks(mk, list, cap, count);
+    }
+
+    // Positions of the k largest elements (ties: the first ones) to list[], or of some more if that is the quicker way: of those above a
+    // run of ties at the lower end, if there are k and no more than cap of them.  n: how many.  Returns a key that none of them
+    // lies below (bf16: without the low bits).  More than k elements reach lo, none is above hi.  Where ties at the lower
+    // end do not decide it, the key is searched by halving, a comparison and two scalar operations per element and step; then the
+    // ties are counted by rows of vectors (lanes side by side hold vectors side by side).  words: NV words of LDS.  Called by
+    // the whole workgroup; ends in a barrier.
+    __device__ __forceinline__ uint32_t list_largest(uint32_t k, uint32_t lo, uint32_t hi, int2 *list, uint32_t cap, uint32_t &n, uint32_t *count,
+                                                     uint32_t *words, uint32_t *misc) {
+        constexpr int drop = (ELT == ATK_BF16) ? 16 : 0;
+        const int tid = threadIdx.x, lane = tid & (kWave - 1), n_waves = blockDim.x >> 6;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        auto value = [](uint32_t t) { return __uint_as_float(bits_of_ukey(max(t << drop, 0x007fffffu))); };  // (no lower than -inf: NaNs lie there)
+        int step = 0;
+        auto reach = [&](uint32_t t) {  // how many elements do; one barrier
+            const float v = value(t);
+            int cnt = 0;
+            each([&](uint32_t bits, int, int) { cnt += __popcll(__ballot(__uint_as_float(bits) >= v)); });
+            uint32_t *sums = misc + 8 + 16 * (step++ & 1);
+            if (lane == 0) sums[wave] = (uint32_t)cnt;
+            __syncthreads();
+            return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u32(lane < n_waves ? sums[lane] : 0u), kWave - 1);
+        };
+        // the least of those that reach lo
+        {
+            const float v = value(lo >> drop);
+            float least = __uint_as_float(0x7f800000u);
+            each([&](uint32_t bits, int, int) {
+                const float f = __uint_as_float(bits);
+                least = f >= v && f < least ? f : least;
+            });
+            uint32_t key = wave_min_u32(ukey_of_bits(__float_as_uint(least)));
+            if (lane == 0) misc[24 + wave] = key;
+            __syncthreads();
+            lo = wave_min_u32(lane < n_waves ? misc[24 + lane] : 0xffffffffu);
+        }
+        uint32_t l = lo >> drop, h = (hi >> drop) + 1u;  // k and more reach l, fewer than k reach h
+        const uint32_t higher = reach(l + 1u);
+        if (higher < k) {
+            h = l + 1u;
+        } else if (higher <= cap) {
+            n = higher;
+            list_from(value(l + 1u), list, cap, count);
+            return l << drop;
+        } else {
+            ++l;
+        }
+        while (h - l > 1u) {
+            const uint32_t mid = l + (h - l) / 2u;
+            if (reach(mid) >= k)
+                l = mid;
+            else
+                h = mid;
+        }
+        n = k;
+        uint32_t above[M], ties[M], mine = 0;
+        masks_from(value(l), ties);
+        masks_from(value(l + 1u), above);
+#pragma unroll
+        for (int w = 0; w < M; ++w) {
+            ties[w] &= ~above[w];
+            mine += (uint32_t)__popc(above[w]);
+        }
+        __syncthreads();  // (the sums have been read)
+        if (tid < NV) words[tid] = 0u;
+        if (tid == 0) misc[8] = 0u;
+        __syncthreads();
+        auto field = [&](int j) { return (ties[j * VE / 32] >> (32 - VE - j * VE % 32)) & ((1u << VE) - 1u); };
+        mine = wave_incl_scan_u32(mine);
+        if (lane == kWave - 1) atomicAdd(&misc[8], mine);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const uint32_t sum = wave_incl_scan_u32((uint32_t)__popc(field(j)));
+            if (lane == kWave - 1 && sum) atomicAdd(&words[j], sum);
+        }
+        __syncthreads();
+        uint32_t left = k - misc[8];  // ties to take
+        int row = 0;                  // all of the vectors' rows before this one, and the first of this one
+        while (row < NV - 1 && words[row] <= left) left -= words[row++];
+        uint32_t here = 0;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (j == row) here = field(j);
+        const uint32_t n_here = (uint32_t)__popc(here), incl = wave_incl_scan_u32(n_here);
+        if (lane == kWave - 1) misc[24 + wave] = incl;
+        __syncthreads();
+        const uint32_t waves = wave_incl_scan_u32(lane < n_waves ? misc[24 + lane] : 0u);
+        uint32_t before = incl - n_here;
+        if (wave > 0) before += (uint32_t)__builtin_amdgcn_readlane((int)waves, wave - 1);
+        uint32_t drop_n = before + n_here > left ? (before >= left ? n_here : before + n_here - left) : 0u;
+        for (; drop_n; --drop_n) here &= here - 1u;  // (the last ones)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const uint32_t f = j < row ? field(j) : (j == row ? here : 0u);
+            above[j * VE / 32] |= f << (32 - VE - j * VE % 32);
+        }
+        list_masks(above, list, k, count);
+        return l << drop;
+    }
 };
+
+// ---- the digit descent in a workgroup (RadixSelect, Appendix D.2), most significant digit first, on the composite without the bits
+// that carry nothing (the low 16 of a bf16 key, the index bits above idx_bits)
+template <int ELT>
+struct RowSqueeze {
+    static constexpr int drop = ELT == ATK_BF16 ? 16 : 0;
+    int keep;
+    __device__ __forceinline__ u64 operator()(u64 c) const { return ((c >> (32 + drop)) << keep) | (c & ((1ull << keep) - 1ull)); }
+    // the key that t's key bits stand for, without the bits that were dropped
+    __device__ __forceinline__ uint32_t key(u64 t) const { return (uint32_t)(t >> keep) << drop; }
+};
+
+// cur[bin] += 1 for every lane with `on`.  Many lanes with one bin (ties) would queue up on one word of LDS: the first bin that
+// comes up in the wavefront is counted by ballot.
+__device__ __forceinline__ void row_count(uint32_t *cur, uint32_t bin, bool on) {
+    const int lane = threadIdx.x & (kWave - 1);
+    u64 todo = __ballot(on);
+#pragma unroll
+    for (int t = 0; t < 1; ++t) {
+        if (!todo) return;  // uniform over the wavefront
+        const int first = __builtin_ctzll(todo);
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
+        const u64 same = __ballot(on && bin == b);
+        if (lane == first) atomicAdd(&cur[b], (uint32_t)__popcll(same));
+        on = on && bin != b;
+        todo &= ~same;
+    }
+    if (on) atomicAdd(&cur[bin], 1u);
+}
+
+// The threshold (squeezed) that exactly `need` of the elements reach: sweep(f) calls f(composite, whether it counts) for every element,
+// the same ones each time, with whole wavefronts together.  k_lo, k_hi: keys between which the need-th largest lies, none above
+// k_hi.  cur: room for 2^lg_bins words, no fewer than the workgroup's lanes.  Called by the whole workgroup; ends in a barrier.
+template <int ELT, typename SWEEP>
+__device__ __forceinline__ u64 row_threshold_by_digits(SWEEP sweep, uint32_t need, uint32_t k_lo, uint32_t k_hi, int idx_bits, int lg_bins,
+                                                       uint32_t *cur, uint32_t *misc) {
+    const int tid = threadIdx.x, T = blockDim.x, n_bins = 1 << lg_bins;
+    const RowSqueeze<ELT> sq{idx_bits + 1};
+    const uint32_t differ = (k_lo ^ k_hi) >> sq.drop;
+    int top = sq.keep + (differ ? 32 - __builtin_clz(differ) : 0);  // bits still open
+    u64 prefix = (((u64)(k_lo >> sq.drop)) << sq.keep) & (top >= 64 ? 0ull : (~0ull << top));
+    for (;;) {
+        const int w = top < lg_bins ? top : lg_bins;
+        const int shift = top - w;
+        const u64 hi_mask = top >= 64 ? 0ull : (~0ull << top);
+        for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
+        __syncthreads();
+        sweep([&](u64 c, bool on) {
+            const u64 q = sq(c);
+            row_count(cur, (uint32_t)(q >> shift) & ((1u << w) - 1u), on && (q & hi_mask) == prefix);
+        });
+        __syncthreads();
+        row_scan(cur, misc, n_bins, need);
+        prefix |= (u64)misc[0] << shift;
+        need -= misc[1];
+        const bool done = misc[2] == need || shift == 0;
+        __syncthreads();  // misc and cur are written again
+        if (done) break;
+        top = shift;
+    }
+    return prefix;
+}
+
+// f(composite, whether it is one) for every element of the vectors v0 .. v1 of row r, read from memory, whole wavefronts
+// together: the ways that few rows take go through the elements like this and not through the registers that hold them, because a
+// loop is small and what RowRegs::each() unrolls is not.
+template <int ELT, typename F>
+__device__ __forceinline__ void row_vec_sweep(const RowParams &p, int64_t r, int v0, int v1, int rot, F f) {
+    constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES, U = 32 / VE;
+    const int T = blockDim.x, lane = threadIdx.x & (kWave - 1), end = rot + p.n;
+    const row_v4u *row = (const row_v4u *)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & ~(uintptr_t)15);
+    for (int w0 = v0 + (int)threadIdx.x - lane; w0 < v1; w0 += U * T) {  // uniform over the wavefront
+        row_v4u q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = w0 + lane + u * T;
+            q[u] = row[v < v1 ? v : v1 - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = w0 + lane + u * T;
+#pragma unroll
+            for (int e = 0; e < VE; ++e) {
+                const int at = v * VE + e;
+                const uint32_t a = q[u][ELT == ATK_F32 ? e : (e >> 1)];
+                const bool ok = v < v1 && at >= rot && at < end;
+                f(make_composite(ELT == ATK_F32 ? a : ((e & 1) ? (a & 0xffff0000u) : (a << 16)), at - rot), ok);
+            }
+        }
+    }
+}
 
 // value bits of element `at` of row r
 template <int ELT>

@@ -39,62 +39,48 @@ __device__ __forceinline__ u64 row_composite(const RowParams &p, int64_t r, int 
     return make_composite(bits, p.xi ? p.xi[r * p.n + i] : i);
 }
 
-// f(composite) for every element of row r that this lane takes, eight loads in flight
+// f(composite, whether it is one) for every element of row r, whole wavefronts together
 template <int ELT, typename F>
 __device__ __forceinline__ void row_sweep(const RowParams &p, int64_t r, F f) {
-    const int T = blockDim.x;
-    int i = threadIdx.x;
-    for (; i + 7 * T < p.n; i += 8 * T) {
-        u64 c[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) c[u] = row_composite<ELT>(p, r, i + u * T);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) f(c[u]);
+    constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES;
+    if (!p.xi) {
+        const int rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & 15) / ES;
+        row_vec_sweep<ELT>(p, r, 0, (rot + p.n + VE - 1) / VE, rot, f);
+        return;
     }
-    for (; i < p.n; i += T) f(row_composite<ELT>(p, r, i));
+    const int T = blockDim.x, lane = threadIdx.x & (kWave - 1);
+    for (int i0 = (int)threadIdx.x - lane; i0 < p.n; i0 += 4 * T) {
+        u64 c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = row_composite<ELT>(p, r, min(i0 + lane + u * T, p.n - 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) f(c[u], i0 + lane + u * T < p.n);
+    }
 }
 
-// Digit by digit over the row, most significant first, on the composite without the bits that carry nothing (the low 16
-// of a bf16 key, the index bits above idx_bits); the k survivors are then put in order.
-template <int ELT>
-__device__ __forceinline__ void row_by_digits(const RowParams &p, int64_t r, u64 *filed, uint32_t *cur, uint32_t *misc) {
+// The elements at or above thr (squeezed), of which there are k, are put in order and written.
+template <int ELT, typename SWEEP>
+__device__ __forceinline__ void row_order_from(const RowParams &p, int64_t r, SWEEP sweep, u64 thr, u64 *filed, uint32_t *cur, uint32_t *misc) {
     const int tid = threadIdx.x, T = blockDim.x;
-    const int drop = ELT == ATK_BF16 ? 16 : 0, keep = p.idx_bits + 1;
-    auto squeeze = [&](u64 c) { return ((c >> (32 + drop)) << keep) | (c & ((1ull << keep) - 1ull)); };
-    const int n_bins = 1 << p.lg_bins;
-    int top = 32 - drop + keep;  // bits still open
-    u64 prefix = 0ull;
-    uint32_t need = (uint32_t)p.k;
-    for (;;) {
-        const int w = top < p.lg_bins ? top : p.lg_bins;
-        const int shift = top - w;
-        const u64 hi_mask = top >= 64 ? 0ull : (~0ull << top);
-        for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
-        __syncthreads();
-        row_sweep<ELT>(p, r, [&](u64 c) {
-            const u64 q = squeeze(c);
-            if ((q & hi_mask) == prefix) atomicAdd(&cur[(uint32_t)(q >> shift) & ((1u << w) - 1u)], 1u);
-        });
-        __syncthreads();
-        row_scan(cur, misc, n_bins, need);
-        prefix |= (u64)misc[0] << shift;
-        need -= misc[1];
-        const bool done = misc[2] == need || shift == 0;
-        __syncthreads();  // misc and cur are written again
-        if (done) break;
-        top = shift;
-    }
+    const RowSqueeze<ELT> sq{p.idx_bits + 1};
     if (tid == 0) misc[5] = 0u;
     for (int i = tid; i < kRankMax; i += T) cur[i] = 0u;
     __syncthreads();
-    row_sweep<ELT>(p, r, [&](u64 c) {
-        if (squeeze(c) >= prefix) {  // k of them
+    sweep([&](u64 c, bool on) {
+        if (on && sq(c) >= thr) {
             const uint32_t at = atomicAdd(&misc[5], 1u);
             if (at < (uint32_t)p.k) filed[at] = c;
         }
     });
     __syncthreads();
     order_write<ELT>(filed, p.k, cur, p.out_vals, p.out_idx, r);
+}
+// Digit by digit over what sweep() goes through, as in row_threshold_by_digits().
+template <int ELT, typename SWEEP>
+__device__ __forceinline__ void row_by_digits(const RowParams &p, int64_t r, SWEEP sweep, uint32_t k_lo, uint32_t k_hi, u64 *filed,
+                                              uint32_t *cur, uint32_t *misc) {
+    const u64 thr = row_threshold_by_digits<ELT>(sweep, (uint32_t)p.k, k_lo, k_hi, p.idx_bits, p.lg_bins, cur, misc);
+    row_order_from<ELT>(p, r, sweep, thr, filed, cur, misc);
 }
 
 // The filed elements (bin by bin, cur[b] the place behind bin b) find their ranks and are written.
@@ -116,7 +102,7 @@ __device__ __forceinline__ void row_rank_write(const RowParams &p, int64_t r, co
     }
 }
 
-// Selects and writes the row's k largest from passed[0 .. n_passed) (value bits, column index), all at or above k_min, k or
+// Selects and writes the row's k largest from those of passed[0 .. n_passed) (value bits, column index) at or above k_min, k or
 // more of them.  cur: zeroed bins.  False where a bin is too full to be ranked: nothing is written then, and k_min is raised to
 // the lower edge of the k-th largest's bin.  Called by the whole workgroup after a barrier.
 template <int ELT>
@@ -127,7 +113,8 @@ __device__ __forceinline__ bool row_select_passed(const RowParams &p, int64_t r,
     bins.template set<ELT>(k_min, k_max, p.idx_bits, n_bins);
     for (uint32_t i = tid; i < n_passed; i += T) {
         const int2 w = passed[i];
-        atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits((uint32_t)w.x), 0x7fffffffu - (uint32_t)w.y)], 1u);
+        const uint32_t key = ukey_of_bits((uint32_t)w.x);
+        if (key >= bins.k_min) atomicAdd(&cur[bins.template bin<ELT>(key, 0x7fffffffu - (uint32_t)w.y)], 1u);
     }
     __syncthreads();
     row_scan(cur, misc, n_bins, (uint32_t)p.k);
@@ -140,8 +127,8 @@ __device__ __forceinline__ bool row_select_passed(const RowParams &p, int64_t r,
     }
     for (uint32_t i = tid; i < n_passed; i += T) {
         const int2 w = passed[i];
-        const uint32_t b = bins.template bin<ELT>(ukey_of_bits((uint32_t)w.x), 0x7fffffffu - (uint32_t)w.y);
-        if (b >= tb) filed[atomicAdd(&cur[b], 1u)] = make_composite((uint32_t)w.x, w.y);
+        const uint32_t key = ukey_of_bits((uint32_t)w.x), b = bins.template bin<ELT>(key, 0x7fffffffu - (uint32_t)w.y);
+        if (key >= bins.k_min && b >= tb) filed[atomicAdd(&cur[b], 1u)] = make_composite((uint32_t)w.x, w.y);
     }
     __syncthreads();
     row_rank_write<ELT>(p, r, bins, filed, (int)cur[tb], cur, n_bins);
@@ -223,7 +210,8 @@ __global__ void __launch_bounds__(1024) ex_row_kernel(RowParams p) {
         // (twice from a raised lower end at most, and once from -inf)
         if (attempt == 3 || (few ? k_min <= lo : lo <= k_min)) {
             __syncthreads();
-            row_by_digits<ELT>(p, r, filed, cur, misc);
+            // (few: NaNs)
+            row_by_digits<ELT>(p, r, [&](auto f) { row_sweep<ELT>(p, r, f); }, few ? 0u : k_min, few ? 0xffffffffu : k_max, filed, cur, misc);
             return;
         }
         k_min = lo;
@@ -247,91 +235,162 @@ __global__ void __launch_bounds__(1024) ex_row_kernel(RowParams p) {
     row_rank_write<ELT>(p, r, bins, filed, (int)cur[tb], cur, n_bins);
 }
 
-// Several workgroups to a row: each holds a part of it in registers, finds a lower bound of its own (fewer of its elements
-// have to reach it: k shared out over the parts, and a margin), and passes on what lies at or above it.  The workgroup
-// that draws the row's last ticket takes the largest of the bounds: every element of the row at or above that was passed on,
-// so if there are k of them they hold the k largest.  Else - parts unlike each other, long runs of ties - it goes through the
-// row digit by digit, alone.  One sweep over memory, one launch: 128 x 2^20 f32, k = 64: 135 us by sampling, copying out and
-// selecting, 103 here; k = 1024: 225 -> 127; one row of 2^20, k = 1000: 52 -> 13.4; 64 x 128256 bf16, k = 256: 13.8 us with a
-// workgroup per row, 11.6 with four (3.7 us to read and bound a part, 1.3 to list, 1.1 to hand over, 4 to select).  The lists go through memory as in the fused kernels' hand-over: agent-scope stores, a wait for
-// their acknowledgement, a ticket.
-template <int ELT, int NV>
-__global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES;
-    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1);
-    const int64_t r = blockIdx.x / (unsigned)p.parts;
-    const int part = (int)(blockIdx.x - (unsigned)r * (unsigned)p.parts);
-    const int n_bins = 1 << p.lg_bins;
-    u64 *filed = (u64 *)smem;
-    uint32_t *cur = (uint32_t *)(filed + p.filed_words);
-    uint32_t *misc = cur + n_bins + 4;
-    int2 *passed = (int2 *)(misc + kRowMisc);
-
-    const int rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & 15) / ES;
-    const int n_vec = (rot + p.n + VE - 1) / VE;
+// A row shared out between workgroups (ex_parts_kernel).
+template <int ELT>
+struct PartsRow {
+    static constexpr int VE = (ELT == ATK_F32) ? 4 : 8;
+    int64_t r;
+    int rot, n_vec, n_bins;
+    u64 *filed;
+    uint32_t *cur, *misc;
+    int2 *passed;
+    __device__ __forceinline__ PartsRow(const RowParams &p, int64_t row, unsigned char *smem) : r(row) {
+        rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * (16 / VE)) & 15) / (16 / VE);
+        n_vec = (rot + p.n + VE - 1) / VE;
+        n_bins = 1 << p.lg_bins;
+        filed = (u64 *)smem;
+        cur = (uint32_t *)(filed + p.filed_words);
+        misc = cur + n_bins + 4;
+        passed = (int2 *)(misc + kRowMisc);
+    }
     // (a part may be empty: the plan counts a vector more for rows off the 16-byte boundaries)
-    const int v0 = min(part * p.part_vecs, n_vec - 1), v1 = part * p.part_vecs < n_vec ? min(v0 + p.part_vecs, n_vec) : v0;
-    {
-        RowRegs<ELT, NV> regs;
-        regs.load(p, r, v0, v1, rot);
-        if (tid == 0) misc[5] = 0u;
-        regs.mask_ends(p, v0, v1, rot);
-        uint32_t k_min, k_max;
-        regs.bound(p.sub, p.rank, misc, k_min, k_max);
-        regs.list_from(__uint_as_float(bits_of_ukey(k_min)), passed, (uint32_t)p.part_cap, &misc[5]);
-        const uint32_t n_passed = misc[5];
-        u64 *list = p.lists + (r * p.parts + part) * p.part_cap;
-        if (n_passed <= (uint32_t)p.part_cap)
-            for (uint32_t i = tid; i < n_passed; i += T) {
-                const int at = passed[i].y;
-                __hip_atomic_store(&list[i], make_composite(row_bits<ELT>(p, r, at), at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        if (tid == 0) {
-            u64 *head = p.heads + (r * p.parts + part) * 2;
-            __hip_atomic_store(&head[0], ((u64)k_min << 32) | n_passed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&head[1], (u64)k_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    __device__ __forceinline__ int first_vec(const RowParams &p, int part) const { return min(part * p.part_vecs, n_vec - 1); }
+    __device__ __forceinline__ int end_vec(const RowParams &p, int part) const {
+        return part * p.part_vecs < n_vec ? min(part * p.part_vecs + p.part_vecs, n_vec) : first_vec(p, part);
     }
-    // (a barrier alone does not wait for stores; the memory clobber keeps the compiler from moving the ticket above this)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t *ticket = p.tickets + r * kTicketStride;
-        const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.parts - 1u;
-        misc[6] = last ? 1u : 0u;
-        misc[5] = 0u;
-        misc[7] = 0u;
-        if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next call
+    __device__ __forceinline__ uint32_t elements(const RowParams &p, int part) const {
+        return (uint32_t)(min(end_vec(p, part) * VE, rot + p.n) - max(first_vec(p, part) * VE, rot));
     }
-    __syncthreads();
-    if (!misc[6]) return;
+    __device__ __forceinline__ void clear() const {  // the bins and the cursors; ends in a barrier
+        for (int i = threadIdx.x; i < n_bins + 4; i += blockDim.x) cur[i] = 0u;
+        if (threadIdx.x == 0) misc[5] = misc[7] = 0u;
+        __syncthreads();
+    }
+    __device__ __forceinline__ void put_head(const RowParams &p, int part, uint32_t low, uint32_t front, uint32_t back, uint32_t k_up, uint32_t k_max) const {
+        if (threadIdx.x != 0) return;
+        u64 *head = p.heads + (r * p.parts + part) * 4;
+        __hip_atomic_store(&head[0], ((u64)low << 32) | front, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&head[1], ((u64)k_max << 32) | back, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&head[2], (u64)k_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ u64 element(const RowParams &p, uint32_t i) const {  // of passed[], where it has a position only
+        const int at = passed[i].y;
+        return make_composite(row_bits<ELT>(p, r, at), at);
+    }
+};
+__device__ __forceinline__ uint32_t key_of(u64 c) { return (uint32_t)(c >> 32); }
 
-    // ---- the row's last workgroup
-    for (int i = tid; i < n_bins + 4; i += T) cur[i] = 0u;
-    // every wavefront reads all the heads: the largest bound, the largest key, whether a part had more than it could pass on,
-    // and how many pieces of 64 elements the lists make (lane i has part i)
-    uint32_t k_min = 0u, k_max = 0u, len = 0u;
-    if (lane < p.parts) {
-        const u64 *head = p.heads + (r * p.parts + lane) * 2;
-        const u64 h0 = __hip_atomic_load(&head[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const u64 h1 = __hip_atomic_load(&head[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        k_min = (uint32_t)(h0 >> 32);
-        k_max = (uint32_t)h1;
-        len = (uint32_t)h0;
-    }
-    k_min = wave_max_u32(k_min);
-    k_max = wave_max_u32(k_max);
-    const bool over = __ballot(len > (uint32_t)p.part_cap) != 0ull;
-    const uint32_t pieces = (len + kWave - 1) / kWave, pieces_end = wave_incl_scan_u32(pieces);
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)pieces_end, kWave - 1);
+// Part `part` passes on the n_passed elements whose positions are in passed[] (none below `low` or above k_max, its k largest among them), or
+// where that is more than it may pass on, those down to the bin of the k-th, or where that bin is too full exactly k.  k_up: the part's
+// upper bound.
+template <int ELT>
+__device__ __forceinline__ void parts_hand_over(const RowParams &p, const PartsRow<ELT> &w, int part, uint32_t n_passed, uint32_t low, uint32_t k_up,
+                                                uint32_t k_max) {
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1);
+    if (tid == 0) w.misc[5] = w.misc[7] = 0u;
     __syncthreads();
-    bool done = false;
-    if (!over) {
-        // the wavefronts take the pieces in turn, eight loads in flight
+    u64 *list = p.lists + (w.r * p.parts + part) * p.part_cap;
+    auto put = [&](u64 c, bool on) {  // whole wavefronts together
+        const bool up = on && key_of(c) >= k_up;
+        const u64 m_up = __ballot(up), m_low = __ballot(on && !up);
+        uint32_t to = 0;
+        if (lane == 0 && m_up) to = atomicAdd(&w.misc[5], (uint32_t)__popcll(m_up));
+        if (lane == 1 && m_low) to = atomicAdd(&w.misc[7], (uint32_t)__popcll(m_low));
+        const uint32_t to_up = (uint32_t)__builtin_amdgcn_readlane((int)to, 0), to_low = (uint32_t)__builtin_amdgcn_readlane((int)to, 1);
+        const u64 mine = up ? m_up : m_low;
+        const uint32_t place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+        const uint32_t at = up ? to_up + place : (uint32_t)p.part_cap - 1u - to_low - place;
+        if (on && at < (uint32_t)p.part_cap) __hip_atomic_store(&list[at], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (n_passed <= (uint32_t)p.part_cap) {
+        for (uint32_t i0 = tid - lane; i0 < n_passed; i0 += T) {
+            const bool on = i0 + lane < n_passed;
+            put(on ? w.element(p, i0 + lane) : 0ull, on);
+        }
+    } else {
+        w.clear();
+        RowBins bins;
+        bins.template set<ELT>(low, k_max, p.idx_bits, w.n_bins);
+        auto bin_of = [&](u64 c) { return bins.template bin<ELT>(key_of(c), (uint32_t)c >> 1); };
+        // (each lane's own entries, which get their values first)
+        for (uint32_t i = tid; i < n_passed; i += T) w.passed[i].x = (int)row_bits<ELT>(p, w.r, w.passed[i].y);
+        auto listed = [&](auto f) {  // whole wavefronts together
+            for (uint32_t i0 = tid - lane; i0 < n_passed; i0 += T) {
+                const bool on = i0 + lane < n_passed;
+                const int2 e = w.passed[on ? i0 + lane : 0u];
+                f(make_composite((uint32_t)e.x, e.y), on);
+            }
+        };
+        listed([&](u64 c, bool on) { row_count(w.cur, on ? bin_of(c) : 0u, on); });
+        __syncthreads();
+        row_scan(w.cur, w.misc, w.n_bins, (uint32_t)p.k);
+        const uint32_t tb = w.misc[0];
+        const bool fits = w.misc[1] + w.misc[2] <= (uint32_t)p.part_cap;
+        __syncthreads();
+        const RowSqueeze<ELT> sq{p.idx_bits + 1};
+        const u64 thr = fits ? 0ull : row_threshold_by_digits<ELT>(listed, (uint32_t)p.k, low, k_max, p.idx_bits, p.lg_bins, w.cur, w.misc);
+        uint32_t least = 0xffffffffu;
+        listed([&](u64 c, bool on) {
+            const bool goes = on && (fits ? bin_of(c) >= tb : sq(c) >= thr);
+            least = goes ? min(least, key_of(c)) : least;
+            put(c, goes);
+        });
+        least = wave_min_u32(least);
+        if (lane == 0) w.misc[8 + (tid >> 6)] = least;
+        __syncthreads();
+        low = wave_min_u32(lane < (T >> 6) ? w.misc[8 + lane] : 0xffffffffu);
+    }
+    __syncthreads();
+    w.put_head(p, part, low, w.misc[5], w.misc[7], k_up, k_max);
+}
+
+// A part whose elements at or above k_min are more than LDS lists: its k largest, from registers that are loaded again (kept from the first
+// time, they would be spilled on the way that most parts take).
+template <int ELT, int NV>
+__device__ __forceinline__ void part_largest(const RowParams &p, const PartsRow<ELT> &w, int part, uint32_t k_min, uint32_t k_up, uint32_t k_max) {
+    RowRegs<ELT, NV> regs;
+    const int v0 = w.first_vec(p, part), v1 = w.end_vec(p, part);
+    __syncthreads();
+    regs.load(p, w.r, v0, v1, w.rot);
+    if (threadIdx.x == 0) w.misc[5] = 0u;
+    regs.mask_ends(p, v0, v1, w.rot);
+    uint32_t n_passed;
+    const uint32_t low = regs.list_largest((uint32_t)p.k, k_min, k_max, w.passed, (uint32_t)p.cap, n_passed, &w.misc[5], w.cur, w.misc);
+    parts_hand_over<ELT>(p, w, part, n_passed, low, k_up, k_max);
+}
+
+// The lists of a row as its last workgroup sees them: lane i of every wavefront has the head of part i.
+struct PartsHeads {
+    uint32_t front = 0u, back = 0u;   // elements in the two pieces
+    uint32_t k_min = 0u, k_max = 0u;  // of the row: its k largest lie between them
+    uint32_t k_up = 0u;               // everything passed on from there on is in the first pieces
+    __device__ __forceinline__ PartsHeads(const RowParams &p, int64_t r) {
+        const int lane = threadIdx.x & (kWave - 1);
+        if (lane < p.parts) {
+            const u64 *head = p.heads + (r * p.parts + lane) * 4;
+            const u64 h0 = __hip_atomic_load(&head[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const u64 h1 = __hip_atomic_load(&head[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            k_up = (uint32_t)__hip_atomic_load(&head[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            front = (uint32_t)h0;
+            back = (uint32_t)h1;
+            k_min = front + back >= (uint32_t)p.k ? (uint32_t)(h0 >> 32) : 0u;  // (k elements of this part reach it)
+            k_max = (uint32_t)(h1 >> 32);
+        }
+        k_min = wave_max_u32(k_min);
+        k_max = wave_max_u32(k_max);
+        k_up = max(wave_max_u32(k_up), k_min);
+    }
+    // f(composite, whether there is one) for every element of the lists' first or second pieces: the wavefronts take 64 in turn, eight
+    // loads in flight
+    template <typename F>
+    __device__ __forceinline__ void sweep(const RowParams &p, int64_t r, bool first_pieces, F f) const {
         constexpr int U = 8;
+        const int lane = threadIdx.x & (kWave - 1);
+        const uint32_t len = first_pieces ? front : back;
         const u64 *lists = p.lists + r * p.parts * p.part_cap;
-        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (uint32_t)T >> 6;
+        const uint32_t pieces = (len + kWave - 1) / kWave, pieces_end = wave_incl_scan_u32(pieces);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)pieces_end, kWave - 1);
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n_waves = blockDim.x >> 6;
         for (uint32_t c0 = wave; c0 < total; c0 += U * n_waves) {
             u64 c[U];
 #pragma unroll
@@ -342,54 +401,160 @@ __global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
                     const int of = __popcll(__ballot(pieces_end <= id));  // the part whose piece it is
                     const uint32_t n_of = (uint32_t)__builtin_amdgcn_readlane((int)len, of);
                     const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)(pieces_end - pieces), of);
-                    const uint32_t i = (id - first) * kWave + (uint32_t)lane;
-                    c[u] = __hip_atomic_load(&lists[(uint32_t)of * (uint32_t)p.part_cap + min(i, n_of - 1u)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const uint32_t i = (id - first) * kWave + (uint32_t)lane, at = min(i, n_of - 1u);
+                    c[u] = __hip_atomic_load(&lists[(uint32_t)of * (uint32_t)p.part_cap + (first_pieces ? at : (uint32_t)p.part_cap - 1u - at)],
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (i >= n_of) c[u] = 0ull;
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool take = (uint32_t)(c[u] >> 32) >= k_min && c[u] != 0ull;
-                const u64 mask = __ballot(take);
-                if (mask) {  // uniform over the wavefront
-                    uint32_t at = 0;
-                    if (lane == 0) at = atomicAdd(&misc[5], (uint32_t)__popcll(mask));
-                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
-                         __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                    if (take && at < (uint32_t)p.cap) passed[at] = make_int2((int)composite_bits(c[u]), composite_index(c[u]));
-                }
-            }
-        }
-        __syncthreads();
-        const uint32_t n_passed = misc[5];
-        if (n_passed >= (uint32_t)p.k && n_passed <= (uint32_t)p.cap) {
-            done = row_select_passed<ELT>(p, r, passed, n_passed, k_min, k_max, filed, cur, misc);
-            if (!done) {  // once more from the raised lower end
-                for (int i = tid; i < n_bins; i += T) cur[i] = 0u;
-                if (tid == 0) misc[7] = 0u;
-                __syncthreads();
-                // (the elements below it drop out: in place, each lane looks at its own entries)
-                int2 own[8];
-                const int per = (int)((n_passed + T - 1) / T);
-                if (per <= 8) {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) own[j] = passed[min((uint32_t)(tid + j * T), n_passed - 1u)];
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const bool take = (uint32_t)(tid + j * T) < n_passed && ukey_of_bits((uint32_t)own[j].x) >= k_min;
-                        if (take) passed[atomicAdd(&misc[7], 1u)] = own[j];
-                    }
-                    __syncthreads();
-                    done = row_select_passed<ELT>(p, r, passed, misc[7], k_min, k_max, filed, cur, misc);
-                }
-            }
+            for (int u = 0; u < U; ++u) f(c[u], c[u] != 0ull);
         }
     }
-    if (!done) {
-        __syncthreads();
-        row_by_digits<ELT>(p, r, filed, cur, misc);
+};
+
+// sweep()'s elements that take() says, side by side into passed[]; returns how many.  Called by the whole workgroup with the cursors cleared.
+template <int ELT, typename SWEEP, typename TAKE>
+__device__ __forceinline__ uint32_t parts_gather(const RowParams &p, const PartsRow<ELT> &w, SWEEP sweep, TAKE take) {
+    const int lane = threadIdx.x & (kWave - 1);
+    sweep([&](u64 c, bool on) {
+        const bool mine = take(c, on);
+        const u64 mask = __ballot(mine);
+        if (mask) {  // uniform over the wavefront
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&w.misc[5], (uint32_t)__popcll(mask));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+                 __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (mine && at < (uint32_t)p.cap) w.passed[at] = make_int2((int)composite_bits(c), composite_index(c));
+        }
+    });
+    __syncthreads();
+    return w.misc[5];
+}
+
+// The row's k largest of what has been gathered (n >= k elements, all at or above k_min, no more than LDS holds) are written.
+template <int ELT>
+__device__ __forceinline__ void parts_finish(const RowParams &p, const PartsRow<ELT> &w, uint32_t n, uint32_t k_min, uint32_t k_max) {
+    const int lane = threadIdx.x & (kWave - 1);
+    for (uint32_t from = k_min;;) {  // once more from a raised lower end
+        const uint32_t was = from;
+        if (row_select_passed<ELT>(p, w.r, w.passed, n, from, k_max, w.filed, w.cur, w.misc)) return;
+        w.clear();
+        if (from == was || was != k_min) break;
     }
+    auto listed = [&](auto f) {  // whole wavefronts together
+        for (uint32_t i0 = threadIdx.x - lane; i0 < n; i0 += blockDim.x) {
+            const bool on = i0 + lane < n;
+            const int2 e = w.passed[on ? i0 + lane : 0u];
+            f(make_composite((uint32_t)e.x, e.y), on);
+        }
+    };
+    row_by_digits<ELT>(p, w.r, listed, k_min, k_max, w.filed, w.cur, w.misc);
+}
+
+// Several workgroups to a row: each holds a part of it in registers, finds a lower bound that at least k of its elements reach, and
+// passes on what lies at or above it, so that the k largest of the row are among what its parts pass on however unlike each other these
+// are (masked stretches, rows with a trend, neighbours that go together).  A part where more reach the bound than it may pass on (long
+// runs of ties) passes on its k largest.  The workgroup that draws the row's last ticket takes the largest of the bounds, which k elements of
+// the row reach, and selects from what was passed on above it.  Where that is more than LDS holds (many parts, large k), the lists are cut
+// at a second bound that fewer elements reach - k shared out over the parts, and a margin - and if k elements of the row
+// reach the largest of these, the first pieces of the lists are enough; else all of them are binned.
+// One sweep over memory, one launch.  us per call, of the launches this replaced (a sample or a histogram, a copy-out, a selection) and here:
+//                                          N(0,1)   first half -inf   ascending   constant   three levels   lagged average
+//   128 x 2^20 f32, k = 64                 135, 122       156, 157     832, 156  2205, 270      1130, 254         138, 145
+//   128 x 2^18 f32, k = 64                  60, 34         69, 41      262, 39    512, 74        320, 72           64, 35
+//   16 x 2^18 f32, k = 64                   31, 12         40, 13       41, 14     92, 21         75, 20           31, 14
+//   64 x 128256 bf16, k = 256               29, 12.6       49, 14       53, 17    223, 19        147, 23           36, 17
+//   one row of 2^20 f32, k = 1000           52, 19         55, 24       51, 63     84, 81         77, 80           51, 23
+// (Parts that pass on little more than their share of k, and a row that starts over, in one workgroup, when their bounds leave fewer than
+// k elements: 104, 30, 9.4, 10.2 and 13 us in the first column, and 220 to 45000 in the others.)
+// The lists go through memory as in the fused kernels' hand-over: agent-scope stores, a wait for their acknowledgement, a ticket.
+template <int ELT, int NV>
+__global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+    const int64_t r = blockIdx.x / (unsigned)p.parts;
+    const int part = (int)(blockIdx.x - (unsigned)r * (unsigned)p.parts);
+    const PartsRow<ELT> w(p, r, smem);
+    uint32_t *misc = w.misc;
+    uint32_t k_min, k_up, k_max, n_passed;
+    {
+        const int v0 = w.first_vec(p, part), v1 = w.end_vec(p, part);
+        RowRegs<ELT, NV> regs;
+        regs.load(p, r, v0, v1, w.rot);
+        if (tid == 0) misc[5] = 0u;
+        regs.mask_ends(p, v0, v1, w.rot);
+        regs.template bound<false, true>(p.sub, p.rank, misc, k_min, k_max, w.cur, p.rank_up, &k_up);
+        regs.list_from(__uint_as_float(bits_of_ukey(k_min)), w.passed, (uint32_t)p.cap, &misc[5]);
+        n_passed = misc[5];
+    }
+    bool over = n_passed > (uint32_t)p.part_cap;  // uniform, as is what follows from it
+    if (over && k_min == k_max && n_passed == w.elements(p, part)) {  // one value throughout: the first k
+        __syncthreads();
+        for (int i = tid; i < p.k; i += (int)blockDim.x) w.passed[i].y = max(w.first_vec(p, part) * w.VE - w.rot, 0) + i;
+        __syncthreads();
+        n_passed = (uint32_t)p.k;
+        over = false;
+    }
+    if (!over && !p.rank_up) {
+        u64 *list = p.lists + (r * p.parts + part) * p.part_cap;
+        for (uint32_t i = tid; i < n_passed; i += blockDim.x)
+            __hip_atomic_store(&list[i], w.element(p, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        w.put_head(p, part, k_min, n_passed, 0u, 0u, k_max);
+    } else if (n_passed > (uint32_t)p.cap) {
+        // (the same addresses as above, which the compiler must not keep until here)
+        RowParams q = p;
+        int same = __builtin_amdgcn_readfirstlane(part);
+        asm volatile("" : "+s"(q.x), "+s"(same));
+        part_largest<ELT, NV>(q, PartsRow<ELT>(q, r, smem), same, k_min, k_up, k_max);
+    } else {
+        parts_hand_over<ELT>(p, w, part, n_passed, k_min, k_up, k_max);
+    }
+    // (a barrier alone does not wait for stores; the memory clobber keeps the compiler from moving the ticket above this)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t *ticket = p.tickets + r * kTicketStride;
+        const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.parts - 1u;
+        misc[6] = last ? 1u : 0u;
+        if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next call
+    }
+    __syncthreads();
+    if (!misc[6]) return;
+    // ---- the row's last workgroup
+    const PartsHeads h(p, r);
+    auto in = [&](u64 c, bool on) { return on && key_of(c) >= h.k_min; };
+    uint32_t from = h.k_up;
+    w.clear();
+    uint32_t n = parts_gather<ELT>(p, w, [&](auto f) { h.sweep(p, r, true, f); }, [&](u64 c, bool on) { return on && key_of(c) >= h.k_up; });
+    if (n < (uint32_t)p.k || n > (uint32_t)p.cap) {  // down to the bin of the k-th
+        auto sweep = [&](auto f) {
+            h.sweep(p, r, true, f);
+            h.sweep(p, r, false, f);
+        };
+        __syncthreads();
+        w.clear();
+        RowBins bins;
+        bins.template set<ELT>(h.k_min, h.k_max, p.idx_bits, w.n_bins);
+        auto bin_of = [&](u64 c) { return bins.template bin<ELT>(key_of(c), (uint32_t)c >> 1); };
+        sweep([&](u64 c, bool on) { row_count(w.cur, in(c, on) ? bin_of(c) : 0u, in(c, on)); });
+        __syncthreads();
+        row_scan(w.cur, misc, w.n_bins, (uint32_t)p.k);
+        const uint32_t tb = misc[0];
+        n = misc[3] < (uint32_t)p.k ? 0u : misc[1] + misc[2];
+        from = max(h.k_min, bins.template edge<ELT>(tb));
+        __syncthreads();
+        w.clear();
+        if (n > (uint32_t)p.cap) {  // (ties)
+            row_by_digits<ELT>(p, r, [&](auto f) { sweep([&](u64 c, bool on) { f(c, in(c, on)); }); }, from, h.k_max, w.filed, w.cur, misc);
+            return;
+        }
+        if (n) parts_gather<ELT>(p, w, sweep, [&](u64 c, bool on) { return in(c, on) && bin_of(c) >= tb; });
+    }
+    if (n >= (uint32_t)p.k)
+        parts_finish<ELT>(p, w, n, from, h.k_max);
+    else  // (NaNs)
+        row_by_digits<ELT>(p, r, [&](auto f) { row_vec_sweep<ELT>(p, r, 0, w.n_vec, w.rot, f); }, 0u, 0xffffffffu, w.filed, w.cur, misc);
 }
 
 // ------------------------------------------------------------------------------------ host
@@ -404,8 +569,8 @@ static int row_nv(int64_t want, bool pairs) {  // vectors per lane of the smalle
 // the upper half of a wavefront's maxima (close to all of them the bound falls off: the smallest of the maxima).  Returns how
 // many of the n_vec vectors' elements may be expected to reach it: among random elements the share above the
 // rank-th of the g maxima of groups of e is 1 - (1 - rank/g)^(1/e), and the smallest over the wavefronts lies
-// two or so deviations further down.
-static double row_bound_plan(RowPlan &p, int T, int64_t n_vec, double want) {
+// two or so deviations further down (`below`; half of one where the wavefronts' counts are summed).
+static double row_bound_plan(RowPlan &p, int T, int64_t n_vec, double want, double below = 2.2) {
     const int ve = p.ve, waves = T / kWave;
     const int sm = p.nv * 4 < 8 ? 4 : 8;
     p.rank = (int)std::ceil(want / waves);
@@ -421,7 +586,7 @@ static double row_bound_plan(RowPlan &p, int T, int64_t n_vec, double want) {
         return (double)(n_vec * ve);
     }
     const double g = 64.0 * p.sub, per_wave = (double)n_vec * ve / waves, e = per_wave / g > 1.0 ? per_wave / g : 1.0;
-    const double low = p.rank + 2.2 * std::sqrt((double)p.rank) + 1.0;
+    const double low = p.rank + below * std::sqrt((double)p.rank) + 1.0;
     const double share = low < g * 0.98 ? 1.0 - std::pow(1.0 - low / g, 1.0 / e) : 1.0;
     return share * per_wave * waves;
 }
@@ -506,15 +671,26 @@ bool plan_exact_parts(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Ro
     if (!p.nv) return false;
     p.parts = (int)parts;
     p.part_vecs = (int)pv;
-    // The largest of the parts' bounds decides how many elements are left, so every part aims at k / parts and a margin
-    const double want = 1.2 * (double)k / (double)parts + 3.0 * std::sqrt((double)k / (double)parts) + 3.0;
-    if (want * 2.0 > (double)(pv * ve)) return false;
-    const double expect = row_bound_plan(p, T, std::min(pv, n_vec), want);
-    p.part_cap = (int)(expect * 1.5 + 8.0 * std::sqrt(expect) + 128.0);
-    const double total = (double)parts * expect;
-    p.cap = ((int)(1.3 * total + 512.0) + 1) & ~1;
-    if (p.cap > 16384) return false;
+    // What a row's parts pass on is about half a MB at most, and no part passes on much of what it reads.
+    if (parts * k > 65536 || (double)k > 0.2 * (double)((pv - parts) * ve)) return false;
+    const double expect = row_bound_plan(p, T, pv, (double)k, 0.5);
+    p.part_cap = (int)(expect * 1.25 + 8.0 * std::sqrt(expect) + 128.0);
+    if (p.part_cap < k) p.part_cap = (int)k;
+    p.cap = 4096;
+    if ((double)parts * expect > 3500.0) {
+        // (not on launches of more than two rounds of workgroups: what a row's last workgroup then does alone, where the row is unlike
+        // itself along its length, is done by all of them in the sweeps of the digit-by-digit path: 128 x 2^20 f32, k = 1000, ascending
+        // 580 us there, 950 here, first half -inf 430 and 510, without order 225 and 207)
+        if (m * parts > 4 * kNumCU) return false;
+        // The largest of the parts' upper bounds decides how many elements are left, so every part aims at k / parts and a margin
+        const double want = 1.5 * (double)k / (double)parts + 3.0 * std::sqrt((double)k / (double)parts) + 3.0;
+        p.rank_up = (int)std::ceil(want / (T / kWave));
+        if (p.rank_up >= p.rank) p.rank_up = 0;
+        const double up = p.rank_up ? (double)p.rank_up * (double)(T / kWave) * (expect / ((double)p.rank * (T / kWave))) : expect;
+        p.cap = std::max(p.cap, ((int)(1.1 * (double)parts * up + 512.0) + 1) & ~1);
+    }
     if (p.cap < p.part_cap) p.cap = (p.part_cap + 1) & ~1;
+    if (p.cap > 16384 || exact_parts_data_bytes(p, m) > (1ll << 30)) return false;
     int lg = 8;
     while (lg < 13 && ((1 << lg) < 2 * k || (1 << lg) < T)) ++lg;
     int64_t kp = 1;
@@ -528,7 +704,7 @@ bool plan_exact_parts(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Ro
     *out = p;
     return true;
 }
-int64_t exact_parts_data_bytes(const RowPlan &p, int64_t m) { return m * p.parts * (16 + (int64_t)p.part_cap * 8); }
+int64_t exact_parts_data_bytes(const RowPlan &p, int64_t m) { return m * p.parts * (32 + (int64_t)p.part_cap * 8); }
 int64_t exact_parts_state_bytes(int64_t m) { return m * kTicketStride * 4; }
 
 template <typename K>
@@ -597,8 +773,9 @@ hipError_t launch_exact_row(const RowPlan &pl, int64_t m, int64_t n, int64_t k, 
     prm.parts = pl.parts;
     prm.part_vecs = pl.part_vecs;
     prm.part_cap = pl.part_cap;
+    prm.rank_up = pl.rank_up;
     prm.heads = (u64 *)data;
-    prm.lists = prm.heads + m * pl.parts * 2;
+    prm.lists = prm.heads + m * pl.parts * 4;
     prm.tickets = (uint32_t *)state;
     if (xi && (((uintptr_t)x | (uintptr_t)xi) & 15u)) return hipErrorInvalidValue;  // never: the pairs lie in the library's scratch
     if (pl.parts && (xi || !state || !data)) return hipErrorInvalidValue;

@@ -110,3 +110,29 @@ def test_rows_in_parts(dtype):
             _check(x.to(t), k)
     _check(workloads.few_levels(2, n, levels=3, seed=9, dtype=dtype), 500)
     _check(workloads.special_values(2, n, seed=9, dtype=dtype), 500)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 1 << 18, 64), (2, 1 << 20, 1000), (70, 1 << 18, 20), (5, 200003, 300)])
+def test_parts_unlike_each_other(shape, dtype):
+    """Rows whose parts hold more or fewer of the winners than their share: masked, with a trend, in one place, neighbours that go
+    together, ties at every place of the range."""
+    m, n, k = shape
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    base = workloads.normal_rows(m, n, seed=n % 977)
+    rows = [base + torch.linspace(0.0, 6.0, n), base.sort(dim=1)[0], torch.full((m, n), 0.3), torch.full((m, n), -0.0)]
+    for at in (slice(0, n // 33), slice(0, n // 2), slice(n - n // 20, n), slice(n // 4, n), slice(0, n - k // 2)):
+        masked = base.clone()
+        masked[:, at] = float("-inf")
+        rows.append(masked)
+    stripes = base.clone()
+    stripes[:, (torch.arange(n) // 4096) % 2 == 0] = float("-inf")
+    block = base.clone()
+    block[:, n // 3: n // 3 + n // 64] += 50.0
+    spikes = torch.zeros(m, n)
+    spikes[:, 5] = 2.0
+    spikes[:, (n * 7) // 9] = 1.0
+    lagged = torch.nn.functional.avg_pool1d(base.unsqueeze(1), 65, 1, 32).squeeze(1) * 8.0
+    rows += [stripes, block, spikes, lagged, torch.relu(base - 1.5), (base * 100.0).round(), torch.randint(0, 3, (m, n)).float()]
+    for x in rows:
+        _check(x.to(t).contiguous(), k, shift=n % 2)
