@@ -36,11 +36,13 @@ struct DealRow {          // per row, on the device
     uint32_t k_min, k_max;   // range of the fine bins
     uint32_t tb;             // the threshold: the lowest fine bin that counts
     uint32_t cursor;         // candidates dealt
-    uint32_t failed;         // a bin holds more than a workgroup orders
+    uint32_t split;          // the bins are cut at elements of the sample, not at fine bins
 };
 struct DealPlan {
     int chunks, bins;        // per row
-    int sample_rank;         // sampled elements above the threshold
+    int sample_rank;         // sampled elements above the threshold, at least
+    int split_rank;          // the same where the bins are cut at sampled elements
+    float expect;            // sampled elements among the k largest
     int rank;                // of the sample's lower bound, as in RowPlan
     int64_t pool_cap;        // candidates per row
     int64_t rows_off, table_off, totals_off, segs_off, pool_off, rest_off, bytes;  // byte offsets into the data pool
@@ -48,7 +50,7 @@ struct DealPlan {
 bool plan_exact_deal(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, DealPlan *out);
 hipError_t launch_exact_deal(const DealPlan &pl, int64_t m, int64_t n, int64_t k, int64_t idx_n, int dtype, const void *x,
                              const int32_t *xi, void *out_vals, int32_t *out_idx, void *data, hipStream_t stream);
-// The rows whose candidates number fewer than k or more than pool_cap, or that are marked failed: one workgroup per row.
+// The rows whose candidates number fewer than k or more than pool_cap: one workgroup per row.
 // buf0, buf1: m * k composites each.
 hipError_t launch_exact_rest_rows(int64_t m, int64_t n, int64_t k, int idx_bits, int dtype, const void *x, const int32_t *xi,
                                   const DealRow *rows, int64_t pool_cap, u64 *buf0, u64 *buf1, void *out_vals, int32_t *out_idx,

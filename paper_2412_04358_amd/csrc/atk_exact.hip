@@ -968,8 +968,7 @@ static uint32_t sort_shifts(int idx_bits) {
     return shifts;
 }
 
-// The rows that the dealing (atk_exact_deal.hip) could not finish: a sample that misjudged the row, a bin with more than one
-// workgroup orders.  Rare, and a launch cannot be skipped without asking the device, so this is one launch whose workgroups
+// The rows that the dealing (atk_exact_deal.hip) could not finish: a sample that misjudged the row.  Rare, and a launch cannot be skipped without asking the device, so this is one launch whose workgroups
 // return at once unless their row is such a one; a workgroup that stays takes its row through all digits alone, collects
 // the k survivors and sorts them.
 template <int ELT>
@@ -982,7 +981,7 @@ __global__ void __launch_bounds__(kMaxThreads) ex_rest_rows_kernel(const void *x
     __shared__ uint32_t s_need, s_done, s_cursor;
     const int r = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
     const DealRow row = rows[r];
-    if (!row.failed && (int64_t)row.cursor >= k && (int64_t)row.cursor <= pool_cap) return;  // uniform over the workgroup
+    if ((int64_t)row.cursor >= k && (int64_t)row.cursor <= pool_cap) return;  // uniform over the workgroup
     if (tid == 0) s_cursor = 0u;
     const u64 prefix = row_threshold<ELT>(x, xi, n, r, sq_bits, 0, n_passes, kExChunk, sq, 0ull, (uint32_t)k, false, lh, wave_tot, s_prefix,
                                           s_need, s_done);

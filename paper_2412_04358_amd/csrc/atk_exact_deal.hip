@@ -4,22 +4,29 @@
 //   ex_sample_kernel  one workgroup per row: a sample of 32768 elements (runs of 64 bytes, one at a random place in
 //                     every piece of the row) gives a threshold that a little more than k elements of the row reach, and cuts
 //                     what lies above it into bins of about 1000 elements: unions of fine bins that are linear in (value
-//                     key, index), so a bin's number is one multiplication and one look into a table.
+//                     key, index), so a bin's number is one multiplication and one look into a table.  Rows with long runs of ties
+//                     are cut between elements of the sample instead, which is sorted for that.
 //   ex_deal_kernel    a workgroup per 16384 elements: what reaches the threshold is brought into the order of the
 //                     bins in LDS and written to the row's pool in one piece, with a table of where each bin starts.  (No bin has
 //                     space set aside for it: however unevenly the sample cut the row, the pool is as full as the threshold lets
 //                     through.)
 //   ex_bins_kernel    a workgroup per bin: its pieces from all the chunks, ordered in LDS by a second set of bins and exact
 //                     ranks, written to their places in the output.
-//   ex_rest_rows_kernel (atk_exact.hip): rows that did not come out - a sample that misjudged the row, a bin that
-//                     holds more than a workgroup orders (long runs of one value) - go digit by digit, one workgroup per row.
+//   ex_rest_rows_kernel (atk_exact.hip): rows that a sample misjudged (fewer than k candidates, or more than the pool
+//                     holds) go digit by digit, one workgroup per row: slow, and rare, as the threshold has a margin of six
+//                     deviations as the sample itself shows them.
 //
 // Every element is read once and every candidate written and read once more; memory is what bounds it: 128 x 2^20 f32,
-// k = 2^18 reads 537 MB, writes and reads back 8 bytes for each of 1.05 k candidates and writes 268 MB of output.
-// Measured there: 22 us to sample, 156 to deal (5.2 TB/s), 187 to order (2.9 TB/s; a chain of short steps per bin that seven
+// k = 2^18 reads 537 MB, writes and reads back 8 bytes for each of 1.06 k candidates and writes 268 MB of output.
+// Measured there: 25 us to sample, 160 to deal (5 TB/s), 188 to order (2.9 TB/s; a chain of short steps per bin that seven
 // workgroups of 256 lanes to a CU overlap - five with more tables in LDS took 262, two of 512 lanes 466), 4 for the last
-// launch that finds nothing to do: 374 us, against 1108 by digit passes, a collecting sweep and a partition sort in 18
-// launches.  k = 65536: 576 -> 193; 64 x 2^21 bf16, k = 2^19: 1690 -> 418; one row of 2^20, k = 2^18: 107 -> 33.
+// launch that finds nothing to do (under the tracer; the call takes 368), against 1113 by digit passes, a collecting sweep
+// and a partition sort in 18 launches.  64 x 2^21 bf16, k = 2^19: 1690 -> 418.  us per call, by digit passes and here:
+//                                      N(0,1)    first quarter -inf  ascending   constant    three levels  lagged average
+//   128 x 2^20 f32, k = 2^18        1113, 368        1306, 410       1457, 904  2487, 1121    1484, 784      1101, 431
+//   32 x 2^18 f32, k = 2^14           112, 42          119, 42        138, 105   176, 156      133, 53        112, 44
+//   8 x 2^21 bf16, k = 2^19           327, 91         334, 112        480, 758   254, 237      222, 143       332, 113
+//   one row of 2^20 f32, k = 2^18     107, 35           82, 44         99, 67     91, 120       96, 155       106, 44
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -42,81 +49,200 @@ constexpr int kBinT = 256;              // threads that order a bin
 constexpr int kBinCap = 2048;           // candidates of a bin that LDS holds
 constexpr int kBinSub = 1024;           // bins inside a bin
 constexpr int kDealChunksMax = 512;     // chunks of a row
+constexpr int kSplitLane = 7;           // sampled elements of a lane that are sorted where bins are cut at elements
+constexpr int kSplitSample = kSplitLane * kDealT;
 
 // What the rows of the sampling cost and save: the threshold lets through about 7 % more than k of a row's elements where k is a
 // quarter of it, twice k where 64 sampled elements lie among the k largest (the least that is taken; with fewer the copy-out path of
 // atk_exact.hip is there).
 struct DealParams : RowParams {
     DealRow *rows;
-    uint16_t *table;      // [row][kDealFine]: bin of each fine bin (0: the largest values)
+    uint16_t *table;      // [row][kDealFine]: bin of each fine bin (0: the largest values); or [row][n_deal] composites: the lowest of each bin
     uint32_t *totals;     // [row][n_deal]: candidates per bin
     uint32_t *segs;       // [row][chunk][n_deal + 1]: where the chunk's piece of each bin starts in the row's pool
     u64 *pool;            // [row][pool_cap] candidates
     int64_t pool_cap;
     int n_deal, chunks;
-    int sample_rank;      // elements of the sample above the threshold
+    int sample_rank;      // elements of the sample above the threshold, at least
+    int split_rank;
+    float expect;         // elements of the sample among the k largest
 };
+
+// Sorts buf[0 .. n), largest first: a bitonic network in which the places past the end up to a power of two count as empty - every
+// comparison puts the larger one first (the first step of a size pairs places mirrored in their block, the others places `stride`
+// apart), so nothing is ever moved there.  Words up to 64 apart are compared by one wavefront, which then needs no barrier between
+// steps.  Called by the whole workgroup after a barrier; ends in one.
+__device__ __forceinline__ void sort_words(u64 *buf, int n) {
+    int kp = 1;
+    while (kp < n) kp <<= 1;
+    for (int size = 2; size <= kp; size <<= 1)
+        for (int stride = size >> 1; stride >= 1; stride >>= 1) {
+            for (int i = threadIdx.x; i < (kp >> 1); i += blockDim.x) {
+                const int lo = ((i & ~(stride - 1)) << 1) | (i & (stride - 1));
+                const int hi = stride == (size >> 1) ? (lo | (size - 1)) - (lo & (size - 1)) : lo + stride;
+                if (hi < n) {
+                    const u64 x = buf[lo], y = buf[hi];
+                    if (y > x) {
+                        buf[lo] = y;
+                        buf[hi] = x;
+                    }
+                }
+            }
+            if (stride > kWave || (stride == 1 ? size : stride >> 1) > kWave) {
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+    __syncthreads();
+}
 
 template <int ELT>
 __global__ void __launch_bounds__(kDealT) ex_sample_kernel(DealParams p) {
     constexpr int VE = ELT == ATK_F32 ? 4 : 8, NV = kDealSample / kDealT / VE;
-    __shared__ __align__(16) uint32_t cur[kDealFine + 4];
+    __shared__ __align__(16) u64 words[kSplitSample];
     __shared__ uint32_t misc[kRowMisc];
-    const int tid = threadIdx.x, T = kDealT;
+    static_assert(sizeof(words) >= (kDealFine + 4) * 4, "the fine bins lie there, too");
+    uint32_t *cur = (uint32_t *)words;
+    const int tid = threadIdx.x, T = kDealT, lane = tid & (kWave - 1);
     const int64_t r = blockIdx.x;
     const uintptr_t addr = (uintptr_t)p.x + (uintptr_t)(r * p.n) * (16 / VE);
     const int rot = (int)(addr & 15) / (16 / VE);
     const int n_vec = (rot + p.n + VE - 1) / VE - 2;  // whole vectors of the row: not the first and the last
     const row_v4u *row = (const row_v4u *)(addr & ~(uintptr_t)15) + 1;
-    // runs of four vectors, each at a place of its own inside its piece of the row
-    constexpr int runs = NV * kDealT / 4;
+    // runs of four vectors, each at a place of its own inside its piece of the row; the pieces are dealt out so that every wavefront's
+    // runs, and every lane's first ones, lie all over the row (masked and rising rows)
+    constexpr int runs = NV * kDealT / 4, waves = kDealT / kWave;
     const int len = n_vec / runs;  // vectors of a piece: at least 4
     RowRegs<ELT, NV> regs;
     int at[NV];  // row position of each vector's first element
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int u = tid + j * T, run = u >> 2;
+        const int run = (((lane >> 2) * NV + j) * waves) + (tid >> 6);
         const uint32_t hash = (((uint32_t)run * 2654435761u) ^ ((uint32_t)r * 2246822519u)) * 3266489917u;
-        const int v = (int)((int64_t)run * n_vec / runs) + (int)__umulhi(hash, (uint32_t)(len - 3)) + (u & 3);
+        const int v = (int)((int64_t)run * n_vec / runs) + (int)__umulhi(hash, (uint32_t)(len - 3)) + (lane & 3);
         at[j] = (v + 1) * VE - rot;
         regs.q[j] = row[v];
     }
     regs.i0 = 0;
     for (int i = tid; i < kDealFine + 4; i += T) cur[i] = 0u;
     for (int i = tid; i < p.n_deal; i += T) p.totals[r * p.n_deal + i] = 0u;
+    auto index_at = [&](int en) {
+        int pos = at[en / VE];
+        asm volatile("" : "+v"(pos));  // (worked out again on each pass, not kept)
+        pos += en % VE;
+        return p.xi ? p.xi[r * p.n + pos] : pos;
+    };
     // a lower bound from a part of the sample (eight elements per lane), with a margin: counted, not trusted
     uint32_t k_min, k_max;
     regs.template bound<true>(8, p.rank, misc, k_min, k_max);
     RowBins bins;
+    // (a range that starts at -inf is taken again from the lower edge of the threshold's bin: a range without what lies far below; one with
+    // too few elements in it, from -inf first)
+    bool raised = k_min > 0x007fffffu, measured = false, cut = false, split = false;
+    uint32_t rank = (uint32_t)p.sample_rank, total, tb;
     for (int pass = 0;; ++pass) {
         bins.template set<ELT>(k_min, k_max, p.idx_bits, kDealFine);
-        const float v_lo = __uint_as_float(bits_of_ukey(k_min));
+        float v_lo = __uint_as_float(bits_of_ukey(k_min));
         regs.each([&](uint32_t bits, int, int en) {
-            if (__uint_as_float(bits) >= v_lo) {
-                int pos = at[en / VE];
-                asm volatile("" : "+v"(pos));  // (worked out again on each pass, not kept)
-                pos += en % VE;
-                const int idx = p.xi ? p.xi[r * p.n + pos] : pos;
-                atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)], 1u);
-            }
+            if (__uint_as_float(bits) >= v_lo)
+                atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)index_at(en))], 1u);
         });
-        if (tid == 0) misc[0] = 0u;
+        if (tid == 0) misc[0] = misc[5] = misc[7] = 0u;
         __syncthreads();
-        row_scan(cur, misc, kDealFine, (uint32_t)p.sample_rank);
-        // too few: from -inf, and then from the lower edge of the threshold's bin (a range without what lies far below)
-        const bool few = misc[3] < (uint32_t)p.sample_rank;
-        if (pass == 2 || (pass == 0 ? !few : few)) break;
-        k_min = pass == 0 ? 0x007fffffu : bins.template edge<ELT>(misc[0]);
+        row_scan(cur, misc, kDealFine, rank);
+        total = misc[3];
+        bool few = total < rank, decide = false;
+        if (pass < 5 && (few ? raised : !raised)) {
+            raised = !few;
+            k_min = few ? 0x007fffffu : bins.template edge<ELT>(misc[0]);
+        } else if (measured) {
+            decide = true;
+        } else {
+            // How far the sample may be off: sixteen elements of a run are as good as one where neighbours go together, so the deviation
+            // is that of the runs' counts above the threshold, not that of single elements.
+            measured = true;
+            v_lo = __uint_as_float(bits_of_ukey(bins.template edge<ELT>(misc[0])));
+            uint32_t n_in[NV], sum = 0, squares = 0;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) n_in[j] = 0u;
+            regs.each([&](uint32_t bits, int, int en) { n_in[en / VE] += __uint_as_float(bits) >= v_lo ? 1u : 0u; });
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                uint32_t c = n_in[j];
+                c += (uint32_t)__shfl_xor((int)c, 1);
+                c += (uint32_t)__shfl_xor((int)c, 2);
+                sum += c;
+                squares += c * c;
+            }
+            sum = wave_incl_scan_u32((lane & 3) ? 0u : sum);
+            squares = wave_incl_scan_u32((lane & 3) ? 0u : squares);
+            if (lane == kWave - 1) {
+                atomicAdd(&misc[5], sum);
+                atomicAdd(&misc[7], squares);
+            }
+            __syncthreads();
+            const float n_above = (float)misc[5], var = (float)misc[7] - n_above * n_above / (float)runs;
+            rank = max(rank, (uint32_t)(p.expect + 6.0f * sqrtf(fmaxf(var, 0.0f)) + 6.0f));
+            few = total < rank;
+            decide = !few || k_min <= 0x007fffffu;
+            if (!decide) {  // counted further down
+                raised = false;
+                k_min = 0x007fffffu;
+            }
+        }
+        if (decide) {
+            // (a sample in which too few reach the bound - NaNs - leaves fewer than k candidates, or it does not: that is counted)
+            rank = min(rank, max(total, (uint32_t)p.sample_rank));
+            // the threshold's bin, and whether the bins from there on are fine enough to cut the row at
+            if (tid == 0) misc[40] = misc[41] = 0u;
+            __syncthreads();
+            const uint32_t crowd = 2u * rank / (uint32_t)p.n_deal + 16u;
+            for (int f = tid; f < kDealFine; f += T) {
+                const uint32_t above = cur[f], with = f > 0 ? cur[f - 1] : total;
+                if (above < rank) {
+                    if (with >= rank) misc[40] = (uint32_t)f;
+                    if (with - above > crowd) misc[41] = 1u;
+                }
+            }
+            __syncthreads();
+            tb = misc[40];
+            split = misc[41] != 0u;
+            const uint32_t edge = bins.template edge<ELT>(tb);
+            if (!split || cut || pass >= 5 || edge <= k_min) break;
+            cut = raised = true;  // once more without what lies below the threshold (a range around zero spans every exponent)
+            k_min = edge;
+        }
         __syncthreads();
         for (int i = tid; i < kDealFine; i += T) cur[i] = 0u;
         __syncthreads();
     }
-    // (a sample in which too few reach the bound - NaNs - leaves fewer than k candidates, or it does not: that is counted)
-    const uint32_t tb = misc[0];
     uint16_t *table = p.table + r * kDealFine;
-    for (int f = tid; f < kDealFine; f += T) {
-        const uint32_t c = (uint32_t)((u64)cur[f] * (u64)p.n_deal / (u64)p.sample_rank);  // cur: sampled elements above
-        table[f] = (uint32_t)f < tb ? (uint16_t)0xffffu : (uint16_t)min(c, (uint32_t)p.n_deal - 1u);
+    if (!split) {
+        for (int f = tid; f < kDealFine; f += T) {
+            const uint32_t c = (uint32_t)((u64)cur[f] * (u64)p.n_deal / (u64)rank);  // cur: sampled elements above
+            table[f] = (uint32_t)f < tb ? (uint16_t)0xffffu : (uint16_t)min(c, (uint32_t)p.n_deal - 1u);
+        }
+    } else {
+        // Long runs of ties: a part of the sample is sorted, ties by index, and the row cut between its elements.
+        __syncthreads();  // (the fine bins have been read)
+        regs.each([&](uint32_t bits, int, int en) {
+            // (one of every four, but for one four of the lane's eight, another one in each wavefront: no place of the row is left out)
+            static_assert(kSplitLane == 7 && kDealSample == 32 * kDealT, "seven of eight fours");
+            const int skip = (tid >> 6) & 7, four = en / 4;
+            if (en % 4 == four % 4 && four != skip)
+                words[(four - (four > skip ? 1 : 0)) * T + tid] =
+                    __uint_as_float(bits) == __uint_as_float(bits) ? make_composite(bits, index_at(en)) : 0ull;
+        });
+        __syncthreads();
+        sort_words(words, kSplitSample);
+        u64 *low = (u64 *)table;
+        for (int b = tid; b < p.n_deal; b += T) {
+            const int last = (int)((int64_t)(b + 1) * p.split_rank / p.n_deal) - 1;
+            low[b] = max(words[max(last, 0)], 1ull);  // (0: nothing)
+        }
     }
     if (tid == 0) {
         DealRow d;
@@ -124,7 +250,7 @@ __global__ void __launch_bounds__(kDealT) ex_sample_kernel(DealParams p) {
         d.k_max = k_max;
         d.tb = tb;
         d.cursor = 0u;
-        d.failed = 0u;
+        d.split = split ? 1u : 0u;
         p.rows[r] = d;
     }
 }
@@ -138,7 +264,7 @@ __global__ void __launch_bounds__(kDealT) ex_deal_kernel(DealParams p) {
     u64 *staged = (u64 *)smem;
     uint32_t *cnt = (uint32_t *)(staged + kDealStage);  // [n_deal + 1] (at most T + 4)
     uint32_t *misc = cnt + kDealBinsMax + 4;
-    uint16_t *tab = (uint16_t *)(misc + kRowMisc);      // [kDealFine]
+    uint16_t *tab = (uint16_t *)(misc + kRowMisc);      // [kDealFine], or [n_deal] composites
     const int tid = threadIdx.x, lane = tid & (kWave - 1), n_waves = T >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t r = blockIdx.y;
@@ -158,9 +284,10 @@ __global__ void __launch_bounds__(kDealT) ex_deal_kernel(DealParams p) {
     if (tid == 0) misc[5] = 0u;
     RowBins bins;
     bins.template set<ELT>(info.k_min, info.k_max, p.idx_bits, kDealFine);
-    const float v_lo = __uint_as_float(bits_of_ukey(bins.template edge<ELT>(info.tb)));
     regs.mask_ends(p, v0, v1, rot);
     __syncthreads();
+    const u64 *low = (const u64 *)tab;  // split: the lowest composite of each bin
+    const float v_lo = __uint_as_float(bits_of_ukey(info.split ? (uint32_t)(low[p.n_deal - 1] >> 32) : bins.template edge<ELT>(info.tb)));
     // ---- what reaches the threshold, side by side in LDS
     uint32_t mine = 0;
     regs.each([&](uint32_t bits, int, int) { mine += __uint_as_float(bits) >= v_lo ? 1u : 0u; });
@@ -178,6 +305,18 @@ __global__ void __launch_bounds__(kDealT) ex_deal_kernel(DealParams p) {
     const uint32_t n_passed = misc[5];
     const bool fits = n_passed <= (uint32_t)kDealStage;
     auto bin_of = [&](uint32_t bits, int idx) {
+        if (info.split) {  // uniform
+            const u64 c = make_composite(bits, idx);
+            int first = 0, end = p.n_deal;
+            while (first < end) {
+                const int mid = (first + end) >> 1;
+                if (c >= low[mid])
+                    end = mid;
+                else
+                    first = mid + 1;
+            }
+            return first < p.n_deal ? (uint32_t)first : 0xffffu;
+        }
         return (uint32_t)tab[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)];  // 0xffff: just below the threshold
     };
     auto index_of = [&](int pos) { return p.xi ? p.xi[r * p.n + pos] : pos; };
@@ -257,6 +396,7 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
     __shared__ __align__(16) u64 buf[kBinCap];
     __shared__ __align__(16) uint32_t cur[kBinSub + 4];
     __shared__ uint32_t misc[kRowMisc];
+    __shared__ u64 ends[2 * W];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t r = blockIdx.y;
@@ -310,7 +450,20 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     if ((uint32_t)(sl + h * G) < pl[u]) f(v[u][h], pt[u] + sl + h * G);
-                for (uint32_t i = sl + 2 * G; i < pl[u]; i += G) f(pool[ps[u] + i], pt[u] + i);
+                // the rest of long pieces (rows in order, runs of ties), one after the other by the whole wavefront
+                for (u64 more = __ballot(sl == 0 && pl[u] > 2u * G); more; more &= more - 1ull) {
+                    const int src = __builtin_ctzll(more);
+                    const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)ps[u], src), n = (uint32_t)__builtin_amdgcn_readlane((int)pl[u], src);
+                    const uint32_t place = (uint32_t)__builtin_amdgcn_readlane((int)pt[u], src);
+                    for (uint32_t i = 2u * G + lane; i - lane < n; i += 2 * kWave) {
+                        u64 w[2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) w[h] = pool[from + min(i + h * kWave, n - 1u)];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            if (i + h * kWave < n) f(w[h], place + i + h * kWave);
+                    }
+                }
             }
         }
     };
@@ -345,7 +498,31 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
     const int n_sub = 1 << lg;
     RowBins bins;
     bins.template set<ELT>(k_min, k_max, p.idx_bits, n_sub);
-    auto sub_of = [&](u64 c) { return bins.template bin<ELT>((uint32_t)(c >> 32), (uint32_t)c >> 1); };
+    // Sub-bins are linear between the bin's lowest and highest key (ties: in the index, from 0 to the row's length); where that puts
+    // dozens into one (one value's ties on a short stretch of the row), between its smallest and its largest composite.
+    const RowSqueeze<ELT> sq{p.idx_bits + 1};
+    u64 q_min = 0ull;
+    int q_shift = -1;
+    auto sub_of = [&](u64 c) {
+        return q_shift < 0 ? bins.template bin<ELT>((uint32_t)(c >> 32), (uint32_t)c >> 1) : (uint32_t)((sq(c) - q_min) >> q_shift);
+    };
+    // mn, mx: this lane's.  Called by the whole workgroup; ends in a barrier, with the sub-bins cleared.
+    auto narrow = [&](u64 mn, u64 mx) {
+        wave_min_max_u64(mn, mx);
+        if (lane == 0) {
+            ends[wave] = mn;
+            ends[W + wave] = mx;
+        }
+        for (int i = tid; i < kBinSub; i += T) cur[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            mn = ends[w] < mn ? ends[w] : mn;
+            mx = ends[W + w] > mx ? ends[W + w] : mx;
+        }
+        q_min = mn;
+        for (q_shift = 0; ((mx - mn) >> q_shift) >= (u64)n_sub;) ++q_shift;
+    };
     // ranks of the ordered-by-sub-bin candidates buf[0 .. n), which are places [first, first + n) of the bin
     auto rank_write = [&](uint32_t n, uint32_t first, auto start_of, auto end_of) {
         for (uint32_t i = tid; i < n; i += T) {
@@ -363,14 +540,89 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
         }
     };
     if (!fits) {
+        // Stretch by stretch from the top, each cut by a histogram of what is left between its smallest and its largest element.  Where the
+        // highest of the 1024 bins alone is more than the LDS holds, the same inside that bin: composites are distinct, so that ends.
+        auto stretches = [&]() {
+            u64 top = ~0ull, bottom = 0ull;  // (squeezed) what is left lies below top; the stretch is looked for from bottom on
+            for (uint32_t first = 0; first < count && first < room;) {
+                __syncthreads();  // (buf and misc have been read)
+                for (int i = tid; i < kBinSub; i += T) cur[i] = 0u;
+                if (tid == 0) misc[5] = 0u;
+                u64 mn = ~0ull, mx = 0ull;
+                gather([&](u64 c, uint32_t) {
+                    const u64 q = sq(c);
+                    if (q >= bottom && q < top) {
+                        mn = q < mn ? q : mn;
+                        mx = q > mx ? q : mx;
+                    }
+                });
+                wave_min_max_u64(mn, mx);
+                if (lane == 0) {
+                    buf[wave] = mn;
+                    buf[W + wave] = mx;
+                }
+                __syncthreads();
+    #pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    mn = buf[w] < mn ? buf[w] : mn;
+                    mx = buf[W + w] > mx ? buf[W + w] : mx;
+                }
+                int shift = 0;
+                while (((mx - mn) >> shift) >= (u64)kBinSub) ++shift;
+                auto bin_at = [&](u64 q) { return (uint32_t)((q - mn) >> shift); };
+                gather([&](u64 c, uint32_t) {
+                    const u64 q = sq(c);
+                    if (q >= mn && q <= mx) atomicAdd(&cur[bin_at(q)], 1u);
+                });
+                __syncthreads();
+                row_scan(cur, misc, kBinSub, count);
+                // the lowest bin down to which LDS holds them all
+                const uint32_t all = misc[3];
+                uint32_t low = (uint32_t)kBinSub;
+                for (int b = tid; b < kBinSub; b += T)
+                    if ((b > 0 ? cur[b - 1] : all) <= (uint32_t)kBinCap) low = min(low, (uint32_t)b);
+                low = wave_min_u32(low);
+                if (lane == 0) misc[8 + wave] = low;
+                __syncthreads();
+    #pragma unroll
+                for (int w = 0; w < W; ++w) low = min(low, misc[8 + w]);
+                const uint32_t n = low < (uint32_t)kBinSub ? (low > 0u ? cur[low - 1u] : all) : 0u;
+                if (n == 0u) {  // (uniform)
+                    bottom = mn + ((u64)bin_at(mx) << shift);
+                    continue;
+                }
+                const u64 from = mn + ((u64)low << shift);
+                gather([&](u64 c, uint32_t) {
+                    const u64 q = sq(c);
+                    if (q >= from && q <= mx) buf[atomicAdd(&misc[5], 1u)] = c;
+                });
+                __syncthreads();
+                sort_words(buf, (int)n);
+                for (uint32_t i = tid; i < n && first + i < room; i += T) write_composite<ELT>(buf[i], p.out_vals, p.out_idx, out + first + i);
+                first += n;
+                top = from;
+                bottom = 0ull;
+            }
+        };
         // More than the LDS holds (a place of the row that the sample saw too little of): the pieces are read once to count and
         // then once for every stretch of sub-bins that fits.
         __syncthreads();  // (misc has been read)
         gather([&](u64 c, uint32_t) { atomicAdd(&cur[sub_of(c)], 1u); });
         __syncthreads();
         row_scan(cur, misc, n_sub, count);
-        if (misc[4] != 0u) {  // ties by the dozen: left to the last launch
-            if (tid == 0) p.rows[r].failed = 1u;
+        if (misc[4] != 0u) {
+            u64 mn = ~0ull, mx = 0ull;
+            gather([&](u64 c, uint32_t) {
+                mn = sq(c) < mn ? sq(c) : mn;
+                mx = sq(c) > mx ? sq(c) : mx;
+            });
+            narrow(mn, mx);
+            gather([&](u64 c, uint32_t) { atomicAdd(&cur[sub_of(c)], 1u); });
+            __syncthreads();
+            row_scan(cur, misc, n_sub, count);
+        }
+        if (misc[4] != 0u) {  // ties by the dozen
+            stretches();
             return;
         }
         // (a sub-bin holds kRowBinMax at most, so those that start inside a window of kBinCap - kRowBinMax places fit)
@@ -407,35 +659,32 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
         own[i] = 0ull;
         if (i * T < (int)count && tid + i * T < (int)count) own[i] = buf[tid + i * T];
     }
+    auto to_sub_bins = [&]() {
 #pragma unroll
-    for (int i = 0; i < S; ++i)
-        if (i * T < (int)count && own[i]) {
-            const uint32_t b = sub_of(own[i]);
-            at[i] = b | (atomicAdd(&cur[b], 1u) << 16);
-        }
-    __syncthreads();
-    row_scan(cur, misc, n_sub, count);
-    if (misc[4] != 0u) {
-        // many candidates in one place of the bin's range (ties): a bitonic network over the bin, the places past its
-        // end up to a power of two counting as empty - every comparison puts the larger one first (the first step of a size
-        // pairs places mirrored in their block, the others places `stride` apart), so nothing is ever moved there
-        int kp = 1;
-        while (kp < (int)count) kp <<= 1;
-        for (int size = 2; size <= kp; size <<= 1)
-            for (int stride = size >> 1; stride >= 1; stride >>= 1) {
-                for (int i = tid; i < (kp >> 1); i += T) {
-                    const int lo = ((i & ~(stride - 1)) << 1) | (i & (stride - 1));
-                    const int hi = stride == (size >> 1) ? (lo | (size - 1)) - (lo & (size - 1)) : lo + stride;
-                    if (hi < (int)count) {
-                        const u64 x = buf[lo], y = buf[hi];
-                        if (y > x) {
-                            buf[lo] = y;
-                            buf[hi] = x;
-                        }
-                    }
-                }
-                __syncthreads();
+        for (int i = 0; i < S; ++i)
+            if (i * T < (int)count && own[i]) {
+                const uint32_t b = sub_of(own[i]);
+                at[i] = b | (atomicAdd(&cur[b], 1u) << 16);
             }
+        __syncthreads();
+        row_scan(cur, misc, n_sub, count);
+        return misc[4] != 0u;
+    };
+    bool crowded = to_sub_bins();
+    if (crowded) {
+        u64 mn = ~0ull, mx = 0ull;
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+            if (own[i]) {
+                mn = sq(own[i]) < mn ? sq(own[i]) : mn;
+                mx = sq(own[i]) > mx ? sq(own[i]) : mx;
+            }
+        narrow(mn, mx);
+        crowded = to_sub_bins();
+    }
+    if (crowded) {
+        // many candidates in one place of the bin's range (ties)
+        sort_words(buf, (int)count);
         for (uint32_t i = tid; i < count && i < room; i += T) write_composite<ELT>(buf[i], p.out_vals, p.out_idx, out + i);
         return;
     }
@@ -465,10 +714,17 @@ bool plan_exact_deal(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Dea
     bins = (bins + 7) / 8 * 8;
     if (bins > kDealBinsMax) return false;
     p.bins = (int)bins;
-    // six standard deviations of the sample's count above what k of n elements make of it; the pool takes as many again
-    p.sample_rank = (int)std::ceil(expect + 6.0 * std::sqrt(expect * (1.0 - q)) + 6.0);
-    const double most = ((double)p.sample_rank + 6.0 * std::sqrt((double)p.sample_rank) + 32.0) * (double)n / kDealSample;
-    p.pool_cap = std::max<int64_t>(k, std::min<int64_t>(n, (int64_t)most));
+    // six standard deviations of the sample's count above what k of n elements make of it; up to four times that where neighbours go
+    // together (sixteen to a run: ex_sample_kernel); the pool takes as many again
+    const double sd = std::sqrt(expect * (1.0 - q));
+    p.expect = (float)expect;
+    p.sample_rank = (int)std::ceil(expect + 6.0 * sd + 6.0);
+    const double most = (expect + 48.0 * sd + 64.0) / kDealSample;
+    // the same for the sample that is sorted, four elements to a run
+    const double share = q * kSplitSample, split_sd = 2.0 * std::sqrt(share * (1.0 - q));
+    p.split_rank = std::min((int)std::ceil(share + 6.0 * split_sd + 6.0), kSplitSample);
+    const double split_most = (share + 12.0 * split_sd + 24.0) / kSplitSample;
+    p.pool_cap = std::max<int64_t>(k, std::min<int64_t>(n, (int64_t)(std::max(most, split_most) * (double)n)));
     // the sample's lower bound: 8192 of its 32768 elements, 512 in each wavefront, five deviations below the threshold
     const double part = (double)p.sample_rank / 4.0 / (kDealT / kWave);
     p.rank = std::min(512, (int)std::ceil(part + 5.0 * std::sqrt(part) + 2.0));
@@ -522,6 +778,8 @@ hipError_t launch_exact_deal(const DealPlan &pl, int64_t m, int64_t n, int64_t k
     prm.n_deal = pl.bins;
     prm.chunks = pl.chunks;
     prm.sample_rank = pl.sample_rank;
+    prm.split_rank = pl.split_rank;
+    prm.expect = pl.expect;
     const hipError_t e = dtype == ATK_F32 ? launch_deal_t<ATK_F32>(pl, prm, m, stream) : launch_deal_t<ATK_BF16>(pl, prm, m, stream);
     if (e != hipSuccess) return e;
     return launch_exact_rest_rows(m, n, k, prm.idx_bits, dtype, x, xi, prm.rows, pl.pool_cap, (u64 *)(base + pl.rest_off), prm.pool, out_vals,

@@ -155,7 +155,7 @@ struct RowRegs {
     // A lower bound: every wavefront's `rank`-th largest of the maxima of its groups - the smallest of these over the wavefronts is
     // reached by rank elements in each of them (and the largest element).  sub (1, 2, 4 or 8) groups per lane.  Where a wavefront has
     // fewer elements than that the bound is the lowest key there is.  rank 0: the smallest of the maxima.  Called by the whole workgroup; two barriers.
-    // FIRST: the groups are the lane's first eight elements, one each (the largest element then is theirs, too).
+    // FIRST: the groups are the lane's first eight elements, one each (k_max is still the largest of all).
     // SUM: not the smallest of the wavefronts' candidates but the largest that, all wavefronts together, rank maxima per wavefront reach:
     // wavefronts may be unlike each other then (masked in part, sorted).  words: 32 words of LDS.  k_up: the same with rank_up (0: none).
     template <bool FIRST = false, bool SUM = false>
@@ -255,6 +255,11 @@ struct RowRegs {
             nth(std::integral_constant<int, 4>());
         else
             nth(std::integral_constant<int, SM>());
+        if constexpr (FIRST) {
+            float most = __uint_as_float(0x7fc00000u);
+            each([&](uint32_t bits, int, int) { most = fmaxf(most, __uint_as_float(bits)); });
+            k_max = key_of(most);
+        }
         if constexpr (!SUM) {
             k_max = wave_max_u32(k_max);
             if (lane == 0) {

@@ -87,6 +87,27 @@ def test_elements_above_the_sampled_ones(n, dtype):
             _check(x.to(t), k)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(2, 200000, 30000), (1, 1 << 20, 1 << 18), (3, 9 * 16384 + 1, 1000)])
+def test_runs_of_ties_and_neighbours_that_go_together(shape, dtype):
+    """Rows that are cut between elements of the sample, bins of many ties on a short stretch of the row, bins past what LDS holds."""
+    m, n, k = shape
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    base = workloads.normal_rows(m, n, seed=n % 983)
+    stairs = (torch.arange(n) // 3000).float().repeat(m, 1)
+    lagged = torch.nn.functional.avg_pool1d(base.unsqueeze(1), 65, 1, 32).squeeze(1) * 8.0
+    spikes = torch.zeros(m, n)
+    spikes[:, 5] = 2.0
+    spikes[:, (n * 7) // 9] = 1.0
+    stripes = base.clone()
+    stripes[:, (torch.arange(n) // 4096) % 2 == 0] = float("-inf")
+    two = torch.full((m, n), 0.3)
+    two[:, n // 2: n // 2 + k // 2] = 0.7
+    for x in (torch.full((m, n), 0.3), stairs, -stairs, lagged, base.cumsum(1) / n ** 0.5, spikes, stripes, two, torch.relu(base - 1.5),
+              torch.randint(0, 3, (m, n)).float(), torch.randint(0, 1000, (m, n)).float(), base + torch.linspace(0.0, 6.0, n)):
+        _check(x.to(t).contiguous(), k, shift=n % 2)
+
+
 def test_many_long_bf16_rows():
     _check(workloads.normal_rows(64, 1 << 21, seed=11, dtype="bf16"), 1 << 19)
 
