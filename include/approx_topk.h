@@ -141,8 +141,8 @@ int atk_check_exact(int64_t m, int64_t n, int64_t k, int dtype);
 /* Largest b*k_b for which Stage 2 can run on-chip in the same launch (more candidates take further launches). */
 int64_t atk_stage2_max_candidates(void);
 
-/* Bytes of library scratch an approx_topk / approx_topk_assign / exact_topk call with these arguments uses at most
- * (0 if none, <0 = error code): rows of more than 8192 elements (candidates, in the second step of approx_topk) count with what
+/* Bytes of library scratch an approx_topk / approx_topk_assign / exact_topk call with these arguments uses at most, with x on a
+ * 16-byte boundary (exact_topk: or off it) (0 if none, <0 = error code): rows of more than 8192 elements (candidates, in the second step of approx_topk) count with what
  * the digit-by-digit path would take, which plan overrides may choose. */
 int64_t atk_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype);
 int64_t atk_workspace_bytes_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment);

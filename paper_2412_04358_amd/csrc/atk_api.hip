@@ -961,8 +961,8 @@ static int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
 // rows go one per workgroup), and the pool sizes cover every block.  The last block has fewer rows and
 // is planned on its own by run_exact(): with fewer rows it may take paths the full blocks do not (the
 // copy-out buffer, a finer sweep), so its needs are not bounded by the first block's.
-// cover: sizes that hold for the digit-by-digit path of long rows as well, which a plan override may choose (what the
-// queries of the workspace report; a call reserves what its own plan takes).
+// cover: sizes that hold for the digit-by-digit path of long rows as well, which a plan override may choose, and for x on a 16-byte boundary
+// or off it (what the queries of the workspace report; a call reserves what its own plan takes).
 static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool ptr16, ExactPlan *first, int64_t *state_bytes,
                             int64_t *data_bytes, bool cover = false) {
     int rc = make_exact_plan(m > kExactRowsPerPass ? kExactRowsPerPass : m, n, k, dtype, pairs, ptr16, first);
@@ -977,7 +977,14 @@ static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pai
         *state_bytes = std::max(*state_bytes, last.state_bytes);
         *data_bytes = std::max(*data_bytes, last.scratch_bytes);
     }
-    if (cover && n > 8192) {
+    if (cover && ptr16) {
+        ExactPlan off;
+        int64_t state_off = 0, data_off = 0;
+        rc = make_exact_plans(m, n, k, dtype, pairs, false, &off, &state_off, &data_off, true);
+        if (rc != ATK_OK) return rc;
+        *state_bytes = std::max(*state_bytes, state_off);
+        *data_bytes = std::max(*data_bytes, data_off);
+    } else if (cover && n > 8192) {
         for (int64_t rows : {std::min(m, kExactRowsPerPass), m % kExactRowsPerPass}) {
             ExactPlan digits;
             if (rows < 1 || make_exact_plan(rows, n, k, dtype, pairs, ptr16, &digits, true) != ATK_OK) continue;

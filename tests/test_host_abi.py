@@ -292,6 +292,20 @@ def test_long_queue_lane_widths(lib):
     assert atk.plan_describe(128, 65536, 16384, 2048, 8).startswith("V=2 KB=8 ")
 
 
+def test_exact_workspace_covers_rows_off_the_16_byte_boundaries(lib):
+    """x off a 16-byte boundary: a chunk more per row than the aligned plan has.  Rows of one element more are planned like
+    that, with at most a handful of bytes more per row in the parts that grow with n."""
+    for (m, n, k) in [(128, 1 << 20, 1 << 18), (3, 1 << 17, 1 << 15), (16, 1 << 18, 64)]:
+        for dt in (0, 1):
+            sizes = []
+            for length in (n, n + 1):
+                st, da = ctypes.c_int64(0), ctypes.c_int64(0)
+                assert lib.atk_exact_workspace_parts(m, length, k, dt, ctypes.byref(st), ctypes.byref(da)) == OK
+                sizes.append((st.value, da.value))
+            assert sizes[0][0] >= sizes[1][0]
+            assert sizes[0][1] >= sizes[1][1] - 32 * m - 2048
+
+
 def test_workspace_bytes(lib):
     assert lib.atk_workspace_bytes(128, 65536, 16384, 16384, 1, 0) == 0
     assert lib.atk_workspace_bytes(128, 65536, 64, 64, 1, 0) == 0  # whole buckets per workgroup: no hand-over
