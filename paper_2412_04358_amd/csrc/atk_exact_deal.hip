@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(kDealT) ex_sample_kernel(DealParams p) {
         float v_lo = __uint_as_float(bits_of_ukey(k_min));
         regs.each([&](uint32_t bits, int, int en) {
             if (__uint_as_float(bits) >= v_lo)
-                atomicAdd(&cur[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)index_at(en))], 1u);
+                atomicAdd(&cur[bins.template bin<ELT, true>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)index_at(en))], 1u);
         });
         if (tid == 0) misc[0] = misc[5] = misc[7] = 0u;
         __syncthreads();
@@ -317,7 +317,7 @@ __global__ void __launch_bounds__(kDealT) ex_deal_kernel(DealParams p) {
             }
             return first < p.n_deal ? (uint32_t)first : 0xffffu;
         }
-        return (uint32_t)tab[bins.template bin<ELT>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)];  // 0xffff: just below the threshold
+        return (uint32_t)tab[bins.template bin<ELT, true>(ukey_of_bits(bits), 0x7fffffffu - (uint32_t)idx)];  // 0xffff: just below the threshold
     };
     auto index_of = [&](int pos) { return p.xi ? p.xi[r * p.n + pos] : pos; };
     // ---- how many in each bin

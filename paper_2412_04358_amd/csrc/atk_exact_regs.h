@@ -486,7 +486,7 @@ __device__ __forceinline__ u64 row_threshold_by_digits(SWEEP sweep, uint32_t nee
 // loop is small and what RowRegs::each() unrolls is not.
 template <int ELT, typename F>
 __device__ __forceinline__ void row_vec_sweep(const RowParams &p, int64_t r, int v0, int v1, int rot, F f) {
-    constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES, U = 32 / VE;
+    constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES, U = 8 / VE;
     const int T = blockDim.x, lane = threadIdx.x & (kWave - 1), end = rot + p.n;
     const row_v4u *row = (const row_v4u *)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & ~(uintptr_t)15);
     for (int w0 = v0 + (int)threadIdx.x - lane; w0 < v1; w0 += U * T) {  // uniform over the wavefront

@@ -40,10 +40,10 @@ __device__ __forceinline__ u64 row_composite(const RowParams &p, int64_t r, int 
 }
 
 // f(composite, whether it is one) for every element of row r, whole wavefronts together
-template <int ELT, typename F>
+template <int ELT, bool XI, typename F>
 __device__ __forceinline__ void row_sweep(const RowParams &p, int64_t r, F f) {
     constexpr int ES = (ELT == ATK_F32) ? 4 : 2, VE = 16 / ES;
-    if (!p.xi) {
+    if constexpr (!XI) {
         const int rot = (int)(((uintptr_t)p.x + (uintptr_t)(r * p.n) * ES) & 15) / ES;
         row_vec_sweep<ELT>(p, r, 0, (rot + p.n + VE - 1) / VE, rot, f);
         return;
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(1024) ex_row_kernel(RowParams p) {
         if (attempt == 3 || (few ? k_min <= lo : lo <= k_min)) {
             __syncthreads();
             // (few: NaNs)
-            row_by_digits<ELT>(p, r, [&](auto f) { row_sweep<ELT>(p, r, f); }, few ? 0u : k_min, few ? 0xffffffffu : k_max, filed, cur, misc);
+            row_by_digits<ELT>(p, r, [&](auto f) { row_sweep<ELT, XI>(p, r, f); }, few ? 0u : k_min, few ? 0xffffffffu : k_max, filed, cur, misc);
             return;
         }
         k_min = lo;

@@ -37,15 +37,16 @@ struct RowBins {
         scale = s >= 4294967040.0f ? 0xffffffffu : (uint32_t)s;
         inv_scale = 4294967296.0f / (float)scale;
     }
-    // key >= k_min; inv_idx: 0x7fffffff - index.  Keys past the upper end (which is a sample's largest, say) lie in the
-    // last bin whatever their index: no bin of a composite is above that of a larger one.
-    template <int ELT>
+    // key >= k_min; inv_idx: 0x7fffffff - index.  ABOVE: keys past the upper end (which is a sample's largest, say) lie in the
+    // last bin whatever their index: no bin of a composite is above that of a larger one.  Without it there must be none (where the
+    // bins of a row's every element are worked out in unrolled code, an instruction more is 3 % of the call).
+    template <int ELT, bool ABOVE = false>
     ATK_HD uint32_t bin(uint32_t key, uint32_t inv_idx) const {
         constexpr int tz = (ELT == ATK_BF16) ? 16 : 0;
         const uint32_t off = (key - k_min) >> tz;
         uint32_t d = s_idx >= 32 ? 0u : (off << s_idx);
         d |= (inv_idx & i_mask) >> r_idx;
-        d = off > span ? 0xffffffffu : d;
+        if (ABOVE) d = off > span ? 0xffffffffu : d;
         const uint32_t b = (uint32_t)(((unsigned long long)d * scale) >> 32);
         return b < (uint32_t)n_bins ? b : (uint32_t)n_bins - 1u;
     }

@@ -80,7 +80,7 @@ __device__ __forceinline__ void insert(float (&val)[KB], int (&tt)[KB], float v,
 // double and the order of the words is the order of the doubles: a compare-exchange is v_max_f64 and v_min_f64, two
 // instructions at full rate, instead of a 64-bit compare and four selects (128 x 65536 f32, k = 16384: k_b = 16:
 // 27.5 -> 20.2 us; k_b = 8, element by element
-// before: 20.2 -> 18.5; one row of 2^20, b = 1024, k_b = 8: 132 -> 30; 64 x 2^20, k = 1024, b = 1024, k_b = 8: 140 -> 88).
+// before: 19.1 -> 17.4; one row of 2^20, b = 1024, k_b = 8: 132 -> 30; 64 x 2^20, k = 1024, b = 1024, k_b = 8: 140 -> 88).
 __device__ __forceinline__ double word_max(double a, double b) {
     double d;
     asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));  // (fmax() would quiet its operands first)

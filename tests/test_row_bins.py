@@ -17,7 +17,8 @@ static void run(uint32_t lo, uint32_t hi, int idx_bits, int n_bins, const uint32
     atk::RowBins b;
     b.set<ELT>(lo, hi, idx_bits, n_bins);
     for (int64_t i = 0; i < n; ++i) {
-        bin[i] = b.bin<ELT>(key[i], 0x7fffffffu - idx[i]);
+        bin[i] = b.bin<ELT, true>(key[i], 0x7fffffffu - idx[i]);
+        if (key[i] <= hi && b.bin<ELT>(key[i], 0x7fffffffu - idx[i]) != bin[i]) bin[i] = 0xffffffffu;
         edge[i] = b.edge<ELT>(bin[i]);
     }
 }
