@@ -287,6 +287,7 @@ template <int ELT>
 __device__ __forceinline__ void parts_hand_over(const RowParams &p, const PartsRow<ELT> &w, int part, uint32_t n_passed, uint32_t low, uint32_t k_up,
                                                 uint32_t k_max) {
     const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1);
+    __syncthreads();  // (the cursor has been read by all)
     if (tid == 0) w.misc[5] = w.misc[7] = 0u;
     __syncthreads();
     u64 *list = p.lists + (w.r * p.parts + part) * p.part_cap;
