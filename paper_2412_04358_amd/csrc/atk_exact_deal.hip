@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(kDealT) ex_sample_kernel(DealParams p) {
     const uintptr_t addr = (uintptr_t)p.x + (uintptr_t)(r * p.n) * (16 / VE);
     const int rot = (int)(addr & 15) / (16 / VE);
     const int n_vec = (rot + p.n + VE - 1) / VE - 2;  // whole vectors of the row: not the first and the last
-    const row_v4u *row = (const row_v4u *)(addr & ~(uintptr_t)15) + 1;
+    const row_v4u *row = row_vectors(p.x, r * p.n * (16 / VE)) + 1;
     // runs of four vectors, each at a place of its own inside its piece of the row; the pieces are dealt out so that every wavefront's
     // runs, and every lane's first ones, lie all over the row (masked and rising rows)
     constexpr int runs = NV * kDealT / 4, waves = kDealT / kWave;
