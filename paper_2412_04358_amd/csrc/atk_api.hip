@@ -159,6 +159,11 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     // (128 x 2^20, b = 64: 85.6 us with 1024 workgroups of 512 lanes, 80.1 with 256, 75.5 with 256
     // of 256 lanes), and every split less is a partial list less through memory.
     if (p.KB == 1) want_threads = 512 * (int64_t)kNumCU;
+    // Packed bf16 queues (5 instructions an element with two slots) come close enough to that: half the lanes again is faster on long
+    // rows with two slots (256 x 2^18, k = b = 2048: 63 -> 33 us; 128 x 2^20, b = 256: 51.5 -> 47.7) and with eight and more, where
+    // a lane that sees more rows also skips more of them (128 x 2^20, b = 128, k_b = 8: 101 -> 87; b = 64, k_b = 16:
+    // 156 -> 127); with four slots it is slower (53 -> 56).  2048 x 65536, b = 64, k_b = 2 alone lost by it (45.3 -> 46.9).
+    if (dtype == ATK_BF16 && !ov.pk_off && (p.KB == 2 || p.KB >= 8) && want_threads > 512 * (int64_t)kNumCU) want_threads = 512 * (int64_t)kNumCU;
     const bool short_rule = p.KB == 1 && p.stage2 && !ov.lm_off && !ov.ln_off && ptr16 && p.V == 16 / es && n % b == 0 &&
                             (n * es) % 16 == 0 && 2 * m <= (int64_t)kNumCU && n <= 65536 && !S_forced;
     const bool lean_shape = ptr16 && p.V == 16 / es && n % b == 0 && (n * es) % 16 == 0;  // what the lean kernels ask of the input
@@ -525,7 +530,7 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     p.S = (int)S;
     p.rows_per_split = (int)rps;
 
-    p.packed = dtype == ATK_BF16 && p.KB >= 4 && p.rows_per_split + 2 < 32768 && !ov.pk_off;
+    p.packed = dtype == ATK_BF16 && p.KB >= 2 && p.rows_per_split + 2 < 65536 && !ov.pk_off;
     // Eight unpacked slots with many lanes of the workgroup on a column, each with many matrix rows: what a lane has
     // seen alone is a poor bound on what still matters (after t rows one element in t/8 still enters its queue, and
     // with 128 lane-columns per wavefront some lane always needs the insertion), so the lanes of a column pool their

@@ -116,7 +116,7 @@ struct Plan {
     bool stage2;      // b*k_b > k
     bool direct;      // every lane owns whole buckets: write results straight from registers
     bool use_scratch; // partial lists go through global scratch + a per-row ticket
-    bool packed;      // bf16, k_b >= 3: 32-bit (key, row) queue words; needs rows_per_split + 2 < 32768
+    bool packed;      // bf16, k_b >= 2: 32-bit (key, row) queue words; needs rows_per_split + 2 < 65536
     int refresh;      // eight unpacked slots, lanes sharing columns: > 0 = the lanes of a column pool what they have seen after this many load batches (then after twice as many, ...) and raise their queues' floors to the k_b-th best of all
     bool lds_max;     // k_b = 1, no scratch, lanes share columns: they meet in LDS by atomic maximum
     bool bound_ok;    // lds_max with Stage 2: the merge yields a tight lower bound on the smallest candidate (see select_binned())

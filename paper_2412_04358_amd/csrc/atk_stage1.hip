@@ -179,44 +179,55 @@ __device__ __forceinline__ void scan_vec(float (&val)[V][KB], int (&tt)[V][KB], 
     for (int e = 0; e < V; ++e) insert<KB>(val[e], tt[e], x[e], t);
 }
 
-// ---- packed queues for bf16 with k_b >= 3 -------------------------------------------------------
-// A bf16 element and its matrix row fit one 32-bit word: [31:16] order-preserving key of the
-// value (-0 folded onto +0), [15:1] 0x7fff - (row - first row of this lane's split), [0] "was -0".
-// Larger word <=> larger value, or equal value and earlier row, so inserting into a descending
-// list is one median-of-three per slot instead of compares and selects on two arrays (measured
-// faster from four slots on; with two the conversion costs what it saves).  0 = empty.
-__device__ __forceinline__ uint32_t pack_bf16(uint32_t xb, uint32_t tl) {  // xb: the bf16 in the high half
-    const uint32_t sgn = (uint32_t)((int32_t)xb >> 31);
-    const uint32_t key = xb ^ ((sgn & 0x7fff0000u) | 0x80000000u);
-    return (xb == 0x80000000u) ? (0x80000001u | tl) : (key | tl);
+// ---- packed queues for bf16 with k_b >= 2 -------------------------------------------------------
+// A bf16 element and its matrix row fit one signed 32-bit word: [31:16] the value's sign and magnitude as a two's complement
+// number (so -0 is +0), [15:0] 0xffff - (row - first row of this lane's split).  Larger word <=> larger value, or
+// equal value and earlier row, so inserting into a descending list is one median-of-three per slot instead of compares and
+// selects on two arrays.  Two elements are converted together, by three packed 16-bit operations, and one more each puts the row
+// beside it.  Which zeros were -0 is looked up in the row at the end, if any is left in a queue.  INT_MIN = empty (no
+// magnitude is 0x8000).  Unpacked queues of two slots take 10.4 instructions per element, which the SIMDs issued in 79 % of their
+// cycles on 128 x 2653751; these take 5 and leave such rows to memory: 136 -> 128 us (5.3 TB/s; k_b = 1: 112), 1024 x 131072,
+// b = 512: 56 -> 48.  (A conversion element by element that carried "was -0" in the word took 6 more per element: no gain at two slots.)
+constexpr int32_t kEmptyPk = (int32_t)0x80000000u;
+typedef int16_t pk2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_keys(uint32_t w) {  // two elements
+    const pk2 v = __builtin_bit_cast(pk2, w);
+    const pk2 sgn = v >> 15;
+    const uint32_t m = (w & 0x7fff7fffu) ^ __builtin_bit_cast(uint32_t, sgn);
+    return __builtin_bit_cast(uint32_t, (pk2)(__builtin_bit_cast(pk2, m) - sgn));
 }
-__device__ __forceinline__ void unpack_bf16(uint32_t c, int t_first, float &v, int &t) {
-    if (c == 0u) {
-        v = __uint_as_float(0x7fc00000u);
-        t = kEmptyT;
-        return;
-    }
-    const uint32_t key = c >> 16;
-    uint32_t bits = (key & 0x8000u) ? (key ^ 0x8000u) : (~key & 0xffffu);
-    if (c & 1u) bits = 0x8000u;
-    v = __uint_as_float(bits << 16);
-    t = t_first + 0x7fff - (int)((c >> 1) & 0x7fffu);
+__device__ __forceinline__ int32_t pack_bf16(uint32_t xb, uint32_t code) {  // xb: the bf16 in the high half
+    return (int32_t)((pack_keys(xb) & 0xffff0000u) | code);
 }
-__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
+__device__ __forceinline__ void unpack_bf16(int32_t c, int t_first, float &v, int &t) {
+    const uint32_t key = (uint32_t)c & 0xffff0000u;
+    const uint32_t bits = c < 0 ? ((0u - key) | 0x80000000u) : key;
+    v = __uint_as_float(c == kEmptyPk ? 0x7fc00000u : bits);
+    t = c == kEmptyPk ? kEmptyT : t_first + 0xffff - (int)((uint32_t)c & 0xffffu);
+}
+__device__ __forceinline__ int32_t med3(int32_t a, int32_t b, int32_t c) {
     return max(min(a, b), min(max(a, b), c));
 }
 template <int KB>
-__device__ __forceinline__ void insert_pk(uint32_t (&q)[KB], uint32_t c) {
+__device__ __forceinline__ void insert_pk(int32_t (&q)[KB], int32_t c) {
 #pragma unroll
-    for (int j = KB - 1; j >= 1; --j) q[j] = umed3(q[j - 1], q[j], c);  // q[j-1] >= q[j]: c clamped between them
+    for (int j = KB - 1; j >= 1; --j) q[j] = med3(q[j - 1], q[j], c);  // q[j-1] >= q[j]: c clamped between them
     q[0] = max(q[0], c);
 }
 template <int ELT, int V, int KB>
-__device__ __forceinline__ void scan_vec_pk(uint32_t (&q)[V][KB], const RowVec<ELT, V> &v, int t_local) {
-    const uint32_t tl = (uint32_t)(0x7fff - t_local) << 1;
-    uint32_t c[V];
+__device__ __forceinline__ void scan_vec_pk(int32_t (&q)[V][KB], const RowVec<ELT, V> &v, int t_local) {
+    const uint32_t code = (uint32_t)(0xffff - t_local);
+    int32_t c[V];
+    if constexpr (V == 1) {
+        c[0] = pack_bf16(v.w[0] << 16, code);
+    } else {
 #pragma unroll
-    for (int e = 0; e < V; ++e) c[e] = pack_bf16(elem_bits<ELT, V>(v, e), tl);
+        for (int w = 0; w < V / 2; ++w) {
+            const uint32_t keys = pack_keys(v.w[w]);
+            c[2 * w] = (int32_t)((keys << 16) | code);
+            c[2 * w + 1] = (int32_t)((keys & 0xffff0000u) | code);
+        }
+    }
     if (KB >= 8) {  // the insertion is cheap: only long queues are worth a wavefront-uniform skip
         bool any = false;
 #pragma unroll
@@ -389,7 +400,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     extern __shared__ __align__(16) unsigned char smem[];
     trace_mark<TR>(p.trace, 0);  // the wavefront has started
     constexpr int ES = (ELT == ATK_F32) ? 4 : 2;
-    constexpr bool PK = PKF && ELT == ATK_BF16 && KB >= 4;  // packed 32-bit queues (host: rows per split < 32766)
+    constexpr bool PK = PKF && ELT == ATK_BF16 && KB >= 2;  // packed 32-bit queues (host: rows per split < 65534)
     // queues of distinct 64-bit words, fed k_b matrix rows at a time (the pooled floors work on the other form)
     constexpr bool BATCH = KB >= 8 && !PK && !RF;
     const int tid = threadIdx.x, T = blockDim.x;
@@ -435,7 +446,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
 
     float val[V][KB];
     int tt[V][KB];
-    uint32_t pk[PK ? V : 1][PK ? KB : 1];
+    int32_t pk[PK ? V : 1][PK ? KB : 1];
     double qw[BATCH ? V : 1][BATCH ? KB : 1];  // BATCH: the queues, as row words
     float last_f[BATCH ? V : 1];            // ... and the value of each queue's last slot (NaN while it is empty)
 #pragma unroll
@@ -444,7 +455,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
         for (int j = 0; j < KB; ++j) {
             val[e][j] = __uint_as_float(0x7fc00000u);
             tt[e][j] = kEmptyT;
-            if constexpr (PK) pk[e][j] = 0u;
+            if constexpr (PK) pk[e][j] = kEmptyPk;
             if constexpr (BATCH) {
                 qw[e][j] = 0.0;
                 last_f[e] = __uint_as_float(0x7fc00000u);
@@ -453,7 +464,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
 #define ATK_FEED_ELEM(e, xb, row)                                                                    \
     do {                                                                                             \
         if constexpr (PK)                                                                            \
-            insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0x7fff - ((row) - t0)) << 1));             \
+            insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - ((row) - t0))));                  \
         else if constexpr (BATCH)                                                                    \
             insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - t0 - ph) / p.P)));                                             \
         else                                                                                         \
@@ -758,10 +769,27 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
             }
     }
     if constexpr (PK) {
+        bool zero = false;
 #pragma unroll
         for (int e = 0; e < V; ++e)
 #pragma unroll
-            for (int j = 0; j < KB; ++j) unpack_bf16(pk[e][j], t0, val[e][j], tt[e][j]);
+            for (int j = 0; j < KB; ++j) {
+                unpack_bf16(pk[e][j], t0, val[e][j], tt[e][j]);
+                zero = zero || __float_as_uint(val[e][j]) == 0u;
+            }
+        if (__ballot(zero) != 0ull) {  // +0 or -0: the element itself says (a column's loads in flight together)
+            const uint16_t *row = (const uint16_t *)p.x + (int64_t)r * p.n;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                uint32_t own[KB];
+#pragma unroll
+                for (int j = 0; j < KB; ++j)
+                    own[j] = row[__float_as_uint(val[e][j]) == 0u ? (int64_t)tt[e][j] * p.b + col0 + e - rot : 0];
+#pragma unroll
+                for (int j = 0; j < KB; ++j)
+                    if (__float_as_uint(val[e][j]) == 0u) val[e][j] = __uint_as_float(own[j] << 16);
+            }
+        }
     }
 
     // ---------------------------------------------------------------- every lane owns whole buckets
@@ -1145,13 +1173,20 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// Matrix rows whose loads a lane with packed queues has in flight, for V columns: 128 bytes' worth of registers at most.  The
+// instances' own batches are about unpacked queues and smaller ones left the lanes waiting (128 x 65536, k = 16384, b = 1024,
+// k_b = 16: two rows 24.8 us, eight 15.6, sixteen 14.2; 128 x 2^20, b = 64, k_b = 16: 247, 173, 157).
+constexpr int packed_batch(int V) { return V == 8 ? 4 : 16; }
+
 template <int ELT, int V, int KB, int U>
 static hipError_t launch_one(const Plan &pl, const S1Params &prm, hipStream_t stream) {
     constexpr int MAXT = max_threads_for_kb(KB);
     if (pl.T > MAXT) return hipErrorInvalidValue;
-    if constexpr (ELT == ATK_BF16 && KB >= 4) {
+    if constexpr (ELT == ATK_BF16 && KB >= 2) {
         if (pl.packed) {
-            hipLaunchKernelGGL((stage1_kernel<ELT, V, KB, U, MAXT, true>), dim3((unsigned)pl.grid),
+            // (packed queues leave registers for more loads in flight than the instance's U, which is about the unpacked ones)
+            constexpr int UP = packed_batch(V);
+            hipLaunchKernelGGL((stage1_kernel<ELT, V, KB, UP, MAXT, true>), dim3((unsigned)pl.grid),
                                dim3((unsigned)pl.T), (size_t)pl.lds_bytes, stream, prm);
             return hipGetLastError();
         }
