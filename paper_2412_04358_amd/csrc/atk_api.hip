@@ -534,12 +534,14 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     // Eight unpacked slots with many lanes of the workgroup on a column, each with many matrix rows: what a lane has
     // seen alone is a poor bound on what still matters (after t rows one element in t/8 still enters its queue, and
     // with 128 lane-columns per wavefront some lane always needs the insertion), so the lanes of a column pool their
-    // queues - after 8 load batches, then 16, 32, ... - and raise their floors to the eighth best of all.  Measured on
-    // 128 x 2^20 f32, k_b = 8: b = 8 (64 lanes a column) 162 -> 116 us, b = 16 (32 lanes) 163 -> 129, b = 32 (16 lanes)
-    // 164 -> 151; with 8 lanes a column or fewer, or under 256 rows a lane, the pooling costs more than it saves.
+    // queues - after 16 matrix rows of each lane (8 pairs of them), then four times as many, ... - and raise their floors to the eighth best of all.  Measured on
+    // 128 x 2^20 f32, k = 64, k_b = 8, without and with: b = 8 (64 lanes a column) 129 -> 100 us, b = 64 (16 lanes) 132 -> 112,
+    // b = 128 133 -> 115, b = 512 (8 lanes) 136 -> 117; 2048 x 65536, b = 16 (8 lanes, 512 rows each) 154 -> 114; 512 x 65536, b = 16 (32 lanes,
+    // 128 rows) 45.5 -> 42.8.  With fewer lanes a column or rows a lane the pooling costs what it saves or more (2048 x 65536, b = 64, 8 lanes,
+    // 128 rows: 125 -> 143; 128 x 2^18, b = 64, 16 lanes, 128 rows: 48.4 -> 50.2; 512 x 131072, b = 128, 4 lanes, 256 rows: 81 -> 91).
     p.refresh = 0;
     if (p.KB == 8 && !p.packed && n % p.V == 0 && ov.rf >= 0 && p.P > 1 &&
-        (ov.rf > 0 || (p.P >= 16 && p.rows_per_split / p.P >= 256)))
+        (ov.rf > 0 || (p.P >= 8 && p.rows_per_split / p.P >= (p.P >= 32 ? 128 : 256))))
         p.refresh = ov.rf > 0 ? ov.rf : 8;
     p.tail_tpc = tail_lanes_per_column(p.stage2 ? b : std::min<int64_t>(b, (int64_t)p.Gw * p.V), p.T, p.KB, p.S);
     p.direct = (p.P == 1 && p.S == 1 && !p.stage2 && helpers == 0);

@@ -48,7 +48,7 @@ struct S1Params {
     int NB;              // short buckets: buckets a lane group takes in turn (0: one bucket per group)
     int lds_max;         // k_b = 1, no scratch: the lanes' running maxima meet in LDS by atomic maximum (see the kernel)
     int bound_ok;        // ... and the lower bound on the smallest candidate that comes with that merge is tight enough for select_binned()
-    int refresh;         // eight unpacked slots: the lanes of a column pool their queues' floors after this many load batches, then twice as many, ... (0: never)
+    int refresh;         // eight unpacked slots: the lanes of a column pool their queues' floors after this many pairs of matrix rows, then four times as many, ... (0: never)
     u64 *trace;          // measurement build only: phase timestamps, [workgroup][wavefront][phase]
 };
 
@@ -136,6 +136,47 @@ __device__ __forceinline__ void insert_word(double (&q)[N], double c) {
     q[0] = word_max(q[0], c);
 }
 
+// ---- queues that elements enter rarely (pooled floors) ----------------------------------------------------------------
+// A queue of words (as above, numbered by matrix row) and one element that waits for it: an element that beats `last` - a comparison, and
+// two selects where any lane of the wavefront has one - is put by, and only where a lane has one already do all lanes work theirs
+// into the queues, some thirty instructions; with 64 lanes that is about one time in ten.  Where a queue of values and rows took its elements
+// one by one, the 40 instructions that some lane needed two times in three bounded these rows (82 % of the SIMDs' cycles): 128 x 2^20, k = 64,
+// b = 128, k_b = 8: 133 -> 115 us; 2048 x 65536, b = 8: 110 -> 97.  `last` may lag behind the queue
+// (what waits has not raised it yet), which lets an element too many through and never one too few; the words put them in order.
+template <int KB>
+struct LazyQueue {
+    double q[KB];
+    float last;     // an element has to beat it: the value in the last slot, or a floor above that (NaN: anything enters)
+    uint32_t wait;  // the waiting element,
+    int wait_t;     // and its number (kEmptyT: none)
+    u64 waiting;    // lanes that have one
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int j = 0; j < KB; ++j) q[j] = 0.0;
+        last = __uint_as_float(0x7fc00000u);
+        wait = 0u;
+        wait_t = kEmptyT;
+        waiting = 0ull;
+    }
+    __device__ __forceinline__ void flush() {
+        const double c = row_word(wait, (uint32_t)wait_t);
+        insert_word<KB>(q, wait_t != kEmptyT ? c : 0.0);
+        wait_t = kEmptyT;
+        waiting = 0ull;
+        const uint32_t key = (uint32_t)((u64)__double_as_longlong(q[KB - 1]) >> 31);
+        last = fmaxf(last, __uint_as_float(bits_of_ukey(key)));  // (empty: the key 0 stands for a NaN, and `last` stays)
+    }
+    __device__ __forceinline__ void feed(uint32_t bits, int t) {
+        const bool in = !(__uint_as_float(bits) <= last);
+        const u64 m = __ballot(in);
+        if (m == 0ull) return;  // uniform over the wavefront
+        if ((m & waiting) != 0ull) flush();
+        waiting |= m;
+        wait = in ? bits : wait;
+        wait_t = in ? t : wait_t;
+    }
+};
+
 // mine <- the N largest of (mine U theirs), as multisets; both sorted descending, result sorted descending.
 template <int N>
 __device__ __forceinline__ void merge_keys(uint32_t (&mine)[N], const uint32_t (&theirs)[N]) {
@@ -156,19 +197,11 @@ __device__ __forceinline__ void merge_keys(uint32_t (&mine)[N], const uint32_t (
 // about 5*k_b lane operations per element, so it is skipped whenever no lane of the wavefront
 // holds an element that beats the last slot of its queue (one compare per element and a
 // wavefront-uniform branch): on long buckets almost every load is rejected that way.
-template <int ELT, int V, int KB, bool PER_COLUMN = false>
+template <int ELT, int V, int KB>
 __device__ __forceinline__ void scan_vec(float (&val)[V][KB], int (&tt)[V][KB], const RowVec<ELT, V> &v, int t) {
     float x[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) x[e] = __uint_as_float(elem_bits<ELT, V>(v, e));
-    if constexpr (PER_COLUMN) {
-        // where insertions are rare (pooled floors) the test is made per column: a wavefront that needs the insertion
-        // for one of its columns does not pay for the others
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (__ballot(!(x[e] <= val[e][KB - 1])) != 0ull) insert<KB>(val[e], tt[e], x[e], t);
-        return;
-    }
     if (KB > 1) {
         bool any = false;
 #pragma unroll
@@ -449,6 +482,11 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     int32_t pk[PK ? V : 1][PK ? KB : 1];
     double qw[BATCH ? V : 1][BATCH ? KB : 1];  // BATCH: the queues, as row words
     float last_f[BATCH ? V : 1];            // ... and the value of each queue's last slot (NaN while it is empty)
+    LazyQueue<KB> lazy[RF ? V : 1];
+    if constexpr (RF) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) lazy[e].clear();
+    }
 #pragma unroll
     for (int e = 0; e < V; ++e)
 #pragma unroll
@@ -465,6 +503,8 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     do {                                                                                             \
         if constexpr (PK)                                                                            \
             insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - ((row) - t0))));                  \
+        else if constexpr (RF)                                                                       \
+            lazy[e].feed(xb, (row) - t0);                                                            \
         else if constexpr (BATCH)                                                                    \
             insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - t0 - ph) / p.P)));                                             \
         else                                                                                         \
@@ -474,23 +514,24 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     do {                                                                                             \
         if constexpr (PK)                                                                            \
             scan_vec_pk<ELT, V, KB>(pk, vec, (row) - t0);                                            \
-        else if constexpr (BATCH) {                                                                  \
+        else if constexpr (BATCH || RF) {                                                            \
             _Pragma("unroll") for (int e_ = 0; e_ < V; ++e_) ATK_FEED_ELEM(e_, (elem_bits<ELT, V>(vec, e_)), (row)); \
         } else                                                                                       \
-            scan_vec<ELT, V, KB, RF>(val, tt, vec, (row));                                           \
+            scan_vec<ELT, V, KB>(val, tt, vec, (row));                                               \
     } while (0)
 
     // ---------------------------------------------------------------- pooled floors (instances of their own: RF)
     // Eight unpacked slots, several lanes of the workgroup on a column, many matrix rows per lane, rows that start on a
     // load boundary (rot = 0; the host sees to all of it).  What a lane has seen alone is a poor bound on what still
     // matters: after t rows one element in t/8 still enters its queue, and with 128 lane-columns per wavefront some
-    // lane always needs the insertion.  So after `stop` load batches - the same number in every lane, and every lane
+    // lane always needs the insertion.  So after `stop` load batches of U matrix rows - the same number in every lane, and every lane
     // has at least that many - the lanes of a column pool what they hold: between them they have seen all elements of
     // a stretch of the row; the eighth best of that stretch bounds the column's final eighth best from below, and every
-    // element still to come has a higher index than all of the stretch, so it has to beat that value outright.  Slots
-    // below it, and empty ones, are set to it and marked empty.  The lanes pool their queues' value keys: a butterfly
+    // element still to come has a higher index than all of the stretch, so it has to beat that value outright.
+    // The lanes pool their queues' value keys: a butterfly
     // inside the wavefront where lanes of a column sit side by side, then through the exchange area in LDS (free
-    // until the lists are merged at the end).  Again after twice as many batches, and so on.
+    // until the lists are merged at the end).  Again after four times as many batches, and so on: as elements wait for the queues, a
+    // floor that lags costs little (128 x 2^20, b = 128: 116 us with twice as many each time).
     int t_resume = t0 + ph;  // the lane's next matrix row
     if constexpr (RF) {
         static_assert(!RF || (KB == 8 && !PKF), "pooled floors: eight unpacked slots");
@@ -498,36 +539,34 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
         const int64_t row_bytes = (int64_t)p.b * ES;
         const int step = p.P;
         const int nfull = ((t1 - t0) / p.P) / U;  // full batches that every row phase has
-        int done = 0;
-        for (int stop = p.refresh; stop > 0 && stop < nfull; stop *= 2) {
+        // (the next batch's loads are issued before the current one is worked on, and before the lanes meet)
+        int stop = max(1, 2 * p.refresh / U);
+        RowVec<ELT, V> v[U], w[U];
+        auto load = [&](RowVec<ELT, V> (&to)[U], int t) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) to[u] = load_vec<ELT, V>(base + (int64_t)(t + u * step) * row_bytes);
+        };
+        if (active && nfull > 0) load(v, t_resume);
+        for (int i = 1; i <= nfull; ++i) {
             if (active) {
-                // the batches up to the stop; the next batch's loads are issued before the current one is worked on
-                const int nb = stop - done;
-                int t = t_resume;
-                RowVec<ELT, V> v[U], w[U];
+                const int t = t_resume;
+                t_resume = t + U * step;
+                if (i < nfull) load(w, t_resume);
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = load_vec<ELT, V>(base + (int64_t)(t + u * step) * row_bytes);
-                for (int i = 0; i < nb; ++i) {
-                    const int tn = t + U * step;
-                    if (i + 1 < nb) {
+                for (int u = 0; u < U; ++u) ATK_FEED_VEC(v[u], t + u * step);
 #pragma unroll
-                        for (int u = 0; u < U; ++u) w[u] = load_vec<ELT, V>(base + (int64_t)(tn + u * step) * row_bytes);
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) ATK_FEED_VEC(v[u], t + u * step);
-#pragma unroll
-                    for (int u = 0; u < U; ++u) v[u] = w[u];
-                    t = tn;
-                }
-                t_resume = t;
+                for (int u = 0; u < U; ++u) v[u] = w[u];
             }
-            done = stop;
+            if (i != stop || i == nfull) continue;  // uniform
+            stop *= 4;
             uint32_t keys[V][KB];
+#pragma unroll
+            for (int e = 0; e < V; ++e) lazy[e].flush();
 #pragma unroll
             for (int e = 0; e < V; ++e)
 #pragma unroll
                 for (int j = 0; j < KB; ++j)
-                    keys[e][j] = (active && tt[e][j] != kEmptyT) ? ukey_of_bits(__float_as_uint(val[e][j])) : 0u;
+                    keys[e][j] = (uint32_t)((u64)__double_as_longlong(lazy[e].q[j]) >> 31);
             if (p.wave_merge) {
                 for (int off = p.Gw; off < kWave; off <<= 1) {
 #pragma unroll
@@ -570,15 +609,8 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
                     const uint32_t fk = keys[e][KB - 1];
-                    if (fk != 0u) {  // eight elements of the column have been seen
-                        const float floor_v = __uint_as_float(bits_of_ukey(fk));
-#pragma unroll
-                        for (int j = 0; j < KB; ++j)
-                            if (tt[e][j] == kEmptyT || val[e][j] < floor_v) {
-                                val[e][j] = floor_v;
-                                tt[e][j] = kEmptyT;
-                            }
-                    }
+                    if (fk != 0u)  // eight elements of the column have been seen
+                        lazy[e].last = fmaxf(lazy[e].last, __uint_as_float(bits_of_ukey(fk)));
                 }
             }
         }
@@ -767,6 +799,20 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
                     tt[e][j] = t0 + ph + (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu)) * p.P;
                 }
             }
+    }
+    if constexpr (RF) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            lazy[e].flush();
+#pragma unroll
+            for (int j = 0; j < KB; ++j) {
+                const u64 c = (u64)__double_as_longlong(lazy[e].q[j]);
+                if (c != 0ull) {
+                    val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 31)));
+                    tt[e][j] = t0 + (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu));
+                }
+            }
+        }
     }
     if constexpr (PK) {
         bool zero = false;
@@ -1194,7 +1240,8 @@ static hipError_t launch_one(const Plan &pl, const S1Params &prm, hipStream_t st
     if (prm.trace) return hipErrorNotSupported;  // the measurement build exists for the lean kernels only
     if constexpr (KB == 8) {
         if (pl.refresh) {
-            hipLaunchKernelGGL((stage1_kernel<ELT, V, KB, U, MAXT, false, false, true>), dim3((unsigned)pl.grid),
+            constexpr int UF = 8;  // matrix rows in flight: with the instance's four 128 x 2^20, b = 128 takes 118 us and not 115, 512 x 2^18, b = 32 142 and not 111
+            hipLaunchKernelGGL((stage1_kernel<ELT, V, KB, UF, MAXT, false, false, true>), dim3((unsigned)pl.grid),
                                dim3((unsigned)pl.T), (size_t)pl.lds_bytes, stream, prm);
             return hipGetLastError();
         }
