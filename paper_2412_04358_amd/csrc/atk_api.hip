@@ -397,6 +397,17 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     return S;
     };
     int64_t S = row_splits();
+    // Eight slots and more in f32 over wide bucket layouts, a lane to a column group, on rows that would be split: four lanes of
+    // the workgroup on a column group meet in LDS, where the splits' lists (half of the survivors and more, once per split) would go through memory to
+    // one workgroup per column block.  f32, k = 1024, b = 1024, k_b = 8: 128 x 2^20 246 us in four splits, 133 with four lanes;
+    // 128 x 2^18 99 -> 53, 256 x 2^18 173 -> 88, 256 x 500000, b = 1000: 227 -> 144; k_b = 16: 128 x 2^20 288 -> 222, 64 x 2^20, k = 4096:
+    // 230 -> 128.  (Two lanes: 165, 58, 87, 143, 213, 163; eight: 135, 57, 92, 152, 246, 140.)
+    // With more matrix rows than 128 to a slot the splits are level or better (64 x 2^21, k = 2048, b = 1024, k_b = 8: 147 -> 153).
+    if (dtype == ATK_F32 && p.KB >= 8 && p.P == 1 && S > 1 && p.L >= 16 * (int64_t)p.KB && p.L <= 128 * (int64_t)p.KB && !T_forced && !P_forced && !S_forced) {
+        layout(4);
+        if (lds > kLdsBudget) return ATK_ERR_UNSUPPORTED;
+        S = row_splits();
+    }
     // Many rows with few column groups came out above with workgroups of one or two wavefronts (a lane per column group
     // fills the chip) and may still get row splits on top - through scratch and a ticket, between workgroups of 64
     // lanes.  Bigger workgroups whose lanes share the columns do the same without memory in between (2048 x 16384 bf16,
