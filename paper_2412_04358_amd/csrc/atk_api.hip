@@ -28,6 +28,8 @@ static int64_t pow2_ceil(int64_t v) {
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+constexpr int64_t kLongRow = 1ll << 30;  // matrix rows (contiguous buckets: loads) from which on Stage 1 always splits
+
 // ------------------------------------------------------------------------------------ checks
 static int check_common(int64_t m, int64_t n, int64_t k, int dtype) {
     if (dtype != ATK_F32 && dtype != ATK_BF16) return ATK_ERR_DTYPE;
@@ -523,6 +525,8 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     }
     if (multi_ok && ov.mh > 0) S = ov.mh + 1;  // (sweeps and tests; clamped like any other count below)
     if (S_forced) S = S_forced;
+    // (a lane's scan looks ahead of its split's end in 32 bits, and queue words count 2^30 rows)
+    if (p.L >= kLongRow && S < 4) S = 4;
     if (S > p.L / p.P) S = p.L / p.P;
     if (S < 1) S = 1;
     int64_t rps = ceil_div(p.L, S);
@@ -728,6 +732,7 @@ int make_contig_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, in
         if (S > s_loads) S = s_loads;
     }
     if (S_forced && p.Gs == T) S = S_forced;
+    if (chunks >= kLongRow && S < 4) S = 4;  // (only one bucket is that long, and a whole workgroup's: Gs = T)
     if (S > chunks) S = chunks;
     if (S < 1) S = 1;
     int64_t cps = ceil_div(chunks, S);

@@ -456,7 +456,9 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     int eph = p.extra_ph + (carry ? 1 : 0);     // the row phase that takes the ragged row
     if (eph >= p.P) eph -= p.P;
     const int t0 = sp * p.rows_per_split;
-    const int t1 = (sp == p.S - 1) ? Lr : min(Lr, t0 + p.rows_per_split);
+    // Matrix rows are numbered from the split's first one, t0: rows of the whole matrix go up to 2^31 - 1 with one bucket, and the
+    // scans below look up to 2^15 rows past the last one (the host keeps splits under 2^30 rows).
+    const int t1 = (sp == p.S - 1) ? Lr - t0 : min(Lr - t0, p.rows_per_split);
     auto bucket_of = [&](int c) { return c - rot + (c < rot ? p.b : 0); };
 
     // One slot per bucket, no hand-over through memory: the lanes that share a column meet in LDS by
@@ -502,22 +504,22 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
 #define ATK_FEED_ELEM(e, xb, row)                                                                    \
     do {                                                                                             \
         if constexpr (PK)                                                                            \
-            insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - ((row) - t0))));                  \
+            insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - (row))));                         \
         else if constexpr (RF)                                                                       \
-            lazy[e].feed(xb, (row) - t0);                                                            \
+            lazy[e].feed(xb, (row));                                                                 \
         else if constexpr (BATCH)                                                                    \
-            insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - t0 - ph) / p.P)));                                             \
+            insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - ph) / p.P)));                    \
         else                                                                                         \
-            insert<KB>(val[e], tt[e], __uint_as_float(xb), (row));                                   \
+            insert<KB>(val[e], tt[e], __uint_as_float(xb), t0 + (row));                              \
     } while (0)
 #define ATK_FEED_VEC(vec, row)                                                                       \
     do {                                                                                             \
         if constexpr (PK)                                                                            \
-            scan_vec_pk<ELT, V, KB>(pk, vec, (row) - t0);                                            \
+            scan_vec_pk<ELT, V, KB>(pk, vec, (row));                                                 \
         else if constexpr (BATCH || RF) {                                                            \
             _Pragma("unroll") for (int e_ = 0; e_ < V; ++e_) ATK_FEED_ELEM(e_, (elem_bits<ELT, V>(vec, e_)), (row)); \
         } else                                                                                       \
-            scan_vec<ELT, V, KB>(val, tt, vec, (row));                                               \
+            scan_vec<ELT, V, KB>(val, tt, vec, t0 + (row));                                          \
     } while (0)
 
     // ---------------------------------------------------------------- pooled floors (instances of their own: RF)
@@ -532,13 +534,13 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     // inside the wavefront where lanes of a column sit side by side, then through the exchange area in LDS (free
     // until the lists are merged at the end).  Again after four times as many batches, and so on: as elements wait for the queues, a
     // floor that lags costs little (128 x 2^20, b = 128: 116 us with twice as many each time).
-    int t_resume = t0 + ph;  // the lane's next matrix row
+    const int64_t row_bytes = (int64_t)p.b * ES;
+    const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n - rot + (int64_t)col0) * ES + t0 * row_bytes;
+    int t_resume = ph;  // the lane's next matrix row
     if constexpr (RF) {
         static_assert(!RF || (KB == 8 && !PKF), "pooled floors: eight unpacked slots");
-        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n + (int64_t)col0) * ES;
-        const int64_t row_bytes = (int64_t)p.b * ES;
         const int step = p.P;
-        const int nfull = ((t1 - t0) / p.P) / U;  // full batches that every row phase has
+        const int nfull = (t1 / p.P) / U;  // full batches that every row phase has
         // (the next batch's loads are issued before the current one is worked on, and before the lanes meet)
         int stop = max(1, 2 * p.refresh / U);
         RowVec<ELT, V> v[U], w[U];
@@ -618,11 +620,9 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
 
     // ---------------------------------------------------------------- streaming scan
     if (active) {
-        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n - rot + (int64_t)col0) * ES;
-        const int64_t row_bytes = (int64_t)p.b * ES;
         const int step = p.P;
         int t = t_resume;
-        if (V > 1 && rot > 0 && cg == 0 && t == 0 && t < t1) {
+        if (V > 1 && rot > 0 && cg == 0 && sp == 0 && t == 0 && t < t1) {
             // the head of the virtual row: its first `rot` elements are not this row's
             RowVec<ELT, V> v = load_vec<ELT, V>(base);
 #pragma unroll
@@ -637,7 +637,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
             // 64 rows 13.4 -> 12.5; 128 x 2^20, b = 1024: 138 -> 130.
             constexpr int D = KB == 8 ? 2 : 1;  // batches ahead
             RowVec<ELT, V> v[KB], w[D][KB];
-            uint32_t seq = (uint32_t)((t - t0 - ph) / step);  // number of the batch's first row among the lane's
+            uint32_t seq = (uint32_t)((t - ph) / step);  // number of the batch's first row among the lane's
             bool have = t < t1;
             auto fetch = [&](RowVec<ELT, V> (&to)[KB], int tb) {
 #pragma unroll
@@ -774,16 +774,16 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
         // first `remr` columns (the short buckets of Figure 2).  It has the highest indices, so
         // it is fed last.
         if (remr > 0 && sp == p.S - 1 && ph == eph && col0 < remr) {
-            const unsigned char *last = base + (int64_t)Lr * row_bytes;
+            const unsigned char *last = base + (int64_t)t1 * row_bytes;
             if (col0 + V <= remr) {
                 RowVec<ELT, V> v = load_vec<ELT, V>(last);
-                ATK_FEED_VEC(v, Lr);
+                ATK_FEED_VEC(v, t1);
             } else {
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     if (col0 + e < remr) {
                         RowVec<ELT, 1> one = load_vec<ELT, 1>(last + e * ES);
-                        ATK_FEED_ELEM(e, (elem_bits<ELT, 1>(one, 0)), Lr);
+                        ATK_FEED_ELEM(e, (elem_bits<ELT, 1>(one, 0)), t1);
                     }
             }
         }
@@ -1143,8 +1143,8 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
     if (active) {
         const int chunks = (int)((run1 - run0) / V);
         const int c0 = sp * p.chunks_per_split;
-        const int c1 = min(chunks, c0 + p.chunks_per_split);
-        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n + run0) * ES;
+        const int c1 = min(chunks - c0, p.chunks_per_split);  // (chunks are numbered from the split's first: c0 + 2^14 may lie past 2^31)
+        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n + run0 + (int64_t)c0 * V) * ES;
         auto feed = [&](const RowVec<ELT, V> &v, int c) {
             float x[V];
 #pragma unroll
@@ -1156,9 +1156,9 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
                 if (__ballot(any) == 0ull) return;
             }
 #pragma unroll
-            for (int e = 0; e < V; ++e) insert<KB>(val, tt, x[e], c * V + e);
+            for (int e = 0; e < V; ++e) insert<KB>(val, tt, x[e], (c0 + c) * V + e);
         };
-        int c = c0 + q;
+        int c = q;
         for (; c + (U - 1) * p.Gs < c1; c += U * p.Gs) {
             RowVec<ELT, V> v[U];
 #pragma unroll

@@ -285,6 +285,20 @@ def test_plan_override(lib, plan_override):
     assert q["T"] in (256, 512)
 
 
+def test_longest_rows_are_split(lib, plan_override):
+    """Lanes look ahead of their split's end in 32 bits, up to 2^15 rows, and queue words number 2^30 rows: no split may come near either."""
+    for spec in (None, "S=1", "S=3,T=64"):
+        plan_override(spec)
+        for dt in (atk.ATK_F32, atk.ATK_BF16):
+            for n in (1 << 30, (1 << 31) - 1):
+                for m, k_b in ((1, 1), (1, 8), (100, 1), (130, 2), (130, 16)):
+                    p = parse_plan(atk.plan_describe(m, n, k_b, 1, k_b, dt))
+                    assert p["rows_per_split"] < (1 << 30) - 2, (spec, m, n, k_b, p)
+                    if n > 1 << 30:
+                        p = parse_contig_plan(atk.plan_describe(m, n, k_b, 1, k_b, dt, atk.ATK_CONTIGUOUS))
+                        assert p["S"] >= 2, (spec, m, n, k_b, p)
+
+
 def test_long_queue_lane_widths(lib):
     """f32 queues of 16 slots take one column per lane while two would leave one wavefront per SIMD, two beyond."""
     assert atk.plan_describe(128, 65536, 16384, 1024, 16).startswith("V=1 KB=16 ")
