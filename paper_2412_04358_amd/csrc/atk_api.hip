@@ -109,7 +109,7 @@ const PlanOverride &plan_override() { return g_plan_override; }
 
 // ------------------------------------------------------------------------------------ approx plan
 static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, bool ptr16,
-                             Plan *pl, bool allow_pair = true) {
+                             Plan *pl, bool allow_pair = true, bool allow_half = true) {
     const int es = (dtype == ATK_F32) ? 4 : 2;
     Plan p;
     memset(&p, 0, sizeof p);
@@ -165,7 +165,12 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     // rows with two slots (256 x 2^18, k = b = 2048: 63 -> 33 us; 128 x 2^20, b = 256: 51.5 -> 47.7) and with eight and more, where
     // a lane that sees more rows also skips more of them (128 x 2^20, b = 128, k_b = 8: 101 -> 87; b = 64, k_b = 16:
     // 156 -> 127); with four slots it is slower (53 -> 56).  2048 x 65536, b = 64, k_b = 2 alone lost by it (45.3 -> 46.9).
-    if (dtype == ATK_BF16 && !ov.pk_off && (p.KB == 2 || p.KB >= 8) && want_threads > 512 * (int64_t)kNumCU) want_threads = 512 * (int64_t)kNumCU;
+    // (Only where the queues do pack then: half the lanes are half the splits, and splits of 65534 matrix rows and more do not.  Such
+    // plans are made again with all lanes, below: 128 x 2^20, b = 8, k_b = 2: 62.6 us unpacked on half of them, 47.3; 203 x 524288, b = 4,
+    // k_b = 16: 161 -> 125; 261 x 524288, b = 8, k_b = 12: 287 -> 164; 512 x 2^20, b = 16, k_b = 8: 302 -> 260.  Where neither packs
+    // all lanes are the better too (512 x 262144, b = 2: k_b = 2 74 -> 57, k_b = 8 93 -> 79), but not with sixteen slots (158 -> 179).)
+    const bool half_lanes = allow_half && dtype == ATK_BF16 && !ov.pk_off && (p.KB == 2 || p.KB >= 8) && want_threads > 512 * (int64_t)kNumCU;
+    if (half_lanes) want_threads = 512 * (int64_t)kNumCU;
     const bool short_rule = p.KB == 1 && p.stage2 && !ov.lm_off && !ov.ln_off && ptr16 && p.V == 16 / es && n % b == 0 &&
                             (n * es) % 16 == 0 && 2 * m <= (int64_t)kNumCU && n <= 65536 && !S_forced;
     const bool lean_shape = ptr16 && p.V == 16 / es && n % b == 0 && (n * es) % 16 == 0;  // what the lean kernels ask of the input
@@ -546,6 +551,13 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     p.rows_per_split = (int)rps;
 
     p.packed = dtype == ATK_BF16 && p.KB >= 2 && p.rows_per_split + 2 < 65536 && !ov.pk_off;
+    if (half_lanes && !p.packed) {
+        Plan q;
+        if (make_plan_aligned(m, n, k, b, k_b, dtype, ptr16, &q, allow_pair, false) == ATK_OK && (q.packed || p.KB < 16)) {
+            *pl = q;
+            return ATK_OK;
+        }
+    }
     // Eight unpacked slots with many lanes of the workgroup on a column, each with many matrix rows: what a lane has
     // seen alone is a poor bound on what still matters (after t rows one element in t/8 still enters its queue, and
     // with 128 lane-columns per wavefront some lane always needs the insertion), so the lanes of a column pool their

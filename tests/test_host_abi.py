@@ -285,6 +285,17 @@ def test_plan_override(lib, plan_override):
     assert q["T"] in (256, 512)
 
 
+def test_half_the_lanes_only_for_packed_queues(lib):
+    """bf16 calls whose queues pack take half the lanes, but never so few that their splits are too long to pack."""
+    for (m, n, k, b, k_b, S) in [(203, 524288, 64, 4, 16, 5), (261, 524288, 86, 8, 12, 3), (128, 1 << 20, 16, 8, 2, 4), (64, 1 << 21, 16, 8, 2, 8),
+                                 (128, 1 << 20, 32, 4, 8, 8), (128, 1 << 20, 64, 4, 16, 8), (512, 1 << 20, 128, 16, 8, 2), (128, 1 << 21, 64, 8, 8, 8)]:
+        p = parse_plan(atk.plan_describe(m, n, k, b, k_b, atk.ATK_BF16))
+        assert p["packed"] == 1 and p["S"] == S, (m, n, k, b, k_b, p)
+    # longer splits than pack with all the lanes: these, not half of them
+    p = parse_plan(atk.plan_describe(512, 262144, 4, 2, 2, atk.ATK_BF16))
+    assert p["packed"] == 0 and p["grid"] * p["T"] >= 2 * 512 * 256, p
+
+
 def test_longest_rows_are_split(lib, plan_override):
     """Lanes look ahead of their split's end in 32 bits, up to 2^15 rows, and queue words number 2^30 rows: no split may come near either."""
     for spec in (None, "S=1", "S=3,T=64"):
