@@ -172,7 +172,7 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * MH=0 / MH=<h> (k_b = 1: split rows never / with h helpers run as helpers and a finisher that meet through
  * mailboxes instead of partial lists and a ticket; HF=0 switches these off as well), BO=0 (Stage 2's bins take their
  * key range from the merged candidates, never from the bounds that come with the merge), RF=0 / RF=<n> (queues of
- * eight slots never / from n load batches on pool their floors).
+ * eight slots never / after 4n matrix rows of a lane for the first time pool their floors).
  * Values the kernels cannot take are ignored or clamped; results never depend on the plan.
  */
 int atk_plan_describe(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, char *buf,

@@ -561,13 +561,14 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     // Eight unpacked slots with many lanes of the workgroup on a column, each with many matrix rows: what a lane has
     // seen alone is a poor bound on what still matters (after t rows one element in t/8 still enters its queue, and
     // with 128 lane-columns per wavefront some lane always needs the insertion), so the lanes of a column pool their
-    // queues - after 16 matrix rows of each lane (8 pairs of them), then four times as many, ... - and raise their floors to the eighth best of all.  Measured on
-    // 128 x 2^20 f32, k = 64, k_b = 8, without and with: b = 8 (64 lanes a column) 129 -> 100 us, b = 64 (16 lanes) 132 -> 112,
-    // b = 128 133 -> 115, b = 512 (8 lanes) 136 -> 117; 2048 x 65536, b = 16 (8 lanes, 512 rows each) 154 -> 114; 512 x 65536, b = 16 (32 lanes,
-    // 128 rows) 45.5 -> 42.8.  With fewer lanes a column or rows a lane the pooling costs what it saves or more (2048 x 65536, b = 64, 8 lanes,
-    // 128 rows: 125 -> 143; 128 x 2^18, b = 64, 16 lanes, 128 rows: 48.4 -> 50.2; 512 x 131072, b = 128, 4 lanes, 256 rows: 81 -> 91).
+    // queues - after 32 matrix rows of each lane, then four times as many, ... - and raise their floors to the eighth best of all.  Measured on
+    // f32, k_b = 8, without and with: 128 x 2^20, b = 8 (64 lanes a column) 127 -> 97 us, b = 64 (16 lanes) 129 -> 104, b = 128 129 -> 107,
+    // b = 512 (8 lanes) 126 -> 107; 2048 x 65536, b = 16 (8 lanes, 512 rows each) 130 -> 96; 512 x 65536, b = 16 (32 lanes, 128 rows) 41.9 -> 36.7;
+    // bf16 rows too long to pack: 1024 x 2^18, b = 4 (64 lanes a column) 228 -> 104, 2048 x 131072, b = 1 272 -> 122.  The line between them and
+    // rows with fewer lanes a column or rows a lane was drawn where an earlier, slower form broke even.
+    // (A lane's offset in a matrix row's worth of the workgroup's lanes is kept in 32 bits.)
     p.refresh = 0;
-    if (p.KB == 8 && !p.packed && n % p.V == 0 && ov.rf >= 0 && p.P > 1 &&
+    if (p.KB == 8 && !p.packed && n % p.V == 0 && ov.rf >= 0 && p.P > 1 && (int64_t)p.P * b * es < (1ll << 31) &&
         (ov.rf > 0 || (p.P >= 8 && p.rows_per_split / p.P >= (p.P >= 32 ? 128 : 256))))
         p.refresh = ov.rf > 0 ? ov.rf : 8;
     p.tail_tpc = tail_lanes_per_column(p.stage2 ? b : std::min<int64_t>(b, (int64_t)p.Gw * p.V), p.T, p.KB, p.S);

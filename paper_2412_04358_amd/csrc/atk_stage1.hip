@@ -48,7 +48,7 @@ struct S1Params {
     int NB;              // short buckets: buckets a lane group takes in turn (0: one bucket per group)
     int lds_max;         // k_b = 1, no scratch: the lanes' running maxima meet in LDS by atomic maximum (see the kernel)
     int bound_ok;        // ... and the lower bound on the smallest candidate that comes with that merge is tight enough for select_binned()
-    int refresh;         // eight unpacked slots: the lanes of a column pool their queues' floors after this many pairs of matrix rows, then four times as many, ... (0: never)
+    int refresh;         // eight unpacked slots: the lanes of a column pool their queues' floors after four times this many matrix rows each, then four times as many, ... (0: never)
     u64 *trace;          // measurement build only: phase timestamps, [workgroup][wavefront][phase]
 };
 
@@ -137,43 +137,62 @@ __device__ __forceinline__ void insert_word(double (&q)[N], double c) {
 }
 
 // ---- queues that elements enter rarely (pooled floors) ----------------------------------------------------------------
-// A queue of words (as above, numbered by matrix row) and one element that waits for it: an element that beats `last` - a comparison, and
-// two selects where any lane of the wavefront has one - is put by, and only where a lane has one already do all lanes work theirs
-// into the queues, some thirty instructions; with 64 lanes that is about one time in ten.  Where a queue of values and rows took its elements
-// one by one, the 40 instructions that some lane needed two times in three bounded these rows (82 % of the SIMDs' cycles): 128 x 2^20, k = 64,
-// b = 128, k_b = 8: 133 -> 115 us; 2048 x 65536, b = 8: 110 -> 97.  `last` may lag behind the queue
-// (what waits has not raised it yet), which lets an element too many through and never one too few; the words put them in order.
+// A queue of words (as above, numbered by the lane's matrix rows) and one element that waits for it: an element that beats `last` - a
+// comparison, and two selects where any lane of the wavefront has one - is put by, and only where a lane has one already do all lanes work
+// theirs into the queues, some thirty instructions; with 64 lanes that is about one time in ten.  Where a queue of values and rows took its
+// elements one by one, the 40 instructions that some lane needed two times in three bounded these rows (82 % of the SIMDs' cycles).  `last` may
+// lag behind the queue (what waits has not raised it yet), which lets an element too many through and never one too few; the words put them
+// in order.  While elements enter often - rows that rise along their length, every row at its start - a batch of matrix rows is sorted and
+// merged in instead, 15 instructions an element where working them in one by one takes 40: rising rows of 2048 x 65536, b = 16 take 137 us so,
+// 240 one by one and 129 without floors; 128 x 2^20, b = 128: 128, 222, 125; without order 95, 113 and 129; 108, 116 and 129.
 template <int KB>
 struct LazyQueue {
     double q[KB];
     float last;     // an element has to beat it: the value in the last slot, or a floor above that (NaN: anything enters)
     uint32_t wait;  // the waiting element,
     int wait_t;     // and its number (kEmptyT: none)
-    u64 waiting;    // lanes that have one
     __device__ __forceinline__ void clear() {
 #pragma unroll
         for (int j = 0; j < KB; ++j) q[j] = 0.0;
         last = __uint_as_float(0x7fc00000u);
         wait = 0u;
         wait_t = kEmptyT;
-        waiting = 0ull;
+    }
+    __device__ __forceinline__ void raise() {
+        const uint32_t key = (uint32_t)((u64)__double_as_longlong(q[KB - 1]) >> 31);
+        last = fmaxf(last, __uint_as_float(bits_of_ukey(key)));  // (empty: the key 0 stands for a NaN, and `last` stays)
     }
     __device__ __forceinline__ void flush() {
         const double c = row_word(wait, (uint32_t)wait_t);
         insert_word<KB>(q, wait_t != kEmptyT ? c : 0.0);
         wait_t = kEmptyT;
-        waiting = 0ull;
-        const uint32_t key = (uint32_t)((u64)__double_as_longlong(q[KB - 1]) >> 31);
-        last = fmaxf(last, __uint_as_float(bits_of_ukey(key)));  // (empty: the key 0 stands for a NaN, and `last` stays)
+        raise();
     }
-    __device__ __forceinline__ void feed(uint32_t bits, int t) {
+    __device__ __forceinline__ void feed(uint32_t bits, int t, int &flushed) {
         const bool in = !(__uint_as_float(bits) <= last);
-        const u64 m = __ballot(in);
-        if (m == 0ull) return;  // uniform over the wavefront
-        if ((m & waiting) != 0ull) flush();
-        waiting |= m;
+        if (__ballot(in) == 0ull) return;
+        if (__ballot(in && wait_t != kEmptyT) != 0ull) {
+            flush();
+            ++flushed;
+        }
         wait = in ? bits : wait;
         wait_t = in ? t : wait_t;
+    }
+    // KB matrix rows numbered t, t + 1, ... at once: sorted, and merged into the queue.  Whether some lane had half of them to put in: elements
+    // still enter often (three and more to six and more measure the same).
+    __device__ __forceinline__ bool feed_sorted(const uint32_t (&bits)[KB], int t) {
+        int n = 0;
+#pragma unroll
+        for (int u = 0; u < KB; ++u) n += __uint_as_float(bits[u]) <= last ? 0 : 1;
+        if (__ballot(n != 0) == 0ull) return false;
+        if (__ballot(wait_t != kEmptyT) != 0ull) flush();
+        double c[KB];
+#pragma unroll
+        for (int u = 0; u < KB; ++u) c[u] = row_word(bits[u], (uint32_t)(t + u));
+        sort_desc<KB>(c);
+        merge_words<KB>(q, c);
+        raise();
+        return __ballot(n >= KB / 2) != 0ull;
     }
 };
 
@@ -429,7 +448,8 @@ __device__ __forceinline__ void row_tail(const S1Params &p, int r, int64_t tk, i
 }
 
 template <int ELT, int V, int KB, int U, int MAXT, bool PKF, bool TR = false, bool RF = false>
-__global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
+// (pooled floors: the launches are laid out for four wavefronts per SIMD, and three are two rounds: 128 x 2^20, b = 128: 116 -> 159 us)
+__global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Params p) {
     extern __shared__ __align__(16) unsigned char smem[];
     trace_mark<TR>(p.trace, 0);  // the wavefront has started
     constexpr int ES = (ELT == ATK_F32) ? 4 : 2;
@@ -485,6 +505,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     double qw[BATCH ? V : 1][BATCH ? KB : 1];  // BATCH: the queues, as row words
     float last_f[BATCH ? V : 1];            // ... and the value of each queue's last slot (NaN while it is empty)
     LazyQueue<KB> lazy[RF ? V : 1];
+    int flushed = KB * V;  // RF: times that waiting elements were worked in of late (at the start all elements enter)
     if constexpr (RF) {
 #pragma unroll
         for (int e = 0; e < V; ++e) lazy[e].clear();
@@ -506,7 +527,7 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
         if constexpr (PK)                                                                            \
             insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - (row))));                         \
         else if constexpr (RF)                                                                       \
-            lazy[e].feed(xb, (row));                                                                 \
+            lazy[e].feed(xb, pooled_rows + ((row) - t_resume), flushed);                             \
         else if constexpr (BATCH)                                                                    \
             insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - ph) / p.P)));                    \
         else                                                                                         \
@@ -533,29 +554,52 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     // The lanes pool their queues' value keys: a butterfly
     // inside the wavefront where lanes of a column sit side by side, then through the exchange area in LDS (free
     // until the lists are merged at the end).  Again after four times as many batches, and so on: as elements wait for the queues, a
-    // floor that lags costs little (128 x 2^20, b = 128: 116 us with twice as many each time).
+    // floor that lags costs little (stops at 32 matrix rows of a lane, 128, 512, ... against 16, 64, ...: 128 x 2^20, b = 512 119 -> 107 us, its
+    // rising rows 129 -> 126 and constant ones 114 -> 107; 512 x 65536, b = 16 37.6 -> 36.7, 48.6 -> 45.9, 37.2 -> 35.3).
     const int64_t row_bytes = (int64_t)p.b * ES;
-    const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n - rot + (int64_t)col0) * ES + t0 * row_bytes;
-    int t_resume = ph;  // the lane's next matrix row
+    int pooled_rows = 0;  // matrix rows that a lane feeds here: they are numbered 0, 1, ..., and the later ones pooled_rows + (row - t_resume)
     if constexpr (RF) {
-        static_assert(!RF || (KB == 8 && !PKF), "pooled floors: eight unpacked slots");
+        static_assert(!RF || (KB == 8 && U == KB && !PKF), "pooled floors: eight unpacked slots");
         const int step = p.P;
         const int nfull = (t1 / p.P) / U;  // full batches that every row phase has
+        pooled_rows = nfull * U;
         // (the next batch's loads are issued before the current one is worked on, and before the lanes meet)
-        int stop = max(1, 2 * p.refresh / U);
+        int stop = max(1, 4 * p.refresh / U);
+        constexpr int kCrowd = 5 * V;  // (4 and 6 a column and batch measure the same)
         RowVec<ELT, V> v[U], w[U];
-        auto load = [&](RowVec<ELT, V> (&to)[U], int t) {
+        const int64_t stride_bytes = (int64_t)step * row_bytes;
+        // (scalar addresses and one offset for all of a lane's loads; the host sees to it that it fits)
+        const unsigned char *next = (const unsigned char *)p.x + ((int64_t)r * p.n * ES + t0 * row_bytes);
+        const uint32_t lane_off = (uint32_t)ph * (uint32_t)row_bytes + (uint32_t)col0 * ES;
+        auto load = [&](RowVec<ELT, V> (&to)[U]) {
+            uint32_t off = lane_off;
+            asm volatile("" : "+v"(off));
 #pragma unroll
-            for (int u = 0; u < U; ++u) to[u] = load_vec<ELT, V>(base + (int64_t)(t + u * step) * row_bytes);
+            for (int u = 0; u < U; ++u) to[u] = load_vec<ELT, V>(next + u * stride_bytes + off);
         };
-        if (active && nfull > 0) load(v, t_resume);
+        if (active && nfull > 0) load(v);
         for (int i = 1; i <= nfull; ++i) {
+            if (i < nfull) next += U * stride_bytes;  // (else the last batch again)
             if (active) {
-                const int t = t_resume;
-                t_resume = t + U * step;
-                if (i < nfull) load(w, t_resume);
+                const bool sorted = __builtin_amdgcn_readfirstlane(flushed) >= kCrowd;  // (uniform: all active lanes count the same)
+                if (!sorted) load(w);  // (sorting takes the registers of a batch)
+                if (sorted) {
+                    flushed = 0;
 #pragma unroll
-                for (int u = 0; u < U; ++u) ATK_FEED_VEC(v[u], t + u * step);
+                    for (int e = 0; e < V; ++e) {
+                        uint32_t bits[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) bits[u] = elem_bits<ELT, V>(v[u], e);
+                        if (lazy[e].feed_sorted(bits, (i - 1) * U)) flushed = kCrowd;
+                    }
+                    load(w);
+                } else {
+                    flushed = 0;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int e = 0; e < V; ++e) lazy[e].feed(elem_bits<ELT, V>(v[u], e), (i - 1) * U + u, flushed);
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) v[u] = w[u];
             }
@@ -619,7 +663,9 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
     }
 
     // ---------------------------------------------------------------- streaming scan
+    const int t_resume = ph + pooled_rows * p.P;  // the lane's next matrix row
     if (active) {
+        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n - rot + (int64_t)col0) * ES + t0 * row_bytes;
         const int step = p.P;
         int t = t_resume;
         if (V > 1 && rot > 0 && cg == 0 && sp == 0 && t == 0 && t < t1) {
@@ -813,7 +859,8 @@ __global__ void __launch_bounds__(MAXT) stage1_kernel(S1Params p) {
                 const u64 c = (u64)__double_as_longlong(lazy[e].q[j]);
                 if (c != 0ull) {
                     val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 31)));
-                    tt[e][j] = t0 + (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu));
+                    const int t = (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu));
+                    tt[e][j] = t0 + (t < pooled_rows ? ph + t * p.P : t_resume + (t - pooled_rows));
                 }
             }
         }
@@ -1244,7 +1291,7 @@ static hipError_t launch_one(const Plan &pl, const S1Params &prm, hipStream_t st
     if (prm.trace) return hipErrorNotSupported;  // the measurement build exists for the lean kernels only
     if constexpr (KB == 8) {
         if (pl.refresh) {
-            constexpr int UF = 8;  // matrix rows in flight: with the instance's four 128 x 2^20, b = 128 takes 118 us and not 115, 512 x 2^18, b = 32 142 and not 111
+            constexpr int UF = KB;  // matrix rows in flight, and sorted at a time
             hipLaunchKernelGGL((stage1_kernel<ELT, V, KB, UF, MAXT, false, false, true>), dim3((unsigned)pl.grid),
                                dim3((unsigned)pl.T), (size_t)pl.lds_bytes, stream, prm);
             return hipGetLastError();

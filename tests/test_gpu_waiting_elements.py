@@ -44,3 +44,75 @@ def test_waiting(case, spec, plan_override):
         ov, oi = oracle.approx_topk(workloads.as_numpy_bits(x), k, b, k_b, threads=8)
         assert np.array_equal(idx.cpu().numpy(), oi)
         assert np.array_equal(vals.cpu().numpy().view(np.uint32), ov.view(np.uint32))
+
+
+def _trends(n, b):
+    """Matrix rows among which elements enter often for a while and rarely for a while: a rise, a rise after rows without order, steps up and
+    down again, single columns that rise, and a rise so slow that some lanes' elements enter and others' do not."""
+    L = n // b
+    z = workloads.normal_rows(6, n, seed=n + b)
+    t = (torch.arange(n) // b).float() / L
+    x = z.clone()
+    x[0] += 40 * t.clamp(max=0.5)
+    x[1] += 40 * (t - 0.5).clamp(min=0)
+    x[2] += 20 * torch.sin(t * 40)
+    x[3] += torch.where(torch.arange(n) % b < 2, 100 * t, torch.zeros(()))
+    x[4] += 3 * t
+    x[5] = (torch.arange(n) // (b * 24) % 7).float()
+    return x
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(65536, 16, 8, ""), (65536, 8, 6, "RF=2,S=2"), (131073 * 2, 18, 8, "P=8,RF=4,S=2"), (70000, 7, 6, "V=1,P=16,RF=3,S=1"),
+                                  (65536, 16, 7, "V=4,P=32,RF=1,S=1"), (8 * (8 * 32 * 5 + 3) + 2, 8, 8, "P=32,T=256,RF=1,S=1")])
+def test_trends(case, dtype, plan_override):
+    """Batches sorted in and elements that wait, in turn: full batches of eight rows a lane, and what is left of lanes that stop early."""
+    n, b, k_b, spec = case
+    x = _trends(n, b)
+    if dtype == "bf16":
+        x = x.to(torch.bfloat16)
+        spec = spec + ("," if spec else "") + "PK=0"
+    if not spec:
+        x = x.repeat(86, 1)  # (a plan of its own pools on launches that fill the chip)
+    elif "RF" not in spec:
+        spec += ",P=16,RF=8,S=1"
+    plan_override(spec)
+    dt = atk.ATK_F32 if dtype == "f32" else atk.ATK_BF16
+    for k in (b * k_b, 40):
+        plan = atk.plan_describe(*x.shape, k, b, k_b, dt)
+        print(n, k, b, k_b, dtype, plan, flush=True)
+        assert " packed=0 " in plan and " refresh=0" not in plan
+        vals, idx = atk.approx_topk(x.cuda(), k, b, k_b)
+        torch.cuda.synchronize()
+        ov, oi = oracle.approx_topk(workloads.as_numpy_bits(x[:6].contiguous()), k, b, k_b, threads=8)
+        assert np.array_equal(idx[:6].cpu().numpy(), oi)
+        bits = vals[:6].cpu().view(torch.int32 if dtype == "f32" else torch.int16).numpy()
+        assert np.array_equal(bits, ov.view(bits.dtype))
+
+
+def _time_us(x, k, b, k_b):
+    best = []
+    for _ in range(5):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        atk.approx_topk(x, k, b, k_b)
+        start.record()
+        for _ in range(20):
+            atk.approx_topk(x, k, b, k_b)
+        stop.record()
+        torch.cuda.synchronize()
+        best.append(start.elapsed_time(stop) * 50.0)
+    return min(best)
+
+
+@pytest.mark.parametrize("case", [(2048, 65536, 64, 16, 8), (512, 65536, 64, 16, 8), (128, 1 << 20, 256, 512, 8)])
+def test_rising_rows_cost_what_they_do_without_pooling(case, plan_override):
+    """Where every element enters, a queue that takes them one by one costs 1.6 to 1.9 times what sorted batches do; pooled rows sort them too
+    (1.05 to 1.1 with the lanes' meetings, and timings vary by a few per cent)."""
+    m, n, k, b, k_b = case
+    x = torch.randn((m, n), device="cuda").sort(dim=1).values
+    assert " refresh=8 " in atk.plan_describe(m, n, k, b, k_b, atk.ATK_F32)
+    pooled = _time_us(x, k, b, k_b)
+    plan_override("RF=0")
+    apart = _time_us(x, k, b, k_b)
+    print(case, "%.1f us pooled, %.1f without" % (pooled, apart), flush=True)
+    assert pooled < 1.3 * apart
