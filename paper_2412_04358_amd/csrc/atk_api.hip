@@ -530,8 +530,8 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     }
     if (multi_ok && ov.mh > 0) S = ov.mh + 1;  // (sweeps and tests; clamped like any other count below)
     if (S_forced) S = S_forced;
-    // (a lane's scan looks ahead of its split's end in 32 bits, and queue words count 2^30 rows)
-    if (p.L >= kLongRow && S < 4) S = 4;
+    // (queue words count 2^30 rows of a split, and the last split is longer than what lanes look ahead, 2^16 rows)
+    if (p.L >= kLongRow) S = std::min<int64_t>(std::max<int64_t>(S, 4), 512);
     if (S > p.L / p.P) S = p.L / p.P;
     if (S < 1) S = 1;
     int64_t rps = ceil_div(p.L, S);

@@ -52,6 +52,11 @@ struct S1Params {
     u64 *trace;          // measurement build only: phase timestamps, [workgroup][wavefront][phase]
 };
 
+// The scans count ahead of their last matrix row (contiguous buckets: load) in 32 bits, by up to three batches of sixteen for each
+// of 1024 lanes.  Only rows of one bucket are long enough for that to pass 2^31; what they have beyond this row is taken one by one.  (The host
+// sees to it that no split starts near it.)
+constexpr int kRowsAhead = 0x7fffffff - (1 << 16);
+
 // Insert (v, t) into the descending list (val, tt); later elements never displace equal
 // earlier ones ("!(v <= slot)" is "v > slot" for numbers and true for the NaN that marks
 // an empty slot).
@@ -476,9 +481,8 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
     int eph = p.extra_ph + (carry ? 1 : 0);     // the row phase that takes the ragged row
     if (eph >= p.P) eph -= p.P;
     const int t0 = sp * p.rows_per_split;
-    // Matrix rows are numbered from the split's first one, t0: rows of the whole matrix go up to 2^31 - 1 with one bucket, and the
-    // scans below look up to 2^15 rows past the last one (the host keeps splits under 2^30 rows).
-    const int t1 = (sp == p.S - 1) ? Lr - t0 : min(Lr - t0, p.rows_per_split);
+    const int t_end = (sp == p.S - 1) ? Lr : min(Lr - t0, p.rows_per_split) + t0;
+    const int t1 = min(t_end, kRowsAhead);  // (where the scans stop that look ahead)
     auto bucket_of = [&](int c) { return c - rot + (c < rot ? p.b : 0); };
 
     // One slot per bucket, no hand-over through memory: the lanes that share a column meet in LDS by
@@ -525,22 +529,22 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
 #define ATK_FEED_ELEM(e, xb, row)                                                                    \
     do {                                                                                             \
         if constexpr (PK)                                                                            \
-            insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - (row))));                         \
+            insert_pk<KB>(pk[e], pack_bf16(xb, (uint32_t)(0xffff - ((row) - t0))));                  \
         else if constexpr (RF)                                                                       \
             lazy[e].feed(xb, pooled_rows + ((row) - t_resume), flushed);                             \
         else if constexpr (BATCH)                                                                    \
-            insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - ph) / p.P)));                    \
+            insert_word<KB>(qw[e], row_word(xb, (uint32_t)(((row) - t0 - ph) / p.P)));               \
         else                                                                                         \
-            insert<KB>(val[e], tt[e], __uint_as_float(xb), t0 + (row));                              \
+            insert<KB>(val[e], tt[e], __uint_as_float(xb), (row));                                   \
     } while (0)
 #define ATK_FEED_VEC(vec, row)                                                                       \
     do {                                                                                             \
         if constexpr (PK)                                                                            \
-            scan_vec_pk<ELT, V, KB>(pk, vec, (row));                                                 \
+            scan_vec_pk<ELT, V, KB>(pk, vec, (row) - t0);                                            \
         else if constexpr (BATCH || RF) {                                                            \
             _Pragma("unroll") for (int e_ = 0; e_ < V; ++e_) ATK_FEED_ELEM(e_, (elem_bits<ELT, V>(vec, e_)), (row)); \
         } else                                                                                       \
-            scan_vec<ELT, V, KB>(val, tt, vec, t0 + (row));                                          \
+            scan_vec<ELT, V, KB>(val, tt, vec, (row));                                               \
     } while (0)
 
     // ---------------------------------------------------------------- pooled floors (instances of their own: RF)
@@ -561,7 +565,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
     if constexpr (RF) {
         static_assert(!RF || (KB == 8 && U == KB && !PKF), "pooled floors: eight unpacked slots");
         const int step = p.P;
-        const int nfull = (t1 / p.P) / U;  // full batches that every row phase has
+        const int nfull = ((t1 - t0) / p.P) / U;  // full batches that every row phase has
         pooled_rows = nfull * U;
         // (the next batch's loads are issued before the current one is worked on, and before the lanes meet)
         int stop = max(1, 4 * p.refresh / U);
@@ -663,12 +667,12 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
     }
 
     // ---------------------------------------------------------------- streaming scan
-    const int t_resume = ph + pooled_rows * p.P;  // the lane's next matrix row
+    const int t_resume = t0 + ph + pooled_rows * p.P;  // the lane's next matrix row
     if (active) {
-        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n - rot + (int64_t)col0) * ES + t0 * row_bytes;
+        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n - rot + (int64_t)col0) * ES;
         const int step = p.P;
         int t = t_resume;
-        if (V > 1 && rot > 0 && cg == 0 && sp == 0 && t == 0 && t < t1) {
+        if (V > 1 && rot > 0 && cg == 0 && t == 0 && t < t1) {
             // the head of the virtual row: its first `rot` elements are not this row's
             RowVec<ELT, V> v = load_vec<ELT, V>(base);
 #pragma unroll
@@ -683,7 +687,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
             // 64 rows 13.4 -> 12.5; 128 x 2^20, b = 1024: 138 -> 130.
             constexpr int D = KB == 8 ? 2 : 1;  // batches ahead
             RowVec<ELT, V> v[KB], w[D][KB];
-            uint32_t seq = (uint32_t)((t - ph) / step);  // number of the batch's first row among the lane's
+            uint32_t seq = (uint32_t)((t - t0 - ph) / step);  // number of the batch's first row among the lane's
             bool have = t < t1;
             auto fetch = [&](RowVec<ELT, V> (&to)[KB], int tb) {
 #pragma unroll
@@ -816,20 +820,26 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
             ATK_PIECE(1)
 #undef ATK_PIECE
         }
+        if (t1 < t_end) {  // (uniform)
+            for (uint32_t tr = (uint32_t)(t0 + ph) + (uint32_t)((t1 - t0 - ph + step - 1) / step) * (uint32_t)step; tr < (uint32_t)t_end; tr += (uint32_t)step) {
+                RowVec<ELT, V> v = load_vec<ELT, V>(base + (int64_t)tr * row_bytes);
+                ATK_FEED_VEC(v, (int)tr);
+            }
+        }
         // The (virtual) row does not end on a matrix row: the last matrix row holds only its
         // first `remr` columns (the short buckets of Figure 2).  It has the highest indices, so
         // it is fed last.
         if (remr > 0 && sp == p.S - 1 && ph == eph && col0 < remr) {
-            const unsigned char *last = base + (int64_t)t1 * row_bytes;
+            const unsigned char *last = base + (int64_t)Lr * row_bytes;
             if (col0 + V <= remr) {
                 RowVec<ELT, V> v = load_vec<ELT, V>(last);
-                ATK_FEED_VEC(v, t1);
+                ATK_FEED_VEC(v, Lr);
             } else {
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     if (col0 + e < remr) {
                         RowVec<ELT, 1> one = load_vec<ELT, 1>(last + e * ES);
-                        ATK_FEED_ELEM(e, (elem_bits<ELT, 1>(one, 0)), t1);
+                        ATK_FEED_ELEM(e, (elem_bits<ELT, 1>(one, 0)), Lr);
                     }
             }
         }
@@ -860,7 +870,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
                 if (c != 0ull) {
                     val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 31)));
                     const int t = (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu));
-                    tt[e][j] = t0 + (t < pooled_rows ? ph + t * p.P : t_resume + (t - pooled_rows));
+                    tt[e][j] = t < pooled_rows ? t0 + ph + t * p.P : t_resume + (t - pooled_rows);
                 }
             }
         }
@@ -1190,8 +1200,9 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
     if (active) {
         const int chunks = (int)((run1 - run0) / V);
         const int c0 = sp * p.chunks_per_split;
-        const int c1 = min(chunks - c0, p.chunks_per_split);  // (chunks are numbered from the split's first: c0 + 2^14 may lie past 2^31)
-        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n + run0 + (int64_t)c0 * V) * ES;
+        const int c_end = min(chunks - c0, p.chunks_per_split) + c0;
+        const int c1 = min(c_end, kRowsAhead);  // (where the scan stops that looks ahead)
+        const unsigned char *base = (const unsigned char *)p.x + ((int64_t)r * p.n + run0) * ES;
         auto feed = [&](const RowVec<ELT, V> &v, int c) {
             float x[V];
 #pragma unroll
@@ -1203,9 +1214,9 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
                 if (__ballot(any) == 0ull) return;
             }
 #pragma unroll
-            for (int e = 0; e < V; ++e) insert<KB>(val, tt, x[e], (c0 + c) * V + e);
+            for (int e = 0; e < V; ++e) insert<KB>(val, tt, x[e], c * V + e);
         };
-        int c = q;
+        int c = c0 + q;
         for (; c + (U - 1) * p.Gs < c1; c += U * p.Gs) {
             RowVec<ELT, V> v[U];
 #pragma unroll
@@ -1228,6 +1239,9 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
             ATK_PIECE(1)
 #undef ATK_PIECE
         }
+        if (c1 < c_end)
+            for (uint32_t cr = (uint32_t)(c0 + q) + (uint32_t)((c1 - c0 - q + p.Gs - 1) >> p.gs_shift) * (uint32_t)p.Gs; cr < (uint32_t)c_end; cr += (uint32_t)p.Gs)
+                feed(load_vec<ELT, V>(base + (int64_t)cr * (V * ES)), (int)cr);
     }
     u64 comp[KB];
 #pragma unroll

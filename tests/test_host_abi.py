@@ -297,17 +297,20 @@ def test_half_the_lanes_only_for_packed_queues(lib):
 
 
 def test_longest_rows_are_split(lib, plan_override):
-    """Lanes look ahead of their split's end in 32 bits, up to 2^15 rows, and queue words number 2^30 rows: no split may come near either."""
-    for spec in (None, "S=1", "S=3,T=64"):
+    """Lanes count up to 2^16 rows past their split's end in 32 bits and queue words number 2^30 rows: no split is that long, and none starts
+    so near the longest row's end that its start itself would be counted past."""
+    for spec in (None, "S=1", "S=3,T=64", "S=4096,T=1024"):
         plan_override(spec)
         for dt in (atk.ATK_F32, atk.ATK_BF16):
             for n in (1 << 30, (1 << 31) - 1):
-                for m, k_b in ((1, 1), (1, 8), (100, 1), (130, 2), (130, 16)):
+                for m, k_b in ((1, 1), (1, 2), (1, 4), (1, 8), (1, 16), (100, 1), (130, 2), (130, 16)):
                     p = parse_plan(atk.plan_describe(m, n, k_b, 1, k_b, dt))
                     assert p["rows_per_split"] < (1 << 30) - 2, (spec, m, n, k_b, p)
-                    if n > 1 << 30:
-                        p = parse_contig_plan(atk.plan_describe(m, n, k_b, 1, k_b, dt, atk.ATK_CONTIGUOUS))
-                        assert p["S"] >= 2, (spec, m, n, k_b, p)
+                    assert n - (p["S"] - 1) * p["rows_per_split"] >= 1 << 17, (spec, m, n, k_b, p)
+                    p = parse_contig_plan(atk.plan_describe(m, n, k_b, 1, k_b, dt, atk.ATK_CONTIGUOUS))
+                    chunks = n // p["V"]
+                    if chunks > 1 << 30:
+                        assert p["S"] >= 2 and chunks - (p["S"] - 1) * -(-chunks // p["S"]) >= 1 << 17, (spec, m, n, k_b, p)
 
 
 def test_long_queue_lane_widths(lib):
