@@ -404,16 +404,33 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     return S;
     };
     int64_t S = row_splits();
-    // Eight slots and more in f32 over wide bucket layouts, a lane to a column group, on rows that would be split: four lanes of
-    // the workgroup on a column group meet in LDS, where the splits' lists (half of the survivors and more, once per split) would go through memory to
-    // one workgroup per column block.  f32, k = 1024, b = 1024, k_b = 8: 128 x 2^20 246 us in four splits, 133 with four lanes;
+    // Eight slots and more in f32 over bucket layouts as wide as a workgroup of its size, a lane to a column group, on rows that would be split:
+    // four lanes of the workgroup on a column group meet in LDS, where the splits' lists (half of the survivors and more, once per split) would go
+    // through memory to one workgroup per column block.  f32, k = 1024, b = 1024, k_b = 8: 128 x 2^20 246 us in four splits, 133 with four lanes;
     // 128 x 2^18 99 -> 53, 256 x 2^18 173 -> 88, 256 x 500000, b = 1000: 227 -> 144; k_b = 16: 128 x 2^20 288 -> 222, 64 x 2^20, k = 4096:
-    // 230 -> 128.  (Two lanes: 165, 58, 87, 143, 213, 163; eight: 135, 57, 92, 152, 246, 140.)
+    // 230 -> 128.  (Two lanes: 165, 58, 87, 143, 213, 163; eight: 135, 57, 92, 152, 246, 140.)  The bucket counts go down to 129, one workgroup of
+    // 192 lanes or two of 128 (128 x 2^18, b = 146, k_b = 12, Stage 2 fused: 190 -> 125; one row of 2^18, b = 139: 75 -> 58; 304 x 65536,
+    // b = 137: 94 -> 56), and up to 95 column blocks (26 x 3781548, b = 6032, k_b = 16, in workgroups halved to 128 lanes: 283 -> 157).
     // With more matrix rows than 128 to a slot the splits are level or better (64 x 2^21, k = 2048, b = 1024, k_b = 8: 147 -> 153).
+    // The layout stays where at most four splits are left, with eight slots also where there are fewer than before, and on launches that leave CUs to
+    // themselves (two workgroups to a CU with eight slots, one to two CUs with sixteen); else the lists of more column blocks go through memory all the
+    // same (in how many splits a lane to a column group -> four lanes: 32 x 101525, b = 145, k_b = 12: 52 us in 8 -> 57 in 5; 23 x 118980, b = 159: 67
+    // in 6 -> 78 in 7; 32 x 65536, b = 141, k_b = 5: 34 in 6 -> 37 in 7; but 45 x 131072, b = 129, k_b = 8: 53 in 8 -> 44 in 5; 3 x 85417, b = 231:
+    // 36 in 6 -> 31 in 6; 17 x 149959, b = 169, k_b = 5: 36 in 6 -> 30 in 6; 3 x 131072, b = 129, k_b = 12: 67 in 7 -> 57 in 8).
     if (dtype == ATK_F32 && p.KB >= 8 && p.P == 1 && S > 1 && p.L >= 16 * (int64_t)p.KB && p.L <= 128 * (int64_t)p.KB && !T_forced && !P_forced && !S_forced) {
+        const Plan p0 = p;
+        const int T0 = T;
+        const int64_t lds0 = lds, S0 = S;
         layout(4);
-        if (lds > kLdsBudget) return ATK_ERR_UNSUPPORTED;
         S = row_splits();
+        if (lds <= kLdsBudget && (S <= 4 || (p.KB == 8 && S < S0) || m * p.colblocks * S <= (p.KB == 8 ? 2 : 0.5) * kNumCU)) {
+            p_want = 4;
+        } else {
+            p = p0;
+            T = T0;
+            lds = lds0;
+            S = S0;
+        }
     }
     // Many rows with few column groups came out above with workgroups of one or two wavefronts (a lane per column group
     // fills the chip) and may still get row splits on top - through scratch and a ticket, between workgroups of 64

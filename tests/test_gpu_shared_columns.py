@@ -1,5 +1,6 @@
 """f32 queues of eight and sixteen slots over wide bucket layouts, which four lanes of a workgroup share where the rows would be split, against the
-oracle, bit for bit: with and without Stage 2, fewer slots used than there are, odd lengths and buckets that do not divide them."""
+oracle, bit for bit: without Stage 2 and with it, in the same launch (one split and several) and apart, fewer slots used than there are, odd lengths,
+buckets that do not divide them, rows off the 16-byte boundaries, workgroups halved for their exchange area, and few rows."""
 import numpy as np
 import pytest
 import torch
@@ -12,13 +13,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("case", [(128, 1 << 18, 1024, 1024, 8, 0), (128, 1 << 18, 8192, 1024, 8, 0), (100, 300001, 1000, 777, 8, 0), (130, 1 << 18, 700, 1026, 5, 0),
-                                  (128, 1 << 20, 1024, 1024, 16, 0), (64, 524289, 10000, 1021, 11, 3)])
+                                  (128, 1 << 20, 1024, 1024, 16, 0), (100, 300001, 1000, 777, 8, 3), (169, 131072, 100, 215, 8, 0),
+                                  (88, 104995, 64, 139, 8, 1), (322, 1 << 18, 4944, 412, 12, 0), (128, 1 << 17, 474, 158, 12, 0), (3, 85417, 462, 231, 8, 2)])
 def test_shared(case):
     assert torch.cuda.is_available(), "this test needs the MI355X"
     m, n, k, b, k_b, shift = case
     plan = atk.plan_describe(m, n, k, b, k_b, atk.ATK_F32)
     print(case, plan, flush=True)
-    assert " P=1 " not in plan, plan
+    assert " P=4 " in plan, plan
     x = workloads.normal_rows(m, n, seed=b + k_b)
     x[1] = x[1].sort().values
     x[2] = workloads.few_levels(1, n, levels=3, seed=1)[0]

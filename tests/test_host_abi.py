@@ -296,6 +296,18 @@ def test_half_the_lanes_only_for_packed_queues(lib):
     assert p["packed"] == 0 and p["grid"] * p["T"] >= 2 * 512 * 256, p
 
 
+def test_four_lanes_a_column_group_stay_where_splits_go(lib):
+    """f32 queues of eight and sixteen slots on rows that would be split: the layout of four lanes a column group is kept, also through the rules
+    that come after it, where it leaves few splits or takes some away, and is given up as a whole where it does not."""
+    for (m, n, k, b, k_b, T, P, S) in [(128, 1 << 18, 1024, 1024, 8, 256, 4, 1), (128, 1 << 18, 876, 146, 12, 128, 4, 2), (84, 1 << 18, 960, 160, 12, 128, 4, 4),
+                                       (256, 183532, 409, 256, 16, 128, 4, 2), (251, 1 << 19, 1024, 1024, 16, 128, 4, 1), (45, 131072, 258, 129, 8, 192, 4, 5),
+                                       (169, 131072, 215, 215, 8, 256, 4, 1), (3, 85417, 462, 231, 8, 256, 4, 6), (32, 101525, 174, 145, 12, 192, 1, 8), (32, 65536, 352, 141, 5, 192, 1, 6),
+                                       (8, 49779, 918, 153, 12, 192, 1, 8)]:
+        p = parse_plan(atk.plan_describe(m, n, k, b, k_b, atk.ATK_F32))
+        assert (p["T"], p["P"], p["S"]) == (T, P, S), (m, n, k, b, k_b, p)
+        assert p["lds"] <= 65536 and p["P"] * p["Gw"] <= p["T"]
+
+
 def test_longest_rows_are_split(lib, plan_override):
     """Lanes count up to 2^16 rows past their split's end in 32 bits and queue words number 2^30 rows: no split is that long, and none starts
     so near the longest row's end that its start itself would be counted past."""
