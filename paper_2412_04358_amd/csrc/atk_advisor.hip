@@ -52,9 +52,12 @@ static double estimate_us(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
     const bool lean = KB == 1 && dtype == ATK_F32;
     double rate = (lean ? 7.2e6 : 6.5e6) * bytes / (bytes + (lean ? 8.0e6 : 6.0e6));  // bytes per microsecond
     if (rate < 0.5e6) rate = 0.5e6;
-    // (sixteen slots: f32 rows go through the sorting-network scan, bf16 rows hold twice the elements per byte)
-    // (eight slots on long buckets: few elements still enter a queue once the lanes of a column have pooled their floors)
-    const double queue = KB <= 1 ? 1.0 : KB == 2 ? 1.07 : KB == 4 ? 1.3 : KB == 8 ? (n / b >= 4096 ? 1.7 : 2.7) : (dtype == ATK_F32 && n / b < 4096 ? 3.9 : 6.9);
+    // (bf16 rows hold twice the elements per byte; on long buckets few elements still enter a queue of eight f32 slots once the lanes of a column
+    // have pooled their floors).  Filling the queues and merging the lanes' takes a time of its own, whatever the rows' length, and half of it where a
+    // lane has its columns to itself.  Fitted to 1181 calls with four slots and more, 8 x 2^18 to 128 x 2653751: 19 of 20 within 1.6 times.
+    const bool f32 = dtype == ATK_F32;
+    const double queue = KB <= 1 ? 1.0 : KB == 2 ? 1.07 : KB == 4 ? 1.15 : KB == 8 ? (f32 ? (n / b >= 2048 ? 1.3 : 1.43) : 1.65) : (f32 ? 2.0 : 2.5);
+    const double fill = KB <= 2 ? 0.0 : KB == 4 ? 4.0 : KB == 8 ? 7.0 : 12.0;
     double us = 1.5 + (rd * queue + wr) / rate;
     const bool stage2 = b * k_b > k;
     const double cand = (double)(b * k_b);
@@ -91,9 +94,9 @@ static double estimate_us(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
     if ((double)m * groups < 16384.0) floor_us = 6.0 + bytes / 16.0e6;
     if (split && !(stage2 && m >= 128)) floor_us = 6.5 + bytes / 12.0e6 + (stage2 ? 1.5 + 0.001 * cand : 0.0);
     if (us < floor_us) us = floor_us;
-    // long queues whose lists go through scratch: the last workgroup's merges of 8- and 16-slot lists (8 x 2^18 f32,
-    // k = 64, b = 16, k_b = 8: 25 us where the bytes and the floor say 10)
-    if (split && KB >= 8) us += KB >= 16 ? 25.0 : 15.0;
+    us += (double)m * groups >= 65536.0 ? 0.5 * fill : fill;
+    // long queues whose lists go through scratch: the last workgroup's merges of 8- and 16-slot lists
+    if (split && KB >= 8) us += KB >= 16 ? 8.0 : 4.0;
     // few rows: many splits per row, merged by the workgroup that finishes the row
     if (split && splits > 2.0) us += 0.04 * splits * (stage2 ? std::max(1.0, cand / 256.0) : 1.0);
     return us;

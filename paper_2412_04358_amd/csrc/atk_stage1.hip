@@ -242,7 +242,9 @@ __device__ __forceinline__ void scan_vec(float (&val)[V][KB], int (&tt)[V][KB], 
 // equal value and earlier row, so inserting into a descending list is one median-of-three per slot instead of compares and
 // selects on two arrays.  Two elements are converted together, by three packed 16-bit operations, and one more each puts the row
 // beside it.  Which zeros were -0 is looked up in the row at the end, if any is left in a queue.  INT_MIN = empty (no
-// magnitude is 0x8000).  Unpacked queues of two slots take 10.4 instructions per element, which the SIMDs issued in 79 % of their
+// magnitude is 0x8000).  (A wavefront that ends with a zero loads all its survivors' elements again: nothing measurable where they
+// are the rows' first ones, 2 us where they lie all over the rows: 2048 x 8192, half of it -0, b = 512, 20.1 -> 22.3 us, as many loads in flight as
+// there are survivors or a column's: the fetch itself is what takes it.)  Unpacked queues of two slots take 10.4 instructions per element, which the SIMDs issued in 79 % of their
 // cycles on 128 x 2653751; these take 5 and leave such rows to memory: 136 -> 128 us (5.3 TB/s; k_b = 1: 112), 1024 x 131072,
 // b = 512: 56 -> 48.  (A conversion element by element that carried "was -0" in the word took 6 more per element: no gain at two slots.)
 constexpr int32_t kEmptyPk = (int32_t)0x80000000u;
@@ -1284,9 +1286,9 @@ __global__ void __launch_bounds__(MAXT) contig_kernel(S1Params p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Matrix rows whose loads a lane with packed queues has in flight, for V columns: 128 bytes' worth of registers at most.  The
-// instances' own batches are about unpacked queues and smaller ones left the lanes waiting (128 x 65536, k = 16384, b = 1024,
-// k_b = 16: two rows 24.8 us, eight 15.6, sixteen 14.2; 128 x 2^20, b = 64, k_b = 16: 247, 173, 157).
+// Matrix rows whose loads a lane with packed queues has in flight, for V columns: 128 bytes' worth of registers at most (with eight slots
+// twice that: the next batch is loaded while one is worked on).  The instances' own batches are about unpacked queues and smaller ones left the
+// lanes waiting (128 x 65536, k = 16384, b = 1024, k_b = 16: two rows 24.8 us, eight 15.6, sixteen 14.2; 128 x 2^20, b = 64, k_b = 16: 247, 173, 157).
 constexpr int packed_batch(int V) { return V == 8 ? 4 : 16; }
 
 template <int ELT, int V, int KB, int U>

@@ -1,5 +1,5 @@
 """Queues of one 32-bit word per slot (bf16, two slots and more) against the oracle, bit for bit: rows whose every survivor is a zero of
-either sign, subnormals next to zero, the largest number of matrix rows a word can tell apart, and one more."""
+either sign, subnormals next to zero, as many matrix rows as are packed, and one more."""
 import numpy as np
 import pytest
 import torch
@@ -52,9 +52,30 @@ def test_zeros(n, k_b):
 
 
 @pytest.mark.parametrize("v", [1, 2, 4, 8])
+@pytest.mark.parametrize("rows", [65533, 65534])
+def test_last_row_number(rows, v, plan_override):
+    """One lane to a column group and one split: `rows` matrix rows in it, the most that pack and one more, a ragged row after them and, in rows
+    that start off a load's boundary, one whole row more; the winners are in the last of these and tie with others at the start."""
+    b = 64 * v
+    plan_override("V=%d,S=1,T=64" % v)
+    n = rows * b + b - 1
+    for k_b in (2, 4, 8) if v <= 2 else (2, 4) if v == 4 else (2,):
+        p = dict(kv.split("=") for kv in atk.plan_describe(3, n, b * k_b, b, k_b, atk.ATK_BF16).split())
+        assert (p["V"], p["P"], p["S"], p["rows_per_split"], p["packed"]) == (str(v), "1", "1", str(rows), "1" if rows < 65534 else "0"), p
+        x = torch.full((3, n), -1.0, dtype=torch.bfloat16)
+        x[0] = workloads.few_levels(1, n, levels=3, seed=v, dtype="bf16")[0]
+        x[1, -b * k_b :: 3] = 1.0
+        x[1, : b * 5] = torch.arange(b * 5).remainder(2).to(torch.bfloat16)
+        x[2, -b:] = 2.0
+        x[2, -2 * b : -b] = torch.arange(b).remainder(5).to(torch.bfloat16)
+        _check(x, b * k_b, b, k_b)
+
+
+@pytest.mark.parametrize("v", [1, 2, 4, 8])
 @pytest.mark.parametrize("rows", [65024, 65535, 65537])
 def test_most_matrix_rows(rows, v, plan_override):
-    """One split of `rows` matrix rows: the last ones packed, then the unpacked queues; the winners at either end and ties between them."""
+    """One split of some 65024 matrix rows, a number of rounds of its lanes, and one round more: packed and unpacked queues; the winners at either
+    end and ties between them."""
     b = 8
     plan_override("V=%d,S=1" % v)
     n = rows * b + 3

@@ -430,7 +430,7 @@ def test_interleaved_flag_is_approx_topk():
 
 @pytest.mark.parametrize("plan", ["", "PK=0", "T=64,S=1"])
 def test_bf16_packed_queues(plan, plan_override):
-    """bf16 with k_b >= 3 keeps (key, row) in one 32-bit word per slot when a lane's share of the row
+    """bf16 with k_b >= 2 keeps (key, row) in one 32-bit word per slot when a lane's share of the row
     is short enough; the results are the same with that path switched off, and on rows whose
     single split is too long for it."""
     if plan:
@@ -1075,5 +1075,27 @@ def test_runtime_estimate_and_advice_against_the_clock():
                             break
                 print("advice k=%d target %.2f: picked b=%d k_b=%d %.2f us; others %s" % (k, target, b, k_b, t_pick, others), flush=True)
                 assert others and t_pick <= band * min(o[0] for o in others)
+        del xs
+        torch.cuda.empty_cache()
+
+
+def test_runtime_estimate_of_queues_against_the_clock():
+    """The same band for queues of two to sixteen slots on rows of 65536 to 2^20 elements: packed bf16 words, pooled floors, sorted batches, lanes that
+    share a column group, and Stage 2 behind them."""
+    band = 1.6
+    shapes = [("bf16", 128, 1 << 20, [(256, 256, 2), (64, 64, 4), (64, 128, 8), (64, 64, 16), (1024, 64, 16)]),
+              ("f32", 128, 1 << 20, [(64, 128, 8), (1024, 1024, 8), (8192, 1024, 8), (1024, 1024, 16)]),
+              ("bf16", 128, 65536, [(16384, 2048, 8), (16384, 1024, 16), (4096, 4096, 2)]),
+              ("f32", 2048, 65536, [(64, 16, 8)]),
+              ("f32", 128, 1 << 18, [(1024, 1024, 8), (4096, 1024, 4)])]
+    for dtype, m, n, cases in shapes:
+        cnt = max(2, min(12, (420 << 20) // (m * n * (4 if dtype == "f32" else 2))))
+        g = torch.Generator(device="cuda").manual_seed(n)
+        xs = [torch.randn((m, n), generator=g, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16) for s in range(cnt)]
+        dt = atk.ATK_F32 if dtype == "f32" else atk.ATK_BF16
+        for (k, b, k_b) in cases:
+            us, est = _time_call_us(xs, k, b, k_b, reps=30), atk.estimate_us(m, n, k, b, k_b, dt)
+            print("estimate %s %dx%d k=%d b=%d k_b=%d: measured %.2f us, estimated %.2f us" % (dtype, m, n, k, b, k_b, us, est), flush=True)
+            assert us / band <= est <= us * band, (dtype, m, n, k, b, k_b, us, est)
         del xs
         torch.cuda.empty_cache()
