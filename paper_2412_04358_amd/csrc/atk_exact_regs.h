@@ -34,7 +34,7 @@ typedef uint32_t row_v4u __attribute__((ext_vector_type(4)));
 
 // The 16-byte boundary at or before row r's first element.  It is reached from x by an offset: an address that has been a number may
 // lie in any memory as far as the compiler knows, and its (flat) loads are waited for together with those of LDS.  Global loads are not:
-// 2048 x 8192 bf16, k = 512: 18.86 -> 18.63 us; 128 x 2^20 f32, k = 2^18: 363.3 -> 361.4; rows in parts the same.
+// 2048 x 8192 bf16, k = 512: 18.86 -> 18.63 us; 128 x 2^20 f32, k = 2^18, and rows in parts the same.
 __device__ __forceinline__ const row_v4u *row_vectors(const void *x, int64_t first_byte) {
     const int64_t off = (int64_t)((((uintptr_t)x + (uintptr_t)first_byte) & ~(uintptr_t)15) - (uintptr_t)x);
     return (const row_v4u *)((const unsigned char *)x + off);

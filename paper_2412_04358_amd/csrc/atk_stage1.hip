@@ -245,7 +245,7 @@ __device__ __forceinline__ void scan_vec(float (&val)[V][KB], int (&tt)[V][KB], 
 // magnitude is 0x8000).  (A wavefront that ends with a zero loads all its survivors' elements again: nothing measurable where they
 // are the rows' first ones, 2 us where they lie all over the rows: 2048 x 8192, half of it -0, b = 512, 20.1 -> 22.3 us, as many loads in flight as
 // there are survivors or a column's: the fetch itself is what takes it.)  Unpacked queues of two slots take 10.4 instructions per element, which the SIMDs issued in 79 % of their
-// cycles on 128 x 2653751; these take 5 and leave such rows to memory: 136 -> 128 us (5.3 TB/s; k_b = 1: 112), 1024 x 131072,
+// cycles on 128 x 2653751; these take 5 and leave such rows to memory: 136 -> 126 us (5.4 TB/s; k_b = 1: 112), 1024 x 131072,
 // b = 512: 56 -> 48.  (A conversion element by element that carried "was -0" in the word took 6 more per element: no gain at two slots.)
 constexpr int32_t kEmptyPk = (int32_t)0x80000000u;
 typedef int16_t pk2 __attribute__((ext_vector_type(2)));
@@ -685,7 +685,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
         if constexpr (BATCH) {
             // k_b matrix rows at a time; the next batches' loads (two with eight slots) are issued before this one is worked on.  Rows past
             // the end re-read the batch's first row and are dropped.  A second batch ahead is for launches of two wavefronts per SIMD,
-            // whose lanes wait for memory together: 256 x 65536, k = 16384, b = 2048, k_b = 8: 29.2 -> 27.2 us; 128 rows 18.1 -> 17.8,
+            // whose lanes wait for memory together: 256 x 65536, k = 16384, b = 2048, k_b = 8: 29.2 -> 27.2 us; 128 rows 17.4 -> 16.9,
             // 64 rows 13.4 -> 12.5; 128 x 2^20, b = 1024: 138 -> 130.
             constexpr int D = KB == 8 ? 2 : 1;  // batches ahead
             RowVec<ELT, V> v[KB], w[D][KB];

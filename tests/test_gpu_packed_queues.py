@@ -17,12 +17,6 @@ def _need_gpu_and_lib():
     atk.load_library()
 
 
-@pytest.fixture
-def plan_override():
-    yield atk.set_plan_override
-    atk.set_plan_override(None)
-
-
 def _check(x, k, b, k_b):
     print("%s k=%d b=%d k_b=%d [%s]" % (tuple(x.shape), k, b, k_b, atk.plan_describe(*x.shape, k, b, k_b, atk.ATK_BF16)), flush=True)
     vals, idx = atk.approx_topk(x.cuda(), k, b, k_b)

@@ -17,12 +17,6 @@ def _need_gpu_and_lib():
     atk.load_library()
 
 
-@pytest.fixture
-def plan_override():
-    yield atk.set_plan_override
-    atk.set_plan_override(None)
-
-
 def _rows(n):
     x = workloads.normal_rows(1, n, seed=n)
     return torch.cat([x, x.sort(dim=1).values, x.sort(dim=1, descending=True).values, workloads.few_levels(1, n, levels=1, seed=1),
