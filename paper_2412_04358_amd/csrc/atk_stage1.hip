@@ -79,13 +79,16 @@ __device__ __forceinline__ void insert(float (&val)[KB], int (&tt)[KB], float v,
 // the queue (short buckets: the top quarter of every bucket is kept when b*k_b = k = n/4) it is cheaper to take
 // k_b matrix rows at a time, sort them with a network, and fold the sorted batch into the queue with the
 // bitonic merge that also joins the lanes' queues.  A network has no notion of "earlier element wins ties", so the queues
-// hold words that are distinct: [62:31] the value's order key, [30:1] 0x3fffffff - the element's number among
-// the lane's rows, [0] "was -0"; 0 = empty.  Bit 63 is clear and, for every number, the exponent field neither
-// all ones nor zero (the key of +inf is 0xff800000, of -inf 0x007fffff), so a word is the bit pattern of a positive normal
-// double and the order of the words is the order of the doubles: a compare-exchange is v_max_f64 and v_min_f64, two
+// hold words that are distinct: [63:32] the float's own bits (-0 as +0), [31:0] 0x7fffffff - the element's number among the lane's
+// rows, inverted where the float is negative.  The order of the words is their order as doubles: sign and magnitude order a
+// double's high word as they order a float, and among equal floats the earlier element has the larger magnitude where that is the
+// larger double, the smaller one where it is not.  The exponent field of +-inf comes out as 0x7f8 (and that of a small float as zero:
+// denormals are kept), so every number makes a finite double, and a compare-exchange is v_max_f64 and v_min_f64, two
 // instructions at full rate, instead of a 64-bit compare and four selects (128 x 65536 f32, k = 16384: k_b = 16:
-// 27.5 -> 20.2 us; k_b = 8, element by element
-// before: 19.1 -> 17.4; one row of 2^20, b = 1024, k_b = 8: 132 -> 30; 64 x 2^20, k = 1024, b = 1024, k_b = 8: 140 -> 88).
+// 27.5 -> 20.2 us; k_b = 8, element by element before: 19.1 -> 17.4; one row of 2^20, b = 1024, k_b = 8: 132 -> 30; 64 x 2^20,
+// k = 1024, b = 1024, k_b = 8: 140 -> 88).  A word is three instructions to make; with the value's order
+// key and "was -0" in it, it took twelve, which with a select for every element of every batch came to half of the scan: 128 x 65536, k = 16384,
+// b = 2048, k_b = 8: 16.9 -> 15.6 us.  Which zeros were -0 is looked up in the row at the end.
 __device__ __forceinline__ double word_max(double a, double b) {
     double d;
     asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));  // (fmax() would quiet its operands first)
@@ -97,10 +100,18 @@ __device__ __forceinline__ double word_min(double a, double b) {
     return d;
 }
 __device__ __forceinline__ double row_word(uint32_t bits, uint32_t s) {
-    const uint32_t key = ukey_of_bits(bits);
-    const uint32_t lo = (key << 31) | ((0x3fffffffu - s) << 1) | (bits == 0x80000000u ? 1u : 0u);
-    return __hiloint2double((int)(key >> 1), (int)lo);
+    const int hi = __float_as_int(__uint_as_float(bits) + 0.0f);
+    return __hiloint2double(hi, (int)(0x7fffffffu - s) ^ (hi >> 31));
 }
+// What marks an empty slot lies below -inf and is a NaN as a float: for bf16 its high half alone.
+constexpr uint32_t kNoWordBits = 0xffef0000u;
+__device__ __forceinline__ double no_word() { return __hiloint2double((int)kNoWordBits, -1); }
+__device__ __forceinline__ uint32_t word_bits(double w) { return (uint32_t)__double2hiint(w); }
+__device__ __forceinline__ bool is_word(double w) { return word_bits(w) <= 0xff800000u; }
+__device__ __forceinline__ uint32_t word_number(double w) {
+    return 0x7fffffffu - (uint32_t)(__double2loint(w) ^ (__double2hiint(w) >> 31));
+}
+__device__ __forceinline__ uint32_t word_key(double w) { return is_word(w) ? ukey_of_bits(word_bits(w)) : 0u; }
 // Batcher's odd-even merge sort of N words, largest first (N a power of two; 19 compare-exchanges for 8, 63 for 16).
 template <int N>
 __device__ __forceinline__ void sort_desc(double (&a)[N]) {
@@ -158,18 +169,17 @@ struct LazyQueue {
     int wait_t;     // and its number (kEmptyT: none)
     __device__ __forceinline__ void clear() {
 #pragma unroll
-        for (int j = 0; j < KB; ++j) q[j] = 0.0;
+        for (int j = 0; j < KB; ++j) q[j] = no_word();
         last = __uint_as_float(0x7fc00000u);
         wait = 0u;
         wait_t = kEmptyT;
     }
     __device__ __forceinline__ void raise() {
-        const uint32_t key = (uint32_t)((u64)__double_as_longlong(q[KB - 1]) >> 31);
-        last = fmaxf(last, __uint_as_float(bits_of_ukey(key)));  // (empty: the key 0 stands for a NaN, and `last` stays)
+        last = fmaxf(last, __uint_as_float(word_bits(q[KB - 1])));  // (empty: a NaN, and `last` stays)
     }
     __device__ __forceinline__ void flush() {
         const double c = row_word(wait, (uint32_t)wait_t);
-        insert_word<KB>(q, wait_t != kEmptyT ? c : 0.0);
+        insert_word<KB>(q, wait_t != kEmptyT ? c : no_word());
         wait_t = kEmptyT;
         raise();
     }
@@ -524,7 +534,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
             tt[e][j] = kEmptyT;
             if constexpr (PK) pk[e][j] = kEmptyPk;
             if constexpr (BATCH) {
-                qw[e][j] = 0.0;
+                qw[e][j] = no_word();
                 last_f[e] = __uint_as_float(0x7fc00000u);
             }
         }
@@ -618,7 +628,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
             for (int e = 0; e < V; ++e)
 #pragma unroll
                 for (int j = 0; j < KB; ++j)
-                    keys[e][j] = (uint32_t)((u64)__double_as_longlong(lazy[e].q[j]) >> 31);
+                    keys[e][j] = word_key(lazy[e].q[j]);
             if (p.wave_merge) {
                 for (int off = p.Gw; off < kWave; off <<= 1) {
 #pragma unroll
@@ -706,27 +716,36 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
                 const int tn = t + KB * step;
                 const bool more = tn < t1;
                 if (tn + (D - 1) * KB * step < t1) fetch(w[D - 1], tn + (D - 1) * KB * step);
+                if (__ballot(t + (KB - 1) * step >= t1) != 0ull) {  // (a lane's last rows)
+#pragma unroll
+                    for (int u = 1; u < KB; ++u)
+                        if (t + u * step >= t1) {
+#pragma unroll
+                            for (int w = 0; w < RowVec<ELT, V>::kWords; ++w) v[u].w[w] = ELT == ATK_F32 ? kNoWordBits : (kNoWordBits | (kNoWordBits >> 16));
+                        }
+                }
                 // one compare per element, and a wavefront-uniform skip, keep long buckets cheap: an element enters
                 // only if it beats the queue's last slot (equal values never displace earlier ones)
                 bool any = false;
 #pragma unroll
                 for (int u = 0; u < KB; ++u)
 #pragma unroll
-                    for (int e = 0; e < V; ++e)
-                        any = any || (t + u * step < t1 && !(__uint_as_float(elem_bits<ELT, V>(v[u], e)) <= last_f[e]));
+                    for (int e = 0; e < V; ++e) any = any || !(__uint_as_float(elem_bits<ELT, V>(v[u], e)) <= last_f[e]);
                 if (__ballot(any) != 0ull) {
+                    const bool first = __ballot(is_word(qw[V - 1][0])) == 0ull;  // (the head of a virtual row holds its last column at least)
 #pragma unroll
                     for (int e = 0; e < V; ++e) {
                         double bt[KB];
 #pragma unroll
-                        for (int u = 0; u < KB; ++u) {
-                            const double c = row_word(elem_bits<ELT, V>(v[u], e), seq + (uint32_t)u);
-                            bt[u] = t + u * step < t1 ? c : 0.0;
-                        }
+                        for (int u = 0; u < KB; ++u) bt[u] = row_word(elem_bits<ELT, V>(v[u], e), seq + (uint32_t)u);
                         sort_desc<KB>(bt);
-                        merge_words<KB>(qw[e], bt);
-                        const u64 lw = (u64)__double_as_longlong(qw[e][KB - 1]);
-                        last_f[e] = __uint_as_float(lw ? bits_of_ukey((uint32_t)(lw >> 31)) : 0x7fc00000u);
+                        if (first) {
+#pragma unroll
+                            for (int j = 0; j < KB; ++j) qw[e][j] = bt[j];
+                        } else {
+                            merge_words<KB>(qw[e], bt);
+                        }
+                        last_f[e] = __uint_as_float(word_bits(qw[e][KB - 1]));
                     }
                 }
                 seq += KB;
@@ -854,40 +873,37 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
 #pragma unroll
         for (int e = 0; e < V; ++e)
 #pragma unroll
-            for (int j = 0; j < KB; ++j) {
-                const u64 c = (u64)__double_as_longlong(qw[e][j]);
-                if (c != 0ull) {
-                    val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 31)));
-                    tt[e][j] = t0 + ph + (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu)) * p.P;
+            for (int j = 0; j < KB; ++j)
+                if (is_word(qw[e][j])) {
+                    val[e][j] = __uint_as_float(word_bits(qw[e][j]));
+                    tt[e][j] = t0 + ph + (int)word_number(qw[e][j]) * p.P;
                 }
-            }
     }
     if constexpr (RF) {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             lazy[e].flush();
 #pragma unroll
-            for (int j = 0; j < KB; ++j) {
-                const u64 c = (u64)__double_as_longlong(lazy[e].q[j]);
-                if (c != 0ull) {
-                    val[e][j] = __uint_as_float(((uint32_t)c & 1u) ? 0x80000000u : bits_of_ukey((uint32_t)(c >> 31)));
-                    const int t = (int)(0x3fffffffu - (((uint32_t)c >> 1) & 0x3fffffffu));
+            for (int j = 0; j < KB; ++j)
+                if (is_word(lazy[e].q[j])) {
+                    val[e][j] = __uint_as_float(word_bits(lazy[e].q[j]));
+                    const int t = (int)word_number(lazy[e].q[j]);
                     tt[e][j] = t < pooled_rows ? t0 + ph + t * p.P : t_resume + (t - pooled_rows);
                 }
-            }
         }
     }
-    if constexpr (PK) {
+    if constexpr (PK || BATCH || RF) {
         bool zero = false;
 #pragma unroll
         for (int e = 0; e < V; ++e)
 #pragma unroll
             for (int j = 0; j < KB; ++j) {
-                unpack_bf16(pk[e][j], t0, val[e][j], tt[e][j]);
+                if constexpr (PK) unpack_bf16(pk[e][j], t0, val[e][j], tt[e][j]);
                 zero = zero || __float_as_uint(val[e][j]) == 0u;
             }
         if (__ballot(zero) != 0ull) {  // +0 or -0: the element itself says (a column's loads in flight together)
-            const uint16_t *row = (const uint16_t *)p.x + (int64_t)r * p.n;
+            typedef typename std::conditional<ELT == ATK_F32, uint32_t, uint16_t>::type word_t;
+            const word_t *row = (const word_t *)p.x + (int64_t)r * p.n;
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 uint32_t own[KB];
@@ -896,7 +912,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
                     own[j] = row[__float_as_uint(val[e][j]) == 0u ? (int64_t)tt[e][j] * p.b + col0 + e - rot : 0];
 #pragma unroll
                 for (int j = 0; j < KB; ++j)
-                    if (__float_as_uint(val[e][j]) == 0u) val[e][j] = __uint_as_float(own[j] << 16);
+                    if (__float_as_uint(val[e][j]) == 0u) val[e][j] = __uint_as_float(own[j] << (ELT == ATK_F32 ? 0 : 16));
             }
         }
     }

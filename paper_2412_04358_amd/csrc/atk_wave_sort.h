@@ -1,0 +1,150 @@
+// A wavefront's 64 * W words, sorted or cut to their largest in its registers.
+#pragma once
+
+#include "atk_common.h"
+#include "atk_select.h"
+
+namespace atk {
+
+#ifdef __HIPCC__
+
+__device__ __forceinline__ int32_t med3_i32(int32_t a, int32_t b, int32_t c) { return max(min(a, b), min(max(a, b), c)); }  // v_med3_i32
+
+// Bitonic networks (Batcher 1968) over words that lie in the lanes' registers: no LDS, no barrier, and the same time whatever the words are.
+// A block is 64 * R words in R registers.  The low bits of a word's place in its block are the register's number - the low bits are
+// compared most often, and there a comparison is a minimum and a maximum - and the next six the lane's: four by DPP (a move and a median
+// for either word), two by v_permlane16_swap / v_permlane32_swap, which bring the words of two registers together and back.  A median with the
+// largest or the smallest word in place of a third one is the maximum or the minimum, as a lane's place in the network wants it.
+// place bits of a lane: x0 x1 x2 x3 with lane = x0 * 1 ^ x1 * 2 ^ x2 * 7 ^ x3 * 8 (what quad_perm, half_mirror and row_ror:8 reach), then bits 4 and 5
+struct LanePlace {
+    int32_t most[6];  // INT_MAX where the bit is clear: there a block's larger words go; else INT_MIN
+    int place;
+    __device__ __forceinline__ LanePlace() {
+        const int lane = threadIdx.x & (kWave - 1);
+        place = lane ^ ((lane & 4) ? 3 : 0);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) most[i] = ((place >> i) & 1) ? (int32_t)0x80000000 : 0x7fffffff;
+    }
+};
+
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp_i32(int32_t v) {
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+
+constexpr int log2_c(int v) { return v <= 1 ? 0 : 1 + log2_c(v >> 1); }
+
+// One step: the words whose places differ in bit J alone, in the direction that bit P of the place says (P = log2(64 R): odd blocks smallest
+// first; P = 31: every block largest first).
+template <int W, int R, int P, int J>
+__device__ __forceinline__ void wave_sort_step(int32_t (&w)[W], const LanePlace &at) {
+    constexpr int LR = log2_c(R), LN = LR + 6;
+    // direction: known at compile time (the register's number decides), or one of the lane's bits
+    constexpr bool by_lane = P >= LR && P < LN;
+    auto up = [](int i) { return P == 31 ? false : (P == LN ? ((i / R) & 1) != 0 : ((i >> P) & 1) != 0); };  // smallest first
+    if constexpr (J < LR) {
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+            if ((i & (1 << J)) == 0) {
+                const int32_t a = w[i], b = w[i | (1 << J)];
+                if constexpr (by_lane) {
+                    const int32_t m = at.most[P - LR];
+                    w[i] = med3_i32(a, b, m);
+                    w[i | (1 << J)] = med3_i32(a, b, ~m);
+                } else {
+                    w[i] = up(i) ? min(a, b) : max(a, b);
+                    w[i | (1 << J)] = up(i) ? max(a, b) : min(a, b);
+                }
+            }
+    } else {
+        constexpr int Q = J - LR;
+        constexpr int32_t kMost = 0x7fffffff;
+        if constexpr (Q < 4) {
+            constexpr int ctrl = Q == 0 ? 0xB1 : (Q == 1 ? 0x4E : (Q == 2 ? 0x141 : 0x128));
+            const int32_t m = by_lane ? (at.most[Q] ^ at.most[by_lane ? P - LR : 0] ^ kMost) : at.most[Q];
+#pragma unroll
+            for (int i = 0; i < W; ++i) w[i] = med3_i32(w[i], dpp_i32<ctrl>(w[i]), !by_lane && up(i) ? ~m : m);
+        } else {
+            const int32_t m = by_lane ? at.most[by_lane ? P - LR : 0] : kMost;
+            auto swap = [](int32_t &a, int32_t &b) {
+                const auto s = Q == 4 ? __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false)
+                                      : __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+                a = (int32_t)s[0];
+                b = (int32_t)s[1];
+            };
+            if constexpr (R >= 2) {
+#pragma unroll
+                for (int i = 0; i < W; i += 2) {
+                    int32_t a = w[i], b = w[i + 1];
+                    swap(a, b);
+                    int32_t x, y;
+                    if constexpr (by_lane) {
+                        x = med3_i32(a, b, m);
+                        y = med3_i32(a, b, ~m);
+                    } else {
+                        x = up(i) ? min(a, b) : max(a, b);
+                        y = up(i) ? max(a, b) : min(a, b);
+                    }
+                    swap(x, y);
+                    w[i] = x;
+                    w[i + 1] = y;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    int32_t a = w[i], b = w[i];
+                    swap(a, b);
+                    const int32_t mine = by_lane ? (at.most[Q] ^ m ^ kMost) : (up(i) ? ~at.most[Q] : at.most[Q]);
+                    w[i] = med3_i32(a, b, mine);
+                }
+            }
+        }
+    }
+}
+
+template <int W, int R, int P, int J>
+__device__ __forceinline__ void wave_sort_steps(int32_t (&w)[W], const LanePlace &at) {  // bits J, J - 1, ... 0
+    wave_sort_step<W, R, P, J>(w, at);
+    if constexpr (J > 0) wave_sort_steps<W, R, P, J - 1>(w, at);
+}
+template <int W, int R, int P>
+__device__ __forceinline__ void wave_sort_blocks(int32_t (&w)[W], const LanePlace &at) {  // from runs of 2^(P - 1) words in alternating order
+    constexpr int LN = log2_c(R) + 6;
+    if constexpr (P < LN) {
+        wave_sort_steps<W, R, P, P - 1>(w, at);
+        wave_sort_blocks<W, R, P + 1>(w, at);
+    } else {
+        wave_sort_steps<W, R, W == R ? 31 : P, P - 1>(w, at);
+    }
+}
+// Blocks sorted largest first and smallest first in turn -> the largest block of all of them, largest first.  Of two such blocks the
+// larger word of each place is among the larger half, and these lie in bitonic order again.
+template <int W, int R>
+__device__ __forceinline__ void wave_join_blocks(const int32_t (&w)[W], int32_t (&top)[R], const LanePlace &at) {
+    if constexpr (W == R) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) top[i] = w[i];
+    } else {
+        constexpr int H = W / 2, LN = log2_c(R) + 6;
+        int32_t h[H];
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int block = i / R, in = i % R;
+            h[i] = max(w[2 * block * R + in], w[(2 * block + 1) * R + in]);
+        }
+        wave_sort_steps<H, R, H == R ? 31 : LN, LN - 1>(h, at);
+        wave_join_blocks<H, R>(h, top, at);
+    }
+}
+// The 64 * R largest of the wavefront's 64 * W words, largest first: lane l's top[i] is number R * at.place + i.  sorted: the words already lie in
+// runs of that many (a power of two below R), in registers side by side, largest first where the run's number is even, smallest first where odd.
+template <int W, int R, int SORTED>
+__device__ __forceinline__ void wave_largest(int32_t (&w)[W], int32_t (&top)[R], const LanePlace &at) {
+    static_assert(SORTED == 1 || SORTED < R, "runs inside a lane's registers of a block");
+    wave_sort_blocks<W, R, log2_c(SORTED) + 1>(w, at);
+    wave_join_blocks<W, R>(w, top, at);
+}
+
+#endif  // __HIPCC__
+
+}  // namespace atk
