@@ -154,8 +154,10 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
 
 /*
  * Writes a one-line, human-readable description of the launch plan the library would use
- * (threads per workgroup, lanes per bucket column, row splits, fused Stage 2, ...) into
+ * (threads per workgroup, lanes per bucket column, row splits, Stage 2, ...) into
  * buf (NUL-terminated, truncated to buflen).  Host only; used by tests and the benchmark log.
+ * stage2=0: none; 1: in the workgroup that streamed, through LDS; 2: by exact_topk's kernels over pairs in scratch or, where wave=<n> is not
+ * 0, by a sort in the registers of the one wavefront that has the row (n words of each lane are written).
  * The plan can be overridden for tuning and tests with the environment variable ATK_PLAN (read once, when
  * the library is loaded) or with atk_set_plan_override(), a comma
  * separated list of: T=<threads per workgroup: 64..1024>, S=<workgroups a row is split over>,
@@ -172,7 +174,8 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * MH=0 / MH=<h> (k_b = 1: split rows never / with h helpers run as helpers and a finisher that meet through
  * mailboxes instead of partial lists and a ticket; HF=0 switches these off as well), BO=0 (Stage 2's bins take their
  * key range from the merged candidates, never from the bounds that come with the merge), RF=0 / RF=<n> (queues of
- * eight slots never / after 4n matrix rows of a lane for the first time pool their floors).
+ * eight slots never / after 4n matrix rows of a lane for the first time pool their floors), WV=0 / WV=1 (bf16 rows are never / wherever
+ * they can be one wavefront's each; a key above that names a plan of approx_topk, WV itself aside, implies WV=0).
  * Values the kernels cannot take are ignored or clamped; results never depend on the plan.
  */
 int atk_plan_describe(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, char *buf,

@@ -94,6 +94,7 @@ static PlanOverride parse_plan_override(const char *e) {
     if (const char *q = field("RF")) o.rf = atoi(q) <= 0 ? -1 : atoi(q);
     if (const char *q = field("SL")) o.sl = atoi(q);
     if (const char *q = field("BO")) o.bo_off = atoi(q) == 0;
+    if (const char *q = field("WV")) o.wv = atoi(q) == 0 ? -1 : 1;
     if (const char *q = field("MH")) {
         const int v = atoi(q);
         o.mh = v <= 0 ? -1 : (v <= 255 ? v : 0);
@@ -102,6 +103,7 @@ static PlanOverride parse_plan_override(const char *e) {
         const int v = atoi(q);
         if (v >= 1 && v <= 63) o.hq = v;
     }
+    if (!o.wv && (o.T || o.S || o.V || o.P || o.pk_off || o.lm_off || o.ln_off || o.ts || o.hf || o.bo_off || o.rf || o.mh)) o.wv = -1;
     return o;
 }
 static PlanOverride g_plan_override = parse_plan_override(getenv("ATK_PLAN"));  // read once, at load
@@ -820,6 +822,25 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
     return false;
 }
 
+// Rows of one wavefront each (atk_wave_row.hip), against the plans that they replace there, over 1664 calls (1 to 4096 rows of 1024 to 65536
+// elements, 128 to 1024 buckets, one to eight slots, k from 64 to 1500):
+//   up to 12288 elements   0.13 to 1.07 times as long, whatever the number of rows: the wavefront sorts in 1 to 4 us where the steps
+//                          with a barrier after each take the workgroup longer (4 x 4096, k = 256, b = 512, 12.6 -> 4.7 us; 2048 x 8192,
+//                          k = 512, b = 512, k_b = 2, 20.6 -> 13.5)
+//   to 16384               0.59 to 1.08 from 768 rows on; with fewer, one wavefront reads a row too slowly (128 rows 0.79 to 1.22)
+//   to 32768               with queues 0.74 to 0.93 from 1024 rows on where the lanes read 16 bytes each, 0.32 to 0.99 from 2048 on; one slot up to 1.15
+//   to 65536               with queues and 1024 and more candidates 0.46 to 0.98 from 2048 rows on
+// k > 1024 (32 sorted words to a lane) takes 1.07 to 1.33 times as long from 256 rows on.
+bool wave_row_wins(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b) {
+    if (plan_override().wv) return plan_override().wv > 0;
+    if (k > 1024) return false;
+    if (n <= 12288) return true;
+    if (n <= 16384) return m >= 768;
+    if (k_b < 2) return false;
+    if (n <= 32768) return m >= (b > 256 ? 1024 : 2048);
+    return m >= 2048 && b * k_b >= 1024;
+}
+
 // ------------------------------------------------------------------------------------ scratch pool
 // Two grow-only allocations per device: `state` (tickets and other words that every kernel
 // leaves zeroed, so that the next call can rely on zeros) and `data` (partial lists and
@@ -999,6 +1020,8 @@ int atk_last_hip_error(void) { return g_last_hip_error; }
 // exact selection over the candidates when there are more of them than one workgroup holds
 struct FullPlan {
     Plan s1;
+    bool wave;               // one wavefront per row: the whole call, without scratch
+    WavePlan wv;
     bool two_step;
     ExactPlan ex;            // two_step: selection over the b*k_b candidates of (a block of) the rows
     int64_t cand_vals_off;   // byte offsets into the data pool
@@ -1049,10 +1072,24 @@ static int make_exact_plans(int64_t m, int64_t n, int64_t k, int dtype, bool pai
 }
 
 static int make_full_plan(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, int assignment,
-                          bool ptr16, FullPlan *fp, bool allow_pair = true, bool cover = false, bool allow_two = true) {
+                          bool ptr16, FullPlan *fp, bool allow_pair = true, bool cover = false, bool allow_two = true, bool allow_wave = true) {
     if (assignment != ATK_INTERLEAVED && assignment != ATK_CONTIGUOUS) return ATK_ERR_BAD_PARAMS;
     const int es = (dtype == ATK_F32) ? 4 : 2;
     const int64_t nc = b * k_b;
+    fp->wave = allow_wave && assignment == ATK_INTERLEAVED && wave_row_wins(m, n, k, b, k_b) && plan_wave_row(m, n, k, b, k_b, dtype, ptr16, &fp->wv);
+    if (fp->wave) {
+        memset(&fp->s1, 0, sizeof fp->s1);
+        fp->s1.V = fp->wv.V;
+        fp->s1.KB = fp->wv.KB;
+        fp->s1.T = fp->s1.Gw = kWave;
+        fp->s1.P = fp->s1.colblocks = fp->s1.S = fp->s1.nparts = 1;
+        fp->s1.rows_per_split = (int)ceil_div(n, b);
+        fp->s1.grid = m;
+        fp->s1.stage2 = fp->s1.packed = true;
+        fp->two_step = false;
+        fp->state_bytes = fp->data_bytes = 0;
+        return ATK_OK;
+    }
     fp->two_step = nc > k && (nc > kStage2MaxCand || (allow_two && stage2_apart(m, n, k, b, k_b, dtype)));
     if (!fp->two_step && nc > k && allow_two && !plan_override().ts && assignment == ATK_CONTIGUOUS) {
         // contiguous buckets: several workgroups per row that meet through a ticket, on launches past two workgroups per CU (128 x
@@ -1117,15 +1154,19 @@ static int run_approx(const void *x, int64_t m, int64_t n, int64_t k, int64_t b,
     if (((uintptr_t)x | (uintptr_t)out_vals) & (uintptr_t)(es - 1)) return ATK_ERR_ALIGN;
     if ((uintptr_t)out_idx & 3u) return ATK_ERR_ALIGN;
     FullPlan fp;
-    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, ((uintptr_t)x & 15u) == 0, &fp, true, false, trace == nullptr);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, ((uintptr_t)x & 15u) == 0, &fp, true, false, trace == nullptr, trace == nullptr);
     if (rc != ATK_OK) return rc;
     if (trace) {  // measurement build: the lean kernels alone, and room for every wavefront's timestamps
         if (fp.two_step || assignment != ATK_INTERLEAVED || !fp.s1.lean) return ATK_ERR_UNSUPPORTED;
         if (trace_bytes < fp.s1.grid * kTraceWaves * kTracePhases * 8 || fp.s1.T > kTraceWaves * kWave) return ATK_ERR_BAD_SHAPE;
     }
+    hipError_t e = hipSuccess;
+    if (fp.wave) {
+        e = launch_wave_row(fp.wv, m, n, k, b, k_b, x, out_vals, out_idx, (hipStream_t)stream);
+        return e == hipSuccess ? ATK_OK : hip_fail(e);
+    }
     void *state = nullptr, *data = nullptr;
     PoolUse pool;
-    hipError_t e = hipSuccess;
     if (fp.state_bytes || fp.data_bytes) {
         e = pool.begin();
         if (e != hipSuccess) return hip_fail(e);
@@ -1232,8 +1273,8 @@ int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, true, &fp, true, true);
     if (rc != ATK_OK) return rc;
     const Plan &pl = fp.s1;
-    // two steps: Stage 2 is the long-row exact selection over the candidates Stage 1 left in scratch
-    const int stage2 = fp.two_step ? 2 : (int)pl.stage2;
+    // 2: not the selection by bins and digits in LDS, but exact_topk's kernels over the pairs Stage 1 left in scratch, or a sort in registers
+    const int stage2 = fp.two_step || fp.wave ? 2 : (int)pl.stage2;
     if (assignment == ATK_CONTIGUOUS)
         snprintf(buf, (size_t)buflen,
                  "contiguous V=%d KB=%d T=%d Gs=%d NB=%d bblocks=%d S=%d chunks_per_split=%d grid=%lld stage2=%d "
@@ -1243,10 +1284,11 @@ int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     else
         snprintf(buf, (size_t)buflen,
                  "V=%d KB=%d T=%d Gw=%d P=%d colblocks=%d S=%d rows_per_split=%d grid=%lld stage2=%d direct=%d "
-                 "scratch=%d wave_merge=%d nparts=%d lds=%d scratch_bytes=%lld packed=%d lean=%d pair_rows=%d refresh=%d helpers=%d",
+                 "scratch=%d wave_merge=%d nparts=%d lds=%d scratch_bytes=%lld packed=%d lean=%d pair_rows=%d refresh=%d helpers=%d wave=%d",
                  pl.V, pl.KB, pl.T, pl.Gw, pl.P, pl.colblocks, pl.S, pl.rows_per_split, (long long)pl.grid, stage2,
                  (int)pl.direct, (int)pl.use_scratch, (int)pl.wave_merge, pl.nparts, pl.lds_bytes,
-                 (long long)(fp.state_bytes + fp.data_bytes), (int)pl.packed, (int)pl.lean, pl.pair_rows, pl.refresh, pl.helpers);
+                 (long long)(fp.state_bytes + fp.data_bytes), (int)pl.packed, (int)pl.lean, pl.pair_rows, pl.refresh, pl.helpers,
+                 fp.wave ? fp.wv.R : 0);
     return ATK_OK;
 }
 
@@ -1294,7 +1336,8 @@ int approx_topk_noalloc(const void *x, int64_t m, int64_t n, int64_t k, int64_t 
         const hipError_t ez = hipGetLastError();
         if (ez != hipSuccess) return hip_fail(ez);
     }
-    const hipError_t e = fp.s1.lean ? launch_approx_lean(fp.s1, x, out_vals, out_idx, nullptr, (hipStream_t)stream)
+    const hipError_t e = fp.wave      ? launch_wave_row(fp.wv, m, n, k, b, k_b, x, out_vals, out_idx, (hipStream_t)stream)
+                         : fp.s1.lean ? launch_approx_lean(fp.s1, x, out_vals, out_idx, nullptr, (hipStream_t)stream)
                                     : launch_approx(fp.s1, x, out_vals, out_idx, base,
                                                     base ? base + ATK_NOALLOC_STATE_BYTES : nullptr, (hipStream_t)stream);
     return e == hipSuccess ? ATK_OK : hip_fail(e);
@@ -1328,7 +1371,7 @@ int64_t atk_trace_bytes(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b,
     int rc = check_approx(m, n, k, b, k_b, dtype);
     if (rc != ATK_OK) return rc;
     FullPlan fp;
-    rc = make_full_plan(m, n, k, b, k_b, dtype, ATK_INTERLEAVED, true, &fp, true, false, false);
+    rc = make_full_plan(m, n, k, b, k_b, dtype, ATK_INTERLEAVED, true, &fp, true, false, false, false);
     if (rc != ATK_OK) return rc;
     return fp.s1.grid * kTraceWaves * kTracePhases * 8;
 }

@@ -89,6 +89,7 @@ struct PlanOverride {
     bool ln_off;      // LN=0: never the lean kernels
     int rf;           // RF=0: queues never pool their floors; RF=<n>: first after 4n matrix rows of a lane (0 not set)
     bool bo_off;      // BO=0: Stage 2's bins never take their range from the merge
+    int wv;           // rows of one wavefront: 0 not set, 1 wherever they can be (WV=1), -1 never (WV=0, and under every key that names another plan)
     int mh;           // MH=0: no helpers + finisher plans for split rows (-1); MH=<h>: that many helpers where legal (0 not set)
 };
 const PlanOverride &plan_override();
@@ -156,6 +157,16 @@ hipError_t launch_approx_contig(const Plan &plan, const void *x, void *out_vals,
 // (plan.scratch_ticket_bytes, zero between calls), else unused.  trace: as for launch_approx.
 hipError_t launch_approx_lean(const Plan &plan, const void *x, void *out_vals, int32_t *out_idx, void *state,
                               hipStream_t stream, void *trace = nullptr);
+
+// approx_topk of bf16 rows that a wavefront takes alone (atk_wave_row.hip): columns per lane, column groups, slots, registers that the sorted outputs
+// take.  false: not such a call.
+struct WavePlan {
+    int V, NG, KB, R;
+};
+bool wave_row_wins(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b);  // (where it can be chosen at all)
+bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, bool ptr16, WavePlan *out);
+hipError_t launch_wave_row(const WavePlan &pl, int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, const void *x, void *out_vals,
+                           int32_t *out_idx, hipStream_t stream);
 
 // ------------------------------------------------------------------------------------
 // Device helpers.

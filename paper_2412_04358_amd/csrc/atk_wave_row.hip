@@ -1,0 +1,269 @@
+// approx_topk of bf16 rows that one wavefront takes from the first load to the last output: batches that give the chip's SIMDs a row
+// or two each, where Stage 2 over lists in LDS (or in scratch, by a launch of its own) is a chain of short steps with a barrier
+// after each.
+//
+//   1. A lane owns V adjacent columns of the row seen as a matrix (twice that, 64 V columns apart, where NG = 2) and walks down all matrix rows,
+//      as in atk_stage1.hip, with queues of packed words.
+//   2. The queues' words exchange the matrix row for the column index, which 16 bits hold, and are the candidates as they stand: larger word,
+//      larger value or equal value and lower index.
+//   3. The wavefront sorts them in its registers (atk_wave_sort.h), cut to the k largest on the way, and lane l has the l-th stretch of the output.
+// No LDS, no barrier, no scratch, no second launch, and the same time for rows without order, sorted ones and ties.
+//
+// What bounds it: on 2048 rows, two to a SIMD, the sort of the rows that are in last, after the memory's 7 us (1270 vector instructions a row where 512 of
+// 1024 words are wanted, one in four cycles: 2.1 us); with more rows memory (3.6 us per 1024 rows of 8192).  2048 x 8192, k = 512, b = 512,
+// k_b = 2: 20.0 -> 12.1 us a call (Stage 1 and the selection from its pairs before, two launches), values on a grid of halves 55 -> 13.5;
+// 4 x 4096, k = 256, b = 512: 12.6 -> 4.7.
+#include <cstring>
+
+#include "atk_common.h"
+#include "atk_packed.h"
+#include "atk_stream.h"
+#include "atk_wave_sort.h"
+
+namespace atk {
+
+struct WaveParams {
+    const void *x;
+    void *out_vals;
+    int32_t *out_idx;
+    int64_t n;
+    int b, L, rem;    // columns, full matrix rows, columns of the ragged last one
+    int k, k_b;
+    int whole;        // every lane has columns, every slot a survivor
+    int vec_store;    // outputs in pieces of min(R, 8) words start on boundaries of as many
+};
+
+typedef uint32_t wave_v4u __attribute__((ext_vector_type(4)));
+typedef uint32_t wave_v2u __attribute__((ext_vector_type(2)));
+
+// The values' bits (bf16, two to a word) of two candidate words
+__device__ __forceinline__ uint32_t wave_pair_bits(int32_t even, int32_t odd) {
+    const uint32_t keys = ((uint32_t)even >> 16) | ((uint32_t)odd & 0xffff0000u);
+    const pk2 v = __builtin_bit_cast(pk2, keys), sgn = v >> 15;
+    const pk2 mag = __builtin_bit_cast(pk2, keys ^ __builtin_bit_cast(uint32_t, sgn)) - sgn;
+    return __builtin_bit_cast(uint32_t, mag) | (__builtin_bit_cast(uint32_t, sgn) & 0x80008000u);
+}
+__device__ __forceinline__ int32_t wave_index(int32_t c) { return (int32_t)(0xffffu - ((uint32_t)c & 0xffffu)); }
+
+// top[0 .. R): outputs first, first + 1, ... of row r
+template <int R>
+__device__ __forceinline__ void wave_write(const WaveParams &p, int64_t r, int first, const int32_t (&top)[R]) {
+    constexpr int H = R < 2 ? 1 : R / 2;
+    uint32_t bits[H];
+    bool zero = false;
+#pragma unroll
+    for (int i = 0; i < H; ++i) bits[i] = wave_pair_bits(top[2 * i], R < 2 ? 0 : top[2 * i + 1]);
+#pragma unroll
+    for (int i = 0; i < R; ++i) zero = zero || ((uint32_t)top[i] >> 16) == 0u;
+    if (__ballot(zero) != 0ull) {  // +0 or -0: the element itself says
+        const uint16_t *row = (const uint16_t *)p.x + r * p.n;
+        uint32_t own[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) own[i] = row[((uint32_t)top[i] >> 16) == 0u ? wave_index(top[i]) : 0];
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            if (((uint32_t)top[i] >> 16) == 0u) bits[i / 2] |= (i & 1) ? own[i] << 16 : own[i];
+    }
+    uint16_t *vals = (uint16_t *)p.out_vals + r * p.k;
+    int32_t *idx = p.out_idx + r * p.k;
+    if (p.vec_store) {  // (p.k is a multiple of the pieces, too)
+        constexpr int C = R < 8 ? R : 8;
+#pragma unroll
+        for (int c = 0; c < R; c += C) {
+            const int o = first + c;
+            if (o >= p.k) break;
+            if constexpr (C == 8) {
+                *(wave_v4u *)(vals + o) = wave_v4u{bits[c / 2], bits[c / 2 + 1], bits[c / 2 + 2], bits[c / 2 + 3]};
+            } else if constexpr (C == 4) {
+                *(wave_v2u *)(vals + o) = wave_v2u{bits[0], bits[1]};
+            } else if constexpr (C == 2) {
+                *(uint32_t *)(vals + o) = bits[0];
+            } else {
+                vals[o] = (uint16_t)bits[0];
+            }
+            if constexpr (C >= 4) {
+#pragma unroll
+                for (int i = 0; i < C; i += 4)
+                    *(wave_v4u *)(idx + o + i) = wave_v4u{(uint32_t)wave_index(top[c + i]), (uint32_t)wave_index(top[c + i + 1]),
+                                                          (uint32_t)wave_index(top[c + i + 2]), (uint32_t)wave_index(top[c + i + 3])};
+            } else {
+#pragma unroll
+                for (int i = 0; i < C; ++i) idx[o + i] = wave_index(top[c + i]);
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (first + i < p.k) {
+            vals[first + i] = (uint16_t)((i & 1) ? bits[i / 2] >> 16 : bits[i / 2]);
+            idx[first + i] = wave_index(top[i]);
+        }
+}
+
+template <int V, int NG, int KB, int R>
+__global__ void __launch_bounds__(64, 2) wave_row_kernel(WaveParams p) {
+    constexpr int W = V * NG * KB, U = V * NG >= 16 ? 8 : 16;  // U matrix rows' loads to a batch
+    constexpr int RUN = KB < R ? KB : 1;
+    typedef RowVec<ATK_BF16, V> Vec;
+    const int lane = threadIdx.x;
+    const uint32_t row_bytes = (uint32_t)p.b * 2u;
+    const LanePlace at;
+    int col0[NG];
+    uint32_t off[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        col0[g] = (g * kWave + lane) * V;
+        off[g] = col0[g] < p.b ? (uint32_t)col0[g] * 2u : 0u;  // (a lane without columns reads the first ones)
+    }
+    const int64_t r = blockIdx.x;
+    const unsigned char *row = (const unsigned char *)p.x + r * p.n * 2;
+    int32_t q[NG * V][KB];
+#pragma unroll
+    for (int c = 0; c < NG * V; ++c)
+#pragma unroll
+        for (int j = 0; j < KB; ++j) q[c][j] = kEmptyPk;
+    auto feed = [&](const Vec &vec, int g, int t) {
+        int32_t part[V][KB];
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+#pragma unroll
+            for (int j = 0; j < KB; ++j) part[e][j] = q[g * V + e][j];
+        scan_vec_pk<ATK_BF16, V, KB>(part, vec, t);
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+#pragma unroll
+            for (int j = 0; j < KB; ++j) q[g * V + e][j] = part[e][j];
+    };
+    // ---- Stage 1.  The next batch is asked for before this one is worked on.
+    {
+        Vec v[U][NG], ahead[U][NG];
+        auto load = [&](Vec (&to)[U][NG], int t) {  // matrix rows t, t + 1, ...; past the last one that again
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned char *from = row + (uint32_t)min(t + u, p.L - 1) * row_bytes;
+#pragma unroll
+                for (int g = 0; g < NG; ++g) to[u][g] = load_vec<ATK_BF16, V>(from + off[g]);
+            }
+        };
+        load(v, 0);
+        for (int t = 0; t < p.L; t += U) {
+            if (t + U < p.L) load(ahead, t + U);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t + U <= p.L) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) feed(v[u][g], g, t + u);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U - 1; ++u)
+                    if (t + u < p.L) {  // uniform
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) feed(v[u][g], g, t + u);
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int g = 0; g < NG; ++g) v[u][g] = ahead[u][g];
+        }
+        if (p.rem > 0) {  // the ragged last matrix row: its first p.rem columns, which end where the row does
+            const unsigned char *last = row + (uint32_t)p.L * row_bytes;
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                if (col0[g] + V <= p.rem) {  // (rem is a multiple of V, as n and b are)
+                    const Vec one = load_vec<ATK_BF16, V>(last + off[g]);
+                    feed(one, g, p.L);
+                }
+        }
+    }
+    // ---- candidates: [31:16] the value, [15:0] 0xffff - index
+    int32_t w[W];
+#pragma unroll
+    for (int c = 0; c < NG * V; ++c) {
+        const uint16_t first = (uint16_t)(0xffffu - 0xffffu * (uint32_t)p.b - (uint32_t)(col0[c / V] + c % V));
+        const bool flip = RUN > 1 && (c & 1);
+#pragma unroll
+        for (int j = 0; j < KB; ++j) {
+            const uint16_t low = (uint16_t)((uint16_t)q[c][j] * (uint16_t)p.b + first);
+            w[c * KB + (flip ? KB - 1 - j : j)] = (int32_t)(((uint32_t)q[c][j] & 0xffff0000u) | low);
+        }
+    }
+    if (!p.whole) {
+#pragma unroll
+        for (int c = 0; c < NG * V; ++c)
+#pragma unroll
+            for (int j = 0; j < KB; ++j) {
+                int32_t &word = w[c * KB + (RUN > 1 && (c & 1) ? KB - 1 - j : j)];
+                word = col0[c / V] < p.b && j < p.k_b ? word : kEmptyPk;
+            }
+    }
+    // ---- Stage 2
+    int32_t top[R];
+    wave_largest<W, R, RUN>(w, top, at);
+    wave_write<R>(p, r, R * at.place, top);
+}
+
+// ------------------------------------------------------------------------------------ host
+// Instances: X(columns per lane V, column groups NG, slots KB); each with R = W, W/2, W/4 and W/8 of its W = V * NG * KB words per lane
+#define ATK_WAVE_INSTANCES(X) X(8, 1, 1) X(8, 1, 2) X(8, 1, 4) X(8, 2, 1) X(8, 2, 2) X(4, 1, 1) X(4, 1, 2) X(4, 1, 4) X(4, 1, 8) X(2, 1, 2) X(2, 1, 4) X(2, 1, 8)
+
+bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, bool ptr16, WavePlan *out) {
+    if (dtype != ATK_BF16 || !ptr16 || n > 65536 || b * k_b <= k || m >= (1ll << 31)) return false;
+    WavePlan p;
+    memset(&p, 0, sizeof p);
+    p.KB = 1;
+    while (p.KB < k_b) p.KB *= 2;
+#define ATK_X(VV, GG, KK)                                                                                                       \
+    if (!p.V && p.KB == KK && b <= 64 * VV * GG && b > 32 * VV * GG && b % VV == 0 && n % VV == 0 && (GG == 1 || b > 64 * VV)) { \
+        p.V = VV;                                                                                                               \
+        p.NG = GG;                                                                                                              \
+    }
+    ATK_WAVE_INSTANCES(ATK_X)
+#undef ATK_X
+    if (!p.V) return false;
+    const int W = p.V * p.NG * p.KB;
+    p.R = W;
+    while (p.R > 1 && p.R > W / 8 && 64ll * (p.R / 2) >= k) p.R /= 2;
+    if (64ll * p.R < k) return false;
+    *out = p;
+    return true;
+}
+
+template <int V, int NG, int KB, int R>
+static hipError_t launch_wave(const WaveParams &prm, int64_t m, hipStream_t stream) {
+    hipLaunchKernelGGL((wave_row_kernel<V, NG, KB, R>), dim3((unsigned)m), dim3(kWave), 0, stream, prm);
+    return hipGetLastError();
+}
+
+hipError_t launch_wave_row(const WavePlan &pl, int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, const void *x, void *out_vals,
+                           int32_t *out_idx, hipStream_t stream) {
+    WaveParams prm;
+    memset(&prm, 0, sizeof prm);
+    prm.x = x;
+    prm.out_vals = out_vals;
+    prm.out_idx = out_idx;
+    prm.n = n;
+    prm.b = (int)b;
+    prm.L = (int)(n / b);
+    prm.rem = (int)(n % b);
+    prm.k = (int)k;
+    prm.k_b = (int)k_b;
+    prm.whole = b == 64ll * pl.V * pl.NG && k_b == pl.KB;
+    const int piece = pl.R < 8 ? pl.R : 8;
+    prm.vec_store = k % piece == 0 && (((uintptr_t)out_vals | (uintptr_t)out_idx) & 15u) == 0;
+#define ATK_X(VV, GG, KK)                                                            \
+    if (pl.V == VV && pl.NG == GG && pl.KB == KK) {                                  \
+        constexpr int W = VV * GG * KK;                                              \
+        if (pl.R == W) return launch_wave<VV, GG, KK, W>(prm, m, stream);            \
+        if (pl.R == W / 2) return launch_wave<VV, GG, KK, W / 2>(prm, m, stream);    \
+        if (pl.R == W / 4) return launch_wave<VV, GG, KK, W / 4>(prm, m, stream);    \
+        if (W >= 8 && pl.R == W / 8) return launch_wave<VV, GG, KK, W >= 8 ? W / 8 : W>(prm, m, stream); \
+    }
+    ATK_WAVE_INSTANCES(ATK_X)
+#undef ATK_X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace atk

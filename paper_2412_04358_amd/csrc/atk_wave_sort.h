@@ -2,13 +2,11 @@
 #pragma once
 
 #include "atk_common.h"
-#include "atk_select.h"
+#include "atk_packed.h"
 
 namespace atk {
 
 #ifdef __HIPCC__
-
-__device__ __forceinline__ int32_t med3_i32(int32_t a, int32_t b, int32_t c) { return max(min(a, b), min(max(a, b), c)); }  // v_med3_i32
 
 // Bitonic networks (Batcher 1968) over words that lie in the lanes' registers: no LDS, no barrier, and the same time whatever the words are.
 // A block is 64 * R words in R registers.  The low bits of a word's place in its block are the register's number - the low bits are
@@ -29,7 +27,7 @@ struct LanePlace {
 
 template <int CTRL>
 __device__ __forceinline__ int32_t dpp_i32(int32_t v) {
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);  // (every lane has a source: no old value to keep, so no copy before the move)
 }
 
 constexpr int log2_c(int v) { return v <= 1 ? 0 : 1 + log2_c(v >> 1); }
@@ -62,8 +60,12 @@ __device__ __forceinline__ void wave_sort_step(int32_t (&w)[W], const LanePlace 
         if constexpr (Q < 4) {
             constexpr int ctrl = Q == 0 ? 0xB1 : (Q == 1 ? 0x4E : (Q == 2 ? 0x141 : 0x128));
             const int32_t m = by_lane ? (at.most[Q] ^ at.most[by_lane ? P - LR : 0] ^ kMost) : at.most[Q];
+            int32_t other[W];
 #pragma unroll
-            for (int i = 0; i < W; ++i) w[i] = med3_i32(w[i], dpp_i32<ctrl>(w[i]), !by_lane && up(i) ? ~m : m);
+            for (int i = 0; i < W; ++i) other[i] = dpp_i32<ctrl>(w[i]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < W; ++i) w[i] = med3_i32(w[i], other[i], !by_lane && up(i) ? ~m : m);
         } else {
             const int32_t m = by_lane ? at.most[by_lane ? P - LR : 0] : kMost;
             auto swap = [](int32_t &a, int32_t &b) {
@@ -74,21 +76,22 @@ __device__ __forceinline__ void wave_sort_step(int32_t (&w)[W], const LanePlace 
             };
             if constexpr (R >= 2) {
 #pragma unroll
+                for (int i = 0; i < W; i += 2) swap(w[i], w[i + 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
                 for (int i = 0; i < W; i += 2) {
-                    int32_t a = w[i], b = w[i + 1];
-                    swap(a, b);
-                    int32_t x, y;
+                    const int32_t a = w[i], b = w[i + 1];
                     if constexpr (by_lane) {
-                        x = med3_i32(a, b, m);
-                        y = med3_i32(a, b, ~m);
+                        w[i] = med3_i32(a, b, m);
+                        w[i + 1] = med3_i32(a, b, ~m);
                     } else {
-                        x = up(i) ? min(a, b) : max(a, b);
-                        y = up(i) ? max(a, b) : min(a, b);
+                        w[i] = up(i) ? min(a, b) : max(a, b);
+                        w[i + 1] = up(i) ? max(a, b) : min(a, b);
                     }
-                    swap(x, y);
-                    w[i] = x;
-                    w[i + 1] = y;
                 }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < W; i += 2) swap(w[i], w[i + 1]);
             } else {
 #pragma unroll
                 for (int i = 0; i < W; ++i) {
@@ -105,6 +108,8 @@ __device__ __forceinline__ void wave_sort_step(int32_t (&w)[W], const LanePlace 
 template <int W, int R, int P, int J>
 __device__ __forceinline__ void wave_sort_steps(int32_t (&w)[W], const LanePlace &at) {  // bits J, J - 1, ... 0
     wave_sort_step<W, R, P, J>(w, at);
+    // (step by step through all the words: word by word through the steps, as the compiler would go, every DPP move waits for the word it reads)
+    __builtin_amdgcn_sched_barrier(0);
     if constexpr (J > 0) wave_sort_steps<W, R, P, J - 1>(w, at);
 }
 template <int W, int R, int P>
