@@ -174,8 +174,8 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * MH=0 / MH=<h> (k_b = 1: split rows never / with h helpers run as helpers and a finisher that meet through
  * mailboxes instead of partial lists and a ticket; HF=0 switches these off as well), BO=0 (Stage 2's bins take their
  * key range from the merged candidates, never from the bounds that come with the merge), RF=0 / RF=<n> (queues of
- * eight slots never / after 4n matrix rows of a lane for the first time pool their floors), WV=0 / WV=1 (bf16 rows are never / wherever
- * they can be one wavefront's each; a key above that names a plan of approx_topk, WV itself aside, implies WV=0).
+ * eight slots never / after 4n matrix rows of a lane for the first time pool their floors), WV=0 / WV=1 (bf16 rows of either
+ * selection are never / wherever they can be one wavefront's each; a key above that names a plan of approx_topk, WV itself aside, implies WV=0).
  * Values the kernels cannot take are ignored or clamped; results never depend on the plan.
  */
 int atk_plan_describe(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, char *buf,

@@ -31,6 +31,16 @@ int64_t exact_parts_data_bytes(const RowPlan &pl, int64_t m);
 // device (told: that kernel's own flags).
 hipError_t allow_whole_cu_lds(const void *kernel, bool (&told)[64]);
 
+// ... short bf16 rows that a wavefront takes alone (atk_wave_exact.hip) ...
+struct WaveExactPlan {
+    int NV;   // 16-byte vectors per lane
+    int R;    // rows sorted as a whole: words per lane that the sorted outputs take (0: not that)
+    int H;    // else: blocks of 64 H words are sorted,
+    int G;    // and the bound comes from 128 G groups of elements
+};
+bool plan_wave_exact(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, WaveExactPlan *out);
+hipError_t launch_wave_exact(const WaveExactPlan &pl, int64_t m, int64_t n, int64_t k, const void *x, void *out_vals, int32_t *out_idx, hipStream_t stream);
+
 // ... long rows with many winners (atk_exact_deal.hip) ...
 struct DealRow {          // per row, on the device
     uint32_t k_min, k_max;   // range of the fine bins
@@ -63,6 +73,8 @@ struct ExactPlan {
     int64_t idx_n;          // column indices are below this (n, unless the rows are lists of (value, index) pairs)
     bool single_wg;         // one workgroup per row, the row in its registers (`row`)
     bool parts;             // several, each with a part of it (`row`)
+    bool wave;              // one wavefront per row (`wv`; single_wg is set, too: no scratch, no limit on the rows)
+    WaveExactPlan wv;
     RowPlan row;
     bool dealt;             // dealt to bins (`deal`)
     DealPlan deal;

@@ -83,10 +83,16 @@ int make_exact_plan(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
     p.filter_cap = kFilterCap;
     p.sample = false;
     p.idx_n = n;
-    p.single_wg = p.parts = p.dealt = false;
+    p.single_wg = p.parts = p.dealt = p.wave = false;
     if (m >= (1ll << 31)) return ATK_ERR_UNSUPPORTED;
     const PlanOverride &ov = plan_override();
     if (!ov.xr_off && !ov.xs && !ov.xc && !by_digits) {
+        p.wave = !pairs && ov.wv >= 0 && plan_wave_exact(m, n, k, dtype, ptr16, &p.wv);
+        if (p.wave) {
+            p.single_wg = true;
+            *pl = p;
+            return ATK_OK;
+        }
         p.parts = !pairs && m <= 65535 && plan_exact_parts(m, n, k, dtype, ptr16, &p.row);
         if (p.parts) {
             p.state_bytes = exact_parts_state_bytes(m);
@@ -1173,6 +1179,7 @@ static hipError_t launch_exact_t(const ExactPlan &pl, const void *x, const int32
 
 hipError_t launch_exact(const ExactPlan &pl, const void *x, const int32_t *xi, void *out_vals, int32_t *out_idx,
                         void *state, void *data, hipStream_t stream) {
+    if (pl.wave) return launch_wave_exact(pl.wv, pl.m, pl.n, pl.k, x, out_vals, out_idx, stream);
     if (pl.single_wg || pl.parts)
         return launch_exact_row(pl.row, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, state, data, stream);
     if (pl.dealt) return launch_exact_deal(pl.deal, pl.m, pl.n, pl.k, pl.idx_n, pl.dtype, x, xi, out_vals, out_idx, data, stream);

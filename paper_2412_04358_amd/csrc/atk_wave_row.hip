@@ -18,6 +18,7 @@
 #include "atk_common.h"
 #include "atk_packed.h"
 #include "atk_stream.h"
+#include "atk_wave_out.h"
 #include "atk_wave_sort.h"
 
 namespace atk {
@@ -32,74 +33,6 @@ struct WaveParams {
     int whole;        // every lane has columns, every slot a survivor
     int vec_store;    // outputs in pieces of min(R, 8) words start on boundaries of as many
 };
-
-typedef uint32_t wave_v4u __attribute__((ext_vector_type(4)));
-typedef uint32_t wave_v2u __attribute__((ext_vector_type(2)));
-
-// The values' bits (bf16, two to a word) of two candidate words
-__device__ __forceinline__ uint32_t wave_pair_bits(int32_t even, int32_t odd) {
-    const uint32_t keys = ((uint32_t)even >> 16) | ((uint32_t)odd & 0xffff0000u);
-    const pk2 v = __builtin_bit_cast(pk2, keys), sgn = v >> 15;
-    const pk2 mag = __builtin_bit_cast(pk2, keys ^ __builtin_bit_cast(uint32_t, sgn)) - sgn;
-    return __builtin_bit_cast(uint32_t, mag) | (__builtin_bit_cast(uint32_t, sgn) & 0x80008000u);
-}
-__device__ __forceinline__ int32_t wave_index(int32_t c) { return (int32_t)(0xffffu - ((uint32_t)c & 0xffffu)); }
-
-// top[0 .. R): outputs first, first + 1, ... of row r
-template <int R>
-__device__ __forceinline__ void wave_write(const WaveParams &p, int64_t r, int first, const int32_t (&top)[R]) {
-    constexpr int H = R < 2 ? 1 : R / 2;
-    uint32_t bits[H];
-    bool zero = false;
-#pragma unroll
-    for (int i = 0; i < H; ++i) bits[i] = wave_pair_bits(top[2 * i], R < 2 ? 0 : top[2 * i + 1]);
-#pragma unroll
-    for (int i = 0; i < R; ++i) zero = zero || ((uint32_t)top[i] >> 16) == 0u;
-    if (__ballot(zero) != 0ull) {  // +0 or -0: the element itself says
-        const uint16_t *row = (const uint16_t *)p.x + r * p.n;
-        uint32_t own[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) own[i] = row[((uint32_t)top[i] >> 16) == 0u ? wave_index(top[i]) : 0];
-#pragma unroll
-        for (int i = 0; i < R; ++i)
-            if (((uint32_t)top[i] >> 16) == 0u) bits[i / 2] |= (i & 1) ? own[i] << 16 : own[i];
-    }
-    uint16_t *vals = (uint16_t *)p.out_vals + r * p.k;
-    int32_t *idx = p.out_idx + r * p.k;
-    if (p.vec_store) {  // (p.k is a multiple of the pieces, too)
-        constexpr int C = R < 8 ? R : 8;
-#pragma unroll
-        for (int c = 0; c < R; c += C) {
-            const int o = first + c;
-            if (o >= p.k) break;
-            if constexpr (C == 8) {
-                *(wave_v4u *)(vals + o) = wave_v4u{bits[c / 2], bits[c / 2 + 1], bits[c / 2 + 2], bits[c / 2 + 3]};
-            } else if constexpr (C == 4) {
-                *(wave_v2u *)(vals + o) = wave_v2u{bits[0], bits[1]};
-            } else if constexpr (C == 2) {
-                *(uint32_t *)(vals + o) = bits[0];
-            } else {
-                vals[o] = (uint16_t)bits[0];
-            }
-            if constexpr (C >= 4) {
-#pragma unroll
-                for (int i = 0; i < C; i += 4)
-                    *(wave_v4u *)(idx + o + i) = wave_v4u{(uint32_t)wave_index(top[c + i]), (uint32_t)wave_index(top[c + i + 1]),
-                                                          (uint32_t)wave_index(top[c + i + 2]), (uint32_t)wave_index(top[c + i + 3])};
-            } else {
-#pragma unroll
-                for (int i = 0; i < C; ++i) idx[o + i] = wave_index(top[c + i]);
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-        if (first + i < p.k) {
-            vals[first + i] = (uint16_t)((i & 1) ? bits[i / 2] >> 16 : bits[i / 2]);
-            idx[first + i] = wave_index(top[i]);
-        }
-}
 
 template <int V, int NG, int KB, int R>
 __global__ void __launch_bounds__(64, 2) wave_row_kernel(WaveParams p) {
@@ -202,7 +135,7 @@ __global__ void __launch_bounds__(64, 2) wave_row_kernel(WaveParams p) {
     // ---- Stage 2
     int32_t top[R];
     wave_largest<W, R, RUN>(w, top, at);
-    wave_write<R>(p, r, R * at.place, top);
+    wave_write<R>((const uint16_t *)p.x + r * p.n, (uint16_t *)p.out_vals + r * p.k, p.out_idx + r * p.k, p.k, p.vec_store, R * at.place, top);
 }
 
 // ------------------------------------------------------------------------------------ host
@@ -210,7 +143,7 @@ __global__ void __launch_bounds__(64, 2) wave_row_kernel(WaveParams p) {
 #define ATK_WAVE_INSTANCES(X) X(8, 1, 1) X(8, 1, 2) X(8, 1, 4) X(8, 2, 1) X(8, 2, 2) X(4, 1, 1) X(4, 1, 2) X(4, 1, 4) X(4, 1, 8) X(2, 1, 2) X(2, 1, 4) X(2, 1, 8)
 
 bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, bool ptr16, WavePlan *out) {
-    if (dtype != ATK_BF16 || !ptr16 || n > 65536 || b * k_b <= k || m >= (1ll << 31)) return false;
+    if (dtype != ATK_BF16 || !ptr16 || n > 65536 || b * k_b <= k) return false;
     WavePlan p;
     memset(&p, 0, sizeof p);
     p.KB = 1;
@@ -233,8 +166,17 @@ bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int 
 
 template <int V, int NG, int KB, int R>
 static hipError_t launch_wave(const WaveParams &prm, int64_t m, hipStream_t stream) {
-    hipLaunchKernelGGL((wave_row_kernel<V, NG, KB, R>), dim3((unsigned)m), dim3(kWave), 0, stream, prm);
-    return hipGetLastError();
+    constexpr int64_t rows = (1ll << 31) / kWave;  // (a launch holds fewer than 2^32 lanes)
+    WaveParams now = prm;
+    for (int64_t r0 = 0; r0 < m; r0 += rows) {
+        now.x = (const uint16_t *)prm.x + r0 * prm.n;
+        now.out_vals = (uint16_t *)prm.out_vals + r0 * prm.k;
+        now.out_idx = prm.out_idx + r0 * prm.k;
+        hipLaunchKernelGGL((wave_row_kernel<V, NG, KB, R>), dim3((unsigned)(m - r0 < rows ? m - r0 : rows)), dim3(kWave), 0, stream, now);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_wave_row(const WavePlan &pl, int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, const void *x, void *out_vals,

@@ -33,13 +33,13 @@ __device__ __forceinline__ int32_t dpp_i32(int32_t v) {
 constexpr int log2_c(int v) { return v <= 1 ? 0 : 1 + log2_c(v >> 1); }
 
 // One step: the words whose places differ in bit J alone, in the direction that bit P of the place says (P = log2(64 R): odd blocks smallest
-// first; P = 31: every block largest first).
+// first, of three the last one too; P = 31: every block largest first).
 template <int W, int R, int P, int J>
 __device__ __forceinline__ void wave_sort_step(int32_t (&w)[W], const LanePlace &at) {
     constexpr int LR = log2_c(R), LN = LR + 6;
     // direction: known at compile time (the register's number decides), or one of the lane's bits
     constexpr bool by_lane = P >= LR && P < LN;
-    auto up = [](int i) { return P == 31 ? false : (P == LN ? ((i / R) & 1) != 0 : ((i >> P) & 1) != 0); };  // smallest first
+    auto up = [](int i) { return P == 31 ? false : (P == LN ? (W == 3 * R ? i / R != 0 : ((i / R) & 1) != 0) : ((i >> P) & 1) != 0); };  // smallest first
     if constexpr (J < LR) {
 #pragma unroll
         for (int i = 0; i < W; ++i)
@@ -148,6 +148,30 @@ __device__ __forceinline__ void wave_largest(int32_t (&w)[W], int32_t (&top)[R],
     static_assert(SORTED == 1 || SORTED < R, "runs inside a lane's registers of a block");
     wave_sort_blocks<W, R, log2_c(SORTED) + 1>(w, at);
     wave_join_blocks<W, R>(w, top, at);
+}
+// The 128 * R largest of 192 * R words, largest first: lane l's top[i] is number R * at.place + i, its top[R + i] number 64 * R + that.  A list of
+// that size, with a margin of half: three blocks cost 0.8 of sorting four (words to 512 of 1024: 1050 and 1270 instructions).
+template <int R>
+__device__ __forceinline__ void wave_largest_two_of_three(int32_t (&w)[3 * R], int32_t (&top)[2 * R], const LanePlace &at) {
+    constexpr int LN = log2_c(R) + 6;
+    wave_sort_blocks<3 * R, R, 1>(w, at);
+    // of the first two blocks the larger half and the smaller one, each largest first
+    auto halves = [&]() {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int32_t a = top[i], b = top[R + i];
+            top[i] = max(a, b);
+            top[R + i] = min(a, b);
+        }
+        wave_sort_steps<2 * R, R, 31, LN - 1>(top, at);
+    };
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i) top[i] = w[i];
+    halves();
+    // the third block, smallest first, against the smaller half: what wins is, behind the larger half, in bitonic order again
+#pragma unroll
+    for (int i = 0; i < R; ++i) top[R + i] = max(top[R + i], w[2 * R + i]);
+    halves();
 }
 
 #endif  // __HIPCC__
