@@ -3,7 +3,8 @@
 Argument marshalling only: every step of the method runs in the HIP library.  The
 library is looked up inside the package (paper_2412_04358_amd/lib/libapprox_topk.so,
 built by __graft_entry__.build()); if it is missing the first call raises - there is
-no CPU fallback.
+no CPU fallback.  Calls on plain tensors are marshalled by an extension module beside it
+(csrc/atk_torch.cpp), everything else here.
 """
 from __future__ import annotations
 
@@ -18,7 +19,10 @@ ATK_BF16 = 1
 ATK_INTERLEAVED = 0
 ATK_CONTIGUOUS = 1
 
+_TORCH_PATH = os.path.join(_HERE, "lib", "_atk_torch.so")
+
 _lib = None
+_plain = None  # the extension module, from the first call on
 
 
 class ApproxTopkError(RuntimeError):
@@ -98,6 +102,22 @@ def load_library():
     return lib
 
 
+def _load_plain():
+    """Load (once, after torch) the extension module that marshals calls on plain tensors."""
+    global _plain
+    import importlib.machinery
+    import importlib.util
+
+    lib = load_library()
+    if not os.path.exists(_TORCH_PATH):
+        raise RuntimeError("%s is not built; run `python -c 'import __graft_entry__ as g; g.build()'` at the repository root." % _TORCH_PATH)
+    loader = importlib.machinery.ExtensionFileLoader("_atk_torch", _TORCH_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_atk_torch", loader))
+    loader.exec_module(module)
+    module.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.approx_topk, lib.approx_topk_assign, lib.exact_topk)))
+    _plain = module
+
+
 def strerror(code: int) -> str:
     return load_library().atk_strerror(code).decode()
 
@@ -154,6 +174,8 @@ def _on_device(torch, x, k, out, call):
     A call of a few microseconds on the GPU waits for its host side, so that is kept short: the device is only made
     current where it is not, and the stream is asked for as the raw handle (torch.cuda.device() and
     torch.cuda.current_stream(), each with an object of its own, took 4 of the 12 us of a small call)."""
+    if _plain is None:
+        _load_plain()
     device = x.device
     index = device.index
     if torch._C._cuda_getDevice() != index:
@@ -178,6 +200,10 @@ def approx_topk(x, k, b, k_b, out=None, assignment=None):
     current stream of x's device.  assignment: None calls approx_topk (interleaved buckets);
     ATK_INTERLEAVED / ATK_CONTIGUOUS call approx_topk_assign.
     """
+    if out is None and _plain is not None:
+        got = _plain.approx(x, k, b, k_b, assignment)
+        if got is not None:
+            return got if type(got) is tuple else _check(got)
     torch, m, n, dt = _tensor_args(x)
     lib = _lib or load_library()
     if assignment is None:
@@ -188,6 +214,10 @@ def approx_topk(x, k, b, k_b, out=None, assignment=None):
 
 def exact_topk(x, k, out=None):
     """Exact top-k (largest first) of every row of a GPU tensor x (m, n)."""
+    if out is None and _plain is not None:
+        got = _plain.exact(x, k)
+        if got is not None:
+            return got if type(got) is tuple else _check(got)
     torch, m, n, dt = _tensor_args(x)
     lib = _lib or load_library()
     return _on_device(torch, x, k, out, lambda v, i, s: lib.exact_topk(x.data_ptr(), m, n, k, dt, v, i, s))
