@@ -84,8 +84,8 @@ __device__ __forceinline__ int count_larger(const u64 *list, int j0, int j1, u64
 template <int CTRL>
 __device__ __forceinline__ u64 dpp_u64(u64 v) {
     uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-    lo = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, 0xf, 0xf, false);
-    hi = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, CTRL, 0xf, 0xf, false);
+    lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)lo, CTRL, 0xf, 0xf, true);
+    hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, CTRL, 0xf, 0xf, true);
     return ((u64)hi << 32) | lo;
 }
 __device__ __forceinline__ u64 readlane_u64(u64 v, int lane) {
@@ -131,7 +131,7 @@ __device__ __forceinline__ void wave_min_max_u64(u64 &lo, u64 &hi) {
 // Minimum / maximum of a 32-bit value over the 64 lanes of a fully active wavefront.
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
 }
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     v = min(v, dpp_u32<0xB1>(v));
