@@ -44,6 +44,21 @@ __device__ __forceinline__ void insert_pk(int32_t (&q)[KB], int32_t c) {
     for (int j = KB - 1; j >= 1; --j) q[j] = med3_i32(q[j - 1], q[j], c);  // q[j-1] >= q[j]: c clamped between them
     q[0] = max(q[0], c);
 }
+// mine <- the N largest of (mine U theirs); both sorted descending, result sorted descending.
+template <int N>
+__device__ __forceinline__ void merge_pk(int32_t (&mine)[N], const int32_t (&theirs)[N]) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) mine[j] = max(mine[j], theirs[N - 1 - j]);
+#pragma unroll
+    for (int stride = N / 2; stride >= 1; stride >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if ((i & stride) == 0) {
+                const int32_t a = mine[i], c = mine[i + stride];
+                mine[i] = max(a, c);
+                mine[i + stride] = min(a, c);
+            }
+}
 template <int ELT, int V, int KB>
 __device__ __forceinline__ void scan_vec_pk(int32_t (&q)[V][KB], const RowVec<ELT, V> &v, int t_local) {
     const uint32_t code = (uint32_t)(0xffff - t_local);

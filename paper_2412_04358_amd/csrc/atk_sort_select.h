@@ -1,0 +1,111 @@
+// Stage 2 by sorting networks: four wavefronts sort a quarter of the candidates each in their registers, cut to the k largest, and one joins their lists.
+#pragma once
+
+#include "atk_common.h"
+#include "atk_packed.h"
+#include "atk_wave_sort.h"
+
+namespace atk {
+
+#ifdef __HIPCC__
+
+constexpr int kSortWaves = 4;
+constexpr int kSortIdxBits = 17;  // column indices that fit a word beside a positive bf16 without its sign
+
+// The 64 * R largest of the workgroup's first four wavefronts' 64 * W words each, largest first, in the first wavefront: its lane's top[i] is number R * place + i.
+// lists: LDS, 4 * 64 * R words.  Called by all four wavefronts and every other one of the workgroup; one barrier.
+template <int W, int R>
+__device__ __forceinline__ void sort_four(int32_t (&w)[W], int32_t (&top)[R], int32_t *lists, const LanePlace &at) {
+    constexpr int N = 64 * R, LN = log2_c(R) + 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (wave < kSortWaves) {  // (uniform over the wavefront)
+        wave_largest<W, R, 1>(w, top, at);
+        if (wave > 0) {
+            // (the second and the fourth list the other way round: of two lists the larger word of each place is then among the N largest)
+#pragma unroll
+            for (int i = 0; i < R; ++i) lists[wave * N + ((wave & 1) ? N - 1 - (R * at.place + i) : R * at.place + i)] = top[i];
+        }
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    int32_t two[2 * R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int o = R * at.place + i;
+        two[i] = max(top[i], lists[N + o]);
+        two[R + i] = max(lists[2 * N + o], lists[3 * N + o]);
+    }
+    wave_sort_steps<2 * R, R, LN, LN - 1>(two, at);
+    wave_join_blocks<2 * R, R>(two, top, at);
+}
+
+// Exact top-k of the `count` distinct composites at cand[0 .. count) (LDS, on a 16-byte boundary, 4112 bytes of free LDS behind them), written largest first to
+// row row_out; false, and nothing is written, where fewer than k of them are positive.  bf16, indices of up to 17 bits: a positive value's 15 bits and the
+// index are one word.  Called by the whole workgroup after a barrier that made cand visible.
+//
+// What it replaces (select_write) is a chain of six barriers: key range, histogram, prefix sum, filing, ranks.  64 x 128256, k = 256, b = 512,
+// k_b = 2: 3.15 us from the last candidate to the last output there.
+template <int ELT>
+__device__ __forceinline__ bool sort_select_fits(int count, int k, int idx_bits) {
+    return ELT == ATK_BF16 && count <= 1024 && k <= 256 && idx_bits <= kSortIdxBits && (int)blockDim.x >= kSortWaves * kWave;
+}
+template <int W, int R>
+__device__ __forceinline__ bool sort_select_words(const u64 *cand, int count, int k, void *out_vals, int32_t *out_idx, int64_t row_out) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const LanePlace at;
+    int32_t *n_pos = (int32_t *)(cand + ((count + 1) & ~1)), *lists = n_pos + 4;
+    const uint32_t none = 0x80000000u;  // (the words are in the order of signed numbers)
+    int32_t w[W], top[R];
+    if (wave < kSortWaves) {
+        int positive = 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            const int c = tid * W + i;
+            const u64 v = c < count ? cand[c] : 0ull;
+            const uint32_t bits = (uint32_t)(v >> 48) & 0x7fffu;
+            const bool on = (v >> 63) != 0ull && bits != 0u;
+            const uint32_t inv = ((uint32_t)v >> 1) & ((1u << kSortIdxBits) - 1u);  // (0x7fffffff - index: the low bits of 0x1ffff - index)
+            w[i] = (int32_t)((on ? bits << kSortIdxBits | inv : 0u) ^ none);
+            positive += __popcll(__ballot(on));
+        }
+        if (lane == 0) n_pos[wave] = positive;
+    }
+    sort_four<W, R>(w, top, lists, at);
+    if (n_pos[0] + n_pos[1] + n_pos[2] + n_pos[3] < k) return false;
+    if (wave > 0) return true;
+    uint16_t *vals = (uint16_t *)out_vals + row_out * k;
+    int32_t *idx = out_idx + row_out * k;
+    const int o = R * at.place;
+    uint32_t b[R], x[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const uint32_t u = (uint32_t)top[i] ^ none;
+        b[i] = u >> kSortIdxBits;
+        x[i] = ((1u << kSortIdxBits) - 1u) - (u & ((1u << kSortIdxBits) - 1u));
+    }
+    if constexpr (R == 4) {
+        if (k % 4 == 0 && (((uintptr_t)out_vals | (uintptr_t)out_idx) & 15u) == 0) {
+            if (o < k) {
+                *(uint2 *)(vals + o) = make_uint2(b[0] | b[1] << 16, b[2] | b[3] << 16);
+                *(uint4 *)(idx + o) = make_uint4(x[0], x[1], x[2], x[3]);
+            }
+            return true;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (o + i < k) {
+            vals[o + i] = (uint16_t)b[i];
+            idx[o + i] = (int32_t)x[i];
+        }
+    return true;
+}
+__device__ __forceinline__ bool sort_select(const u64 *cand, int count, int k, void *out_vals, int32_t *out_idx, int64_t row_out) {
+    if (k > 64) return sort_select_words<4, 4>(cand, count, k, out_vals, out_idx, row_out);
+    if (count > 256) return sort_select_words<4, 1>(cand, count, k, out_vals, out_idx, row_out);
+    return sort_select_words<1, 1>(cand, count, k, out_vals, out_idx, row_out);
+}
+
+#endif  // __HIPCC__
+
+}  // namespace atk

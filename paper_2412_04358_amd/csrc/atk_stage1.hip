@@ -20,6 +20,7 @@
 #include "atk_common.h"
 #include "atk_packed.h"
 #include "atk_select.h"
+#include "atk_sort_select.h"
 #include "atk_stream.h"
 
 namespace atk {
@@ -400,6 +401,13 @@ __device__ __forceinline__ void row_tail(const S1Params &p, int r, int64_t tk, i
 
     // ---------------------------------------------------------------- Stage 2 in LDS
     trace_mark<TR>(p.trace, 3);  // all candidates of the row are in LDS
+    if (sort_select_fits<ELT>(p.b * p.k_b, p.k, p.idx_bits)) {
+        if (sort_select(cand, p.b * p.k_b, p.k, p.out_vals, p.out_idx, (int64_t)r)) {
+            trace_mark<TR>(p.trace, 8);
+            return;
+        }
+        __syncthreads();  // (few positive candidates)
+    }
     select_write<ELT, TR>(cand, p.b * p.k_b, p.k, p.idx_bits, p.out_vals, p.out_idx, (int64_t)r, p.trace);
     trace_mark<TR>(p.trace, 8);  // outputs written
 }
@@ -832,7 +840,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
                 }
         }
     }
-    if constexpr (PK || BATCH || RF) {
+    if (BATCH || RF || (PK && p.direct)) {
         bool zero = false;
 #pragma unroll
         for (int e = 0; e < V; ++e)
@@ -971,6 +979,80 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
         }
     }
 
+    // ---------------------------------------------------------------- packed queues meet as they are
+    // The words of the lanes that share a column count the same split's matrix rows, so their queues are merged as words of 32 bits, and only
+    // what is left of them becomes values, rows and composites.
+    if constexpr (PK) {
+        u64 *cand = (u64 *)(smem + p.lds_cand_off);
+        auto emit = [&](int c, const int32_t(&q)[KB]) {  // column c of the (virtual) matrix
+            float v[KB];
+            int t[KB];
+            bool zero = false;
+#pragma unroll
+            for (int j = 0; j < KB; ++j) {
+                unpack_bf16(q[j], t0, v[j], t[j]);
+                zero = zero || __float_as_uint(v[j]) == 0u;
+            }
+            if (__ballot(zero) != 0ull) {  // +0 or -0: the element itself says
+                const uint16_t *row = (const uint16_t *)p.x + (int64_t)r * p.n;
+#pragma unroll
+                for (int j = 0; j < KB; ++j) {
+                    const bool is = __float_as_uint(v[j]) == 0u;
+                    const uint32_t own = row[is ? (int64_t)t[j] * p.b + c - rot : 0];
+                    if (is) v[j] = __uint_as_float(own << 16);
+                }
+            }
+            u64 list[KB];
+#pragma unroll
+            for (int j = 0; j < KB; ++j) list[j] = t[j] != kEmptyT ? make_composite(__float_as_uint(v[j]), t[j] * p.b + c - rot) : 0ull;
+            emit_list<ELT, KB>(p, r, sp, bucket_of(c), list, cand);
+        };
+        if (p.wave_merge) {
+            for (int off = p.Gw; off < kWave; off <<= 1) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    int32_t theirs[KB];
+#pragma unroll
+                    for (int j = 0; j < KB; ++j) theirs[j] = __shfl_xor(pk[e][j], off, kWave);
+                    merge_pk<KB>(pk[e], theirs);
+                }
+            }
+        }
+        if (p.nparts > 1) {
+            int32_t *xch = (int32_t *)(smem + p.lds_xch_off);  // [part][column of the workgroup][slot]
+            const int part = p.wave_merge ? (tid >> 6) : ph, colbase = cb * p.Gw * V, wcols = min(p.Gw * V, p.b - colbase), stride = p.Gw * V;
+            if (active && (!p.wave_merge || (tid & (kWave - 1)) < p.Gw)) {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+#pragma unroll
+                    for (int j = 0; j < KB; ++j) xch[((int64_t)part * stride + cgl * V + e) * KB + j] = pk[e][j];
+            }
+            __syncthreads();
+            for (int c = tid; c < wcols; c += T) {
+                int32_t acc[KB];
+#pragma unroll
+                for (int j = 0; j < KB; ++j) acc[j] = xch[(int64_t)c * KB + j];
+                for (int q = 1; q < p.nparts; ++q) {
+                    int32_t theirs[KB];
+#pragma unroll
+                    for (int j = 0; j < KB; ++j) theirs[j] = xch[((int64_t)q * stride + c) * KB + j];
+                    merge_pk<KB>(acc, theirs);
+                }
+                emit(colbase + c, acc);
+            }
+        } else if (active && (!p.wave_merge || (tid & (kWave - 1)) < p.Gw)) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) emit(col0 + e, pk[e]);
+        }
+        trace_mark<TR>(p.trace, 2);
+        const bool all = p.stage2 != 0;
+        row_tail<ELT, KB, TR>(p, r, all ? (int64_t)r : (int64_t)r * p.colblocks + cb, all ? 0 : cb * p.Gw * V,
+                              all ? p.b : min(p.b, (cb + 1) * p.Gw * V), all ? 0 : rot, smem);
+        trace_mark<TR>(p.trace, 9);
+        return;
+    }
+
+    if constexpr (!PK) {
     // ---------------------------------------------------------------- to composites
     u64 comp[V][KB];
 #pragma unroll
@@ -1039,6 +1121,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
     row_tail<ELT, KB, TR>(p, r, whole ? (int64_t)r : (int64_t)r * p.colblocks + cb, whole ? 0 : cb * p.Gw * V,
                           whole ? p.b : min(p.b, (cb + 1) * p.Gw * V), whole ? 0 : rot, smem);
     trace_mark<TR>(p.trace, 9);  // done
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
