@@ -3,6 +3,7 @@
 
 #include "atk_common.h"
 #include "atk_packed.h"
+#include "atk_select.h"
 #include "atk_wave_sort.h"
 
 namespace atk {
@@ -12,31 +13,32 @@ namespace atk {
 constexpr int kSortWaves = 4;
 constexpr int kSortIdxBits = 17;  // column indices that fit a word beside a positive bf16 without its sign
 
-// The 64 * R largest of the workgroup's first four wavefronts' 64 * W words each, largest first, in the first wavefront: its lane's top[i] is number R * place + i.
-// lists: LDS, 4 * 64 * R words.  Called by all four wavefronts and every other one of the workgroup; one barrier.
-template <int W, int R>
-__device__ __forceinline__ void sort_four(int32_t (&w)[W], int32_t (&top)[R], int32_t *lists, const LanePlace &at) {
-    constexpr int N = 64 * R, LN = log2_c(R) + 6;
+// The 64 * R largest of the workgroup's first NWV (4 or 8) wavefronts' 64 * W words each, largest first, in the first wavefront: its lane's top[i] is number
+// R * place + i.  lists: LDS, NWV * 64 * R words.  Called by the whole workgroup; one barrier.
+template <int NWV, int W, int R, typename T>
+__device__ __forceinline__ void sort_waves(T (&w)[W], T (&top)[R], T *lists, const LanePlace &at) {
+    constexpr int N = 64 * R, LN = log2_c(R) + 6, H = NWV / 2;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (wave < kSortWaves) {  // (uniform over the wavefront)
+    if (wave < NWV) {  // (uniform over the wavefront)
         wave_largest<W, R, 1>(w, top, at);
         if (wave > 0) {
-            // (the second and the fourth list the other way round: of two lists the larger word of each place is then among the N largest)
+            // (every second list the other way round: of two lists the larger word of each place is then among the N largest)
 #pragma unroll
             for (int i = 0; i < R; ++i) lists[wave * N + ((wave & 1) ? N - 1 - (R * at.place + i) : R * at.place + i)] = top[i];
         }
     }
     __syncthreads();
     if (wave > 0) return;
-    int32_t two[2 * R];
+    T both[H * R];
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const int o = R * at.place + i;
-        two[i] = max(top[i], lists[N + o]);
-        two[R + i] = max(lists[2 * N + o], lists[3 * N + o]);
-    }
-    wave_sort_steps<2 * R, R, LN, LN - 1>(two, at);
-    wave_join_blocks<2 * R, R>(two, top, at);
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int o = R * at.place + i;
+            both[h * R + i] = larger(h ? lists[2 * h * N + o] : top[i], lists[(2 * h + 1) * N + o]);
+        }
+    wave_sort_steps<H * R, R, LN, LN - 1>(both, at);
+    wave_join_blocks<H * R, R>(both, top, at);
 }
 
 // Exact top-k of the `count` distinct composites at cand[0 .. count) (LDS, on a 16-byte boundary, 4112 bytes of free LDS behind them), written largest first to
@@ -70,7 +72,7 @@ __device__ __forceinline__ bool sort_select_words(const u64 *cand, int count, in
         }
         if (lane == 0) n_pos[wave] = positive;
     }
-    sort_four<W, R>(w, top, lists, at);
+    sort_waves<kSortWaves, W, R>(w, top, lists, at);
     if (n_pos[0] + n_pos[1] + n_pos[2] + n_pos[3] < k) return false;
     if (wave > 0) return true;
     uint16_t *vals = (uint16_t *)out_vals + row_out * k;
@@ -104,6 +106,22 @@ __device__ __forceinline__ bool sort_select(const u64 *cand, int count, int k, v
     if (k > 64) return sort_select_words<4, 4>(cand, count, k, out_vals, out_idx, row_out);
     if (count > 256) return sort_select_words<4, 1>(cand, count, k, out_vals, out_idx, row_out);
     return sort_select_words<1, 1>(cand, count, k, out_vals, out_idx, row_out);
+}
+
+// The k <= 64 largest of the `count` composites at cand[0 .. count) (LDS, in any order, 0 for none; count <= 64 * W * NWV), written largest first to row row_out.
+// 512 * NWV bytes of free LDS behind them, on a 16-byte boundary.  Called by the whole workgroup, of NWV wavefronts at least, after a barrier that made
+// cand visible.
+template <int ELT, int NWV, int W>
+__device__ __forceinline__ void sort_select_few(const u64 *cand, int count, int k, void *out_vals, int32_t *out_idx, int64_t row_out) {
+    const LanePlace at;
+    u64 w[W], top[1];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const int c = (int)threadIdx.x + i * NWV * kWave;
+        w[i] = c < count ? cand[c] : 0ull;
+    }
+    sort_waves<NWV, W, 1>(w, top, (u64 *)cand + ((count + 1) & ~1), at);
+    if ((int)threadIdx.x < kWave && at.place < k) write_composite<ELT>(top[0], out_vals, out_idx, row_out * k + at.place);
 }
 
 #endif  // __HIPCC__
