@@ -6,6 +6,7 @@
 
 #include "atk_common.h"
 #include "atk_exact.h"
+#include "atk_packed.h"
 #include "atk_row_bins.h"
 #include "atk_select.h"
 
@@ -31,6 +32,11 @@ struct RowParams {
 };
 
 typedef uint32_t row_v4u __attribute__((ext_vector_type(4)));
+
+// The order key of the float that a packed bf16 key (a two's complement number of 16 bits, -0 as +0) stands for, and the least packed key whose float has the order key
+// u or a higher one, for u of the kind that bounds are: bits below the sixteenth clear, or a bf16's.
+__device__ __forceinline__ uint32_t ukey_of_pk(int s) { return (((uint32_t)s << 16) ^ 0x80000000u) + (uint32_t)(s >> 31); }
+__device__ __forceinline__ int pk_of_ukey(uint32_t u) { return (int)(u >> 16) - (u & 0x80000000u ? 0x8000 : 0x7fff); }
 
 // The 16-byte boundary at or before row r's first element.  It is reached from x by an offset: an address that has been a number may
 // lie in any memory as far as the compiler knows, and its (flat) loads are waited for together with those of LDS.  Global loads are not:
@@ -165,7 +171,8 @@ struct RowRegs {
     // FIRST: the groups are the lane's first eight elements, one each (k_max is still the largest of all).
     // SUM: not the smallest of the wavefronts' candidates but the largest that, all wavefronts together, rank maxima per wavefront reach:
     // wavefronts may be unlike each other then (masked in part, sorted).  words: 32 words of LDS.  k_up: the same with rank_up (0: none).
-    template <bool FIRST = false, bool SUM = false>
+    // KEYS: the words hold keys (to_keys()).
+    template <bool FIRST = false, bool SUM = false, bool KEYS = false>
     __device__ __forceinline__ void bound(int sub, int rank, uint32_t *misc, uint32_t &k_min, uint32_t &k_max, uint32_t *words = nullptr,
                                           int rank_up = 0, uint32_t *k_up = nullptr) {
         const int tid = threadIdx.x, lane = tid & (kWave - 1), n_waves = blockDim.x >> 6;
@@ -176,7 +183,7 @@ struct RowRegs {
         for (int i = 0; i < SM; ++i) mx[i] = __uint_as_float(0x7fc00000u);
 #pragma unroll
         for (int w = 0; w < NV * 4; ++w) {
-            if (FIRST) break;
+            if (FIRST || KEYS) break;
             const uint32_t a = q[w >> 2][w & 3];
             const float f = ELT == ATK_F32 ? __uint_as_float(a) : fmaxf(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u));
             mx[w % SM] = fmaxf(mx[w % SM], f);  // (the number where one of the two is NaN)
@@ -189,7 +196,22 @@ struct RowRegs {
                 mx[i] = __uint_as_float(ELT == ATK_F32 ? a : ((i & 1) ? (a & 0xffff0000u) : (a << 16)));
             }
         }
-        auto key_of = [](float f) { return f == f ? ukey_of_bits(__float_as_uint(f)) : 0u; };
+        if constexpr (KEYS) {  // (a group's maximum in the upper half of its word, as a number; the lower one is the maximum of the other half of its elements)
+            uint32_t pm[SM];
+#pragma unroll
+            for (int w = 0; w < NV * 4; ++w) {
+                const uint32_t a = q[w >> 2][w & 3];
+                pm[w % SM] = w < SM ? a : __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(pk2, pm[w % SM]), __builtin_bit_cast(pk2, a)));
+            }
+#pragma unroll
+            for (int i = 0; i < SM; ++i) mx[i] = __int_as_float(max((int)pm[i], (int)(pm[i] << 16)) >> 16);
+        }
+        // (of two groups' maxima as they stand: the larger)
+        auto top_of = [](float a, float b) { return KEYS ? __int_as_float(max(__float_as_int(a), __float_as_int(b))) : fmaxf(a, b); };
+        auto key_of = [](float f) {
+            if constexpr (KEYS) return ukey_of_pk(__float_as_int(f));
+            return f == f ? ukey_of_bits(__float_as_uint(f)) : 0u;
+        };
         if (SUM && tid < 32) words[tid] = 0u;
         // The rank-th largest of the S * 64 keys of a wavefront, to its highest 16 bits (the bits below stay zero, which
         // can only lower the bound, by under one part in 128): bit by bit from the top, counting the keys that agree so far.
@@ -201,7 +223,7 @@ struct RowRegs {
             for (int i = 0; i < S; ++i) {
                 float m = mx[i];
 #pragma unroll
-                for (int j = i + S; j < SM; j += S) m = fmaxf(m, mx[j]);
+                for (int j = i + S; j < SM; j += S) m = top_of(m, mx[j]);
                 key[i] = key_of(m);
                 top = max(top, key[i]);
             }
@@ -240,9 +262,18 @@ struct RowRegs {
                 const bool is = lane < n_waves;
                 auto reached = [&](uint32_t theirs, uint32_t *sums) {  // lane j: the j-th wavefront's candidate
                     int mine = 0;  // maxima of this wavefront that reach it
-                    for (int j = 0; j < n_waves; ++j) {
-                        const int cnt = count((uint32_t)__builtin_amdgcn_readlane((int)theirs, j));
-                        if (lane == j) mine = cnt;
+                    if (S == 1 && n_waves > 4) {
+                        // (all counts at once: one after the other each waits for its own comparison; 64 x 128256 bf16, k = 256: 13.03 -> 12.75 us)
+                        int cnt[16];
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) cnt[j] = __popcll(__ballot(key[0] >= (uint32_t)__builtin_amdgcn_readlane((int)theirs, j)));
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) mine = lane == j ? cnt[j] : mine;
+                    } else {
+                        for (int j = 0; j < n_waves; ++j) {
+                            const int cnt = count((uint32_t)__builtin_amdgcn_readlane((int)theirs, j));
+                            if (lane == j) mine = cnt;
+                        }
                     }
                     if (is && mine) atomicAdd(&sums[lane], (uint32_t)mine);
                 };
@@ -281,6 +312,48 @@ struct RowRegs {
         if (k_min > k_max) k_min = k_max;
         if constexpr (SUM) *k_up = rank_up ? min(*k_up, k_max) : 0u;
         __syncthreads();  // (the words are used again)
+    }
+
+    // ---- bf16: the words as keys, two signed 16-bit numbers each in the order of the values (elements that are none, as NaNs, below all): a comparison is then
+    // a subtraction for two elements at once (rows in parts; 64 x 128256, k = 256: 13.25 -> 12.75 us, k = 64 12.2 -> 11.8)
+    __device__ __forceinline__ void to_keys() {
+        static_assert(ELT == ATK_BF16, "");
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[j][i] = pack_keys(q[j][i]);
+    }
+    // list_from() of keys: positions of the elements whose (order) keys are k_lo and above
+    __device__ __forceinline__ void list_keys(uint32_t k_lo, int2 *list, uint32_t cap, uint32_t *count) {
+        static_assert(ELT == ATK_BF16, "");
+        constexpr int W = NV * 4, MW = (W + 15) / 16;
+        const int lane = threadIdx.x & (kWave - 1), T = blockDim.x;
+        const int from = pk_of_ukey(k_lo);
+        const pk2 below = {(int16_t)(from - 1), (int16_t)(from - 1)};
+        uint32_t mk[MW], cnt = 0;  // bit 16 h + i of mask w: element h of word 16 w + i (a last mask of n words: from bit 16 - n on)
+#pragma unroll
+        for (int w = 0; w < MW; ++w) {
+            mk[w] = 0u;
+#pragma unroll
+            for (int i = 16 * w; i < 16 * w + 16 && i < W; ++i)
+                mk[w] = (mk[w] >> 1) | (__builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(below, __builtin_bit_cast(pk2, (uint32_t)q[i >> 2][i & 3]))) & 0x80008000u);
+            cnt += (uint32_t)__popc(mk[w]);
+        }
+        const uint32_t incl = wave_incl_scan_u32(cnt);
+        uint32_t at = 0;
+        if (lane == kWave - 1) at = atomicAdd(count, incl);
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + incl - cnt;
+#pragma unroll
+        for (int w = 0; w < MW; ++w) {
+            const int n_w = W - 16 * w < 16 ? W - 16 * w : 16;
+            uint32_t b = mk[w];
+            while (b && at < cap) {  // (once the list is full, the number alone matters)
+                const int bit = __builtin_ctz(b), word = (bit & 15) - (16 - n_w) + 16 * w;
+                b &= b - 1u;
+                list[at++].y = i0 + (word >> 2) * T * VE + (word & 3) * 2 + (bit >> 4);
+            }
+        }
+        __syncthreads();
     }
 
     static constexpr int M = (E + 31) / 32;  // masks of 32 elements, the last perhaps of fewer: element en has bit 31 - en % 32 of word en / 32

@@ -261,8 +261,11 @@ struct PartsRow {
     __device__ __forceinline__ uint32_t elements(const RowParams &p, int part) const {
         return (uint32_t)(min(end_vec(p, part) * VE, rot + p.n) - max(first_vec(p, part) * VE, rot));
     }
-    __device__ __forceinline__ void clear() const {  // the bins and the cursors; ends in a barrier
+    __device__ __forceinline__ void clear_bins() const {
         for (int i = threadIdx.x; i < n_bins + 4; i += blockDim.x) cur[i] = 0u;
+    }
+    __device__ __forceinline__ void clear() const {  // the bins and the cursors; ends in a barrier
+        clear_bins();
         if (threadIdx.x == 0) misc[5] = misc[7] = 0u;
         __syncthreads();
     }
@@ -464,8 +467,8 @@ __device__ __forceinline__ void parts_finish(const RowParams &p, const PartsRow<
 //                                          N(0,1)   first half -inf   ascending   constant   three levels   lagged average
 //   128 x 2^20 f32, k = 64                 135, 122       156, 157     832, 156  2205, 270      1130, 254         138, 145
 //   128 x 2^18 f32, k = 64                  60, 34         69, 41      262, 39    512, 74        320, 72           64, 35
-//   16 x 2^18 f32, k = 64                   31, 12         40, 13       41, 14     92, 21         75, 20           31, 14
-//   64 x 128256 bf16, k = 256               29, 12.6       49, 14       53, 17    223, 19        147, 23           36, 17
+//   16 x 2^18 f32, k = 64                   31, 12         40, 13       41, 15     92, 16         75, 21           31, 15
+//   64 x 128256 bf16, k = 256               29, 12.8       49, 13.7     53, 17.6  223, 18.6      147, 22.7         36, 17.5
 //   one row of 2^20 f32, k = 1000           52, 19         55, 24       51, 63     84, 81         77, 80           51, 23
 // (Parts that pass on little more than their share of k, and a row that starts over, in one workgroup, when their bounds leave fewer than
 // k elements: 104, 30, 9.4, 10.2 and 13 us in the first column, and 220 to 45000 in the others.)
@@ -485,8 +488,14 @@ __global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
         regs.load(p, r, v0, v1, w.rot);
         if (tid == 0) misc[5] = 0u;
         regs.mask_ends(p, v0, v1, w.rot);
-        regs.template bound<false, true>(p.sub, p.rank, misc, k_min, k_max, w.cur, p.rank_up, &k_up);
-        regs.list_from(__uint_as_float(bits_of_ukey(k_min)), w.passed, (uint32_t)p.cap, &misc[5]);
+        if constexpr (ELT == ATK_BF16) {
+            regs.to_keys();
+            regs.template bound<false, true, true>(p.sub, p.rank, misc, k_min, k_max, w.cur, p.rank_up, &k_up);
+            regs.list_keys(k_min, w.passed, (uint32_t)p.cap, &misc[5]);
+        } else {
+            regs.template bound<false, true>(p.sub, p.rank, misc, k_min, k_max, w.cur, p.rank_up, &k_up);
+            regs.list_from(__uint_as_float(bits_of_ukey(k_min)), w.passed, (uint32_t)p.cap, &misc[5]);
+        }
         n_passed = misc[5];
     }
     bool over = n_passed > (uint32_t)p.part_cap;  // uniform, as is what follows from it
@@ -511,6 +520,8 @@ __global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
     } else {
         parts_hand_over<ELT>(p, w, part, n_passed, k_min, k_up, k_max);
     }
+    if (over || p.rank_up) __syncthreads();  // (they have worked in the bins; above, the lists end in a barrier)
+    w.clear_bins();  // (by all of the workgroups, while the stores are under way, not by the last one when all wait for it: 64 x 128256 bf16, k = 64: 12.1 -> 11.8 us, k = 256 13.05 -> 12.75)
     // (a barrier alone does not wait for stores; the memory clobber keeps the compiler from moving the ticket above this)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -518,6 +529,7 @@ __global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
         uint32_t *ticket = p.tickets + r * kTicketStride;
         const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.parts - 1u;
         misc[6] = last ? 1u : 0u;
+        misc[5] = misc[7] = 0u;
         if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next call
     }
     __syncthreads();
@@ -526,7 +538,6 @@ __global__ void __launch_bounds__(1024) ex_parts_kernel(RowParams p) {
     const PartsHeads h(p, r);
     auto in = [&](u64 c, bool on) { return on && key_of(c) >= h.k_min; };
     uint32_t from = h.k_up;
-    w.clear();
     uint32_t n = parts_gather<ELT>(p, w, [&](auto f) { h.sweep(p, r, true, f); }, [&](u64 c, bool on) { return on && key_of(c) >= h.k_up; });
     if (n < (uint32_t)p.k || n > (uint32_t)p.cap) {  // down to the bin of the k-th
         auto sweep = [&](auto f) {
