@@ -48,6 +48,7 @@ constexpr int kDealBinMean = 1024;      // candidates per bin aimed at
 constexpr int kBinT = 256;              // threads that order a bin
 constexpr int kBinCap = 2048;           // candidates of a bin that LDS holds
 constexpr int kBinSub = 1024;           // bins inside a bin
+constexpr int kBinPeers = 4;            // places of a sub-bin that are looked at together
 constexpr int kDealChunksMax = 512;     // chunks of a row
 constexpr int kSplitLane = 7;           // sampled elements of a lane that are sorted where bins are cut at elements
 constexpr int kSplitSample = kSplitLane * kDealT;
@@ -393,7 +394,7 @@ __global__ void __launch_bounds__(kDealT) ex_deal_kernel(DealParams p) {
 template <int ELT>
 __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
     constexpr int T = kBinT, S = kBinCap / T, W = T >> 6;
-    __shared__ __align__(16) u64 buf[kBinCap];
+    __shared__ __align__(16) u64 buf[kBinCap + kBinPeers];
     __shared__ __align__(16) uint32_t cur[kBinSub + 4];
     __shared__ uint32_t misc[kRowMisc];
     __shared__ u64 ends[2 * W];
@@ -490,6 +491,10 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
         k_min = min(k_min, misc[8 + w]);
         k_max = max(k_max, misc[24 + w]);
     }
+    // (the same in every lane: scalars from here on, and what the bins are made of with them)
+    k_min = (uint32_t)__builtin_amdgcn_readfirstlane((int)k_min);
+    k_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)k_max);
+    start = (uint32_t)__builtin_amdgcn_readfirstlane((int)start);
     if (start >= (uint32_t)p.k) return;  // uniform
     const int64_t out = r * p.k + start;
     const uint32_t room = (uint32_t)p.k - start;  // outputs left from here on
@@ -503,8 +508,13 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
     const RowSqueeze<ELT> sq{p.idx_bits + 1};
     u64 q_min = 0ull;
     int q_shift = -1;
+    const int s_idx = __builtin_amdgcn_readfirstlane(bins.s_idx), r_idx = __builtin_amdgcn_readfirstlane(bins.r_idx);
+    const uint32_t scale = (uint32_t)__builtin_amdgcn_readfirstlane((int)bins.scale);
     auto sub_of = [&](u64 c) {
-        return q_shift < 0 ? bins.template bin<ELT>((uint32_t)(c >> 32), (uint32_t)c >> 1) : (uint32_t)((sq(c) - q_min) >> q_shift);
+        if (q_shift >= 0) return (uint32_t)((sq(c) - q_min) >> q_shift);
+        // (RowBins::bin(); an index has 31 bits at most, so s_idx is no more)
+        const uint32_t d = ((((uint32_t)(c >> 32) - k_min) >> (ELT == ATK_BF16 ? 16 : 0)) << s_idx) | __builtin_amdgcn_ubfe((uint32_t)c, 1 + r_idx, s_idx);
+        return (uint32_t)min(__umulhi(d, scale), (uint32_t)n_sub - 1u);
     };
     // mn, mx: this lane's.  Called by the whole workgroup; ends in a barrier, with the sub-bins cleared.
     auto narrow = [&](u64 mn, u64 mx) {
@@ -522,20 +532,23 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
         }
         q_min = mn;
         for (q_shift = 0; ((mx - mn) >> q_shift) >= (u64)n_sub;) ++q_shift;
+        q_shift = __builtin_amdgcn_readfirstlane(q_shift);
     };
-    // ranks of the ordered-by-sub-bin candidates buf[0 .. n), which are places [first, first + n) of the bin
+    // Ranks of the ordered-by-sub-bin candidates buf[0 .. n), which are places [first, first + n) of the bin; kBinPeers zeros behind them.  (What lies behind a
+    // sub-bin's candidates is smaller than they are, so the first few places from its start on are looked at whosever they are: 128 x 2^20 f32, k = 2^18: 364 us
+    // with a choice of each address, 358 without; ranks kept in registers and brought into order in LDS, for wider stores: 380 and 390.)
     auto rank_write = [&](uint32_t n, uint32_t first, auto start_of, auto end_of) {
         for (uint32_t i = tid; i < n; i += T) {
             const u64 c = buf[i];
             const uint32_t b = sub_of(c);
             const uint32_t s = start_of(b) - first, e = end_of(b) - first;
-            u64 peer[4];
+            u64 peer[kBinPeers];
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) peer[u] = buf[s + u < e ? s + u : i];  // (itself: not larger)
+            for (int u = 0; u < kBinPeers; ++u) peer[u] = buf[s + u];
             uint32_t rank = first + s;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) rank += peer[u] > c ? 1u : 0u;
-            for (uint32_t j = s + 4; j < e; ++j) rank += buf[j] > c ? 1u : 0u;
+            for (int u = 0; u < kBinPeers; ++u) rank += peer[u] > c ? 1u : 0u;
+            for (uint32_t j = s + kBinPeers; j < e; ++j) rank += buf[j] > c ? 1u : 0u;
             if (rank < room) write_composite<ELT>(c, p.out_vals, p.out_idx, out + rank);
         }
     };
@@ -643,6 +656,7 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
                 const uint32_t b = sub_of(c);
                 if (b >= low && b <= (uint32_t)top) buf[atomicAdd(&cur[b], 1u) - first] = c;
             });
+            if (tid < kBinPeers) buf[end - first + tid] = 0ull;
             __syncthreads();
             rank_write(end - first, first, [&](uint32_t b) { return b == (uint32_t)top ? first : cur[b + 1u]; }, [&](uint32_t b) { return cur[b]; });
             __syncthreads();
@@ -691,6 +705,7 @@ __global__ void __launch_bounds__(kBinT, 7) ex_bins_kernel(DealParams p) {
 #pragma unroll
     for (int i = 0; i < S; ++i)
         if (i * T < (int)count && own[i]) buf[cur[at[i] & 0xffffu] + (at[i] >> 16)] = own[i];
+    if (tid < kBinPeers) buf[count + tid] = 0ull;
     __syncthreads();
     rank_write(count, 0u, [&](uint32_t b) { return cur[b]; }, [&](uint32_t b) { return b > 0u ? cur[b - 1u] : count; });
 }
