@@ -41,8 +41,10 @@ static double estimate_us(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_
         // (fitted to 1125 calls: 0.76 to 1.16 times the estimate for 19 of 20, 0.6 to 1.5 at the ends)
         const double lg = std::log2(64.0 * wave.R), steps = (double)(b * k_b) / 64.0 * lg * (lg + 1.0) / 2000.0;
         const double rows = std::max(1.0, (double)m / 1024.0), len = (double)n / 8192.0;
-        return 2.4 + len * (1.2 + (k_b > 2 ? 0.8 * rows : 0.0) + (k_b > 4 ? 2.5 : 0.0)) + steps * (0.4 + 3.0 * rows) +
-               (double)m * (2.0 * (double)n + 6.0 * (double)k) * 0.14e-6;
+        // (loads of one or two elements: 283 calls above 6 us, 0.7 to 1.4 times the estimate for 19 of 20)
+        const double narrow = wave.NG > 1 && wave.V < 4 ? (wave.V == 1 ? 1.6 : 1.35) : 1.0;
+        return narrow * (2.4 + len * (1.2 + (k_b > 2 ? 0.8 * rows : 0.0) + (k_b > 4 ? 2.5 : 0.0)) + steps * (0.4 + 3.0 * rows) +
+               (double)m * (2.0 * (double)n + 6.0 * (double)k) * 0.14e-6);
     }
     if (b * k_b > k && (b * k_b > atk_stage2_max_candidates() || stage2_apart(m, n, k, b, k_b, dtype))) {
         // Stage 2 as a launch of its own over the (value, index) pairs that Stage 1 leaves in scratch: a launch, a chain of steps

@@ -2,7 +2,7 @@
 // or two each, where Stage 2 over lists in LDS (or in scratch, by a launch of its own) is a chain of short steps with a barrier
 // after each.
 //
-//   1. A lane owns V adjacent columns of the row seen as a matrix (twice that, 64 V columns apart, where NG = 2) and walks down all matrix rows,
+//   1. A lane owns V adjacent columns of the row seen as a matrix (NG times that, 64 V columns apart) and walks down all matrix rows,
 //      as in atk_stage1.hip, with queues of packed words.
 //   2. The queues' words exchange the matrix row for the column index, which 16 bits hold, and are the candidates as they stand: larger word,
 //      larger value or equal value and lower index.
@@ -36,7 +36,7 @@ struct WaveParams {
 
 template <int V, int NG, int KB, int R>
 __global__ void __launch_bounds__(64, 2) wave_row_kernel(WaveParams p) {
-    constexpr int W = V * NG * KB, U = V * NG >= 16 ? 8 : 16;  // U matrix rows' loads to a batch
+    constexpr int W = V * NG * KB, VW = NG * (V < 2 ? 1 : V / 2), U = VW > 4 ? 64 / VW : 16;  // U matrix rows' loads to a batch, VW registers each
     constexpr int RUN = KB < R ? KB : 1;
     typedef RowVec<ATK_BF16, V> Vec;
     const int lane = threadIdx.x;
@@ -140,7 +140,10 @@ __global__ void __launch_bounds__(64, 2) wave_row_kernel(WaveParams p) {
 
 // ------------------------------------------------------------------------------------ host
 // Instances: X(columns per lane V, column groups NG, slots KB); each with R = W, W/2, W/4 and W/8 of its W = V * NG * KB words per lane
-#define ATK_WAVE_INSTANCES(X) X(8, 1, 1) X(8, 1, 2) X(8, 1, 4) X(8, 2, 1) X(8, 2, 2) X(4, 1, 1) X(4, 1, 2) X(4, 1, 4) X(4, 1, 8) X(2, 1, 2) X(2, 1, 4) X(2, 1, 8)
+#define ATK_WAVE_INSTANCES(X)                                                                                                                              \
+    X(8, 1, 1) X(8, 1, 2) X(8, 1, 4) X(8, 2, 1) X(8, 2, 2) X(4, 1, 1) X(4, 1, 2) X(4, 1, 4) X(4, 1, 8) X(2, 1, 2) X(2, 1, 4) X(2, 1, 8)                    \
+    X(2, 2, 1) X(2, 2, 2) X(2, 2, 4) X(2, 4, 1) X(2, 4, 2) X(2, 8, 1) X(2, 8, 2)                                                                           \
+    X(1, 2, 2) X(1, 2, 4) X(1, 2, 8) X(1, 4, 1) X(1, 4, 2) X(1, 4, 4) X(1, 8, 1) X(1, 8, 2) X(1, 16, 1) X(1, 16, 2)
 
 bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int dtype, bool ptr16, WavePlan *out) {
     if (dtype != ATK_BF16 || !ptr16 || n > 65536 || b * k_b <= k) return false;
@@ -156,6 +159,13 @@ bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int 
     ATK_WAVE_INSTANCES(ATK_X)
 #undef ATK_X
     if (!p.V) return false;
+    // Bucket counts or row lengths that leave loads of one or two elements, in more groups: short rows, batches that give a SIMD a second row to issue
+    // from, or so many winners that the selection replaced is the longer part.  Against the plans replaced, 649 calls (4 to 4000 rows of 2047 to 12288
+    // elements, 99 to 1023 buckets): 0.08 to 1.04 times as long where this says so, half of them below 0.49 (4 x 3816, k = 402, b = 201, k_b = 4:
+    // 39.8 -> 7.3 us; 256 x 8190, k = b = 1023, k_b = 2: 37.3 -> 12.4; 2048 x 12288 0.16 to 1.04, but 1500 rows of them 1.27); elsewhere up to 1.8.
+    if (p.V < 4 && p.NG > 1 && plan_override().wv <= 0 &&
+        !(n <= 2048 || (n <= 4096 && m >= 1024) || (n <= 8192 && (m >= 2048 || (k > 256 && k > 96 * p.KB)))))
+        return false;
     const int W = p.V * p.NG * p.KB;
     p.R = W;
     while (p.R > 1 && p.R > W / 8 && 64ll * (p.R / 2) >= k) p.R /= 2;

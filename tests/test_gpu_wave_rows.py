@@ -67,6 +67,31 @@ def test_layouts(b, k_b):
                 _check(x, k, b, k_b)
 
 
+# loads of one and of two elements, in every number of groups and with every length of queues that is compiled
+NARROW = [(b, k_b) for b, kbs in ((65, (2, 3, 8)), (127, (2, 4, 7)), (129, (1, 2, 4)), (130, (1, 2, 4)), (254, (1, 2, 3)), (255, (1, 2, 3)), (257, (1, 2)),
+                                  (258, (1, 2)), (510, (1, 2)), (511, (1, 2)), (513, (1, 2)), (514, (1, 2)), (1022, (1, 2)), (1023, (1, 2))) for k_b in kbs]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("b, k_b", NARROW)
+def test_narrow_loads(b, k_b):
+    try:
+        atk.set_plan_override("WV=1")
+        v = 2 - b % 2
+        for n in {b * k_b, b * 3 + 1, b * 16, b * 17 + v, b * 33 - v}:
+            if n < b * k_b or n > 12288:
+                continue
+            x = _rows(7, n, n + k_b)
+            for k in {k_b, 64, 65, b * k_b // 2 + 1, b * k_b - 1}:
+                if k_b <= k < b * k_b and k <= 1024:
+                    print(n, k, b, k_b, flush=True)
+                    p = _plan(7, n, k, b, k_b)
+                    assert int(p["wave"]) > 0 and int(p["V"]) == (2 if b % 2 == 0 and n % 2 == 0 else 1)
+                    _check(x, k, b, k_b)
+    finally:
+        atk.set_plan_override(None)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [(2049, 2048, 100, 128, 2), (1030, 16384, 500, 512, 1), (2048, 65536, 700, 512, 4)])
 def test_many_rows(case):
@@ -110,8 +135,10 @@ def test_plans_fit_the_kernel():
             continue
         seen += 1
         v, kb = int(p["V"]), int(p["KB"])
-        groups = -(-b // (64 * v))
-        assert b % v == 0 and n % v == 0 and groups <= (2 if v == 8 else 1)
+        groups = 1  # (a power of two)
+        while 64 * v * groups < b:
+            groups *= 2
+        assert b % v == 0 and n % v == 0 and groups <= (16 // v if v < 4 else 2 if v == 8 else 1)
         assert kb >= k_b and v * groups * kb <= 32
         words = v * groups * kb
         assert words % r == 0 and 64 * r >= k and r * 8 >= words and k < b * k_b and n <= 65536
