@@ -677,6 +677,25 @@ static int make_plan_aligned(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     return ATK_OK;
 }
 
+// Stage 2 of the lean kernels: by the candidates per lane, and by whether the merge's key range serves the bins.
+LeanForm lean_form(const Plan &pl) {
+    const int64_t per_lane = ceil_div(pl.b, pl.T);
+    if (per_lane > kBkSlots) return {0, false, INT64_MAX};
+    const bool binned = pl.bound_ok != 0;
+    // Up to 64 winners are sorted out by networks where the key range would have to be found first (short rows: lanes that see few of them):
+    // 0.63 to 0.96 times as long (256 x 8192 f32, k = 64, b = 256: 5.75 -> 4.73 us; 128 x 8192 bf16, b = 512: 5.87 -> 4.39), whatever the data;
+    // with the range at hand the bins are as quick on rows without order (128 x 65536 f32, b = 512: 9.65, sorted 10.2).  Two candidates to a lane on many rows
+    // cost their SIMDs more than the barriers they save (1024 x 8192 f32, b = 1024: 11.1, sorted 12.3).
+    // The smallest network that holds the row's candidates; more of them - workgroups of 320, 384 and 448 lanes come with up to 1792 - are ranked.
+    if (!binned && pl.k <= 64 && (pl.b <= 512 || pl.m <= 512) && pl.T >= 4 * kWave) {
+        const int waves = pl.T >= 8 * kWave ? 8 : 4;
+        for (int lg = 0; lg <= (waves == 8 ? 1 : 2); ++lg)
+            if (pl.b <= ((int64_t)waves * kWave) << lg) return {(waves == 8 ? kFormSort8 : kFormSort4) + lg, false, ((int64_t)waves * kWave) << lg};
+    }
+    const int ns = per_lane <= 1 ? 1 : per_lane <= 2 ? 2 : kBkSlots;
+    return {ns, binned, (int64_t)ns * pl.T};
+}
+
 // ------------------------------------------------------------------------------------ contiguous plan
 // Gs lanes per bucket, chosen so that a lane has about 8 loads while the launch still has
 // enough lanes for the chip; buckets longer than a workgroup can chew are also split.
@@ -1275,6 +1294,7 @@ int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     const Plan &pl = fp.s1;
     // 2: not the selection by bins and digits in LDS, but exact_topk's kernels over the pairs Stage 1 left in scratch, or a sort in registers
     const int stage2 = fp.two_step || fp.wave ? 2 : (int)pl.stage2;
+    const LeanForm form = pl.lean && pl.stage2 ? lean_form(pl) : LeanForm{-1, false, 0};
     if (assignment == ATK_CONTIGUOUS)
         snprintf(buf, (size_t)buflen,
                  "contiguous V=%d KB=%d T=%d Gs=%d NB=%d bblocks=%d S=%d chunks_per_split=%d grid=%lld stage2=%d "
@@ -1284,11 +1304,12 @@ int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     else
         snprintf(buf, (size_t)buflen,
                  "V=%d KB=%d T=%d Gw=%d P=%d colblocks=%d S=%d rows_per_split=%d grid=%lld stage2=%d direct=%d "
-                 "scratch=%d wave_merge=%d nparts=%d lds=%d scratch_bytes=%lld packed=%d lean=%d pair_rows=%d refresh=%d helpers=%d wave=%d",
+                 "scratch=%d wave_merge=%d nparts=%d lds=%d scratch_bytes=%lld packed=%d lean=%d pair_rows=%d refresh=%d helpers=%d wave=%d "
+                 "lean_form=%d lean_holds=%lld",
                  pl.V, pl.KB, pl.T, pl.Gw, pl.P, pl.colblocks, pl.S, pl.rows_per_split, (long long)pl.grid, stage2,
                  (int)pl.direct, (int)pl.use_scratch, (int)pl.wave_merge, pl.nparts, pl.lds_bytes,
                  (long long)(fp.state_bytes + fp.data_bytes), (int)pl.packed, (int)pl.lean, pl.pair_rows, pl.refresh, pl.helpers,
-                 fp.wave ? fp.wv.R : 0);
+                 fp.wave ? fp.wv.R : 0, form.ns, (long long)form.holds);
     return ATK_OK;
 }
 

@@ -158,6 +158,16 @@ hipError_t launch_approx_contig(const Plan &plan, const void *x, void *out_vals,
 hipError_t launch_approx_lean(const Plan &plan, const void *x, void *out_vals, int32_t *out_idx, void *state,
                               hipStream_t stream, void *trace = nullptr);
 
+// Form of Stage 2 in a lean kernel, over the b candidates of a row: ns is the kernel's NS - 0 digit by digit, 1, 2 or 4 candidates per lane in registers
+// (by bins where `binned`, else ranked), or sorted by four or eight wavefronts, + log2 of the candidates of each of their lanes.
+constexpr int kFormSort4 = 16, kFormSort8 = 24;
+struct LeanForm {
+    int ns;
+    bool binned;
+    int64_t holds;   // candidates that it takes: never below b
+};
+LeanForm lean_form(const Plan &plan);
+
 // approx_topk of bf16 rows that a wavefront takes alone (atk_wave_row.hip): columns per lane, column groups, slots, registers that the sorted outputs
 // take.  false: not such a call.
 struct WavePlan {

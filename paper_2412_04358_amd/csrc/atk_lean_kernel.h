@@ -56,7 +56,6 @@ struct LeanParams {
 
 enum { kLeanOut = 0, kLeanSelect = 1, kLeanPair = 2, kLeanMulti = 3 };
 constexpr int kFormOut = 8;  // value of NS in a pair without Stage 2 (b*k_b = k): the finisher writes the row of maxima
-constexpr int kFormSort4 = 16, kFormSort8 = 24;  // ... with k <= 64: sorted by four or eight wavefronts; + log2 of the candidates of each of their lanes
 constexpr int kLeanU = 8;  // loads in flight per lane
 
 // NS, BINNED: the form of Stage 2, fixed by the host so that a kernel holds the code of one form only (all of them
@@ -392,28 +391,21 @@ static hipError_t launch_lean_mode(const Plan &pl, const LeanParams &prm, hipStr
     } else {
         if constexpr (MODE == kLeanPair || MODE == kLeanMulti)
             if (!pl.stage2) return launch_lean_form<ELT, MODE, kFormOut, false>(pl, prm, stream);
-        // Stage 2 over the b candidates of the row (one column block): candidates per lane, and whether the merge's
-        // key range serves the bins
-        const int64_t per_lane = (pl.b + pl.T - 1) / pl.T;
-        if (per_lane > kBkSlots) return launch_lean_form<ELT, MODE, 0, false>(pl, prm, stream);
-        const bool binned = pl.bound_ok != 0;
-        // Up to 64 winners are sorted out by networks where the key range would have to be found first (short rows: lanes that see few of them):
-        // 0.63 to 0.96 times as long (256 x 8192 f32, k = 64, b = 256: 5.75 -> 4.73 us; 128 x 8192 bf16, b = 512: 5.87 -> 4.39), whatever the data;
-        // with the range at hand the bins are as quick on rows without order (128 x 65536 f32, b = 512: 9.65, sorted 10.2).  Two candidates to a lane on many rows
-        // cost their SIMDs more than the barriers they save (1024 x 8192 f32, b = 1024: 11.1, sorted 12.3).
-        const bool sorted = !binned && pl.k <= 64 && (pl.b <= 512 || pl.m <= 512);
-        if (sorted && pl.T >= 512) {
-            if (pl.b <= 512) return launch_lean_form<ELT, MODE, kFormSort8, false>(pl, prm, stream);
-            if (pl.b <= 1024) return launch_lean_form<ELT, MODE, kFormSort8 + 1, false>(pl, prm, stream);
-        } else if (sorted && pl.T >= 256) {
-            if (pl.b <= 256) return launch_lean_form<ELT, MODE, kFormSort4, false>(pl, prm, stream);
-            if (pl.b <= 512) return launch_lean_form<ELT, MODE, kFormSort4 + 1, false>(pl, prm, stream);
-            return launch_lean_form<ELT, MODE, kFormSort4 + 2, false>(pl, prm, stream);
+        const LeanForm form = lean_form(pl);
+        if (form.holds < pl.b) return hipErrorInvalidValue;  // never: a form that holds fewer candidates would drop the others
+        switch (form.ns) {
+            case kFormSort8: return launch_lean_form<ELT, MODE, kFormSort8, false>(pl, prm, stream);
+            case kFormSort8 + 1: return launch_lean_form<ELT, MODE, kFormSort8 + 1, false>(pl, prm, stream);
+            case kFormSort4: return launch_lean_form<ELT, MODE, kFormSort4, false>(pl, prm, stream);
+            case kFormSort4 + 1: return launch_lean_form<ELT, MODE, kFormSort4 + 1, false>(pl, prm, stream);
+            case kFormSort4 + 2: return launch_lean_form<ELT, MODE, kFormSort4 + 2, false>(pl, prm, stream);
+            case 0: return launch_lean_form<ELT, MODE, 0, false>(pl, prm, stream);
+            case 1: return form.binned ? launch_lean_form<ELT, MODE, 1, true>(pl, prm, stream) : launch_lean_form<ELT, MODE, 1, false>(pl, prm, stream);
+            case 2: return form.binned ? launch_lean_form<ELT, MODE, 2, true>(pl, prm, stream) : launch_lean_form<ELT, MODE, 2, false>(pl, prm, stream);
+            case kBkSlots:
+                return form.binned ? launch_lean_form<ELT, MODE, kBkSlots, true>(pl, prm, stream) : launch_lean_form<ELT, MODE, kBkSlots, false>(pl, prm, stream);
         }
-        if (per_lane <= 1) return binned ? launch_lean_form<ELT, MODE, 1, true>(pl, prm, stream) : launch_lean_form<ELT, MODE, 1, false>(pl, prm, stream);
-        if (per_lane <= 2) return binned ? launch_lean_form<ELT, MODE, 2, true>(pl, prm, stream) : launch_lean_form<ELT, MODE, 2, false>(pl, prm, stream);
-        return binned ? launch_lean_form<ELT, MODE, kBkSlots, true>(pl, prm, stream)
-                      : launch_lean_form<ELT, MODE, kBkSlots, false>(pl, prm, stream);
+        return hipErrorInvalidValue;
     }
 }
 

@@ -51,6 +51,29 @@ def test_one_slot(n, b, spec, dtype, plan_override):
             _check(x, k, b, 1, dtype)
 
 
+# workgroups of 320, 384 and 448 lanes: more buckets than four wavefronts sort, where the lanes see too few matrix rows for bins
+@pytest.mark.parametrize("dtype, b", [("f32", 1024), ("f32", 1028), ("f32", 1100), ("f32", 1280), ("f32", 1536), ("f32", 1788), ("f32", 1792), ("bf16", 1024),
+                                      ("bf16", 1032), ("bf16", 1040), ("bf16", 1152), ("bf16", 1536)])
+def test_more_buckets_than_networks_hold(dtype, b):
+    for L in (8, 16):
+        n = L * b
+        x = _rows(8, n, n + b, dtype)
+        x[6] = torch.where(torch.arange(n) % b >= min(1024, b - 4), x[6].abs() + 10.0, x[6])  # winners in the last buckets alone
+        for k in (1, 33, 64):
+            _check(x, k, b, 1, dtype)
+            g = x.cuda()
+            vals, idx = torch.empty((8, k), dtype=x.dtype, device="cuda"), torch.empty((8, k), dtype=torch.int32, device="cuda")
+            assert atk.approx_topk_noalloc_raw(g.data_ptr(), 8, n, k, b, 1, atk.ATK_F32 if dtype == "f32" else atk.ATK_BF16, vals.data_ptr(), idx.data_ptr(),
+                                               torch.cuda.current_stream().cuda_stream) == 0
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), oracle.approx_topk(workloads.as_numpy_bits(x), k, b, 1, threads=8)[1])
+
+
+def test_advised_buckets():
+    b, k_b = atk.advise(1, 9216, 24, atk.ATK_F32, 0.9)[:2]
+    _check(_rows(8, 9216, 24, "f32")[:1], 24, b, k_b, "f32")
+
+
 @pytest.mark.parametrize("n", [50000, 128256, 131072, 131080])
 @pytest.mark.parametrize("b, k_b", [(512, 2), (64, 4), (250, 4), (128, 8), (60, 16), (100, 3)])
 def test_words(n, b, k_b):

@@ -218,6 +218,36 @@ def test_helper_and_pair_plans_fit_what_the_kernels_index(lib):
     assert n_multi > 500 and n_pair > 100, (n_multi, n_pair)
 
 
+def test_lean_selections_hold_every_bucket(lib, plan_override):
+    """The form of Stage 2 in the specialised one-slot kernels takes all of a row's b candidates, whatever the workgroup's size: networks of four or eight
+    wavefronts take 64 words of each wavefront's lanes per word of a lane, the others a number of candidates per lane."""
+    forms, wide = {}, 0
+    for spec in (None, "BO=0", "HF=1,HT=256", "HF=1,HT=256,BO=0"):
+        plan_override(spec)
+        for dt, width in ((atk.ATK_F32, 4), (atk.ATK_BF16, 8)):
+            for b in range(width, 2049, width):
+                for L in (2, 8, 11, 24) if spec is None else (8, 256):
+                    for m, k in ((1, 1), (64, 64), (513, 33)):
+                        if k >= b or (spec and b % 32):
+                            continue
+                        d = atk.plan_describe(m, b * L, k, b, 1, dt)
+                        p = parse_plan(d)
+                        ns, holds = p["lean_form"], p["lean_holds"]
+                        if not p["lean"] or not p["stage2"] or p["wave"]:
+                            assert ns == -1, d
+                            continue
+                        forms[ns] = forms.get(ns, 0) + 1
+                        if ns >= 24:
+                            assert p["T"] >= 512 and ns <= 25 and holds == 512 << (ns - 24), d
+                        elif ns >= 16:
+                            assert p["T"] >= 256 and ns <= 18 and holds == 256 << (ns - 16), d
+                        elif ns:
+                            assert ns in (1, 2, 4) and holds == ns * p["T"], d
+                        assert holds >= b, d
+                        wide += b > 1024 and 256 <= p["T"] < 512
+    assert set(forms) == {1, 2, 4, 16, 17, 18, 24, 25} and wide > 500, (forms, wide)
+
+
 def parse_contig_plan(s):
     assert s.startswith("contiguous ")
     return parse_plan(s[len("contiguous "):])
