@@ -4,7 +4,7 @@ Argument marshalling only: every step of the method runs in the HIP library.  Th
 library is looked up inside the package (paper_2412_04358_amd/lib/libapprox_topk.so,
 built by __graft_entry__.build()); if it is missing the first call raises - there is
 no CPU fallback.  Calls on plain tensors are marshalled by an extension module beside it
-(csrc/atk_torch.cpp), everything else here.
+(csrc/atk_torch.cpp) where that can be loaded, everything else here.
 """
 from __future__ import annotations
 
@@ -22,7 +22,7 @@ ATK_CONTIGUOUS = 1
 _TORCH_PATH = os.path.join(_HERE, "lib", "_atk_torch.so")
 
 _lib = None
-_plain = None  # the extension module, from the first call on
+_plain = None  # the extension module, from the first call without `out` on; False where it cannot be used
 
 
 class ApproxTopkError(RuntimeError):
@@ -102,19 +102,28 @@ def load_library():
     return lib
 
 
-def _load_plain():
-    """Load (once, after torch) the extension module that marshals calls on plain tensors."""
+def _load_plain(torch):
+    """Load (once, after torch) the extension module that marshals calls on plain tensors.  It only saves time: where it is missing, or was built for
+    another torch, a warning says so and the calls are marshalled here."""
     global _plain
     import importlib.machinery
     import importlib.util
 
     lib = load_library()
-    if not os.path.exists(_TORCH_PATH):
-        raise RuntimeError("%s is not built; run `python -c 'import __graft_entry__ as g; g.build()'` at the repository root." % _TORCH_PATH)
-    loader = importlib.machinery.ExtensionFileLoader("_atk_torch", _TORCH_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_atk_torch", loader))
-    loader.exec_module(module)
-    module.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.approx_topk, lib.approx_topk_assign, lib.exact_topk)))
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_atk_torch", _TORCH_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_atk_torch", loader))
+        loader.exec_module(module)
+        if module.torch_version != torch.__version__.split("+")[0]:
+            raise ImportError("built for torch %s, this is %s" % (module.torch_version, torch.__version__))
+        module.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.approx_topk, lib.approx_topk_assign, lib.exact_topk)))
+    except ImportError as e:
+        import warnings
+
+        _plain = False
+        warnings.warn("%s cannot be used (%s): calls take some microseconds more on the host.  `python -c 'import __graft_entry__ as g; g.build()'` at the "
+                      "repository root builds it." % (_TORCH_PATH, e), RuntimeWarning, stacklevel=4)
+        return
     _plain = module
 
 
@@ -174,8 +183,8 @@ def _on_device(torch, x, k, out, call):
     A call of a few microseconds on the GPU waits for its host side, so that is kept short: the device is only made
     current where it is not, and the stream is asked for as the raw handle (torch.cuda.device() and
     torch.cuda.current_stream(), each with an object of its own, took 4 of the 12 us of a small call)."""
-    if _plain is None:
-        _load_plain()
+    if out is None and _plain is None:
+        _load_plain(torch)
     device = x.device
     index = device.index
     if torch._C._cuda_getDevice() != index:
@@ -200,7 +209,7 @@ def approx_topk(x, k, b, k_b, out=None, assignment=None):
     current stream of x's device.  assignment: None calls approx_topk (interleaved buckets);
     ATK_INTERLEAVED / ATK_CONTIGUOUS call approx_topk_assign.
     """
-    if out is None and _plain is not None:
+    if out is None and _plain:
         got = _plain.approx(x, k, b, k_b, assignment)
         if got is not None:
             return got if type(got) is tuple else _check(got)
@@ -214,7 +223,7 @@ def approx_topk(x, k, b, k_b, out=None, assignment=None):
 
 def exact_topk(x, k, out=None):
     """Exact top-k (largest first) of every row of a GPU tensor x (m, n)."""
-    if out is None and _plain is not None:
+    if out is None and _plain:
         got = _plain.exact(x, k)
         if got is not None:
             return got if type(got) is tuple else _check(got)

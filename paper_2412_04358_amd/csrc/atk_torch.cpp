@@ -15,6 +15,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
+#include <torch/version.h>
 
 #include "../../include/approx_topk.h"
 
@@ -127,4 +128,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_atk_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__atk_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__atk_torch() {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) {  // (this file knows torch's own structures: for that release alone)
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,6 +1,7 @@
 """Calls on plain tensors, which an extension module marshals, against the same calls with `out`, which binding.py does itself; and what is no plain call:
 subclasses, modes, arguments that are no integers, tensors and parameters that are refused."""
 import threading
+import warnings
 
 import numpy as np
 import pytest
@@ -57,6 +58,33 @@ def test_plain(dtype):
         [t.join() for t in threads]
         for g in got:
             _same(g, want)
+
+
+@pytest.mark.parametrize("why", ["missing", "damaged", "another torch"])
+def test_without_the_module(why, tmp_path, monkeypatch):
+    """Calls need the library alone: with `out` the module is not even asked for, without a warning says that it cannot be used."""
+    x = workloads.normal_rows(3, 4096, seed=4).cuda()
+    want = atk.approx_topk(x, 64, 128, 1), atk.exact_topk(x, 64)
+    if why == "another torch":
+        monkeypatch.setattr(torch, "__version__", "0.0.1")
+    else:
+        path = tmp_path / "_atk_torch.so"
+        if why == "damaged":
+            path.write_bytes(b"no library")
+        monkeypatch.setattr(binding, "_TORCH_PATH", str(path))
+    monkeypatch.setattr(binding, "_plain", None)
+    out = (torch.empty((3, 64), device="cuda"), torch.empty((3, 64), dtype=torch.int32, device="cuda"))
+    _same(atk.approx_topk(x, 64, 128, 1, out=out), want[0])
+    _same(atk.exact_topk(x, 64, out=out), want[1])
+    assert binding._plain is None
+    with pytest.warns(RuntimeWarning, match="cannot be used"):
+        _same(atk.exact_topk(x, 64), want[1])
+    assert binding._plain is False
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")  # (once is enough)
+        _same(atk.approx_topk(x, 64, 128, 1), want[0])
+    with pytest.raises(binding.ApproxTopkError):
+        atk.exact_topk(x, 0)
 
 
 def test_not_plain():

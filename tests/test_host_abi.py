@@ -98,6 +98,26 @@ def test_noalloc_rejects_what_does_not_fit(lib):
     assert lib.approx_topk_noalloc(fake + 2, 4, 4096, 64, 64, 1, 0, fake, fake, None) == -7
 
 
+def test_marshalling_module_is_optional(lib, tmp_path, monkeypatch):
+    """The extension module for calls on torch tensors is loaded where it was built for this torch; else a warning, and no error, says that it is not used."""
+    import torch
+
+    from paper_2412_04358_amd import binding
+
+    monkeypatch.setattr(binding, "_plain", None)
+    binding._load_plain(torch)
+    assert binding._plain and binding._plain.torch_version == torch.__version__.split("+")[0]
+    damaged = tmp_path / "damaged.so"
+    damaged.write_bytes(b"no library")
+    for path, version in ((str(tmp_path / "missing.so"), torch.__version__), (str(damaged), torch.__version__), (binding._TORCH_PATH, "0.0.1")):
+        monkeypatch.setattr(binding, "_TORCH_PATH", path)
+        monkeypatch.setattr(torch, "__version__", version)
+        monkeypatch.setattr(binding, "_plain", None)
+        with pytest.warns(RuntimeWarning, match="cannot be used"):
+            binding._load_plain(torch)
+        assert binding._plain is False
+
+
 def test_strerror(lib):
     seen = set()
     for code in range(0, -9, -1):
