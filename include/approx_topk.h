@@ -156,8 +156,8 @@ int atk_exact_workspace_parts(int64_t m, int64_t n, int64_t k, int dtype, int64_
  * Writes a one-line, human-readable description of the launch plan the library would use
  * (threads per workgroup, lanes per bucket column, row splits, Stage 2, ...) into
  * buf (NUL-terminated, truncated to buflen).  Host only; used by tests and the benchmark log.
- * stage2=0: none; 1: in the workgroup that streamed, through LDS; 2: by exact_topk's kernels over pairs in scratch or, where wave=<n> is not
- * 0, by a sort in the registers of the one wavefront that has the row (n words of each lane are written).
+ * stage2=0: none; 1: in the workgroup that streamed, through LDS; 2: by exact_topk's kernels over pairs in scratch; 3: by a sort in the
+ * registers of the one wavefront that has the row, of which wave=<n> words of each lane are written (0: not such a plan).
  * lean=1 with Stage 2: lean_form is the form of the selection (0: digit by digit; 1, 2, 4: candidates per lane in registers; 16 + l, 24 + l: networks
  * of four, eight wavefronts with 2^l candidates per lane; -1: none) and lean_holds the candidates that it takes, never below b.
  * The plan can be overridden for tuning and tests with the environment variable ATK_PLAN (read once, when

@@ -1292,8 +1292,7 @@ int atk_plan_describe_assign(int64_t m, int64_t n, int64_t k, int64_t b, int64_t
     rc = make_full_plan(m, n, k, b, k_b, dtype, assignment, true, &fp, true, true);
     if (rc != ATK_OK) return rc;
     const Plan &pl = fp.s1;
-    // 2: not the selection by bins and digits in LDS, but exact_topk's kernels over the pairs Stage 1 left in scratch, or a sort in registers
-    const int stage2 = fp.two_step || fp.wave ? 2 : (int)pl.stage2;
+    const int stage2 = fp.wave ? 3 : fp.two_step ? 2 : (int)pl.stage2;
     const LeanForm form = pl.lean && pl.stage2 ? lean_form(pl) : LeanForm{-1, false, 0};
     if (assignment == ATK_CONTIGUOUS)
         snprintf(buf, (size_t)buflen,

@@ -40,11 +40,19 @@ def _check(x, k, b, k_b, assignment=None, shift=0):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("case", [(4, 8192, 1024, 2048, 1), (40, 8192, 512, 1024, 1), (1, 65536, 1024, 512, 8), (2, 65536, 64, 4096, 1),
                                   (1100, 4096, 64, 512, 2), (1030, 2048, 300, 128, 8), (3, 20000, 2000, 683, 4), (2, 16384, 1024, 1024, 2)])
-def test_chosen(case, dtype):
+def test_chosen(case, dtype, plan_override):
+    """The pairs' launch; bf16 rows that one wavefront would take alone by their own plan, off the 16-byte boundaries, and kept off it."""
     m, n, k, b, k_b = case
+    x = workloads.normal_rows(m, n, seed=b, dtype=dtype)
     plan = atk.plan_describe(m, n, k, b, k_b, atk.ATK_F32 if dtype == "f32" else atk.ATK_BF16)
-    assert " stage2=2 " in plan + " ", plan
-    _check(workloads.normal_rows(m, n, seed=b, dtype=dtype), k, b, k_b)
+    if " wave=0 " not in plan:
+        assert dtype == "bf16" and " stage2=3 " in plan, plan
+        _check(x, k, b, k_b)
+        _check(x, k, b, k_b, shift=1)
+        plan_override("WV=0")
+        plan = atk.plan_describe(m, n, k, b, k_b, atk.ATK_BF16)
+    assert " stage2=2 " in plan and " wave=0 " in plan and " scratch_bytes=0 " not in plan, plan
+    _check(x, k, b, k_b)
     if m <= 40:
         _check(workloads.few_levels(m, n, levels=3, seed=b, dtype=dtype), k, b, k_b)
         _check(workloads.special_values(m, n, seed=b, dtype=dtype), k, b, k_b)

@@ -131,6 +131,7 @@ def test_plans_fit_the_kernel():
         k, m = rng.randint(k_b, b * k_b), rng.choice((1, 100, 1024, 5000))
         p = _plan(m, n, k, b, k_b)
         r = int(p["wave"])
+        assert (p["stage2"] == "3") == (r > 0)
         if not r:
             continue
         seen += 1
