@@ -1,20 +1,21 @@
 // exact_topk of short bf16 rows, a wavefront each: the row in its registers, a bound that k elements reach, the few elements that do in a list in
 // LDS, and these sorted in registers (atk_wave_sort.h).
 //
-//   1. A lane holds up to 16 vectors of 16 bytes.  A lower bound on the k-th largest: of 1024 groups of elements (16 to a lane) the k-th largest
-//      maximum, or one a little below, by halving; two elements to an instruction, as signed 16-bit numbers.  Where the bound is
-//      above zero that is right for bf16 as it stands (what is negative is below it, whatever its order); else the row is
-//      converted to two's complement first.
+//   1. A lane holds up to 16 vectors of 16 bytes.  A lower bound on the k-th largest: of 1024 or 2048 groups of elements (16 or 32 to a lane) the
+//      k-th largest maximum, or one a little below, by interpolation and halving; two elements to an instruction, as signed 16-bit numbers.  Where the
+//      bound is above zero that is right for bf16 as it stands (what is negative is below it, whatever its order); else the row is
+//      converted to two's complement first (2048 x 8192, k = 512, logarithms of probabilities: 15.9 us, 13.5 for N(0,1)).
 //   2. The elements that reach the bound are marked, three instructions to two of them, and listed in LDS one mark at a time; every lane then takes an
 //      equal share of the list, with the values from a copy of the row in LDS (registers have no index).
 //   3. Where more reach it than the list holds (rows unlike their groups: masked in part; ties), the value of the k-th is searched
-//      among all elements, and of ties at it the first are marked.
+//      among all elements, and of ties at it the first are marked, until there are k.  (Element by element in all the row's vectors: 7 x 7000 of
+//      three values, k = 36, 13.2 us; whole vectors but for the one where they end, and none behind it: 7.1, ex_row_kernel 8.2.)
 //   4. The list is sorted, cut to the k largest.
 // Rows of up to 1024 elements are sorted as a whole.
 //
 // What bounds it: vector instructions, with two rows to a SIMD about 2400 for each of 8192 elements and k = 512, of which the sort takes 1050, the bound 660, the list
 // and its values 500.  2048 x 8192, k = 512: 19.4 us (ex_row_kernel, 29 instructions an element) -> 15.7; k = 64: 12.7 -> 10.9; on a grid of halves,
-// k = 512: 112 -> 32; 2048 x 4096, k = 256: 12.3 -> 10.4; 512 x 1024, k = 512: 0.17 times as long.
+// k = 512: 112 -> 32; 2048 x 4096, k = 256: 12.3 -> 10.4; 512 x 1024, k = 512: 0.17 times as long; 2048 x 8192 of one value, k = 512: 34.4 -> 15.5.
 #include <cmath>
 #include <cstring>
 #include <utility>
@@ -58,8 +59,10 @@ __device__ __forceinline__ void wave_mask_row(uint32_t (&q)[NV * 4], int n_vec) 
     if (n_vec >= NV * kWave) return;
 #pragma unroll
     for (int j = 0; j < NV; ++j)
+        if ((j + 1) * kWave > n_vec) {  // (uniform: the row's last vectors alone)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) q[4 * j + i] = j * kWave + (int)threadIdx.x < n_vec ? q[4 * j + i] : kNoKeys;
+            for (int i = 0; i < 4; ++i) q[4 * j + i] = j * kWave + (int)threadIdx.x < n_vec ? q[4 * j + i] : kNoKeys;
+        }
 }
 
 // How many of the wavefront's 128 * N numbers reach `from` (above -32768), three operations to two of them.  (Ballots and scalar counts of them, two to
@@ -140,7 +143,7 @@ __global__ void __launch_bounds__(64, 2) wave_exact_kernel(WaveExactParams p) {
         int h = most + 1, n_h = 0, n_t = 0;  // n_h < k reach h, n_t reach t
         for (int d = 256;; d *= 4) {
             t = max(most - d, least);
-            n_t = reach(t);
+            n_t = most < least ? 0 : reach(t);
             if (n_t >= k || t == least) break;
             h = t;
             n_h = n_t;
@@ -219,19 +222,22 @@ __global__ void __launch_bounds__(64, 2) wave_exact_kernel(WaveExactParams p) {
             for (int w = 0; w < M; ++w) {
                 uint32_t ties = mk[w] & ~above[w], kept = 0u;
 #pragma clang loop unroll(disable)
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < 4 && left > 0; ++j) {
                     const uint32_t here = ties & (0x000f000fu << (4 * j)), n_here = (uint32_t)__popc(here), to_here = wave_incl_scan_u32(n_here);
-                    const int before = (int)(to_here - n_here), all = __builtin_amdgcn_readlane((int)to_here, kWave - 1);
-                    int room = max(left, 0) - before;
+                    int room = left - (int)(to_here - n_here);
+                    if ((int)n_here <= room) {
+                        kept |= here;
+                    } else if (room > 0) {  // (one lane of the row)
 #pragma clang loop unroll(disable)
-                    for (int e = 0; e < 8; ++e) {  // in the order of the row
-                        const uint32_t bit = 1u << ((e & 1) * 16 + 4 * j + (e >> 1));
-                        if ((here & bit) && room > 0) {
-                            kept |= bit;
-                            --room;
+                        for (int e = 0; e < 8 && room > 0; ++e) {  // in the order of the row
+                            const uint32_t bit = 1u << ((e & 1) * 16 + 4 * j + (e >> 1));
+                            if (here & bit) {
+                                kept |= bit;
+                                --room;
+                            }
                         }
                     }
-                    left -= all;
+                    left -= __builtin_amdgcn_readlane((int)to_here, kWave - 1);
                 }
                 mk[w] = above[w] | kept;
             }
