@@ -303,13 +303,19 @@ bool plan_wave_exact(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Wav
     if (dtype != ATK_BF16 || !ptr16 || n % 8 || n > 8192) return false;
     WaveExactPlan p;
     memset(&p, 0, sizeof p);
-    // Against ex_row_kernel over 1 to 8192 rows, whole rows 0.13 to 0.99 times as long (2048 x 512, k = 256: 0.22) but for few
-    // winners in large batches, which need no sort of all elements (8192 x 1024, k = 1: 1.17); with a bound and a list 0.62 to 1.05 from 1024 rows on.  A
-    // few rows leave a wavefront's steps nobody's to hide behind, and four wavefronts have them in less time (256 x 8192, k = 512:
-    // 1.28): then only rows of up to 2048 elements (0.75 to 0.96) and short lists (0.72 to 1.02).
+    // Against ex_row_kernel over 1 to 8192 rows of 520 to 8192 elements, 19 values of k, whole rows 0.13 to 0.99 times as long (2048 x 512, k = 256: 0.22)
+    // but for few winners in large batches, which need no sort of all elements (8192 x 1024, k = 1: 1.17); with a bound and a list 0.27 to 1.05 on N(0,1)
+    // and 0.54 to 1.16 on logarithms of probabilities, which are converted first, where it is taken.  A few rows leave a wavefront's steps nobody's to hide behind, and
+    // four wavefronts have them in less time (256 x 8192, k = 512: 1.28): then only rows of up to 2048 elements (0.26 to 0.98, logarithms to 1.1) and short
+    // lists (0.72 to 1.04, logarithms to 1.12).  The list's sort is as long as the next power of two of k needs: where k is little above one, and the
+    // row short against it or the sort the longer part, ex_row_kernel has the row sooner -
+    //   k > 512 on 1537 to 2304 elements        0.49 to 1.32, logarithms 0.81 to 1.55, one value 0.8 to 1.75
+    //   k up to 575 on more than 4096           0.87 to 1.12, logarithms 0.96 to 1.30
+    //   k from 257 to 384 on more than 6144, from 2049 rows on   1.00 to 1.07, logarithms 1.07 to 1.21 (up to 2048 rows 0.81 to 1.01 and 0.92 to 1.14)
     const bool forced = plan_override().wv > 0;
     if (!forced && n <= 1024 && ((n > 512 && m > 1024 && k < 128) || (m > 4096 && k < 32))) return false;
     if (!forced && n > 2048 && m < 1024 && k > 64) return false;
+    if (!forced && ((k > 512 && n > 1536 && n <= 2304) || (k > 512 && k < 576 && n > 4096) || (k > 256 && k <= 384 && n > 6144 && m > 2048))) return false;
     if (n <= 1024) {
         p.NV = n <= 512 ? 1 : 2;
         p.R = 8 * p.NV;

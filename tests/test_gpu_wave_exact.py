@@ -54,7 +54,10 @@ def test_sizes(n, plan_override):
             _check(x, k)
 
 
-@pytest.mark.parametrize("m, n, k", [(1100, 8192, 512), (1024, 6144, 129), (3, 2048, 300), (5, 4096, 64), (2500, 1024, 200), (4, 512, 512)])
+@pytest.mark.parametrize("m, n, k", [(1100, 8192, 512), (1024, 6144, 129), (3, 2048, 300), (5, 4096, 64), (2500, 1024, 200), (4, 512, 512),
+                                     # either side of the lists that a workgroup a row is quicker with
+                                     (3, 1536, 513), (3, 1544, 513), (3, 2048, 512), (1030, 2304, 513), (1030, 2312, 513), (1030, 4104, 575),
+                                     (1030, 4104, 576), (2049, 8192, 256), (2049, 8192, 384), (2049, 8192, 385), (2048, 6152, 300)])
 def test_chosen(m, n, k):
     _check(_rows(n, k).repeat(-(-m // 12), 1)[:m].contiguous(), k)
 
