@@ -843,16 +843,21 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
 
 // Rows of one wavefront each (atk_wave_row.hip), against the plans that they replace there, over 1664 calls (1 to 4096 rows of 1024 to 65536
 // elements, 128 to 1024 buckets, one to eight slots, k from 64 to 1500):
-//   up to 12288 elements   0.13 to 1.07 times as long, whatever the number of rows: the wavefront sorts in 1 to 4 us where the steps
+//   up to 12288 elements   0.13 to 1.07 times as long for 128, 256, 512 and 1024 buckets, whatever the number of rows: the wavefront sorts in 1 to 4 us where the steps
 //                          with a barrier after each take the workgroup longer (4 x 4096, k = 256, b = 512, 12.6 -> 4.7 us; 2048 x 8192,
 //                          k = 512, b = 512, k_b = 2, 20.6 -> 13.5)
 //   to 16384               0.59 to 1.08 from 768 rows on; with fewer, one wavefront reads a row too slowly (128 rows 0.79 to 1.22)
 //   to 32768               with queues 0.74 to 0.93 from 1024 rows on where the lanes read 16 bytes each, 0.32 to 0.99 from 2048 on; one slot up to 1.15
 //   to 65536               with queues and 1024 and more candidates 0.46 to 0.98 from 2048 rows on
 // k > 1024 (32 sorted words to a lane) takes 1.07 to 1.33 times as long from 256 rows on.
+// With 65 and more buckets, multiples of nothing among them (5000 calls of N(0,1) rows): few buckets leave lanes without columns and the others many
+// matrix rows, batch after batch of loads (256 x 12276, k = 131, b = 66, k_b = 2: 8.0 us in a workgroup, 11.7 so; k_b = 8 13.5 and 20).  Above 110
+// matrix rows to a lane (200 on rows past 12288 elements, which only large batches take) 0.5 to 1.6, level on the whole; up to there 99 of 100 calls 0.07
+// to 1.04, the others - half of the lanes idle and four slots, or k below a hundredth of the candidates - to 1.40 (1 x 12160, k = 4, b = 320, k_b = 4:
+// 7.8 and 11.0; the same rows with 296 buckets, whose candidates are full of ties, 33 and 10.7).
 bool wave_row_wins(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b) {
     if (plan_override().wv) return plan_override().wv > 0;
-    if (k > 1024) return false;
+    if (k > 1024 || n > (n <= 12288 ? 110 : 200) * b) return false;
     if (n <= 12288) return true;
     if (n <= 16384) return m >= 768;
     if (k_b < 2) return false;

@@ -113,6 +113,12 @@ def test_addresses():
     _check(_rows(m, n, 5), k, b, k_b, out=(vals, idx))
 
 
+def test_rows_too_long_for_their_buckets():
+    """Few buckets leave the lanes long columns: those rows are a workgroup's."""
+    for n, b, wave in ((7260, 66, True), (7262, 66, False), (12276, 66, False), (12288, 112, True), (16384, 82, True), (16384, 80, False)):
+        assert (int(_plan(2048, n, 64, b, 2)["wave"]) > 0) == wave, (n, b)
+
+
 def test_plans_fit_the_kernel():
     rng = random.Random(1)
     seen = 0
