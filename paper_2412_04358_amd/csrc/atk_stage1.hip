@@ -1006,28 +1006,40 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
     // what is left of them becomes values, rows and composites.
     if constexpr (PK) {
         u64 *cand = (u64 *)(smem + p.lds_cand_off);
-        auto emit = [&](int c, const int32_t(&q)[KB]) {  // column c of the (virtual) matrix
-            float v[KB];
-            int t[KB];
+        auto emit = [&](int c, const auto &q) {  // columns c, c + 1, ... of the (virtual) matrix, a queue each
+            constexpr int N = sizeof(q) / sizeof(q[0]);
+            float v[N][KB];
+            int t[N][KB];
             bool zero = false;
 #pragma unroll
-            for (int j = 0; j < KB; ++j) {
-                unpack_bf16(q[j], t0, v[j], t[j]);
-                zero = zero || __float_as_uint(v[j]) == 0u;
-            }
-            if (__ballot(zero) != 0ull) {  // +0 or -0: the element itself says
-                const uint16_t *row = (const uint16_t *)p.x + (int64_t)r * p.n;
+            for (int e = 0; e < N; ++e)
 #pragma unroll
                 for (int j = 0; j < KB; ++j) {
-                    const bool is = __float_as_uint(v[j]) == 0u;
-                    const uint32_t own = row[is ? (int64_t)t[j] * p.b + c - rot : 0];
-                    if (is) v[j] = __uint_as_float(own << 16);
+                    unpack_bf16(q[e][j], t0, v[e][j], t[e][j]);
+                    zero = zero || __float_as_uint(v[e][j]) == 0u;
                 }
-            }
-            u64 list[KB];
+            // +0 or -0: the element itself says (the loads of all columns in flight together: 6 x 222784, k = 15104, b = 1888, k_b = 8, mostly zeros:
+            // 10.0 us with a wait for each column, 9.0)
+            if (__ballot(zero) != 0ull) {
+                const uint16_t *row = (const uint16_t *)p.x + (int64_t)r * p.n;
+                uint32_t own[N][KB];
 #pragma unroll
-            for (int j = 0; j < KB; ++j) list[j] = t[j] != kEmptyT ? make_composite(__float_as_uint(v[j]), t[j] * p.b + c - rot) : 0ull;
-            emit_list<ELT, KB>(p, r, sp, bucket_of(c), list, cand);
+                for (int e = 0; e < N; ++e)
+#pragma unroll
+                    for (int j = 0; j < KB; ++j) own[e][j] = row[__float_as_uint(v[e][j]) == 0u ? (int64_t)t[e][j] * p.b + c + e - rot : 0];
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+#pragma unroll
+                    for (int j = 0; j < KB; ++j)
+                        if (__float_as_uint(v[e][j]) == 0u) v[e][j] = __uint_as_float(own[e][j] << 16);
+            }
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                u64 list[KB];
+#pragma unroll
+                for (int j = 0; j < KB; ++j) list[j] = t[e][j] != kEmptyT ? make_composite(__float_as_uint(v[e][j]), t[e][j] * p.b + c + e - rot) : 0ull;
+                emit_list<ELT, KB>(p, r, sp, bucket_of(c + e), list, cand);
+            }
         };
         if (p.wave_merge) {
             for (int off = p.Gw; off < kWave; off <<= 1) {
@@ -1051,20 +1063,19 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
             }
             __syncthreads();
             for (int c = tid; c < wcols; c += T) {
-                int32_t acc[KB];
+                int32_t acc[1][KB];
 #pragma unroll
-                for (int j = 0; j < KB; ++j) acc[j] = xch[(int64_t)c * KB + j];
+                for (int j = 0; j < KB; ++j) acc[0][j] = xch[(int64_t)c * KB + j];
                 for (int q = 1; q < p.nparts; ++q) {
                     int32_t theirs[KB];
 #pragma unroll
                     for (int j = 0; j < KB; ++j) theirs[j] = xch[((int64_t)q * stride + c) * KB + j];
-                    merge_pk<KB>(acc, theirs);
+                    merge_pk<KB>(acc[0], theirs);
                 }
                 emit(colbase + c, acc);
             }
         } else if (active && (!p.wave_merge || (tid & (kWave - 1)) < p.Gw)) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) emit(col0 + e, pk[e]);
+            emit(col0, pk);
         }
         trace_mark<TR>(p.trace, 2);
         const bool all = p.stage2 != 0;
