@@ -651,8 +651,6 @@ bool plan_exact_row(int64_t m, int64_t n, int64_t k, int dtype, bool pairs, bool
     return true;
 }
 
-constexpr int kPartsMaxKShort = 700;  // of f32 rows that one workgroup holds
-
 // Several workgroups to a row.  false: the row is too long for that, or k too large.
 bool plan_exact_parts(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, RowPlan *out) {
     const int ve = dtype == ATK_F32 ? 4 : 8;
@@ -662,14 +660,15 @@ bool plan_exact_parts(int64_t m, int64_t n, int64_t k, int dtype, bool ptr16, Ro
     const int64_t n_vec = ptr16 && n % ve == 0 ? n / ve : (n + 2 * ve - 2) / ve;
     const PlanOverride &ov = plan_override();
     // Rows that one workgroup holds are shared out only where that gives CUs without a row something to do, down to 1024 vectors a part, from
-    // 12288 vectors on (128 x 32768 f32, k = 64: 8.1 us in one workgroup, 10.5 in two), and f32 rows only for k up to 700: what the parts of a row
-    // pass on, and its last workgroup goes through alone, grows with k.  f32, in parts and in one workgroup: 64 x 65536, k = 256 12.4 and 10.6 N(0,1), 15.5 and
-    // 19.4 averaged over neighbours, 17 and 50 constant; k = 1000 17.9 and 12.6, 22.7 and 23.7, 24 and 35; k = 2048 23.6 and 14.8, 24.2 and 27.2, 38
-    // and 32.  bf16 rows, which are full of ties: 64 x 131072, k = 1000 18.6 and 16.3, 35.7 and 40.4, 26 and 64; k = 4096 35.7 and 52.4 N(0,1).
+    // 12288 vectors on (128 x 32768 f32, k = 64: 8.1 us in one workgroup, 10.5 in two).  Parts are the safer way, not the quicker one on every row: what
+    // they pass on, and the row's last workgroup goes through alone, grows with k, but rows full of ties cost one workgroup its whole row again and
+    // again.  65536 f32, in parts and in one workgroup: 128 rows, k = 1000: N(0,1) 16.5 and 11.8, averaged over neighbours 24.6 and 24.5, three levels
+    // 24.2 and 27.4, constant 19.6 and 34.3, zeros but for one in 200 47.7 and 183; k = 3000 32.7 and 17.1, 33 and 32, 41 and 31, 35 and 32, 96 and
+    // 197; 64 rows, k = 701: 16.0 and 10.7, 19.8 and 22.1, 22.8 and 26.9, 21.4 and 33.8, 47 and 181.
     // Longer rows take parts of up to 8192 vectors, two workgroups of 512 lanes to a CU.
     int64_t parts = std::min<int64_t>(std::min<int64_t>(kNumCU / m, 32), n_vec / 1024);
     if (parts < 1) parts = 1;
-    if (n_vec <= 16 * 1024 && (2 * m > kNumCU || n_vec < 12288 || (dtype == ATK_F32 && k > kPartsMaxKShort)) && !ov.S) return false;
+    if (n_vec <= 16 * 1024 && (2 * m > kNumCU || n_vec < 12288) && !ov.S) return false;
     if (ov.S) parts = ov.S;
     int64_t pv = (n_vec + parts - 1) / parts;
     int t_max = 1024;

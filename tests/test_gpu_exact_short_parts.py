@@ -1,4 +1,5 @@
-"""exact_topk of f32 rows that one workgroup holds, on both sides of the line in k up to which they are shared out between workgroups, against the oracle."""
+"""exact_topk of f32 rows that one workgroup holds and that are shared out between workgroups, on both sides of the lines in length and in rows, and for k
+up to where one row after another goes back to one workgroup, against the oracle."""
 import numpy as np
 import pytest
 import torch
