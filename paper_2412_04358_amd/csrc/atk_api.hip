@@ -103,7 +103,7 @@ static PlanOverride parse_plan_override(const char *e) {
         const int v = atoi(q);
         if (v >= 1 && v <= 63) o.hq = v;
     }
-    if (!o.wv && (o.T || o.S || o.V || o.P || o.pk_off || o.lm_off || o.ln_off || o.ts || o.hf || o.bo_off || o.rf || o.mh)) o.wv = -1;
+    if (!o.wv && (o.T || o.S || o.V || o.P || o.pk_off || o.lm_off || o.ln_off || o.ts || o.hf || o.hq || o.ht || o.sl || o.bo_off || o.rf || o.mh)) o.wv = -1;
     return o;
 }
 static PlanOverride g_plan_override = parse_plan_override(getenv("ATK_PLAN"));  // read once, at load

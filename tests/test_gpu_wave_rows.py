@@ -119,6 +119,15 @@ def test_rows_too_long_for_their_buckets():
         assert (int(_plan(2048, n, 64, b, 2)["wave"]) > 0) == wave, (n, b)
 
 
+@pytest.mark.parametrize("spec", ["T=256", "S=2", "V=4", "P=2", "PK=0", "TS=0", "LN=0", "LM=0", "HF=0", "HF=1", "HQ=40", "HT=512", "SL=128", "MH=0", "MH=2", "BO=0", "RF=0", "RF=4"])
+def test_a_key_that_names_another_plan_is_obeyed(spec, plan_override):
+    assert int(_plan(64, 8192, 100, 256, 1)["wave"]) > 0
+    plan_override(spec)
+    assert int(_plan(64, 8192, 100, 256, 1)["wave"]) == 0
+    plan_override(spec + ",WV=1")
+    assert int(_plan(64, 8192, 100, 256, 1)["wave"]) > 0
+
+
 def test_plans_fit_the_kernel():
     rng = random.Random(1)
     seen = 0
