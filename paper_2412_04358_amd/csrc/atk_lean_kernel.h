@@ -93,6 +93,7 @@ __global__ void __launch_bounds__(512) lean_kernel(LeanParams p) {
     const int col0 = cg * V;
     const int colbase = cb * p.Gw * V;
     const int wcols = min(p.Gw * V, p.b - colbase);  // columns of this workgroup
+    const int groups = wcols / V;                    // column groups: p.Gw, fewer in a last column block that is narrower
     const int t_lo = MODE == kLeanMulti ? w * p.Lh : ((MODE == kLeanPair && !helper) ? p.Lh : 0);
     const int t_hi = MODE == kLeanMulti ? (helper ? (w + 1) * p.Lh : p.L) : ((MODE == kLeanPair && helper) ? p.Lh : p.L);
 
@@ -195,8 +196,9 @@ __global__ void __launch_bounds__(512) lean_kernel(LeanParams p) {
         for (int e = 0; e < V; ++e)
             if (tt[e] != kEmptyT) {
                 const u64 c = make_composite(__float_as_uint(val[e]), tt[e] * p.b + col0 + e);
-                // column e of column group cgl sits at e*Gw + cgl: side-by-side lanes, side-by-side words
-                __hip_atomic_fetch_max(&cand[e * p.Gw + cgl], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                // column e of column group cgl sits at e * groups + cgl: side-by-side lanes, side-by-side words, and the
+                // columns fill words 0 .. wcols - 1, which is what is cleared, handed over and waited for
+                __hip_atomic_fetch_max(&cand[e * groups + cgl], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 const uint32_t key = (uint32_t)(c >> 32);
                 k_own_min = key < k_own_min ? key : k_own_min;
                 k_max = key > k_max ? key : k_max;
@@ -206,7 +208,7 @@ __global__ void __launch_bounds__(512) lean_kernel(LeanParams p) {
         __syncthreads();
         trace_mark<TR>(p.trace, 2);
         for (int lc = tid; lc < wcols; lc += T)
-            write_composite<ELT>(cand[(lc % V) * p.Gw + lc / V], p.out_vals, p.out_idx, (int64_t)r * p.k + colbase + lc);
+            write_composite<ELT>(cand[(lc % V) * groups + lc / V], p.out_vals, p.out_idx, (int64_t)r * p.k + colbase + lc);
         trace_mark<TR>(p.trace, 9);
         return;
     }
@@ -342,7 +344,7 @@ __global__ void __launch_bounds__(512) lean_kernel(LeanParams p) {
     trace_mark<TR>(p.trace, 3);  // all candidates of the row are in LDS, their key range is known
     if constexpr (NS == kFormOut) {
         for (int lc = tid; lc < wcols; lc += T)
-            write_composite<ELT>(cand[(lc % V) * p.Gw + lc / V], p.out_vals, p.out_idx, (int64_t)r * p.k + colbase + lc);
+            write_composite<ELT>(cand[(lc % V) * groups + lc / V], p.out_vals, p.out_idx, (int64_t)r * p.k + colbase + lc);
     } else if constexpr (NS >= kFormSort8)
         sort_select_few<ELT, 8, 1 << (NS - kFormSort8)>(cand, wcols, p.k, p.out_vals, p.out_idx, (int64_t)r);
     else if constexpr (NS >= kFormSort4)

@@ -947,7 +947,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
         if (p.lds_max) {
             u64 *cand = (u64 *)(smem + p.lds_cand_off);
             const int colbase = cb * p.Gw * V;
-            const int wcols = min(p.Gw * V, p.b - colbase);
+            const int wcols = min(p.Gw * V, p.b - colbase), groups = wcols / V;  // (a last column block may be narrower: fewer than Gw)
             const bool binned = p.stage2 && binned_fits(wcols) && p.bound_ok;
             uint32_t k_min = 0xffffffffu, k_max = 0u;
             bool whole = active;  // this lane holds an element of every one of its V columns
@@ -958,8 +958,8 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
                 for (int e = 0; e < V; ++e)
                     if (tt[e][0] != kEmptyT) {
                         const u64 c = make_composite(__float_as_uint(val[e][0]), tt[e][0] * p.b + col0 + e - rot);
-                        // column e of column group cgl sits at e*Gw + cgl: side-by-side lanes, side-by-side words
-                        __hip_atomic_fetch_max(&cand[e * p.Gw + cgl], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        // column e of column group cgl sits at e * groups + cgl: side-by-side lanes, side-by-side words, wcols of them
+                        __hip_atomic_fetch_max(&cand[e * groups + cgl], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         const uint32_t key = (uint32_t)(c >> 32);
                         k_min = key < k_min ? key : k_min;
                         k_max = key > k_max ? key : k_max;
@@ -985,7 +985,7 @@ __global__ void __launch_bounds__(MAXT, RF && V <= 2 ? 4 : 1) stage1_kernel(S1Pa
             __syncthreads();
             if (!p.stage2) {
                 for (int lc = tid; lc < wcols; lc += T)
-                    write_composite<ELT>(cand[(lc % V) * p.Gw + lc / V], p.out_vals, p.out_idx,
+                    write_composite<ELT>(cand[(lc % V) * groups + lc / V], p.out_vals, p.out_idx,
                                          (int64_t)r * p.k + bucket_of(colbase + lc));
                 trace_mark<TR>(p.trace, 9);
                 return;
