@@ -850,11 +850,13 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
 //   to 32768               with queues 0.74 to 0.93 from 1024 rows on where the lanes read 16 bytes each, 0.32 to 0.99 from 2048 on; one slot up to 1.15
 //   to 65536               with queues and 1024 and more candidates 0.46 to 0.98 from 2048 rows on
 // k > 1024 (32 sorted words to a lane) takes 1.07 to 1.33 times as long from 256 rows on.
-// With 65 and more buckets, multiples of nothing among them (5000 calls of N(0,1) rows): few buckets leave lanes without columns and the others many
-// matrix rows, batch after batch of loads (256 x 12276, k = 131, b = 66, k_b = 2: 8.0 us in a workgroup, 11.7 so; k_b = 8 13.5 and 20).  Above 110
-// matrix rows to a lane (200 on rows past 12288 elements, which only large batches take) 0.5 to 1.6, level on the whole; up to there 99 of 100 calls 0.07
-// to 1.04, the others - half of the lanes idle and four slots, or k below a hundredth of the candidates - to 1.40 (1 x 12160, k = 4, b = 320, k_b = 4:
-// 7.8 and 11.0; the same rows with 296 buckets, whose candidates are full of ties, 33 and 10.7).
+// With 65 and more buckets, multiples of nothing among them, few buckets leave lanes without columns and the others many matrix rows, batch after batch
+// of loads (256 x 12276, k = 131, b = 66, k_b = 2: 8.0 us in a workgroup, 11.7 so; k_b = 8 13.5 and 20): above 110 matrix rows to a lane (200 on rows past
+// 12288 elements, which only large batches take) 0.5 to 1.6, level on the whole.  Up to there, against what the other plans take by now, over 16000 calls
+// of N(0,1) rows and logarithms of probabilities: 0.38 to 1.26 up to 3072 elements, 0.6 on the whole; 1025 and more rows 0.4 to 0.8, one call in a hundred
+// above 1.04; up to 256 rows of 6145 to 12288 elements, queues of two to four slots, at most 1024 candidates and 256 winners, 0.91 to 1.21 (8 x 8192,
+// k = 250, b = 256, k_b = 4: 5.9 us in a workgroup, 6.2 so) - where logarithms of probabilities, which the workgroup does not sort as words, take 1.36
+// times as long in it (23 x 8568, k = 75, b = 504, k_b = 2: 8.05 and 5.9), so these stay.
 bool wave_row_wins(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b) {
     if (plan_override().wv) return plan_override().wv > 0;
     if (k > 1024 || n > (n <= 12288 ? 110 : 200) * b) return false;
