@@ -1,5 +1,7 @@
-"""exact_topk of bf16 rows in parts - marked as packed keys, few winners of short positive lists sorted by networks - against the oracle, bit for bit: rows off
-the vectors' boundaries, negative rows, rows unlike themselves, ties, every workgroup size."""
+"""exact_topk of bf16 rows in parts, marked as packed keys, against the oracle, bit for bit: rows off the vectors' boundaries, negative rows, rows
+unlike themselves, ties (which a part cuts before it passes them on), every workgroup size.  k at the edges of the plans for 9 rows: groups of
+twice as many maxima from 257, 513 and 1025 on, a second bound that cuts the parts' lists from 121 to 337 on (817 with three parts), and 1600 near
+the largest k of twelve and more parts."""
 import numpy as np
 import pytest
 import torch
@@ -37,7 +39,7 @@ def _rows(n, seed):
 def test_parts(n, spec, plan_override):
     plan_override(spec)
     x = _rows(n, n)
-    for k in (1, 63, 64, 65, 200, 256, 257):
+    for k in (1, 63, 64, 65, 200, 256, 257, 513, 816, 817, 1025, 1600):
         print(n, k, spec, flush=True)
         vals, idx = atk.exact_topk(x.cuda(), k)
         torch.cuda.synchronize()
