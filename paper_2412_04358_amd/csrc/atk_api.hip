@@ -841,11 +841,11 @@ bool stage2_apart(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int d
     return false;
 }
 
-// Rows of one wavefront each (atk_wave_row.hip), against the plans that they replace there, over 1664 calls (1 to 4096 rows of 1024 to 65536
+// Rows of one wavefront each (atk_wave_row.hip), against the plans that they replaced there, over 1664 calls (as these plans were then; 1 to 4096 rows of 1024 to 65536
 // elements, 128 to 1024 buckets, one to eight slots, k from 64 to 1500):
 //   up to 12288 elements   0.13 to 1.07 times as long for 128, 256, 512 and 1024 buckets, whatever the number of rows: the wavefront sorts in 1 to 4 us where the steps
 //                          with a barrier after each take the workgroup longer (4 x 4096, k = 256, b = 512, 12.6 -> 4.7 us; 2048 x 8192,
-//                          k = 512, b = 512, k_b = 2, 20.6 -> 13.5)
+//                          k = 512, b = 512, k_b = 2, 20.6 -> 13.5; by now 5.6 -> 3.6 and 19.4 -> 11.4 on preallocated outputs)
 //   to 16384               0.59 to 1.08 from 768 rows on; with fewer, one wavefront reads a row too slowly (128 rows 0.79 to 1.22)
 //   to 32768               with queues 0.74 to 0.93 from 1024 rows on where the lanes read 16 bytes each, 0.32 to 0.99 from 2048 on; one slot up to 1.15
 //   to 65536               with queues and 1024 and more candidates 0.46 to 0.98 from 2048 rows on

@@ -12,7 +12,8 @@
 // What bounds it: on 2048 rows, two to a SIMD, the sort of the rows that are in last, after the memory's 7 us (1270 vector instructions a row where 512 of
 // 1024 words are wanted, one in four cycles: 2.1 us); with more rows memory (3.6 us per 1024 rows of 8192).  2048 x 8192, k = 512, b = 512,
 // k_b = 2: 20.0 -> 12.1 us a call (Stage 1 and the selection from its pairs before, two launches), values on a grid of halves 55 -> 13.5;
-// 4 x 4096, k = 256, b = 512: 12.6 -> 4.7.
+// 4 x 4096, k = 256, b = 512: 12.6 -> 4.7.  (Against the other plans as they are by now, one launch on preallocated outputs: 19.4 -> 11.4 and
+// 5.6 -> 3.6.)
 #include <cstring>
 
 #include "atk_common.h"
@@ -162,7 +163,8 @@ bool plan_wave_row(int64_t m, int64_t n, int64_t k, int64_t b, int64_t k_b, int 
     // Bucket counts or row lengths that leave loads of one or two elements, in more groups: short rows, batches that give a SIMD a second row to issue
     // from, or so many winners that the selection replaced is the longer part.  Against the plans replaced, 649 calls (4 to 4000 rows of 2047 to 12288
     // elements, 99 to 1023 buckets): 0.08 to 1.04 times as long where this says so, half of them below 0.49 (4 x 3816, k = 402, b = 201, k_b = 4:
-    // 39.8 -> 7.3 us; 256 x 8190, k = b = 1023, k_b = 2: 37.3 -> 12.4; 2048 x 12288 0.16 to 1.04, but 1500 rows of them 1.27); elsewhere up to 1.8.
+    // 39.8 -> 7.3 us, 7.4 -> 6.9 since a workgroup's ranks no longer go through their bins one lane at a time; 256 x 8190, k = b = 1023, k_b = 2:
+    // 37.3 -> 12.4, both then and now; 2048 x 12288 0.16 to 1.04, but 1500 rows of them 1.27); elsewhere up to 1.8.
     if (p.V < 4 && p.NG > 1 && plan_override().wv <= 0 &&
         !(n <= 2048 || (n <= 4096 && m >= 1024) || (n <= 8192 && (m >= 2048 || (k > 256 && k > 96 * p.KB)))))
         return false;
